@@ -14,27 +14,29 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libqmm.so")
-SOURCES = ["qmm_api.hip", "qmm_scale.hip", "qmm_quantize.hip", "qmm_metric.hip", "qmm_gemm.hip", "qmm_diag.hip", "qmm_moments.hip", "qmm_dequantize.hip"]
+GEMM_PARTS = 6                      # qmm_gemm.hip is compiled once per operand-format pair, side by side
+SOURCES = ["qmm_api.hip", "qmm_scale.hip", "qmm_quantize.hip", "qmm_metric.hip", "qmm_diag.hip", "qmm_moments.hip", "qmm_dequantize.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function", "-Wno-inline-asm",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 
-def _compile(src, force):
-    obj = os.path.join(OBJDIR, src.replace(".hip", ".o"))
+def _compile(src, force, part=None):
+    obj = os.path.join(OBJDIR, src.replace(".hip", ".o" if part is None else f"_{part}.o"))
     path = os.path.join(CSRC, src)
     deps = [path, os.path.join(CSRC, "qmm_device.h"), os.path.join(ROOT, "include", "qmm.h")]
     if not force and os.path.exists(obj) and all(os.path.getmtime(obj) >= os.path.getmtime(d) for d in deps):
         return obj
-    subprocess.run([HIPCC, *FLAGS, "-c", path, "-o", obj], check=True)
+    subprocess.run([HIPCC, *FLAGS, *([] if part is None else [f"-DQMM_GEMM_PART={part}"]), "-c", path, "-o", obj], check=True)
     return obj
 
 
 def build(force=False):
     os.makedirs(OBJDIR, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=5) as ex:
-        objs = list(ex.map(lambda s: _compile(s, force), SOURCES))
+    jobs = [("qmm_gemm.hip", p) for p in range(GEMM_PARTS)] + [(s, None) for s in SOURCES]
+    with ThreadPoolExecutor(max_workers=6) as ex:
+        objs = list(ex.map(lambda j: _compile(j[0], force, j[1]), jobs))
     if force or not os.path.exists(LIB) or any(os.path.getmtime(o) > os.path.getmtime(LIB) for o in objs):
         subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], check=True)
     return LIB
@@ -50,10 +52,14 @@ def check_asm():
     compiler waits for such a load with vmcnt(0), i.e. for every store), (6) the registers its inline-assembly loads fill without waiting (a tile's step
     sizes) are touched by nothing before two step barriers have passed.  Returns a list of findings (empty = clean)."""
     os.makedirs(OBJDIR, exist_ok=True)
-    asm = os.path.join(OBJDIR, "qmm_gemm.s")
-    subprocess.run([HIPCC, *[f for f in FLAGS if f != "-fPIC"], "--cuda-device-only", "-S",
-                    os.path.join(CSRC, "qmm_gemm.hip"), "-o", asm], check=True)
-    text = open(asm).read()
+
+    def assemble(part):
+        asm = os.path.join(OBJDIR, f"qmm_gemm_{part}.s")
+        subprocess.run([HIPCC, *[f for f in FLAGS if f != "-fPIC"], f"-DQMM_GEMM_PART={part}", "--cuda-device-only", "-S",
+                        os.path.join(CSRC, "qmm_gemm.hip"), "-o", asm], check=True)
+        return open(asm).read()
+    with ThreadPoolExecutor(max_workers=GEMM_PARTS) as ex:
+        text = "\n".join(ex.map(assemble, range(GEMM_PARTS)))
     findings = []
     names = list(dict.fromkeys(re.findall(r"^(_ZN3qmm\S*(?:gemm_kernel|gemm_shortk_kernel|gemm_stream_kernel)\S*):", text, flags=re.M)))
     for nm in names:

@@ -44,25 +44,6 @@
 #include "qmm_device.h"
 
 namespace qmm {
-namespace {
-
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef int v16i __attribute__((ext_vector_type(16)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
-enum Kind { KIND_I8 = 0, KIND_F8 = 1, KIND_BF16 = 2 };
-
-constexpr int kWavesM = 2;                 // wavefronts along M in a workgroup (along N: template parameter)
-constexpr int kASlots = 3, kBSlots = 2;   // LDS ring depths of the two operands
-constexpr int kSlabBytes = 128;      // K bytes per row per pipeline step = one LDS row
-constexpr int kNumXcd = 8;
-
-
 struct GemmArgs {
     const uint8_t* a;        // [batch][M][rowbytes]
     const uint8_t* b;        // [batch][N][rowbytes]
@@ -83,6 +64,35 @@ struct GemmArgs {
     double* nsr_out;                  // NSR variant: the two folded sums
     int stagger;                      // gemm_stream_kernel: every other workgroup of an XCD starts this many sleeps late
 };
+
+// This file is compiled once per operand-format pair, side by side (QMM_GEMM_PART = one of the numbers below; without
+// it, everything at once): each part holds the kernels of its pair behind one entry, part 0 also the C functions.
+enum GemmPart { PART_BF16 = 0, PART_INT8, PART_E4M3_E4M3, PART_E4M3_E5M2, PART_E5M2_E4M3, PART_E5M2_E5M2 };
+template <int PART> __attribute__((visibility("hidden"))) qmm_status launch_part(GemmArgs& g, hipStream_t s, int fuse);
+#ifdef QMM_GEMM_PART
+#define QMM_GEMM_HAS(part) (QMM_GEMM_PART == (part))
+#else
+#define QMM_GEMM_HAS(part) 1
+#endif
+
+namespace {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef int v16i __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+enum Kind { KIND_I8 = 0, KIND_F8 = 1, KIND_BF16 = 2 };
+
+constexpr int kWavesM = 2;                 // wavefronts along M in a workgroup (along N: template parameter)
+constexpr int kASlots = 3, kBSlots = 2;   // LDS ring depths of the two operands
+constexpr int kSlabBytes = 128;      // K bytes per row per pipeline step = one LDS row
+constexpr int kNumXcd = 8;
+
 
 // 16 bytes per lane from global memory into LDS: lane l lands at lds_unit + 16*l.
 QMM_DEV void dma16(const uint8_t* gptr, uint8_t* lds_unit)
@@ -128,6 +138,30 @@ template <typename AccT, int NI, int NJ> QMM_DEV void pin_accumulators(AccT (&ac
 #pragma unroll
         for (int j = 0; j < NJ; ++j) asm volatile("" : "+a"(acc[i][j]));
 #endif
+}
+
+// T consecutive values of an output row, aligned to their element only (rows of N elements start anywhere when N is
+// odd): one store instruction all the same, global memory takes vector stores at any element boundary.
+template <int T> QMM_DEV void store_f32(float* dst, const float (&v)[T])
+{
+    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+    typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
+    static_assert(T == 2 || T == 4, "accumulator columns of a lane");
+    if constexpr (T == 4) *reinterpret_cast<f4u*>(dst) = f4u{v[0], v[1], v[2], v[3]};
+    else *reinterpret_cast<f2u*>(dst) = f2u{v[0], v[1]};
+}
+template <int T> QMM_DEV void store_bf16(uint16_t* dst, const float (&v)[T])
+{
+    typedef uint32_t u2u __attribute__((ext_vector_type(2), aligned(2)));
+    typedef uint32_t u1u __attribute__((ext_vector_type(1), aligned(2)));
+    typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    static_assert(T == 2 || T == 4, "accumulator columns of a lane");
+    uint32_t pk[T / 2];
+#pragma unroll
+    for (int q = 0; q < T / 2; ++q) pk[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{v[2 * q], v[2 * q + 1]}, bf2));
+    if constexpr (T == 4) *reinterpret_cast<u2u*>(dst) = u2u{pk[0], pk[1]};
+    else *reinterpret_cast<u1u*>(dst) = u1u{pk[0]};
 }
 
 // FUSE: bit 0 / bit 1 = the A / B operand arrives as bfloat16 values and is quantized (RTNE, with its step sizes)
@@ -676,8 +710,8 @@ gemm_kernel(GemmArgs g)
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-    } else if (interior && g.y && !g.y_bf16 && !g.acc_out && TILES_N % 4 == 0) {
-        // whole tile inside the matrix, binary32 output only: 16 bytes per store
+    } else if (interior && g.y && !g.y_bf16 && !g.acc_out) {
+        // whole tile inside the matrix, binary32 output only: 4*TILES_N bytes per lane and store
         float* ybase = static_cast<float*>(g.y) + (bidx * g.M + m_base) * g.N + n;
         float sl_rows[BLOCKS_M][REGS];
 #pragma unroll
@@ -697,26 +731,72 @@ gemm_kernel(GemmArgs g)
 #pragma unroll
             for (int r = 0; r < REGS; ++r) {
                 const int ml = ia * R + row_in_block(r);
-                float* dst = ybase + (int64_t)ml * g.N;
-                float rv[TILES_N];
+                float rv[TILES_N], v[TILES_N];
                 if constexpr (NSR != 0) nsr_row(m_base + ml, rv);
+                uint32_t raw;
 #pragma unroll
-                for (int q = 0; q < TILES_N / 4; ++q) {
-                    uint32_t raw;
-                    v4f v;
+                for (int e = 0; e < TILES_N; ++e) v[e] = value(ia, r, e, sl_rows[ia][r], raw);
+                if constexpr (NSR != 0) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = value(ia, r, 4 * q + e, sl_rows[ia][r], raw);
-                    if constexpr (NSR != 0) {
+                    for (int e = 0; e < TILES_N; ++e) nsr_add(v[e], rv[e]);
+                }
+                store_f32<TILES_N>(ybase + (int64_t)ml * g.N, v);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else if (NSR == 0 && g.y && !g.acc_out) {
+        // Edge tiles and rows that start off a vector boundary, output in y alone: the same stores as above under a row
+        // mask, element by element only in the lane that straddles the last column.  Blocks below the last row are left out.
+        // (Written element by element, with a test and a 64-bit address for each, the epilogue took longer than the matrix
+        // work: E4M3 1031 x 1000 x 784 with binary32 output 17.4 -> 10.4 us, INT8 4097 x 3070 x 768 with bfloat16 38.4 ->
+        // 22.3 us; binary32 output of the 32 x 32 instructions, whole tiles: INT8 4096 x 768 x 768 19.7 -> 10.4 us,
+        // bfloat16 operands 16384 x 4096 x 1024 166 -> 151 us.)
+        const bool whole = n + TILES_N <= g.N;
+        const int64_t rows_left = g.M - m_base;
+        float sl_rows[BLOCKS_M][REGS];
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) nsr_add(v[e], rv[4 * q + e]);
+        for (int ia = 0; ia < BLOCKS_M; ++ia)
+#pragma unroll
+            for (int r = 0; r < REGS; ++r) {
+                sl_rows[ia][r] = sa_scalar;
+                if constexpr (descale) {
+                    if (g.da_per_channel) {
+                        const int64_t m = m_base + ia * R + row_in_block(r);
+                        sl_rows[ia][r] = da[m < g.M ? m : g.M - 1];
                     }
-                    *reinterpret_cast<v4f*>(dst + 4 * q) = v;
+                }
+            }
+        const int64_t first = (bidx * g.M + m_base) * g.N + n;
+#pragma unroll
+        for (int ia = 0; ia < BLOCKS_M; ++ia) {
+            if (ia * R < rows_left) {
+#pragma unroll
+                for (int r = 0; r < REGS; ++r) {
+                    const int ml = ia * R + row_in_block(r);
+                    float v[TILES_N];
+                    uint32_t raw;
+#pragma unroll
+                    for (int e = 0; e < TILES_N; ++e) v[e] = value(ia, r, e, sl_rows[ia][r], raw);
+                    if (ml < rows_left && n < g.N) {
+                        const int64_t o = first + (int64_t)ml * g.N;
+                        if (whole) {
+                            if (g.y_bf16) store_bf16<TILES_N>(static_cast<uint16_t*>(g.y) + o, v);
+                            else store_f32<TILES_N>(static_cast<float*>(g.y) + o, v);
+                        } else {
+#pragma unroll
+                            for (int e = 0; e < TILES_N; ++e)
+                                if (n + e < g.N) {
+                                    if (g.y_bf16) static_cast<__bf16*>(g.y)[o + e] = (__bf16)v[e];
+                                    else static_cast<float*>(g.y)[o + e] = v[e];
+                                }
+                        }
+                    }
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
         }
     } else if (n < g.N) {
-        // general path: edge tiles, raw accumulators, narrow lanes; element-wise with bounds checks
+        // general path: raw accumulators, and edge tiles of the variant with the error sums; element-wise with bounds checks
 #pragma unroll
         for (int ia = 0; ia < BLOCKS_M; ++ia) {
 #pragma unroll
@@ -1052,8 +1132,9 @@ gemm_shortk_kernel(GemmArgs g)
 // operations outstanding".  At a tile boundary the copies that the next tile's first step would request before its
 // barrier are requested in front of the stores instead; that step then requests none and waits with the exact number
 // of stores allowed outstanding, and the stores are only waited for one step later (they have had 2-3 us by then).
-// Codes in, whole tiles, whole slabs, no split, output in y alone; same fragment, accumulator and store layout as
-// gemm_kernel.
+// Operands as they are (codes, or bfloat16 for the reference product), whole tiles, whole slabs, no split, output in y
+// alone; same fragment, accumulator and store layout as gemm_kernel.  The reference product gains least, its 268 MB of
+// binary32 output being what it waits for: 16384 x 4096 x 1024 151 -> 147 us back to back against gemm_kernel.
 template <int KIND, int FA, int FB>
 __global__ void __launch_bounds__(512, 1)
 gemm_stream_kernel(GemmArgs g)
@@ -1076,9 +1157,9 @@ gemm_stream_kernel(GemmArgs g)
     constexpr int STORES_W = STORES > 63 ? 63 : STORES;            // (the counter has six bits: waiting for more is safe)
     static_assert(kASlots == 3 && kBSlots == 2, "slot arithmetic below");
     static_assert(NC <= N1 && NB_TAIL <= MMAS_PER_BLOCK, "one copy per MFMA at most");
-    using AccT = typename std::conditional<F8, v4f, v16i>::type;
+    using AccT = typename std::conditional<F8, v4f, typename std::conditional<KIND == KIND_I8, v16i, v16f>::type>::type;
     using Frag = typename std::conditional<F8, v8i, v4i>::type;
-    static_assert(KIND == KIND_F8 || KIND == KIND_I8, "8-bit codes only");
+    constexpr bool descale = (KIND != KIND_BF16);
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
     const int lane = threadIdx.x & 63;
@@ -1167,8 +1248,10 @@ gemm_stream_kernel(GemmArgs g)
                     asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, 0 blgp:1" : "=a"(c) : "v"(fa), "v"(fb));
                 else
                     asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, 0" : "=a"(c) : "v"(fa), "v"(fb));
-            } else {
+            } else if constexpr (KIND == KIND_I8) {
                 asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, 0" : "=a"(c) : "v"(fa), "v"(fb));
+            } else {
+                asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=a"(c) : "v"(fa), "v"(fb));
             }
         } else {
             if constexpr (F8) {
@@ -1180,8 +1263,10 @@ gemm_stream_kernel(GemmArgs g)
                     asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, %0 blgp:1" : "+a"(c) : "v"(fa), "v"(fb));
                 else
                     asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, %0" : "+a"(c) : "v"(fa), "v"(fb));
-            } else {
+            } else if constexpr (KIND == KIND_I8) {
                 asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+a"(c) : "v"(fa), "v"(fb));
+            } else {
+                asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(fa), "v"(fb));
             }
         }
 #endif
@@ -1226,10 +1311,13 @@ gemm_stream_kernel(GemmArgs g)
     // to scalar registers at once: inside the loop there is then no load the compiler knows of, only stores -- with
     // both kinds outstanding it places full waits (vmcnt(0)) in front of the first use of a loaded register, and on
     // the way round the loop such a wait landed in the first step of every tile, behind all of the stores.
-    const float delta_a = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, g.da[0])));
-    const float delta_b = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, g.db[0])));
+    float delta_a = 1.0f, delta_b = 1.0f;
+    if constexpr (descale) {
+        delta_a = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, g.da[0])));
+        delta_b = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, g.db[0])));
+    }
     // any other granularity: the step sizes are fetched per tile, in the epilogue
-    const bool scales_in_loop = g.da_per_channel || g.db_per_channel || g.da_groups != 1 || g.db_groups != 1;
+    const bool scales_in_loop = descale && (g.da_per_channel || g.db_per_channel || g.da_groups != 1 || g.db_groups != 1);
 
     // step sizes of the current tile when they are not one per operand: rows lane and 64 + lane, the lane's columns
     float sc_a0 = 0.0f, sc_a1 = 0.0f, sc_b0 = 0.0f, sc_b1 = 0.0f, sc_b2 = 0.0f, sc_b3 = 0.0f;
@@ -1451,8 +1539,11 @@ gemm_stream_kernel(GemmArgs g)
         // ---- epilogue of a whole tile: (acc * deltaA[row]) * deltaB[column], in that order
         if (!scales_in_loop) {
             before_stores();
-            store_tile([&](int ia, int r, int tt) -> float { return (accumulator(ia, r, tt) * delta_a) * delta_b; });
-        } else {
+            store_tile([&](int ia, int r, int tt) -> float {
+                if constexpr (descale) return (accumulator(ia, r, tt) * delta_a) * delta_b;
+                else return accumulator(ia, r, tt);
+            });
+        } else if constexpr (descale) {
             // Step sizes per channel or per batch group were requested behind the tile's first step (above) and have
             // landed long since: every later step's wait left only operations newer than them outstanding.  A lane
             // holds the step sizes of rows lane and 64 + lane of the wavefront's 128; the one for an accumulator's row
@@ -1848,7 +1939,7 @@ qmm_status launch_shortk(GemmArgs& g, hipStream_t s)
     return launch_status();
 }
 
-// gemm_stream_kernel: codes in, no split, whole 256 x 256 tiles, whole slabs and at
+// gemm_stream_kernel: nothing quantized on load, no split, whole 256 x 256 tiles, whole slabs and at
 // least three of them, output in y alone, and more tiles than workgroups in the grid (with one tile each there is nothing to overlap).
 constexpr int kStreamGrid = 256;
 bool use_stream(const GemmArgs& g, int fuse)
@@ -1890,7 +1981,7 @@ qmm_status launch_fuse(GemmArgs& g, hipStream_t s)
     if constexpr (FUSE == 0) {
         if (use_direct(g, 0)) return launch_direct<KIND, FA, FB>(g, s);
         if (use_shortk<KIND>(g, 0)) return launch_shortk<KIND, FA, FB>(g, s);
-        if constexpr (KIND != KIND_BF16) { if (use_stream(g, 0)) return launch_stream<KIND, FA, FB>(g, s); }
+        if (use_stream(g, 0)) return launch_stream<KIND, FA, FB>(g, s);
     }
     // 256 x 256 tiles (eight wavefronts, two per SIMD: while one waits at a copy or a fragment read the other
     // issues matrix instructions) when they still give every CU work, else 128 x 128 tiles (four wavefronts, two
@@ -1915,6 +2006,36 @@ qmm_status launch_kind(GemmArgs& g, hipStream_t s, int fuse)
         return launch_fuse<KIND, FA, FB, 3>(g, s);
     }
 }
+
+}  // namespace
+
+#define QMM_GEMM_ENTRY(PART, KIND, FA, FB) \
+    template <> qmm_status launch_part<PART>(GemmArgs& g, hipStream_t s, int fuse) { return launch_kind<KIND, FA, FB>(g, s, fuse); }
+#if QMM_GEMM_HAS(0)
+QMM_GEMM_ENTRY(PART_BF16, KIND_BF16, QMM_FMT_BF16, QMM_FMT_BF16)
+#endif
+#if QMM_GEMM_HAS(1)
+QMM_GEMM_ENTRY(PART_INT8, KIND_I8, QMM_FMT_INT8, QMM_FMT_INT8)
+#endif
+#if QMM_GEMM_HAS(2)
+QMM_GEMM_ENTRY(PART_E4M3_E4M3, KIND_F8, QMM_FMT_E4M3, QMM_FMT_E4M3)
+#endif
+#if QMM_GEMM_HAS(3)
+QMM_GEMM_ENTRY(PART_E4M3_E5M2, KIND_F8, QMM_FMT_E4M3, QMM_FMT_E5M2)
+#endif
+#if QMM_GEMM_HAS(4)
+QMM_GEMM_ENTRY(PART_E5M2_E4M3, KIND_F8, QMM_FMT_E5M2, QMM_FMT_E4M3)
+#endif
+#if QMM_GEMM_HAS(5)
+QMM_GEMM_ENTRY(PART_E5M2_E5M2, KIND_F8, QMM_FMT_E5M2, QMM_FMT_E5M2)
+#endif
+#undef QMM_GEMM_ENTRY
+
+}  // namespace qmm
+
+#if QMM_GEMM_HAS(0)
+namespace qmm {
+namespace {
 
 bool is8(int f) { return f == QMM_FMT_INT8 || f == QMM_FMT_E4M3 || f == QMM_FMT_E5M2; }
 
@@ -2005,12 +2126,12 @@ qmm_status gemm_impl(const qmm_operand* a, const qmm_operand* b, int64_t batch, 
     }
     hipStream_t s = as_stream(stream);
 
-    if (bf) return launch_kind<KIND_BF16, QMM_FMT_BF16, QMM_FMT_BF16>(g, s, 0);
-    if (a->format == QMM_FMT_INT8) return launch_kind<KIND_I8, QMM_FMT_INT8, QMM_FMT_INT8>(g, s, fuse);
-    if (a->format == QMM_FMT_E4M3 && b->format == QMM_FMT_E4M3) return launch_kind<KIND_F8, QMM_FMT_E4M3, QMM_FMT_E4M3>(g, s, fuse);
-    if (a->format == QMM_FMT_E4M3) return launch_kind<KIND_F8, QMM_FMT_E4M3, QMM_FMT_E5M2>(g, s, fuse);
-    if (b->format == QMM_FMT_E4M3) return launch_kind<KIND_F8, QMM_FMT_E5M2, QMM_FMT_E4M3>(g, s, fuse);
-    return launch_kind<KIND_F8, QMM_FMT_E5M2, QMM_FMT_E5M2>(g, s, fuse);
+    if (bf) return launch_part<PART_BF16>(g, s, 0);
+    if (a->format == QMM_FMT_INT8) return launch_part<PART_INT8>(g, s, fuse);
+    if (a->format == QMM_FMT_E4M3 && b->format == QMM_FMT_E4M3) return launch_part<PART_E4M3_E4M3>(g, s, fuse);
+    if (a->format == QMM_FMT_E4M3) return launch_part<PART_E4M3_E5M2>(g, s, fuse);
+    if (b->format == QMM_FMT_E4M3) return launch_part<PART_E5M2_E4M3>(g, s, fuse);
+    return launch_part<PART_E5M2_E5M2>(g, s, fuse);
 }
 }  // namespace
 
@@ -2045,3 +2166,4 @@ extern "C" qmm_status qmm_gemm_nsr(const qmm_operand* a, const qmm_operand* b, i
     if (!y_ref) return QMM_ERR_NULL;
     return gemm_impl(a, b, batch, M, N, K, y, y_dtype, nullptr, y_ref, out2, workspace, workspace_bytes, stream);
 }
+#endif  // QMM_GEMM_HAS(0)

@@ -150,6 +150,19 @@ qmm_status qmm_quantize(const qmm_tensor* x, qmm_format fmt, const qmm_granulari
                         uint8_t* codes_out, void* stream);
 
 /*
+ * qmm_scale_quantize -- steps 1 and 2 of one tensor in one call: delta_out and codes_out are exactly what qmm_scale and
+ * then qmm_quantize with those step sizes write, with fewer launches and passes over x: one step size per row (rows up
+ * to 8192 bfloat16 / 4096 binary32 elements, every matrix a batch group of its own) takes a single pass; otherwise the
+ * quantize pass forms the step sizes from the partial maxima where that pays.
+ *   workspace  device scratch of at least qmm_scale_quantize_workspace_size() bytes, 16-byte aligned (0: may be NULL).
+ * An empty tensor writes its groups' step sizes (1) and no codes.  Errors as for the two calls.
+ */
+size_t qmm_scale_quantize_workspace_size(const qmm_tensor* x, const qmm_granularity* g);
+qmm_status qmm_scale_quantize(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, qmm_round mode,
+                              uint64_t seed, uint64_t offset, float* delta_out, uint8_t* codes_out,
+                              void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * qmm_scale_multi / qmm_quantize_multi -- steps 1 and 2 (Eq. 1) for `count` tensors in one call each, e.g. the
  * activations and the weights of one product: the results are those of `count` calls of qmm_scale / qmm_quantize.
  *   x, g        host arrays of `count` descriptors / granularities.

@@ -109,53 +109,43 @@ template <int FMT> QMM_DEV qmm_u32x4 encode16_bf16_rtne(qmm_u32x4 w0, qmm_u32x4 
     return out;
 }
 
-// Stochastic rounding: up iff u24 / 2^24 < (|t| - lo) / (hi - lo).  All
-// quantities in the comparison are exact.
-template <int FMT> QMM_DEV uint32_t encode_fp8_sr(float t, uint32_t u24)
+// Stochastic rounding: up iff u24 / 2^24 < (|t| - lo) / (hi - lo), u24 the top 24 bits of a random word.  With Y the
+// magnitude in units of the grid step there, times 2^24 and rounded up to an integer, that is a carry into bit 24 of
+// Y + (2^24 - 1 - u24): u24 < frac holds iff u24 < ceil(frac).  2^24 - 1 - u24 is the top of the word's complement.  In a
+// format's normal range the magnitude's own bit pattern is Y (23 - M fraction bits, so the complement is shifted by
+// M + 1 more); below it, and for INT8, Y comes from an exact multiplication by a power of two.  No branch, 14
+// instructions with the selects; the comparisons of fractions this replaces took the normal and the subnormal branch
+// one after the other in nearly every wavefront (quantizing 4096 x 768 to E5M2 with its rows contracting: 7.4 -> 6.2 us).
+template <int FMT> QMM_DEV uint32_t encode_fp8_sr(float t, uint32_t word)
 {
     using F = Fp8<FMT>;
-    const uint32_t u = __float_as_uint(t);
+    const uint32_t u = __float_as_uint(t), inv = ~word;
     const uint32_t sign = (u >> 24) & 0x80u;
-    const uint32_t a = u & 0x7FFFFFFFu;
-    if (a > 0x7F800000u) return 0x7Fu;
-    if (a >= F::MAX_BITS) return sign | F::MAX_CODE;
-    uint32_t code;
-    if (a >= F::MINNORM_BITS) {
-        const uint32_t rem = a & ((1u << (23 - F::M)) - 1u);              // fraction of one ulp, 23-M bits
-        const uint32_t lo = (a >> (23 - F::M)) - ((127u - F::BIAS) << F::M);
-        code = lo + (u24 < (rem << (F::M + 1)) ? 1u : 0u);
-    } else {
-        const float s = __uint_as_float(a) * F::TO_SUBNORMAL_UNITS;       // in units of the min subnormal
-        const float lo = floorf(s);
-        const float frac = s - lo;
-        code = (uint32_t)lo + ((float)u24 < frac * 16777216.0f ? 1u : 0u);
-    }
-    return sign | code;
+    const uint32_t a = min(u & 0x7FFFFFFFu, F::MAX_BITS);              // the maximum itself has no fraction: never up
+    const uint32_t normal = ((a + (inv >> (9 + F::M))) >> (23 - F::M)) - ((127u - F::BIAS) << F::M);
+    const float y = __builtin_ceilf(__uint_as_float(a) * (F::TO_SUBNORMAL_UNITS * 16777216.0f));   // exact product
+    const uint32_t sub = ((uint32_t)fminf(y, 268435456.0f) + (inv >> 8)) >> 24;     // (the cap: not used above 2^27)
+    const uint32_t code = a >= F::MINNORM_BITS ? normal : sub;
+    return t != t ? 0x7Fu : (sign | code);
 }
 
-QMM_DEV uint32_t encode_int8_sr(float t, uint32_t u24)
+QMM_DEV uint32_t encode_int8_sr(float t, uint32_t word)
 {
-    if (t != t) return 0u;
-    const float a = fabsf(t);
-    float r;
-    if (a >= 127.0f) r = 127.0f;
-    else {
-        const float lo = floorf(a);
-        const float frac = a - lo;
-        r = lo + ((float)u24 < frac * 16777216.0f ? 1.0f : 0.0f);
-    }
-    const int q = (int)(__float_as_uint(t) >> 31 ? -r : r);
-    return (uint32_t)q & 0xFFu;
+    const float y = __builtin_ceilf(fminf(fabsf(t), 127.0f) * 16777216.0f);        // exact product; at most 127 * 2^24
+    const int r = (int)(((uint32_t)y + (~word >> 8)) >> 24);
+    const int q = (__float_as_uint(t) >> 31) ? -r : r;
+    return t != t ? 0u : ((uint32_t)q & 0xFFu);
 }
 
-template <int FMT, int MODE> QMM_DEV uint32_t encode(float t, uint32_t u24)
+// word: the element's random word (stochastic rounding only)
+template <int FMT, int MODE> QMM_DEV uint32_t encode(float t, uint32_t word)
 {
     if constexpr (MODE == QMM_ROUND_RTNE) {
         if constexpr (FMT == QMM_FMT_INT8) return encode_int8_rtne(t);
         else return encode_fp8_rtne<FMT>(t);
     } else {
-        if constexpr (FMT == QMM_FMT_INT8) return encode_int8_sr(t, u24);
-        else return encode_fp8_sr<FMT>(t, u24);
+        if constexpr (FMT == QMM_FMT_INT8) return encode_int8_sr(t, word);
+        else return encode_fp8_sr<FMT>(t, word);
     }
 }
 
@@ -178,14 +168,14 @@ QMM_DEV Philox4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3
     return Philox4{{c0, c1, c2, c3}};
 }
 
-// 24 random bits of output element number g under key `seed`.
+// Random word of output element number g under key `seed` (its top 24 bits are used).
 struct SrStream {
     uint64_t seed;
     uint64_t cached_block;
     Philox4 cached;
     bool valid;
     QMM_DEV explicit SrStream(uint64_t s) : seed(s), cached_block(0), cached{}, valid(false) {}
-    QMM_DEV uint32_t bits(uint64_t g)
+    QMM_DEV uint32_t word(uint64_t g)
     {
         const uint64_t blk = g >> 2;
         if (!valid || blk != cached_block) {
@@ -195,8 +185,7 @@ struct SrStream {
         }
         // selected by compares: indexing the four words with a run-time index would put them in scratch memory
         const uint32_t j = (uint32_t)g & 3u;
-        const uint32_t w = j == 0 ? cached.v[0] : j == 1 ? cached.v[1] : j == 2 ? cached.v[2] : cached.v[3];
-        return w >> 8;
+        return j == 0 ? cached.v[0] : j == 1 ? cached.v[1] : j == 2 ? cached.v[2] : cached.v[3];
     }
 };
 
@@ -287,6 +276,19 @@ QMM_DEV bool arrive_last(uint32_t* slot, unsigned id, unsigned total)
     __syncthreads();
     return s_last != 0;
 }
+
+// The scale pass in two halves (qmm_scale.hip), for the call that hands the partial maxima to the quantize pass.
+struct ScalePartials {
+    int64_t batch, P, C;       // layout of the partial maxima: [batch][P][C] (C = channels of a step size each, else 1)
+    bool done;                 // the step sizes have been written already
+};
+qmm_status scale_arguments(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, const float* delta_out,
+                           const void* workspace, size_t workspace_bytes);
+qmm_status scale_partials(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, float* delta_out, uint32_t* partial,
+                          bool fold_here, ScalePartials* out, hipStream_t s);
+qmm_status scale_fold(const ScalePartials& pp, const uint32_t* partial, qmm_format fmt, const qmm_granularity* g,
+                      float* delta_out, hipStream_t s);
+inline float host_qmax(qmm_format fmt) { return fmt == QMM_FMT_INT8 ? 127.0f : (fmt == QMM_FMT_E4M3 ? 448.0f : 57344.0f); }
 
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 inline qmm_status launch_status() { return hipGetLastError() == hipSuccess ? QMM_OK : QMM_ERR_LAUNCH; }

@@ -4,7 +4,12 @@
 // is x * (1/delta) with one IEEE reciprocal per thread-row and one product per
 // element.  Codes are written with the contracting axis contiguous; when the
 // input contracts over its rows the tile is transposed through LDS.
+// qmm_scale_quantize: both steps.  The step size is formed where it is used:
+// with one per row in a single pass that keeps the row in registers, otherwise
+// by the quantize pass, which folds the partial maxima of its scale group
+// while its first elements are on their way.
 #include <algorithm>
+#include <type_traits>
 #include "qmm_device.h"
 
 namespace qmm {
@@ -13,69 +18,285 @@ namespace {
 constexpr int kThreads = 256;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+// global memory takes vector accesses at any element boundary: rows of odd length need no path of their own
+typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+typedef unsigned int u32x4_byte __attribute__((ext_vector_type(4), aligned(1)));
+typedef unsigned int u32x2_byte __attribute__((ext_vector_type(2), aligned(1)));
+typedef unsigned int u32_byte __attribute__((aligned(1)));
 
 struct QArgs {
     const void* x;
-    const float* delta;
+    float* delta;          // step sizes: read, or (FOLD, one-pass kernel) formed and written
     uint8_t* codes;
     int64_t batch, rows, cols, batch_stride, row_stride;
     int64_t groups;        // batch groups
     int64_t inner;         // consecutive matrices sharing a group: group = (b / inner) % groups
     int64_t channels;      // step sizes per group (1 when not per-channel)
     uint64_t seed, offset;
+    const uint32_t* partial;   // FOLD: partial maxima [batch][P][channels]; one scale group: fold_total of them
+    int64_t P;
+    int fold_total;
+    float qmax;
 };
 
 template <typename T> QMM_DEV float load_f32(const T* p);
 template <> QMM_DEV float load_f32<uint16_t>(const uint16_t* p) { return bf16_bits_to_f32(*p); }
 template <> QMM_DEV float load_f32<float>(const float* p) { return *p; }
 
+// A 16-byte vector of a tensor: 8 bfloat16 or 4 binary32 elements.
+template <typename T> struct Vec;
+template <> struct Vec<uint16_t> {
+    static constexpr int V = 8;
+    static QMM_DEV float at(const u32x4& w, int e) { return __uint_as_float((e & 1) ? (w[e >> 1] & 0xFFFF0000u) : (w[e >> 1] << 16)); }
+    static QMM_DEV uint32_t max_bits(const u32x4& w)
+    {
+        uint32_t m = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m = max(m, max((w[i] << 16) & 0x7FFFFFFFu, w[i] & 0x7FFF0000u));
+        return m;
+    }
+    static QMM_DEV u32x4 partial_load(const uint16_t* p, int left)       // the first `left` elements, zeros behind them
+    {
+        u32x4 w = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+            if (e < left) w[e >> 1] |= (uint32_t)p[e] << (16 * (e & 1));
+        return w;
+    }
+};
+template <> struct Vec<float> {
+    static constexpr int V = 4;
+    static QMM_DEV float at(const u32x4& w, int e) { return __uint_as_float(w[e]); }
+    static QMM_DEV uint32_t max_bits(const u32x4& w)
+    {
+        return max(max(w[0] & 0x7FFFFFFFu, w[1] & 0x7FFFFFFFu), max(w[2] & 0x7FFFFFFFu, w[3] & 0x7FFFFFFFu));
+    }
+    static QMM_DEV u32x4 partial_load(const float* p, int left)
+    {
+        u32x4 w = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+            if (e < left) w[e] = __float_as_uint(p[e]);
+        return w;
+    }
+};
+
+// Codes of four consecutive output elements, the first of them number g of the random stream, packed into a dword.
+template <int FMT, int MODE> QMM_DEV uint32_t encode4(float t0, float t1, float t2, float t3, uint64_t g, uint64_t seed)
+{
+    if constexpr (MODE == QMM_ROUND_RTNE) {
+        if constexpr (FMT == QMM_FMT_INT8)
+            return encode_int8_rtne(t0) | (encode_int8_rtne(t1) << 8) | (encode_int8_rtne(t2) << 16) | (encode_int8_rtne(t3) << 24);
+        else return encode_fp8_rtne_pair<FMT>(t0, t1) | (encode_fp8_rtne_pair<FMT>(t2, t3) << 16);
+    } else {
+        // The four elements are one block of the generator when the first of them starts one (always, unless the caller's
+        // offset or the row length is not a multiple of 4), else parts of two.
+        const uint64_t c = g >> 2;
+        const uint32_t j = (uint32_t)g & 3u;
+        const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+        Philox4 p = philox4x32_10((uint32_t)c, (uint32_t)(c >> 32), 0u, 0u, k0, k1);
+        if (j != 0u) {
+            const Philox4 q = philox4x32_10((uint32_t)(c + 1), (uint32_t)((c + 1) >> 32), 0u, 0u, k0, k1);
+            uint32_t w[4];
+#pragma unroll
+            for (uint32_t e = 0; e < 4; ++e) {       // word j + e of the eight, by compares (an indexed array would live in memory)
+                const uint32_t s = j + e;
+                w[e] = s == 1 ? p.v[1] : s == 2 ? p.v[2] : s == 3 ? p.v[3] : s == 4 ? q.v[0] : s == 5 ? q.v[1] : q.v[2];
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p.v[e] = w[e];
+        }
+        return encode<FMT, MODE>(t0, p.v[0]) | (encode<FMT, MODE>(t1, p.v[1]) << 8) | (encode<FMT, MODE>(t2, p.v[2]) << 16) |
+               (encode<FMT, MODE>(t3, p.v[3]) << 24);
+    }
+}
+
+// The V codes of a vector, from `rho` and the number of its first element.
+template <typename T, int FMT, int MODE> QMM_DEV u32x2 encode_vec(const u32x4& w, float rho, uint64_t g, uint64_t seed)
+{
+    u32x2 out = {0u, 0u};
+#pragma unroll
+    for (int q = 0; q < Vec<T>::V / 4; ++q)
+        out[q] = encode4<FMT, MODE>(Vec<T>::at(w, 4 * q) * rho, Vec<T>::at(w, 4 * q + 1) * rho, Vec<T>::at(w, 4 * q + 2) * rho,
+                                    Vec<T>::at(w, 4 * q + 3) * rho, g + 4 * q, seed);
+    return out;
+}
+template <typename T> QMM_DEV void store_codes(uint8_t* dst, u32x2 c, int64_t left)
+{
+    if (left >= Vec<T>::V) {
+        if constexpr (Vec<T>::V == 8) *reinterpret_cast<u32x2_byte*>(dst) = c;
+        else *reinterpret_cast<u32_byte*>(dst) = c[0];
+    } else {
+#pragma unroll
+        for (int e = 0; e < Vec<T>::V; ++e)
+            if (e < left) dst[e] = (uint8_t)(c[e >> 2] >> (8 * (e & 3)));
+    }
+}
+
+QMM_DEV int64_t group_of(const QArgs& a, int64_t b) { return (b / a.inner) % a.groups; }
+
+QMM_DEV uint32_t block_max_u32(uint32_t v)
+{
+    __shared__ uint32_t s[kThreads / kWave];
+    v = wave_max_u32(v);
+    if ((threadIdx.x & (kWave - 1)) == 0) s[threadIdx.x / kWave] = v;
+    __syncthreads();
+    uint32_t r = s[0];
+#pragma unroll
+    for (int i = 1; i < kThreads / kWave; ++i) r = max(r, s[i]);
+    return r;
+}
+
+// Step size of matrix b (one per batch group), folded by the whole workgroup from the group's partial maxima (at most
+// kFoldMax of them: host).  `writer`: this workgroup also writes it out.
+constexpr int kFoldMax = 1024;
+QMM_DEV float fold_delta(const QArgs& a, int64_t b, bool writer)
+{
+    const int64_t g = group_of(a, b);
+    uint32_t m = 0;
+    if (a.groups == 1) {
+#pragma unroll
+        for (int k = 0; k < kFoldMax / kThreads; ++k) {
+            const int i = threadIdx.x + k * kThreads;
+            if (i < a.fold_total) m = max(m, a.partial[i]);
+        }
+    } else {
+        // the k-th matrix of group g is ((k / inner) * G + g) * inner + k % inner, increasing with k
+        for (int64_t it = threadIdx.x;; it += kThreads) {
+            const int64_t k = it / a.P, p = it - k * a.P;
+            const int64_t mb = ((k / a.inner) * a.groups + g) * a.inner + k % a.inner;
+            if (mb >= a.batch) break;
+            m = max(m, a.partial[mb * a.P + p]);
+        }
+    }
+    const float d = delta_from_absmax_bits(block_max_u32(m), a.qmax);
+    if (writer && threadIdx.x == 0) a.delta[g] = d;
+    return d;
+}
+// the workgroup of a grid that writes a group's step size: the first of its first matrix
+QMM_DEV bool writes_group(const QArgs& a, int64_t b) { return b % a.inner == 0 && b / a.inner < a.groups; }
+
 // Row-contracting fast path: bfloat16, cols % 16 == 0, 16-byte aligned rows.  One thread = 16 consecutive
 // elements of a row: two 16-byte loads, one 16-byte store.  grid (ceil(rows*cols/16 / 256), batch).
-template <int FMT, int MODE> __global__ void __launch_bounds__(kThreads)
+template <int FMT, int MODE, bool FOLD> __global__ void __launch_bounds__(kThreads)
 quantize_rows_bf16x16(QArgs a)
 {
     const int64_t vpr = a.cols >> 4;
     const int64_t v = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (v >= vpr * a.rows) return;
     const int64_t b = blockIdx.y;
-    const int64_t r = v / vpr, cv = v - r * vpr;
-    const float d = a.delta[((b / a.inner) % a.groups) * a.channels + (a.channels > 1 ? r : 0)];
-    const float rho = 1.0f / d;
+    const bool live = v < vpr * a.rows;
+    if (!FOLD && !live) return;
+    // (a matrix with one step size comes in as one row: host; otherwise 32-bit arithmetic where it reaches)
+    int64_t r = 0;
+    if (a.rows > 1) r = vpr * a.rows <= 0xFFFFFFFFll ? (int64_t)((uint32_t)v / (uint32_t)vpr) : v / vpr;
+    const int64_t cv = v - r * vpr;
     const u32x4* src = reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(a.x) + b * a.batch_stride +
                                                       r * a.row_stride + cv * 16);
-    const u32x4 w0 = src[0], w1 = src[1];
+    u32x4 w0 = {0u, 0u, 0u, 0u}, w1 = {0u, 0u, 0u, 0u};
+    if (live) { w0 = src[0]; w1 = src[1]; }
+    float d;
+    if constexpr (FOLD) {
+        d = fold_delta(a, b, blockIdx.x == 0 && writes_group(a, b));
+        if (!live) return;
+    } else {
+        d = a.delta[group_of(a, b) * a.channels + (a.channels > 1 ? r : 0)];
+    }
+    const float rho = 1.0f / d;
     const int64_t p0 = (b * a.rows + r) * a.cols + cv * 16;
     u32x4 out;
     if constexpr (MODE == QMM_ROUND_RTNE) {
         out = encode16_bf16_rtne<FMT>(w0, w1, rho);
     } else {
-        // element number g = p0 + e + offset draws word g % 4 of Philox block g / 4.  When the thread's first element
-        // starts a block (always, unless the caller's offset is not a multiple of 4) its 16 elements are exactly the
-        // four blocks g0/4 .. g0/4 + 3, one per output dword; otherwise the generic stream looks each element up.
         const uint64_t g0 = (uint64_t)p0 + a.offset;
-        const bool aligned = (g0 & 3u) == 0;              // uniform over the grid
-        SrStream sr(a.seed);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            Philox4 blk{};
-            if (aligned) {
-                const uint64_t c = (g0 >> 2) + q;
-                blk = philox4x32_10((uint32_t)c, (uint32_t)(c >> 32), 0u, 0u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
-            }
-            uint32_t packed = 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int e = q * 4 + j;
-                const uint32_t word = e < 8 ? w0[e >> 1] : w1[(e - 8) >> 1];
-                const float xv = (e & 1) ? __uint_as_float(word & 0xFFFF0000u) : __uint_as_float(word << 16);
-                const float t = xv * rho;
-                const uint32_t u24 = aligned ? blk.v[j] >> 8 : sr.bits(g0 + e);
-                packed |= encode<FMT, MODE>(t, u24) << (8 * j);
-            }
-            out[q] = packed;
+        for (int h = 0; h < 2; ++h) {
+            const u32x2 c = encode_vec<uint16_t, FMT, MODE>(h ? w1 : w0, rho, g0 + 8 * h, a.seed);
+            out[2 * h] = c[0]; out[2 * h + 1] = c[1];
         }
     }
     *reinterpret_cast<u32x4*>(a.codes + p0) = out;
+}
+
+// Row-contracting, any type, extent, stride and alignment: a wavefront takes a row, a lane one 16-byte vector of it at a
+// time (wavefronts walk the rows of all matrices).  Dense tensors with one step size come in as one long row per matrix
+// and are shared out by pieces of a row: `pieces` wavefronts per row.
+template <typename T, int FMT, int MODE, bool FOLD> __global__ void __launch_bounds__(kThreads)
+quantize_rows(QArgs a, int64_t pieces)
+{
+    constexpr int V = Vec<T>::V;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t b = blockIdx.y;
+    const T* base = static_cast<const T*>(a.x) + b * a.batch_stride;
+    float d = 0.0f;
+    if constexpr (FOLD) d = fold_delta(a, b, blockIdx.x == 0 && writes_group(a, b));
+    const int64_t step = (int64_t)gridDim.x * (kThreads / kWave);
+    for (int64_t u = (int64_t)blockIdx.x * (kThreads / kWave) + threadIdx.x / kWave; u < a.rows * pieces; u += step) {
+        const int64_t r = u / pieces, piece = u - r * pieces;
+        if constexpr (!FOLD) d = a.delta[group_of(a, b) * a.channels + (a.channels > 1 ? r : 0)];
+        const float rho = 1.0f / d;
+        const int64_t p_row = (b * a.rows + r) * a.cols;
+        const T* row = base + r * a.row_stride;
+        for (int64_t c = (piece * kWave + lane) * V; c < a.cols; c += pieces * kWave * V) {
+            const int64_t left = a.cols - c;
+            u32x4 w;
+            if (left >= V) w = *reinterpret_cast<const u32x4_any*>(row + c);
+            else w = Vec<T>::partial_load(row + c, (int)left);
+            store_codes<T>(a.codes + p_row + c, encode_vec<T, FMT, MODE>(w, rho, (uint64_t)(p_row + c) + a.offset, a.seed), left);
+        }
+    }
+}
+
+// Both steps in one pass, one step size per row: LPR lanes (a part of a wavefront, a wavefront, or the four of a
+// workgroup) take a row, hold it in registers (NV vectors a lane), form its step size and write it and the codes.  The row
+// is read once (2 B + 1 B per bfloat16 element) where the two passes read it twice, in one launch instead of two.  Any
+// type, stride and alignment, cols <= LPR * NV * V (host).
+template <typename T, int FMT, int MODE, int LPR, int NV> __global__ void __launch_bounds__(kThreads)
+scale_quantize_rows(QArgs a)
+{
+    constexpr int V = Vec<T>::V, RPB = kThreads / LPR;       // rows per workgroup
+    __shared__ uint32_t s_max[kThreads / kWave];
+    const int64_t total = a.batch * a.rows;
+    const int c0 = (int)(threadIdx.x % LPR) * V;
+    for (int64_t blk = blockIdx.x; blk * RPB < total; blk += gridDim.x) {
+        const int64_t row_id = blk * RPB + threadIdx.x / LPR;
+        const bool live = row_id < total;
+        const int64_t b = live && a.batch > 1 ? row_id / a.rows : 0, r = live ? row_id - b * a.rows : 0;
+        const T* row = static_cast<const T*>(a.x) + b * a.batch_stride + r * a.row_stride;
+        const int cols = live ? (int)a.cols : 0;
+        u32x4 w[NV];
+        uint32_t m = 0;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int c = c0 + i * LPR * V, left = cols - c;
+            w[i] = u32x4{0u, 0u, 0u, 0u};
+            if (left >= V) w[i] = *reinterpret_cast<const u32x4_any*>(row + c);
+            else if (left > 0) w[i] = Vec<T>::partial_load(row + c, left);
+        }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) m = max(m, Vec<T>::max_bits(w[i]));
+#pragma unroll
+        for (int off = (LPR < kWave ? LPR : kWave) / 2; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, kWave));
+        if constexpr (LPR > kWave) {
+            static_assert(LPR <= kWave || LPR == kThreads, "a row of several wavefronts takes the whole workgroup");
+            if ((threadIdx.x & (kWave - 1)) == 0) s_max[threadIdx.x / kWave] = m;
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < kThreads / kWave; ++k) m = max(m, s_max[k]);
+            __syncthreads();                                 // reused by the next row
+        }
+        if (!live) continue;                                 // (LPR > 64: never, a workgroup's only row is live)
+        const float d = delta_from_absmax_bits(m, a.qmax);
+        if (threadIdx.x % LPR == 0) a.delta[row_id] = d;
+        const float rho = 1.0f / d;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int c = c0 + i * LPR * V, left = cols - c;
+            if (left > 0) {
+                const int64_t p = row_id * a.cols + c;
+                store_codes<T>(a.codes + p, encode_vec<T, FMT, MODE>(w[i], rho, (uint64_t)p + a.offset, a.seed), left);
+            }
+        }
+    }
 }
 
 // Several dense bfloat16 tensors with one step size each, RTNE, rows contracting, in one launch
@@ -99,162 +320,199 @@ quantize_flat_multi(MultiQ a)
     reinterpret_cast<u32x4*>(a.codes[t])[v] = encode16_bf16_rtne<FMT>(w0, w1, rho);
 }
 
-// Generic path: one thread per output code, any dtype / stride / contracting axis.
-template <typename T, int FMT, int MODE> __global__ void __launch_bounds__(kThreads)
-quantize_generic(QArgs a, int contract_axis)
+// Column-contracting (the input is [K][N], codes are [N][K]): any type, extent, stride and alignment.  Workgroup tile =
+// 128 k x kTileN n (64, or 128 for large bfloat16 tensors).  A thread loads RT rows (k) x one 16-byte vector (n), packs
+// the codes of each column along k into dwords and parks them in an LDS tile [n][k]; then every thread writes 16-byte
+// pieces of finished code rows, 128 contiguous bytes per n.  The narrow tile gives the small tensors, which left CUs idle,
+// twice the workgroups, and a head dimension of 64 no idle half; from 2048 wide tiles on the wide one's 256 contiguous
+// bytes per input row count for more (bfloat16 16384 x 3072: 29.7 against 32.8 us; 16384 x 1024, 1024 wide tiles: 12.1
+// against 11.5 us; 512 matrices of 512 x 64: 14.9 against 11.2 us).
+// grid (tiles, batch), tiles numbered along n first; workgroups loop where the grid would be too large to launch.
+constexpr int kTileK = 128;
+constexpr int kTileRowBytes = kTileK + 16;   // padded row of the LDS code tile
+constexpr int kFoldSlabs = 32;               // partial maxima per column that FOLD takes, at most
+
+template <typename T, int FMT, int MODE, bool FOLD, int kTileN> __global__ void __launch_bounds__(kThreads)
+quantize_cols(QArgs a, int64_t tiles_n, int64_t tiles)
 {
-    const int64_t NC = contract_axis == 1 ? a.rows : a.cols;
-    const int64_t KC = contract_axis == 1 ? a.cols : a.rows;
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= NC * KC) return;
+    constexpr int V = Vec<T>::V;
+    constexpr int TN = kTileN / V, TK = kThreads / TN, RT = kTileK / TK;       // 8 x 32 threads of 4 rows, or 16 x 16 of 8
+    constexpr int Q = kThreads / kTileN;                                       // threads per column in the fold
+    static_assert(RT % 4 == 0, "codes are packed four rows at a time");
+    __shared__ __attribute__((aligned(16))) uint8_t tile[kTileN * kTileRowBytes];
+    __shared__ uint32_t s_max[Q][kTileN];
+    __shared__ float s_rho[kTileN];
+    const int tn = threadIdx.x % TN, tk = threadIdx.x / TN;
     const int64_t b = blockIdx.y;
-    const int64_t n = i / KC, k = i - n * KC;
-    const int64_t r = contract_axis == 1 ? n : k, c = contract_axis == 1 ? k : n;
-    const float d = a.delta[((b / a.inner) % a.groups) * a.channels + (a.channels > 1 ? n : 0)];
-    const float rho = 1.0f / d;
-    const float t = load_f32<T>(static_cast<const T*>(a.x) + b * a.batch_stride + r * a.row_stride + c) * rho;
-    const int64_t p = (b * NC + n) * KC + k;
-    uint32_t u24 = 0;
-    if constexpr (MODE == QMM_ROUND_STOCHASTIC) {
-        SrStream sr(a.seed);
-        u24 = sr.bits((uint64_t)p + a.offset);
-    }
-    a.codes[p] = (uint8_t)encode<FMT, MODE>(t, u24);
-}
-
-// Column-contracting fast path (the input is [K][N], codes are [N][K]): bfloat16, rows % 16 == 0 is NOT
-// required; cols % 8 == 0 and 16-byte aligned rows are.  Workgroup tile = 128 k x 128 n.  Thread (tn, tk)
-// loads 8 rows (k) x 8 columns (n) as eight 16-byte vectors, packs the 8 codes of each column into two
-// dwords and parks them in an LDS tile [n][k]; then every thread writes 16-byte pieces of finished code
-// rows, 128 contiguous bytes per n.  grid (ceil(cols/128), ceil(rows/128), batch).
-constexpr int kTile = 128;
-constexpr int kTileRowBytes = kTile + 16;   // padded row of the LDS code tile
-
-template <int FMT, int MODE> __global__ void __launch_bounds__(kThreads)
-quantize_cols_bf16(QArgs a)
-{
-    __shared__ __attribute__((aligned(16))) uint8_t tile[kTile * kTileRowBytes];
-    const int tn = threadIdx.x & 15, tk = threadIdx.x >> 4;
-    const int64_t b = blockIdx.z;
-    const int64_t n0 = (int64_t)blockIdx.x * kTile, k0 = (int64_t)blockIdx.y * kTile;
     const int64_t K = a.rows, N = a.cols;
-    const int64_t n = n0 + tn * 8;
-    const uint16_t* base = static_cast<const uint16_t*>(a.x) + b * a.batch_stride;
-    float rho[8];
+    // 16-byte chunk c of code row n lies at chunk position c ^ ((n >> 3) & 7): the eight column vectors of a wavefront's
+    // dword stores would otherwise meet in the same banks
+    auto place = [](int n, int k) { return n * kTileRowBytes + ((((k >> 4) ^ (n >> 3)) & 7) << 4) + (k & 15); };
+    for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+        const int64_t tile_k = t / tiles_n, tile_n = t - tile_k * tiles_n;
+        const int64_t n0 = tile_n * kTileN, k0 = tile_k * kTileK;
+        const int64_t n = n0 + tn * V, k_first = k0 + tk * RT;
+        const T* base = static_cast<const T*>(a.x) + b * a.batch_stride + n;
+        const int n_left = (int)max((int64_t)0, min((int64_t)V, N - n));          // columns of this thread inside the matrix
+        u32x4 w[RT];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int64_t nn = n + j < N ? n + j : N - 1;
-        rho[j] = 1.0f / a.delta[((b / a.inner) % a.groups) * a.channels + (a.channels > 1 ? nn : 0)];
-    }
-    uint32_t lo[8] = {}, hi[8] = {};
-    SrStream sr(a.seed);
-    if constexpr (MODE == QMM_ROUND_STOCHASTIC) {
-        // Column by column: the eight codes of a column are consecutive output elements, i.e. two whole Philox
-        // blocks when the column's first element number is a multiple of 4 (K and the caller's offset both are);
-        // going row by row instead would draw a fresh block for every single element.
-        if (n < N) {
-            u32x4 w[8];
-#pragma unroll
-            for (int kk = 0; kk < 8; ++kk) {
-                const int64_t k = k0 + tk * 8 + kk;
-                w[kk] = u32x4{0u, 0u, 0u, 0u};
-                if (k < K) w[kk] = *reinterpret_cast<const u32x4*>(base + k * a.row_stride + n);
+        for (int i = 0; i < RT; ++i) {
+            const int64_t k = k_first + i;
+            w[i] = u32x4{0u, 0u, 0u, 0u};
+            if (k < K) {
+                if (n_left == V) w[i] = *reinterpret_cast<const u32x4_any*>(base + k * a.row_stride);
+                else if (n_left > 0) w[i] = Vec<T>::partial_load(base + k * a.row_stride, n_left);
             }
-            const bool aligned = ((K & 3) == 0) && ((a.offset & 3u) == 0);           // uniform over the grid
-            auto column = [&](int j, int kk, uint32_t u24) {
-                const uint32_t word = w[kk][j >> 1];
-                const float xv = (j & 1) ? __uint_as_float(word & 0xFFFF0000u) : __uint_as_float(word << 16);
-                const uint32_t code = encode<FMT, MODE>(xv * rho[j], u24);
-                if (kk < 4) lo[j] |= code << (8 * kk); else hi[j] |= code << (8 * (kk - 4));
-            };
-            const uint64_t g_first = (uint64_t)((b * N + n) * K + k0 + tk * 8) + a.offset;    // column j: + j * K
-            if (aligned) {
+        }
+        // step sizes of the tile's columns, while the elements are on their way
+        const int c = threadIdx.x & (kTileN - 1), q4 = threadIdx.x / kTileN;
+        const int64_t col = n0 + c;
+        if (FOLD && a.channels > 1) {
+            // one scale group per matrix (host): fold the column's P partial maxima, four threads a column
+            uint32_t m = 0;
+            if (col < N) {
+                const uint32_t* p = a.partial + b * a.P * N + col;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const uint64_t c = (g_first + (uint64_t)j * (uint64_t)K) >> 2;
-                    const Philox4 ba = philox4x32_10((uint32_t)c, (uint32_t)(c >> 32), 0u, 0u, (uint32_t)a.seed,
-                                                     (uint32_t)(a.seed >> 32));
-                    const Philox4 bb = philox4x32_10((uint32_t)(c + 1), (uint32_t)((c + 1) >> 32), 0u, 0u, (uint32_t)a.seed,
-                                                     (uint32_t)(a.seed >> 32));
-#pragma unroll
-                    for (int kk = 0; kk < 8; ++kk) column(j, kk, (kk < 4 ? ba.v[kk] : bb.v[kk - 4]) >> 8);
-                    // one column at a time: interleaved, the sixteen generator blocks of a thread need 240 registers
-                    __builtin_amdgcn_sched_barrier(0);
+                for (int i = 0; i < kFoldSlabs / Q; ++i) {
+                    const int64_t s = q4 + Q * i;
+                    if (s < a.P) m = max(m, p[s * N]);
                 }
+            }
+            s_max[q4][c] = m;
+            __syncthreads();
+            if (q4 == 0) {
+#pragma unroll
+                for (int i = 1; i < Q; ++i) m = max(m, s_max[i][c]);
+                const float d = delta_from_absmax_bits(m, a.qmax);
+                s_rho[c] = 1.0f / d;
+                if (tile_k == 0 && col < N) a.delta[group_of(a, b) * N + col] = d;
+            }
+        } else if (FOLD) {
+            const float d = fold_delta(a, b, t == 0 && writes_group(a, b));
+            if (q4 == 0) s_rho[c] = 1.0f / d;
+        } else if (q4 == 0) {
+            s_rho[c] = 1.0f / a.delta[group_of(a, b) * a.channels + (a.channels > 1 ? min(col, N - 1) : 0)];
+        }
+        __syncthreads();
+        // column by column: RT codes of consecutive output elements
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            const float rho = s_rho[tn * V + j];
+            const uint64_t g = (uint64_t)((b * N + n + j) * K + k_first) + a.offset;
+#pragma unroll
+            for (int q = 0; q < RT / 4; ++q) {
+                const uint32_t code = encode4<FMT, MODE>(Vec<T>::at(w[4 * q], j) * rho, Vec<T>::at(w[4 * q + 1], j) * rho,
+                                                         Vec<T>::at(w[4 * q + 2], j) * rho, Vec<T>::at(w[4 * q + 3], j) * rho,
+                                                         g + 4 * q, a.seed);
+                *reinterpret_cast<uint32_t*>(&tile[place(tn * V + j, tk * RT + 4 * q)]) = code;
+            }
+            // (one column at a time: interleaved, the generator blocks of a thread need 240 registers)
+            if constexpr (MODE == QMM_ROUND_STOCHASTIC) __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();
+        // kTileN code rows x 8 pieces of 16 bytes, 2 or 4 per thread
+#pragma unroll
+        for (int it = 0; it < kTileN * kTileK / 16 / kThreads; ++it) {
+            const int piece = it * kThreads + threadIdx.x;
+            const int row = piece >> 3, seg = piece & 7;
+            const int64_t nn = n0 + row, kk = k0 + seg * 16;
+            if (nn >= N || kk >= K) continue;
+            uint8_t* dst = a.codes + (b * N + nn) * K + kk;
+            const uint8_t* srcp = &tile[place(row, seg * 16)];
+            if (kk + 16 <= K) {
+                *reinterpret_cast<u32x4_byte*>(dst) = *reinterpret_cast<const u32x4*>(srcp);
             } else {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-#pragma unroll
-                    for (int kk = 0; kk < 8; ++kk) column(j, kk, sr.bits(g_first + (uint64_t)j * (uint64_t)K + kk));
-                    __builtin_amdgcn_sched_barrier(0);
-                }
+                for (int e = 0; e < 16 && kk + e < K; ++e) dst[e] = srcp[e];
             }
         }
-    } else if (n < N) {
-        // rows in pairs: the FP8 formats go through the two-at-a-time hardware converter (encode_fp8_rtne_pair)
-#pragma unroll
-        for (int kk = 0; kk < 8; kk += 2) {
-            const int64_t k = k0 + tk * 8 + kk;
-            u32x4 wa = {0u, 0u, 0u, 0u}, wb = {0u, 0u, 0u, 0u};
-            if (k < K) wa = *reinterpret_cast<const u32x4*>(base + k * a.row_stride + n);
-            if (k + 1 < K) wb = *reinterpret_cast<const u32x4*>(base + (k + 1) * a.row_stride + n);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const uint32_t worda = wa[j >> 1], wordb = wb[j >> 1];
-                const float ta = ((j & 1) ? __uint_as_float(worda & 0xFFFF0000u) : __uint_as_float(worda << 16)) * rho[j];
-                const float tb = ((j & 1) ? __uint_as_float(wordb & 0xFFFF0000u) : __uint_as_float(wordb << 16)) * rho[j];
-                uint32_t pair;
-                if constexpr (FMT == QMM_FMT_INT8) pair = encode_int8_rtne(ta) | (encode_int8_rtne(tb) << 8);
-                else pair = encode_fp8_rtne_pair<FMT>(ta, tb);
-                if (kk < 4) lo[j] |= pair << (8 * kk); else hi[j] |= pair << (8 * (kk - 4));
-            }
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        u32x2 v = {lo[j], hi[j]};
-        *reinterpret_cast<u32x2*>(&tile[(tn * 8 + j) * kTileRowBytes + tk * 8]) = v;
-    }
-    __syncthreads();
-    // 128 code rows x 8 pieces of 16 bytes = 1024 pieces, 4 per thread
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-        const int piece = it * kThreads + threadIdx.x;
-        const int row = piece >> 3, seg = piece & 7;
-        const int64_t nn = n0 + row, kk = k0 + seg * 16;
-        if (nn >= N || kk >= K) continue;
-        uint8_t* dst = a.codes + (b * N + nn) * K + kk;
-        const uint8_t* srcp = &tile[row * kTileRowBytes + seg * 16];
-        if (kk + 16 <= K && (K & 15) == 0) {
-            *reinterpret_cast<u32x4*>(dst) = *reinterpret_cast<const u32x4*>(srcp);
-        } else {
-            for (int e = 0; e < 16 && kk + e < K; ++e) dst[e] = srcp[e];
-        }
+        if (t + gridDim.x < tiles) __syncthreads();          // the tile and the step sizes are reused
     }
 }
 
-template <int FMT, int MODE> qmm_status launch(const qmm_tensor* x, const QArgs& a, hipStream_t s)
+// fold: the step sizes are formed by this pass from a.partial, else read from a.delta.
+template <int FMT, int MODE, bool FOLD> qmm_status launch(const qmm_tensor* x, const QArgs& a, hipStream_t s)
 {
     const bool bf16 = x->dtype == QMM_DT_BF16;
-    const bool aligned = aligned16(x->data) && (x->row_stride % 8 == 0) && (x->batch_stride % 8 == 0);
-    if (bf16 && aligned && x->contract_axis == 1 && (x->cols % 16 == 0) && aligned16(a.codes)) {
-        const int64_t nv = x->rows * (x->cols / 16);
-        quantize_rows_bf16x16<FMT, MODE><<<dim3((unsigned)((nv + kThreads - 1) / kThreads), (unsigned)x->batch), kThreads, 0, s>>>(a);
-    } else if (bf16 && aligned && x->contract_axis == 0 && (x->cols % 8 == 0) && aligned16(a.codes)) {
-        quantize_cols_bf16<FMT, MODE><<<dim3((unsigned)((x->cols + kTile - 1) / kTile), (unsigned)((x->rows + kTile - 1) / kTile),
-                                              (unsigned)x->batch), kThreads, 0, s>>>(a);
-    } else {
-        const int64_t n = x->rows * x->cols;
-        const dim3 grid((unsigned)((n + kThreads - 1) / kThreads), (unsigned)x->batch);
-        if (bf16) quantize_generic<uint16_t, FMT, MODE><<<grid, kThreads, 0, s>>>(a, x->contract_axis);
-        else quantize_generic<float, FMT, MODE><<<grid, kThreads, 0, s>>>(a, x->contract_axis);
+    if (x->contract_axis == 0) {
+        const int64_t tiles_k = (x->rows + kTileK - 1) / kTileK;
+        const bool wide = bf16 && tiles_k * (x->cols / 128) * x->batch >= 2048;
+        const int64_t tiles_n = wide ? (x->cols + 127) / 128 : (x->cols + 63) / 64, tiles = tiles_n * tiles_k;
+        const dim3 grid((unsigned)std::min<int64_t>(tiles, 1 << 23), (unsigned)x->batch);
+        if (wide) quantize_cols<uint16_t, FMT, MODE, FOLD, 128><<<grid, kThreads, 0, s>>>(a, tiles_n, tiles);
+        else if (bf16) quantize_cols<uint16_t, FMT, MODE, FOLD, 64><<<grid, kThreads, 0, s>>>(a, tiles_n, tiles);
+        else quantize_cols<float, FMT, MODE, FOLD, 64><<<grid, kThreads, 0, s>>>(a, tiles_n, tiles);
+        return launch_status();
     }
+    // a matrix that is dense with one step size is one long row
+    QArgs q = a;
+    if (q.channels == 1 && q.row_stride == q.cols) {
+        q.cols *= q.rows;
+        q.row_stride = q.cols;
+        q.rows = 1;
+    }
+    const bool aligned = aligned16(x->data) && (q.row_stride % 8 == 0 || q.rows == 1) && (x->batch_stride % 8 == 0 || x->batch == 1);
+    if (bf16 && aligned && (q.cols % 16 == 0) && aligned16(a.codes)) {
+        const int64_t nv = q.rows * (q.cols / 16);
+        quantize_rows_bf16x16<FMT, MODE, FOLD><<<dim3((unsigned)((nv + kThreads - 1) / kThreads), (unsigned)x->batch), kThreads, 0, s>>>(q);
+        return launch_status();
+    }
+    // rows go to wavefronts, a long row in pieces of 4 vectors a lane
+    int64_t pieces = 1;
+    if (q.rows == 1) {
+        const int64_t span = (int64_t)kWave * 4 * (bf16 ? 8 : 4);
+        pieces = std::max<int64_t>(1, (q.cols + span - 1) / span);
+    }
+    constexpr int kWaves = kThreads / kWave;
+    const int64_t blocks = std::min<int64_t>((q.rows * pieces + kWaves - 1) / kWaves, 65536);
+    const dim3 grid((unsigned)blocks, (unsigned)q.batch);
+    if (bf16) quantize_rows<uint16_t, FMT, MODE, FOLD><<<grid, kThreads, 0, s>>>(q, pieces);
+    else quantize_rows<float, FMT, MODE, FOLD><<<grid, kThreads, 0, s>>>(q, pieces);
     return launch_status();
 }
 
 template <int FMT> qmm_status launch_mode(const qmm_tensor* x, const QArgs& a, qmm_round mode, hipStream_t s)
 {
-    return mode == QMM_ROUND_RTNE ? launch<FMT, QMM_ROUND_RTNE>(x, a, s) : launch<FMT, QMM_ROUND_STOCHASTIC>(x, a, s);
+    return mode == QMM_ROUND_RTNE ? launch<FMT, QMM_ROUND_RTNE, false>(x, a, s) : launch<FMT, QMM_ROUND_STOCHASTIC, false>(x, a, s);
+}
+
+// One step size per row, every matrix a scale group of its own, rows that fit the registers of one wavefront (8 vectors a
+// lane: 4096 bfloat16 / 2048 binary32 elements) or of the four of a workgroup (4 vectors a lane: 8192 / 4096).
+bool one_pass(const qmm_tensor* x, const qmm_granularity* g)
+{
+    return g->per_channel && x->contract_axis == 1 && x->batch == g->batch_groups && g->batch_inner <= 1 &&
+           x->cols <= (x->dtype == QMM_DT_BF16 ? 8192 : 4096);
+}
+template <typename T, int FMT, int MODE> qmm_status launch_one_pass(const QArgs& a, hipStream_t s)
+{
+    constexpr int V = Vec<T>::V;
+    const int64_t rows = a.batch * a.rows;
+    const int64_t nvec = (a.cols + V - 1) / V;
+    auto blocks = [&](int lpr) { return (unsigned)std::min<int64_t>((rows + kThreads / lpr - 1) / (kThreads / lpr), 1 << 23); };
+    // lanes x vectors with little idle: 96 and 384 vectors (768 and 3072 bfloat16 columns) in three and six rather than four
+    // and eight (stochastic rounding is bound by the generator's multiplies, and idle lanes wait for them)
+    auto run = [&](auto lpr, auto nv) { scale_quantize_rows<T, FMT, MODE, lpr.value, nv.value><<<blocks(lpr.value), kThreads, 0, s>>>(a); };
+    if (nvec <= 8) run(std::integral_constant<int, 8>{}, std::integral_constant<int, 1>{});
+    else if (nvec <= 16) run(std::integral_constant<int, 16>{}, std::integral_constant<int, 1>{});
+    else if (nvec <= 32) run(std::integral_constant<int, 32>{}, std::integral_constant<int, 1>{});
+    else if (nvec <= 64) run(std::integral_constant<int, 64>{}, std::integral_constant<int, 1>{});
+    else if (nvec <= 96) run(std::integral_constant<int, 32>{}, std::integral_constant<int, 3>{});
+    else if (nvec <= 128) run(std::integral_constant<int, 64>{}, std::integral_constant<int, 2>{});
+    else if (nvec <= 192) run(std::integral_constant<int, 64>{}, std::integral_constant<int, 3>{});
+    else if (nvec <= 256) run(std::integral_constant<int, 64>{}, std::integral_constant<int, 4>{});
+    else if (nvec <= 384) run(std::integral_constant<int, 64>{}, std::integral_constant<int, 6>{});
+    else if (nvec <= 512) run(std::integral_constant<int, 64>{}, std::integral_constant<int, 8>{});
+    else run(std::integral_constant<int, 256>{}, std::integral_constant<int, 4>{});
+    return launch_status();
+}
+template <int FMT> qmm_status launch_one_pass_mode(const qmm_tensor* x, const QArgs& a, qmm_round mode, hipStream_t s)
+{
+    if (x->dtype == QMM_DT_BF16)
+        return mode == QMM_ROUND_RTNE ? launch_one_pass<uint16_t, FMT, QMM_ROUND_RTNE>(a, s) : launch_one_pass<uint16_t, FMT, QMM_ROUND_STOCHASTIC>(a, s);
+    return mode == QMM_ROUND_RTNE ? launch_one_pass<float, FMT, QMM_ROUND_RTNE>(a, s) : launch_one_pass<float, FMT, QMM_ROUND_STOCHASTIC>(a, s);
+}
+template <int FMT> qmm_status launch_fold_mode(const qmm_tensor* x, const QArgs& a, qmm_round mode, hipStream_t s)
+{
+    return mode == QMM_ROUND_RTNE ? launch<FMT, QMM_ROUND_RTNE, true>(x, a, s) : launch<FMT, QMM_ROUND_STOCHASTIC, true>(x, a, s);
 }
 
 }  // namespace
@@ -280,6 +538,21 @@ qmm_status quantize_check(const qmm_tensor* x, qmm_format fmt, const qmm_granula
     if (!x->data || !delta || !codes_out) return QMM_ERR_NULL;
     return QMM_OK;
 }
+
+QArgs quantize_args(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, float* delta, uint64_t seed, uint64_t offset,
+                    uint8_t* codes_out)
+{
+    QArgs a{};
+    a.x = x->data; a.delta = delta; a.codes = codes_out;
+    a.batch = x->batch; a.rows = x->rows; a.cols = x->cols;
+    a.batch_stride = x->batch_stride; a.row_stride = x->row_stride;
+    a.groups = g->batch_groups;
+    a.inner = g->batch_inner > 0 ? g->batch_inner : 1;
+    a.channels = g->per_channel ? (x->contract_axis == 1 ? x->rows : x->cols) : 1;
+    a.seed = seed; a.offset = offset;
+    a.qmax = host_qmax(fmt);
+    return a;
+}
 }  // namespace
 
 extern "C" qmm_status qmm_quantize(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, const float* delta,
@@ -289,15 +562,71 @@ extern "C" qmm_status qmm_quantize(const qmm_tensor* x, qmm_format fmt, const qm
     if (chk != QMM_OK) return chk;
     if (x->batch * x->rows * x->cols == 0) return QMM_OK;
 
-    QArgs a;
-    a.x = x->data; a.delta = delta; a.codes = codes_out;
-    a.batch = x->batch; a.rows = x->rows; a.cols = x->cols;
-    a.batch_stride = x->batch_stride; a.row_stride = x->row_stride;
-    a.groups = g->batch_groups;
-    a.inner = g->batch_inner > 0 ? g->batch_inner : 1;
-    a.channels = g->per_channel ? (x->contract_axis == 1 ? x->rows : x->cols) : 1;
-    a.seed = seed; a.offset = offset;
+    const QArgs a = quantize_args(x, fmt, g, const_cast<float*>(delta), seed, offset, codes_out);
     hipStream_t s = as_stream(stream);
+    switch (fmt) {
+    case QMM_FMT_INT8: return launch_mode<QMM_FMT_INT8>(x, a, mode, s);
+    case QMM_FMT_E4M3: return launch_mode<QMM_FMT_E4M3>(x, a, mode, s);
+    default: return launch_mode<QMM_FMT_E5M2>(x, a, mode, s);
+    }
+}
+
+extern "C" size_t qmm_scale_quantize_workspace_size(const qmm_tensor* x, const qmm_granularity* g)
+{
+    if (!x || !g || one_pass(x, g)) return 0;
+    return qmm_scale_workspace_size(x, g);
+}
+
+extern "C" qmm_status qmm_scale_quantize(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, qmm_round mode,
+                                         uint64_t seed, uint64_t offset, float* delta_out, uint8_t* codes_out,
+                                         void* workspace, size_t workspace_bytes, void* stream)
+{
+    // the arguments of both steps first; a call that needs no workspace is checked against one of full size
+    if (!x || !g) return QMM_ERR_NULL;
+    const bool single = one_pass(x, g);
+    qmm_status st = scale_arguments(x, fmt, g, delta_out, single ? reinterpret_cast<const void*>(uintptr_t(256)) : workspace,
+                                    single ? ~size_t(0) : workspace_bytes);
+    if (st != QMM_OK) return st;
+    st = quantize_check(x, fmt, g, delta_out, mode, codes_out);
+    if (st != QMM_OK) return st;
+    if (x->batch * x->rows * x->cols == 0) {       // no codes; the groups of an empty tensor still get their step size
+        if (qmm_num_scales(x, g) == 0) return QMM_OK;
+        const ScalePartials none{0, 0, g->per_channel ? (x->contract_axis == 1 ? x->rows : x->cols) : 1, false};
+        return scale_fold(none, nullptr, fmt, g, delta_out, as_stream(stream));
+    }
+    hipStream_t s = as_stream(stream);
+    QArgs a = quantize_args(x, fmt, g, delta_out, seed, offset, codes_out);
+    if (single) {
+        switch (fmt) {
+        case QMM_FMT_INT8: return launch_one_pass_mode<QMM_FMT_INT8>(x, a, mode, s);
+        case QMM_FMT_E4M3: return launch_one_pass_mode<QMM_FMT_E4M3>(x, a, mode, s);
+        default: return launch_one_pass_mode<QMM_FMT_E5M2>(x, a, mode, s);
+        }
+    }
+    // The quantize pass folds the partial maxima when every group has a matrix (its first workgroup writes the step size), a
+    // group's partial maxima are few -- each workgroup fetches them -- and the tensor is of at most 2^24 elements: per
+    // workgroup the fold costs about what it fetches, against one small kernel and its launch.  (bfloat16, one step size per
+    // column, fold / small kernel apart from its launch: 4096 x 3072 +1.7 / 3.8 us, 16384 x 3072 +11 / 3.8 us; one step size,
+    // 256 x 768: +0.6 / 1.4 us.)  One step size per column: one matrix per group.
+    uint32_t* partial = static_cast<uint32_t*>(workspace);
+    const size_t words = qmm_scale_workspace_size(x, g) / sizeof(uint32_t);
+    const bool all_groups = (a.groups - 1) * a.inner < a.batch;
+    const bool small = x->batch * x->rows * x->cols <= (int64_t(1) << 24);
+    bool fold;
+    if (a.channels == 1) fold = small && all_groups && (int64_t)words <= kFoldMax * a.groups;
+    else fold = small && x->contract_axis == 0 && a.groups == a.batch && a.inner == 1;
+    ScalePartials pp;
+    st = scale_partials(x, fmt, g, delta_out, partial, fold, &pp, s);
+    if (st != QMM_OK) return st;
+    if (!pp.done && !fold) { st = scale_fold(pp, partial, fmt, g, delta_out, s); if (st != QMM_OK) return st; }
+    if (fold && !pp.done) {
+        a.partial = partial; a.P = pp.P; a.fold_total = (int)(pp.batch * pp.P);
+        switch (fmt) {
+        case QMM_FMT_INT8: return launch_fold_mode<QMM_FMT_INT8>(x, a, mode, s);
+        case QMM_FMT_E4M3: return launch_fold_mode<QMM_FMT_E4M3>(x, a, mode, s);
+        default: return launch_fold_mode<QMM_FMT_E5M2>(x, a, mode, s);
+        }
+    }
     switch (fmt) {
     case QMM_FMT_INT8: return launch_mode<QMM_FMT_INT8>(x, a, mode, s);
     case QMM_FMT_E4M3: return launch_mode<QMM_FMT_E4M3>(x, a, mode, s);

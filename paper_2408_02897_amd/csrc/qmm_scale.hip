@@ -16,10 +16,12 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kMaxFlatBlocks = 1024;   // 4 workgroups per CU on 256 CUs; 4 partials per thread in the fold
-constexpr int kColSlabRows = 128;      // rows folded by one workgroup in the column-group kernel
+constexpr int kColSlabRows = 128;      // rows folded by one workgroup in the column-group kernel, at least
+constexpr int kMaxColSlabs = 32;       // and at most this many slabs: what the quantize pass can fold on its way (qmm_quantize.hip)
 
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(2)));   // global memory takes vector loads at any element boundary
 
 QMM_DEV uint32_t block_max_u32(uint32_t v)
 {
@@ -50,6 +52,51 @@ QMM_DEV uint32_t finish_bf16(const u16x2 (&m)[4])
     return r << 16;   // bfloat16 magnitude -> binary32 magnitude bits
 }
 
+template <typename T> QMM_DEV uint32_t mag_bits(T v);
+template <> QMM_DEV uint32_t mag_bits<uint16_t>(uint16_t v) { return ((uint32_t)v & 0x7FFFu) << 16; }
+template <> QMM_DEV uint32_t mag_bits<float>(float v) { return __float_as_uint(v) & 0x7FFFFFFFu; }
+
+// Running maxima over 16-byte vectors (8 bfloat16 or 4 binary32 elements), kept per position.
+template <typename T> struct VecMax;
+template <> struct VecMax<uint16_t> {
+    static constexpr int V = 8;
+    u16x2 m[4] = {};
+    QMM_DEV void fold(u32x4 w) { fold_bf16x8(w, m); }
+    QMM_DEV uint32_t finish() const { return finish_bf16(m); }
+    QMM_DEV void words(uint32_t (&out)[4]) const
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[i] = __builtin_bit_cast(uint32_t, m[i]);
+    }
+    QMM_DEV void fold_words(const uint32_t (&in)[4])
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m[i] = __builtin_elementwise_max(m[i], __builtin_bit_cast(u16x2, in[i]));
+    }
+    QMM_DEV uint32_t at(int e) const { return (uint32_t)m[e >> 1][e & 1] << 16; }
+};
+template <> struct VecMax<float> {
+    static constexpr int V = 4;
+    uint32_t m[4] = {};
+    QMM_DEV void fold(u32x4 w)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m[i] = max(m[i], w[i] & 0x7FFFFFFFu);
+    }
+    QMM_DEV uint32_t finish() const { return max(max(m[0], m[1]), max(m[2], m[3])); }
+    QMM_DEV void words(uint32_t (&out)[4]) const
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[i] = m[i];
+    }
+    QMM_DEV void fold_words(const uint32_t (&in)[4])
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m[i] = max(m[i], in[i]);
+    }
+    QMM_DEV uint32_t at(int e) const { return m[e]; }
+};
+
 // The fold of a tensor's partial maxima by the workgroup that arrived last: all of them are one scale group.
 QMM_DEV void fold_all_partials(const uint32_t* partial, int64_t count, float qmax, float* delta)
 {
@@ -65,14 +112,17 @@ QMM_DEV void fold_all_partials(const uint32_t* partial, int64_t count, float qma
     if (threadIdx.x == 0) delta[0] = delta_from_absmax_bits(m, qmax);
 }
 
-// Dense matrix (row_stride == cols), bfloat16, 16-byte vectors: grid (nblk, batch).  With `slot` (one scale group
-// for the whole batch) the workgroup that arrives last folds the partial maxima and writes the step size.
-__global__ void __launch_bounds__(kThreads)
-absmax_flat_bf16(const uint16_t* __restrict__ x, int64_t batch_stride, int64_t nvec, uint32_t* __restrict__ partial,
-                 uint32_t* __restrict__ slot, float qmax, float* __restrict__ delta)
+// Dense matrix (row_stride == cols) from a 16-byte boundary on, n elements: grid (nblk, batch).  With `slot` (one scale
+// group for the whole batch) the workgroup that arrives last folds the partial maxima and writes the step size.
+template <typename T> __global__ void __launch_bounds__(kThreads)
+absmax_flat(const T* __restrict__ x, int64_t batch_stride, int64_t n, uint32_t* __restrict__ partial,
+            uint32_t* __restrict__ slot, float qmax, float* __restrict__ delta)
 {
-    const u32x4* p = reinterpret_cast<const u32x4*>(x + (int64_t)blockIdx.y * batch_stride);
-    u16x2 m[4] = {};
+    constexpr int V = VecMax<T>::V;
+    const T* base = x + (int64_t)blockIdx.y * batch_stride;
+    const u32x4* p = reinterpret_cast<const u32x4*>(base);
+    const int64_t nvec = n / V;
+    VecMax<T> m;
     // A workgroup takes four consecutive 4 KB pieces per trip and the grid sweeps the tensor front to back: the
     // four loads a thread has in flight are then neighbours in memory.  (With the loads a whole grid stride apart
     // the same kernel reads a large tensor up to 25 % slower: four distant streams per thread.)  Ordinary loads on
@@ -83,14 +133,16 @@ absmax_flat_bf16(const uint16_t* __restrict__ x, int64_t batch_stride, int64_t n
     for (; i + 3 * kThreads < nvec; i += stride) {
         const u32x4 a = p[i], b = p[i + kThreads];
         const u32x4 c = p[i + 2 * kThreads], d = p[i + 3 * kThreads];
-        fold_bf16x8(a, m); fold_bf16x8(b, m); fold_bf16x8(c, m); fold_bf16x8(d, m);
+        m.fold(a); m.fold(b); m.fold(c); m.fold(d);
     }
-    // the ragged end: at most three pieces of one workgroup
+    // the ragged end: at most three pieces of one workgroup, and the elements past the last whole vector
     if (i < nvec) {
         for (int u = 0; u < 4; ++u)
-            if (i + u * kThreads < nvec) fold_bf16x8(p[i + u * kThreads], m);
+            if (i + u * kThreads < nvec) m.fold(p[i + u * kThreads]);
     }
-    const uint32_t r = block_max_u32(finish_bf16(m));
+    uint32_t r = m.finish();
+    if (blockIdx.x == 0 && threadIdx.x < (unsigned)(n % V)) r = max(r, mag_bits<T>(base[nvec * V + threadIdx.x]));
+    r = block_max_u32(r);
     const unsigned id = blockIdx.y * gridDim.x + blockIdx.x, total = gridDim.x * gridDim.y;
     if (threadIdx.x == 0) {
         if (slot) publish_u32(partial + id, r); else partial[id] = r;
@@ -143,10 +195,6 @@ absmax_flat_multi(MultiFlat a)
     }
 }
 
-template <typename T> QMM_DEV uint32_t mag_bits(T v);
-template <> QMM_DEV uint32_t mag_bits<uint16_t>(uint16_t v) { return ((uint32_t)v & 0x7FFFu) << 16; }
-template <> QMM_DEV uint32_t mag_bits<float>(float v) { return __float_as_uint(v) & 0x7FFFFFFFu; }
-
 // One wavefront per (matrix, row): partial[b*rows + r] = absmax of the row.  Any stride, any dtype.
 template <typename T> __global__ void __launch_bounds__(kThreads)
 absmax_rows(const T* __restrict__ x, int64_t batch_stride, int64_t row_stride, int64_t rows, int64_t cols,
@@ -157,19 +205,12 @@ absmax_rows(const T* __restrict__ x, int64_t batch_stride, int64_t row_stride, i
     const int64_t b = wr / rows, r = wr % rows;
     const T* p = x + b * batch_stride + r * row_stride;
     const int lane = threadIdx.x & (kWave - 1);
-    uint32_t m = 0;
-    if constexpr (sizeof(T) == 2) {
-        if ((cols & 7) == 0 && (reinterpret_cast<uintptr_t>(p) & 15u) == 0) {
-            const u32x4* pv = reinterpret_cast<const u32x4*>(p);
-            u16x2 mm[4] = {};
-            for (int64_t i = lane; i < cols / 8; i += kWave) fold_bf16x8(pv[i], mm);
-            m = finish_bf16(mm);
-        } else {
-            for (int64_t i = lane; i < cols; i += kWave) m = max(m, mag_bits<T>(p[i]));
-        }
-    } else {
-        for (int64_t i = lane; i < cols; i += kWave) m = max(m, mag_bits<T>(p[i]));
-    }
+    constexpr int V = VecMax<T>::V;
+    VecMax<T> mm;
+    const int64_t nvec = cols / V;
+    for (int64_t i = lane; i < nvec; i += kWave) mm.fold(*reinterpret_cast<const u32x4_any*>(p + i * V));
+    uint32_t m = mm.finish();
+    if (lane < (int)(cols - nvec * V)) m = max(m, mag_bits<T>(p[nvec * V + lane]));
     m = wave_max_u32(m);
     // delta != NULL: every row is a scale group of its own (one step size per row, one matrix per batch group), so
     // the row's maximum is final and the step size is written here, without the second kernel
@@ -199,60 +240,59 @@ absmax_rows_short(const uint16_t* __restrict__ x, int64_t batch_stride, int64_t 
     if (v == 0 && row < total_rows) { if (delta) delta[row] = delta_from_absmax_bits(m, qmax); else partial[row] = m; }
 }
 
-// Column groups: workgroup = 32 column-vectors (256 columns) x 8 row lanes over a slab of rows.
-// partial[(b*nslab + slab)*cols + c].  bfloat16, cols % 8 == 0, 16-byte aligned rows.
-__global__ void __launch_bounds__(kThreads)
-absmax_cols_bf16(const uint16_t* __restrict__ x, int64_t batch_stride, int64_t row_stride, int64_t rows, int64_t cols,
-                 uint32_t* __restrict__ partial)
+// Column groups: workgroup = 16 column-vectors (128 bfloat16 or 64 binary32 columns: 256 contiguous bytes of every row)
+// x 16 row lanes over a slab of rows.  partial[(b*nslab + slab)*cols + c].  Any extent, stride and alignment: a vector
+// that straddles the last column is read element by element.
+template <typename T> __global__ void __launch_bounds__(kThreads)
+absmax_cols(const T* __restrict__ x, int64_t batch_stride, int64_t row_stride, int64_t rows, int64_t cols, int64_t slab_rows,
+            uint32_t* __restrict__ partial)
 {
-    __shared__ uint32_t s[8][32][4];
-    const int cv = threadIdx.x & 31, rl = threadIdx.x >> 5;
-    const int64_t vcol = (int64_t)blockIdx.x * 32 + cv;
-    const int64_t r0 = (int64_t)blockIdx.y * kColSlabRows;
-    const int64_t r1 = min(rows, r0 + (int64_t)kColSlabRows);
-    u16x2 m[4] = {};
-    if (vcol * 8 < cols) {
-        const uint16_t* base = x + (int64_t)blockIdx.z * batch_stride + vcol * 8;
+    constexpr int V = VecMax<T>::V, RL = kThreads / 16;
+    __shared__ uint32_t s[RL][16][5];            // (five words: a column vector's sixteen row lanes fall into different banks)
+    const int cv = threadIdx.x & 15, rl = threadIdx.x >> 4;
+    const int64_t c0 = ((int64_t)blockIdx.x * 16 + cv) * V;
+    const int64_t r0 = (int64_t)blockIdx.y * slab_rows;
+    const int64_t r1 = min(rows, r0 + slab_rows);
+    VecMax<T> m;
+    const T* base = x + (int64_t)blockIdx.z * batch_stride + c0;
+    if (c0 + V <= cols) {
+        auto row = [&](int64_t r) { return *reinterpret_cast<const u32x4_any*>(base + r * row_stride); };
         int64_t r = r0 + rl;
         // four rows per trip: the loads are in flight together
-        for (; r + 24 < r1; r += 32) {
-            const u32x4 a = *reinterpret_cast<const u32x4*>(base + r * row_stride);
-            const u32x4 b = *reinterpret_cast<const u32x4*>(base + (r + 8) * row_stride);
-            const u32x4 c = *reinterpret_cast<const u32x4*>(base + (r + 16) * row_stride);
-            const u32x4 d = *reinterpret_cast<const u32x4*>(base + (r + 24) * row_stride);
-            fold_bf16x8(a, m); fold_bf16x8(b, m); fold_bf16x8(c, m); fold_bf16x8(d, m);
+        for (; r + 3 * RL < r1; r += 4 * RL) {
+            const u32x4 a = row(r), b = row(r + RL), c = row(r + 2 * RL), d = row(r + 3 * RL);
+            m.fold(a); m.fold(b); m.fold(c); m.fold(d);
         }
-        for (; r < r1; r += 8)
-            fold_bf16x8(*reinterpret_cast<const u32x4*>(base + r * row_stride), m);
-    }
+        for (; r < r1; r += RL) m.fold(row(r));
+    } else if (c0 < cols) {
+        const int left = (int)(cols - c0);
+        for (int64_t r = r0 + rl; r < r1; r += RL) {
+            u32x4 w = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) s[rl][cv][i] = __builtin_bit_cast(uint32_t, m[i]);
+            for (int e = 0; e < V; ++e)
+                if (e < left) {
+                    if constexpr (sizeof(T) == 2) w[e >> 1] |= (uint32_t)base[r * row_stride + e] << (16 * (e & 1));
+                    else w[e] = __float_as_uint(base[r * row_stride + e]);
+                }
+            m.fold(w);
+        }
+    }
+    uint32_t w[4];
+    m.words(w);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s[rl][cv][i] = w[i];
     __syncthreads();
-    if (rl == 0 && vcol * 8 < cols) {
+    if (rl == 0 && c0 < cols) {
+        for (int k = 1; k < RL; ++k) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            u16x2 a = m[i];
-            for (int k = 1; k < 8; ++k) a = __builtin_elementwise_max(a, __builtin_bit_cast(u16x2, s[k][cv][i]));
-            uint32_t* out = partial + ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * cols + vcol * 8 + 2 * i;
-            out[0] = (uint32_t)a[0] << 16;
-            out[1] = (uint32_t)a[1] << 16;
+            for (int i = 0; i < 4; ++i) w[i] = s[k][cv][i];
+            m.fold_words(w);
         }
+        uint32_t* out = partial + ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * cols + c0;
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+            if (c0 + e < cols) out[e] = m.at(e);
     }
-}
-
-// Generic column groups (any dtype / alignment): one thread per column over a slab of rows.
-template <typename T> __global__ void __launch_bounds__(kThreads)
-absmax_cols_generic(const T* __restrict__ x, int64_t batch_stride, int64_t row_stride, int64_t rows, int64_t cols,
-                    uint32_t* __restrict__ partial)
-{
-    const int64_t c = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (c >= cols) return;
-    const int64_t r0 = (int64_t)blockIdx.y * kColSlabRows;
-    const int64_t r1 = min(rows, r0 + (int64_t)kColSlabRows);
-    const T* base = x + (int64_t)blockIdx.z * batch_stride + c;
-    uint32_t m = 0;
-    for (int64_t r = r0; r < r1; ++r) m = max(m, mag_bits<T>(base[r * row_stride]));
-    partial[((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * cols + c] = m;
 }
 
 // Fold partial[b][P][C] over the matrices b of group g, (b / inner) % G == g, and over p; then delta = absmax / qmax.
@@ -324,10 +364,11 @@ finalize_channels(const uint32_t* __restrict__ partial, int64_t batch, int64_t P
 }
 
 struct Plan {
-    enum Kind { FLAT, ROWS, COLS_VEC, COLS_GENERIC } kind;
-    int64_t P;        // partials per matrix (per channel for the column kinds)
+    enum Kind { FLAT, ROWS, COLS } kind;
+    int64_t P;        // partials per matrix (per channel for the column kind)
     int64_t C;        // channels
     int flat_blocks;
+    int64_t slab_rows;
     bool vec;         // bfloat16 with 16-byte aligned rows of whole 8-element vectors
 };
 
@@ -344,24 +385,33 @@ bool valid_tensor(const qmm_tensor* x, qmm_status* st)
     return true;
 }
 
+// A batch whose matrices lie back to back and share one step size is one matrix.
+qmm_tensor one_matrix(const qmm_tensor* x, const qmm_granularity* g)
+{
+    qmm_tensor t = *x;
+    if (!g->per_channel && g->batch_groups == 1 && t.batch > 1 && t.row_stride == t.cols && t.batch_stride == t.rows * t.cols) {
+        t.rows *= t.batch;
+        t.batch = 1;
+    }
+    return t;
+}
+
 Plan make_plan(const qmm_tensor* x, const qmm_granularity* g)
 {
     Plan p{};
     const bool bf16 = x->dtype == QMM_DT_BF16;
-    const bool vec_ok = bf16 && aligned16(x->data) && (x->cols % 8 == 0) && (x->row_stride % 8 == 0) &&
-                        (x->batch_stride % 8 == 0);
-    p.vec = vec_ok;
+    const int64_t es = bf16 ? 2 : 4;
+    const bool base_ok = aligned16(x->data) && (x->batch <= 1 || x->batch_stride * es % 16 == 0);
+    p.vec = bf16 && base_ok && (x->cols % 8 == 0) && (x->row_stride % 8 == 0);
     if (!g->per_channel) {
         p.C = 1;
         const int64_t n = x->rows * x->cols;
-        if (vec_ok && x->row_stride == x->cols && n > 0) {
+        if (base_ok && (x->row_stride == x->cols || x->rows == 1) && n > 0) {
             p.kind = Plan::FLAT;
-            const int64_t nvec = n / 8;
-            int64_t nb = (nvec + (int64_t)kThreads * 4 - 1) / ((int64_t)kThreads * 4);
+            const int64_t trips = (n * es + kThreads * 64 - 1) / (kThreads * 64);       // pieces of 16 KB
             const int64_t cap = x->batch > 1 ? (kMaxFlatBlocks + x->batch - 1) / x->batch : kMaxFlatBlocks;
-            nb = nb < 1 ? 1 : (nb > cap ? cap : nb);
-            p.flat_blocks = (int)nb;
-            p.P = nb;
+            p.flat_blocks = (int)std::min(trips, cap);
+            p.P = p.flat_blocks;
         } else {
             p.kind = Plan::ROWS;
             p.P = x->rows;
@@ -371,8 +421,9 @@ Plan make_plan(const qmm_tensor* x, const qmm_granularity* g)
         p.P = 1;
         p.C = x->rows;
     } else {
-        p.kind = vec_ok ? Plan::COLS_VEC : Plan::COLS_GENERIC;
-        p.P = (x->rows + kColSlabRows - 1) / kColSlabRows;
+        p.kind = Plan::COLS;
+        p.slab_rows = std::max<int64_t>(kColSlabRows, (x->rows + kMaxColSlabs - 1) / kMaxColSlabs);
+        p.P = (x->rows + p.slab_rows - 1) / p.slab_rows;
         p.C = x->cols;
     }
     return p;
@@ -394,8 +445,9 @@ extern "C" size_t qmm_scale_workspace_size(const qmm_tensor* x, const qmm_granul
 {
     qmm_status st;
     if (!g || !valid_tensor(x, &st)) return 0;
-    const Plan p = make_plan(x, g);
-    const int64_t words = x->batch * p.P * p.C;
+    const qmm_tensor t = one_matrix(x, g);
+    const Plan p = make_plan(&t, g);
+    const int64_t words = t.batch * p.P * p.C;
     return (size_t)(words > 0 ? words : 1) * sizeof(uint32_t);
 }
 
@@ -418,89 +470,109 @@ qmm_status scale_check(const qmm_tensor* x, qmm_format fmt, const qmm_granularit
 }
 }  // namespace
 
+namespace qmm {
+// The first half of qmm_scale on checked arguments: partial maxima to `partial`, laid out [batch][P][C] (`out` says how).
+// out->done: the step sizes have been written as well.  `fold_here`: the caller folds the partial maxima itself, so a
+// large tensor's last workgroup need not.
+qmm_status scale_partials(const qmm_tensor* x0, qmm_format fmt, const qmm_granularity* g, float* delta_out, uint32_t* partial,
+                          bool fold_here, ScalePartials* out, hipStream_t s)
+{
+    const qmm_tensor t = one_matrix(x0, g);
+    const qmm_tensor* x = &t;
+    const Plan p = make_plan(x, g);
+    const float qmax = host_qmax(fmt);
+    const bool bf16 = x->dtype == QMM_DT_BF16;
+    const int64_t nelem = x->batch * x->rows * x->cols;
+    out->batch = nelem > 0 ? x->batch : 0;        // an empty tensor: fold over no matrices, every group gets delta = 1
+    out->P = p.P; out->C = p.C;
+    out->done = false;
+    if (nelem == 0) return QMM_OK;
+    switch (p.kind) {
+    case Plan::FLAT: {
+        // One scale group for the whole batch and a large tensor: one launch, the workgroup that arrives last folds.
+        // (Publishing, counting and the coherent reads of the fold are a chain of device-wide round trips of
+        // 2-3 us each: about 11 us for a tensor of any size up to 32 MB, against 9-10 us for two small launches;
+        // from 32 MB on the single launch wins, 25 us against 27 us at 134 MB.)
+        uint32_t* slot = nullptr;
+        if (!fold_here && g->batch_groups == 1 && nelem >= (int64_t(1) << 24) && arrival_slots(1, &slot) != QMM_OK) slot = nullptr;
+        const dim3 grid(p.flat_blocks, (unsigned)x->batch);
+        const int64_t n = x->rows * x->cols;
+        if (bf16) absmax_flat<uint16_t><<<grid, kThreads, 0, s>>>(static_cast<const uint16_t*>(x->data), x->batch_stride, n, partial, slot, qmax, delta_out);
+        else absmax_flat<float><<<grid, kThreads, 0, s>>>(static_cast<const float*>(x->data), x->batch_stride, n, partial, slot, qmax, delta_out);
+        out->done = slot != nullptr;
+        break;
+    }
+    case Plan::ROWS: {
+        // one step size per row with every matrix a batch group of its own: a row's maximum is its group's maximum
+        const bool rows_are_groups = g->per_channel && x->batch == g->batch_groups && g->batch_inner <= 1;
+        const int64_t total = x->batch * x->rows;
+        float* direct = rows_are_groups ? delta_out : nullptr;
+        const unsigned nb = (unsigned)((total + kThreads / kWave - 1) / (kThreads / kWave));
+        if (p.vec && x->cols <= 256) {
+            const uint16_t* xp = static_cast<const uint16_t*>(x->data);
+            const int nvec = (int)(x->cols / 8);
+            const int lpr = nvec <= 1 ? 1 : nvec <= 2 ? 2 : nvec <= 4 ? 4 : nvec <= 8 ? 8 : nvec <= 16 ? 16 : 32;
+            const int64_t waves = (total + kWave / lpr - 1) / (kWave / lpr);
+            const unsigned nbs = (unsigned)((waves + kThreads / kWave - 1) / (kThreads / kWave));
+#define QMM_ROWS_SHORT(L) absmax_rows_short<L><<<nbs, kThreads, 0, s>>>(xp, x->batch_stride, x->row_stride, x->rows, x->cols, total, partial, qmax, direct)
+            if (lpr == 1) QMM_ROWS_SHORT(1); else if (lpr == 2) QMM_ROWS_SHORT(2); else if (lpr == 4) QMM_ROWS_SHORT(4);
+            else if (lpr == 8) QMM_ROWS_SHORT(8); else if (lpr == 16) QMM_ROWS_SHORT(16); else QMM_ROWS_SHORT(32);
+#undef QMM_ROWS_SHORT
+        } else if (bf16)
+            absmax_rows<uint16_t><<<nb, kThreads, 0, s>>>(static_cast<const uint16_t*>(x->data), x->batch_stride,
+                                                           x->row_stride, x->rows, x->cols, total, partial, qmax, direct);
+        else
+            absmax_rows<float><<<nb, kThreads, 0, s>>>(static_cast<const float*>(x->data), x->batch_stride,
+                                                        x->row_stride, x->rows, x->cols, total, partial, qmax, direct);
+        out->done = rows_are_groups;
+        break;
+    }
+    case Plan::COLS: {
+        const int64_t cols_per_block = bf16 ? 128 : 64;
+        const dim3 grid((unsigned)((x->cols + cols_per_block - 1) / cols_per_block), (unsigned)p.P, (unsigned)x->batch);
+        if (bf16)
+            absmax_cols<uint16_t><<<grid, kThreads, 0, s>>>(static_cast<const uint16_t*>(x->data), x->batch_stride,
+                                                             x->row_stride, x->rows, x->cols, p.slab_rows, partial);
+        else
+            absmax_cols<float><<<grid, kThreads, 0, s>>>(static_cast<const float*>(x->data), x->batch_stride,
+                                                          x->row_stride, x->rows, x->cols, p.slab_rows, partial);
+        break;
+    }
+    }
+    return launch_status();
+}
+
+// The second half: partial maxima -> step sizes.
+qmm_status scale_fold(const ScalePartials& pp, const uint32_t* partial, qmm_format fmt, const qmm_granularity* g,
+                      float* delta_out, hipStream_t s)
+{
+    const int64_t G = g->batch_groups, inner = g->batch_inner > 0 ? g->batch_inner : 1;
+    if (pp.C == 1)
+        finalize_single<<<(unsigned)G, kThreads, 0, s>>>(partial, pp.batch, pp.batch > 0 ? pp.P : 0, G, inner, host_qmax(fmt), delta_out);
+    else
+        finalize_channels<<<dim3((unsigned)((pp.C + 31) / 32), (unsigned)G), kThreads, 0, s>>>(
+            partial, pp.batch, pp.batch > 0 ? pp.P : 0, pp.C, G, inner, host_qmax(fmt), delta_out);
+    return launch_status();
+}
+
+qmm_status scale_arguments(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, const float* delta_out,
+                           const void* workspace, size_t workspace_bytes)
+{
+    return scale_check(x, fmt, g, delta_out, workspace, workspace_bytes);
+}
+}  // namespace qmm
+
 extern "C" qmm_status qmm_scale(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, float* delta_out,
                                 void* workspace, size_t workspace_bytes, void* stream)
 {
     const qmm_status chk = scale_check(x, fmt, g, delta_out, workspace, workspace_bytes);
     if (chk != QMM_OK) return chk;
     if (qmm_num_scales(x, g) == 0) return QMM_OK;
-
     hipStream_t s = as_stream(stream);
     uint32_t* partial = static_cast<uint32_t*>(workspace);
-    const Plan p = make_plan(x, g);
-    const float qmax = fmt == QMM_FMT_INT8 ? 127.0f : (fmt == QMM_FMT_E4M3 ? 448.0f : 57344.0f);
-    const bool bf16 = x->dtype == QMM_DT_BF16;
-    const int64_t nelem = x->batch * x->rows * x->cols;
-    const int64_t C = p.C;
-    int64_t P = p.P;
-
-    // one step size per row with every matrix a batch group of its own: a row's maximum is its group's maximum
-    const bool rows_are_groups = nelem > 0 && p.kind == Plan::ROWS && g->per_channel && x->contract_axis == 1 && p.P == 1 &&
-                                 x->batch == g->batch_groups && g->batch_inner <= 1;
-    if (nelem > 0) {
-        switch (p.kind) {
-        case Plan::FLAT: {
-            // One scale group for the whole batch and a large tensor: one launch, the workgroup that arrives last folds.
-            // (Publishing, counting and the coherent reads of the fold are a chain of device-wide round trips of
-            // 2-3 us each: about 11 us for a tensor of any size up to 32 MB, against 9-10 us for two small launches;
-            // from 32 MB on the single launch wins, 25 us against 27 us at 134 MB.)
-            uint32_t* slot = nullptr;
-            if (g->batch_groups == 1 && nelem >= (int64_t(1) << 24) && arrival_slots(1, &slot) != QMM_OK) slot = nullptr;
-            absmax_flat_bf16<<<dim3(p.flat_blocks, (unsigned)x->batch), kThreads, 0, s>>>(
-                static_cast<const uint16_t*>(x->data), x->batch_stride, x->rows * x->cols / 8, partial, slot, qmax, delta_out);
-            if (slot) return launch_status();
-            break;
-        }
-        case Plan::ROWS: {
-            const int64_t total = x->batch * x->rows;
-            float* direct = rows_are_groups ? delta_out : nullptr;
-            const unsigned nb = (unsigned)((total + kThreads / kWave - 1) / (kThreads / kWave));
-            if (p.vec && x->cols <= 256) {
-                const uint16_t* xp = static_cast<const uint16_t*>(x->data);
-                const int nvec = (int)(x->cols / 8);
-                const int lpr = nvec <= 1 ? 1 : nvec <= 2 ? 2 : nvec <= 4 ? 4 : nvec <= 8 ? 8 : nvec <= 16 ? 16 : 32;
-                const int64_t waves = (total + kWave / lpr - 1) / (kWave / lpr);
-                const unsigned nbs = (unsigned)((waves + kThreads / kWave - 1) / (kThreads / kWave));
-#define QMM_ROWS_SHORT(L) absmax_rows_short<L><<<nbs, kThreads, 0, s>>>(xp, x->batch_stride, x->row_stride, x->rows, x->cols, total, partial, qmax, direct)
-                if (lpr == 1) QMM_ROWS_SHORT(1); else if (lpr == 2) QMM_ROWS_SHORT(2); else if (lpr == 4) QMM_ROWS_SHORT(4);
-                else if (lpr == 8) QMM_ROWS_SHORT(8); else if (lpr == 16) QMM_ROWS_SHORT(16); else QMM_ROWS_SHORT(32);
-#undef QMM_ROWS_SHORT
-            } else if (bf16)
-                absmax_rows<uint16_t><<<nb, kThreads, 0, s>>>(static_cast<const uint16_t*>(x->data), x->batch_stride,
-                                                               x->row_stride, x->rows, x->cols, total, partial, qmax, direct);
-            else
-                absmax_rows<float><<<nb, kThreads, 0, s>>>(static_cast<const float*>(x->data), x->batch_stride,
-                                                            x->row_stride, x->rows, x->cols, total, partial, qmax, direct);
-            break;
-        }
-        case Plan::COLS_VEC:
-            absmax_cols_bf16<<<dim3((unsigned)((x->cols / 8 + 31) / 32), (unsigned)P, (unsigned)x->batch), kThreads, 0, s>>>(
-                static_cast<const uint16_t*>(x->data), x->batch_stride, x->row_stride, x->rows, x->cols, partial);
-            break;
-        case Plan::COLS_GENERIC: {
-            const dim3 grid((unsigned)((x->cols + kThreads - 1) / kThreads), (unsigned)P, (unsigned)x->batch);
-            if (bf16)
-                absmax_cols_generic<uint16_t><<<grid, kThreads, 0, s>>>(static_cast<const uint16_t*>(x->data),
-                                                                        x->batch_stride, x->row_stride, x->rows, x->cols, partial);
-            else
-                absmax_cols_generic<float><<<grid, kThreads, 0, s>>>(static_cast<const float*>(x->data), x->batch_stride,
-                                                                     x->row_stride, x->rows, x->cols, partial);
-            break;
-        }
-        }
-        if (hipGetLastError() != hipSuccess) return QMM_ERR_LAUNCH;
-        if (rows_are_groups) return launch_status();
-    }
-    // An empty tensor has no partials: fold over zero matrices so every group gets delta = 1.
-    const int64_t fold_batch = nelem > 0 ? x->batch : 0;
-    if (nelem == 0) P = 0;
-    const int64_t G = g->batch_groups, inner = g->batch_inner > 0 ? g->batch_inner : 1;
-    if (C == 1)
-        finalize_single<<<(unsigned)G, kThreads, 0, s>>>(partial, fold_batch, P, G, inner, qmax, delta_out);
-    else
-        finalize_channels<<<dim3((unsigned)((C + 31) / 32), (unsigned)G), kThreads, 0, s>>>(
-            partial, fold_batch, P, C, G, inner, qmax, delta_out);
-    return launch_status();
+    ScalePartials pp;
+    const qmm_status st = scale_partials(x, fmt, g, delta_out, partial, false, &pp, s);
+    return st != QMM_OK || pp.done ? st : scale_fold(pp, partial, fmt, g, delta_out, s);
 }
 
 // ---- qmm_scale_static: the same kernels with their partial maxima in a scratch array of the device image.
@@ -603,7 +675,7 @@ extern "C" qmm_status qmm_scale_multi(int32_t count, const qmm_tensor* x, qmm_fo
         max_blk = std::max(max_blk, p.flat_blocks);
         ws += multi_slice(x + t, g + t);
     }
-    a.qmax = fmt == QMM_FMT_INT8 ? 127.0f : (fmt == QMM_FMT_E4M3 ? 448.0f : 57344.0f);
+    a.qmax = host_qmax(fmt);
     const qmm_status sl = arrival_slots(count, &a.slots);
     if (sl != QMM_OK) return sl;
     hipStream_t s = as_stream(stream);

@@ -13,7 +13,7 @@ INT8, E4M3, E5M2, BF16 = 0, 1, 2, 3
 DT_BF16, DT_F32 = 0, 1
 RTNE, STOCHASTIC = 0, 1
 FORMATS = {"int8": INT8, "e4m3": E4M3, "e5m2": E5M2, "bf16": BF16}
-EXPORTS = ["qmm_num_scales", "qmm_scale_workspace_size", "qmm_scale", "qmm_scale_static", "qmm_quantize", "qmm_scale_multi_workspace_size", "qmm_scale_multi", "qmm_quantize_multi",
+EXPORTS = ["qmm_num_scales", "qmm_scale_workspace_size", "qmm_scale", "qmm_scale_static", "qmm_quantize", "qmm_scale_quantize_workspace_size", "qmm_scale_quantize", "qmm_scale_multi_workspace_size", "qmm_scale_multi", "qmm_quantize_multi",
            "qmm_gemm_workspace_size",
            "qmm_gemm", "qmm_gemm_nsr_workspace_size", "qmm_gemm_nsr", "qmm_metric_workspace_size", "qmm_metric", "qmm_dequantize", "qmm_moments_workspace_size", "qmm_moments", "qmm_mfma_rate", "qmm_hbm_rate", "qmm_status_string", "qmm_version"]
 
@@ -57,6 +57,8 @@ def lib():
         L.qmm_scale.restype = i32; L.qmm_scale.argtypes = [TP, i32, GP, vp, vp, sz, vp]
         L.qmm_scale_static.restype = i32; L.qmm_scale_static.argtypes = [TP, i32, GP, vp, vp]
         L.qmm_quantize.restype = i32; L.qmm_quantize.argtypes = [TP, i32, GP, vp, i32, u64, u64, vp, vp]
+        L.qmm_scale_quantize_workspace_size.restype = sz; L.qmm_scale_quantize_workspace_size.argtypes = [TP, GP]
+        L.qmm_scale_quantize.restype = i32; L.qmm_scale_quantize.argtypes = [TP, i32, GP, i32, u64, u64, vp, vp, vp, sz, vp]
         L.qmm_scale_multi_workspace_size.restype = sz; L.qmm_scale_multi_workspace_size.argtypes = [i32, vp, vp]
         L.qmm_scale_multi.restype = i32; L.qmm_scale_multi.argtypes = [i32, vp, i32, vp, vp, vp, sz, vp]
         L.qmm_quantize_multi.restype = i32; L.qmm_quantize_multi.argtypes = [i32, vp, i32, vp, vp, i32, u64, vp, vp, vp]
@@ -261,10 +263,23 @@ def gemm_nsr(a, b, y_ref, out_dtype=torch.bfloat16, out=None, out2=None, workspa
     return y, out2
 
 
+def scale_quantize(x, contract_axis, fmt, per_channel=False, batch_groups=1, mode=RTNE, seed=0, offset=0, batch_inner=1):
+    """qmm_scale_quantize: (uint8 codes [batch, non-contracting, contracting], step sizes) as scale and quantize give them."""
+    L = lib()
+    t, g = tensor_desc(x, contract_axis), granularity(per_channel, batch_groups, batch_inner)
+    nc, kc = (t.rows, t.cols) if contract_axis == 1 else (t.cols, t.rows)
+    delta = torch.empty(L.qmm_num_scales(ctypes.byref(t), ctypes.byref(g)), dtype=torch.float32, device=x.device)
+    codes = torch.empty((t.batch, nc, kc), dtype=torch.uint8, device=x.device)
+    need = L.qmm_scale_quantize_workspace_size(ctypes.byref(t), ctypes.byref(g))
+    workspace = _workspace(need, x.device)
+    _check(L.qmm_scale_quantize(ctypes.byref(t), fmt, ctypes.byref(g), mode, seed, offset, delta.data_ptr(), codes.data_ptr(),
+                                workspace.data_ptr(), workspace.numel(), _stream()), "qmm_scale_quantize")
+    return codes, delta
+
+
 def quantized_operand(x, contract_axis, fmt, per_channel=False, batch_groups=1, mode=RTNE, seed=0, batch_inner=1):
     """scale + quantize; returns ((codes, Operand), delta)."""
-    d = scale(x, contract_axis, fmt, per_channel, batch_groups, batch_inner=batch_inner)
-    c = quantize(x, contract_axis, fmt, d, per_channel, batch_groups, mode, seed, batch_inner=batch_inner)
+    c, d = scale_quantize(x, contract_axis, fmt, per_channel, batch_groups, mode, seed, batch_inner=batch_inner)
     return (c, operand(c, fmt, d, per_channel, batch_groups, batch_inner=batch_inner)), d
 
 

@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import oracle as O
 from paper_2408_02897_amd import qmm, workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -61,3 +62,64 @@ def test_reference_product_in_resident_workgroups(batch, m, n, k, out_dtype):
     ref = a[0][-1][rows].double() @ b[0][-1].double().t()
     bound = 1e-5 * (a[0][-1][rows].double().abs() @ b[0][-1].double().abs().t())
     assert bool(((acc[-1][rows].double() - ref).abs() <= bound).all())
+
+
+# (shape, view): dense, a column slice of a wider matrix, a slice whose rows start off every vector boundary, a batch with gaps
+def tensor_form(form, rows, cols, batch, dtype, seed):
+    x = W.student_t((batch, rows + 1, cols + 9), 4, seed=seed).to(dtype).to(DEV)
+    if dtype == torch.float32:
+        x = x * (1.0 + 2.0 ** -20 * torch.arange(x.numel(), device=DEV).view_as(x) % 64)      # mantissas beyond bfloat16's
+    if form == "dense":
+        return x[:, :rows, :cols].contiguous()
+    if form == "sliced":
+        return x[:, :rows, :cols]
+    if form == "shifted":
+        return x[:, :rows, 1:cols + 1]
+    flat = x.reshape(-1)[1:1 + batch * rows * cols]                                           # dense, off the 16-byte boundary
+    return flat.view(batch, rows, cols)
+
+
+# Every form against the oracle: step sizes and codes, by the two calls and by the one.  Extents around the vectors (4, 8,
+# 16), the lanes of a row in the one-pass kernel (8 .. 256 lanes, 1 .. 4 vectors), the tiles of the transposing pass
+# (64 x 128) and the slabs of its step sizes (32 of 128 rows and more).
+@pytest.mark.parametrize("mode", [qmm.RTNE, qmm.STOCHASTIC])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("form", ["dense", "sliced", "shifted", "offset"])
+@pytest.mark.parametrize("batch,rows,cols,groups,inner", [
+    (1, 1, 1, 1, 1), (1, 5, 7, 1, 1), (1, 129, 65, 1, 1), (1, 3, 2048, 1, 1), (1, 2, 4100, 1, 1), (1, 3, 8200, 1, 1), (1, 4230, 33, 1, 1),
+    (1, 300, 1031, 1, 1), (6, 40, 72, 3, 1), (6, 70, 96, 3, 2), (4, 33, 50, 4, 1), (2, 20, 40, 5, 1), (12, 130, 64, 4, 1)])
+def test_scale_and_quantize_of_every_form(batch, rows, cols, groups, inner, form, dtype, mode):
+    x = tensor_form(form, rows, cols, batch, dtype, seed=rows * 7 + cols)
+    xn = x.float().cpu().numpy()
+    for fmt in (qmm.E4M3, qmm.INT8):
+        for axis in (0, 1):
+            for per_channel in (False, True):
+                kw = dict(per_channel=per_channel, batch_groups=groups, batch_inner=inner)
+                want_d = O.scale(xn, axis, fmt, per_channel, groups, inner)
+                want_c = O.quantize(xn, axis, fmt, want_d, per_channel, groups, mode, 77, 0, inner)
+                d = qmm.scale(x, axis, fmt, **kw)
+                c = qmm.quantize(x, axis, fmt, d, mode=mode, seed=77, **kw)
+                c1, d1 = qmm.scale_quantize(x, axis, fmt, mode=mode, seed=77, **kw)
+                assert np.array_equal(d.cpu().numpy().view(np.uint32), want_d.view(np.uint32)), (fmt, axis, per_channel)
+                assert np.array_equal(c.cpu().numpy(), want_c), (fmt, axis, per_channel)
+                assert torch.equal(d1.view(torch.int32), d.view(torch.int32)) and torch.equal(c1, c), (fmt, axis, per_channel)
+
+
+# Sizes where the single call changes its way: partial maxima folded by the quantize pass (up to 1024 of a group) or not, the
+# large tensors' one-launch maximum (2^24 elements), empty tensors, groups without a matrix, NaN and infinity.
+@pytest.mark.parametrize("shape,axis,per_channel,groups", [
+    ((1, 2048, 4096), 1, False, 1), ((1, 4096, 4096), 1, False, 1), ((1, 1025, 100), 1, False, 1), ((40, 64, 512), 1, False, 2),
+    ((512, 33, 64), 1, False, 16), ((3, 600, 200), 0, True, 3), ((3, 600, 200), 0, True, 1), ((0, 8, 16), 1, False, 2),
+    ((1, 0, 16), 0, True, 1), ((1, 70000, 24), 1, True, 1), ((1, 12, 9000), 1, True, 1)])
+def test_scale_quantize_equals_the_two_calls(shape, axis, per_channel, groups):
+    x = W.student_t(shape, 4, seed=3).to(DEV)
+    if x.numel() > 4096:
+        x.view(-1)[17] = float("inf")
+        if groups > 1:
+            x.view(-1)[-3] = float("nan")
+    kw = dict(per_channel=per_channel, batch_groups=groups)
+    for fmt in (qmm.INT8, qmm.E4M3, qmm.E5M2):
+        d = qmm.scale(x, axis, fmt, **kw)
+        c = qmm.quantize(x, axis, fmt, d, seed=5, mode=qmm.STOCHASTIC, **kw)
+        c1, d1 = qmm.scale_quantize(x, axis, fmt, mode=qmm.STOCHASTIC, seed=5, **kw)
+        assert torch.equal(d1.view(torch.int32), d.view(torch.int32)) and torch.equal(c1, c)

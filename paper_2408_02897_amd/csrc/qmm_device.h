@@ -208,17 +208,47 @@ QMM_DEV uint32_t wave_max_u32(uint32_t v)
     for (int off = 32; off > 0; off >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, off, kWave));
     return v;
 }
+// Butterflies on the vector unit alone: rotations within the rows of sixteen lanes, then the gfx950 swaps of neighbouring
+// rows and of wavefront halves (of two copies of a value the swap leaves one lane set in the first and the other in the
+// second, so first op second is the pair's result in every lane).  A shuffle goes through the LDS crossbar and back, and
+// the fourteen sums of the metric pass were 132 of them, one behind the other (qmm_metric.hip).
+template <int N> QMM_DEV double row_rotate(double v)
+{
+    constexpr int ROW_ROR = 0x120;
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, ROW_ROR + N, 0xF, 0xF, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), ROW_ROR + N, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+template <int WIDTH> QMM_DEV void swap_copies(double v, double& first, double& second)
+{
+    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
+    u2 l, h;
+    if constexpr (WIDTH == 16) {
+        l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+        h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    } else {
+        l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+        h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    }
+    first = __builtin_bit_cast(double, ((uint64_t)h[0] << 32) | l[0]);
+    second = __builtin_bit_cast(double, ((uint64_t)h[1] << 32) | l[1]);
+}
 QMM_DEV double wave_sum_f64(double v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-    return v;
+    v += row_rotate<8>(v); v += row_rotate<4>(v); v += row_rotate<2>(v); v += row_rotate<1>(v);
+    double a, b;
+    swap_copies<16>(v, a, b); v = a + b;
+    swap_copies<32>(v, a, b); return a + b;
 }
 QMM_DEV double wave_max_f64(double v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, kWave));
-    return v;
+    v = fmax(v, row_rotate<8>(v)); v = fmax(v, row_rotate<4>(v)); v = fmax(v, row_rotate<2>(v)); v = fmax(v, row_rotate<1>(v));
+    double a, b;
+    swap_copies<16>(v, a, b); v = fmax(a, b);
+    swap_copies<32>(v, a, b); return fmax(a, b);
 }
 
 // ---------------------------------------------------------------------------

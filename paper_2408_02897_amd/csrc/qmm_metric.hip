@@ -12,20 +12,21 @@ namespace qmm {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kMaxBlocks = 1024;   // 4 workgroups per CU (what 126 registers keep resident); also 4 partials per thread in the final fold
+constexpr int kMaxBlocks = 1024;   // 4 workgroups per CU (what up to 128 registers keep resident); also 4 partials per thread in the final fold
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 // Quotients n / d in binary64 for finite n >= 0 and finite d > 0 where d was converted from binary32 (24 significant
 // bits) and n is such a value or the difference of two (exponents within +-150 or so).
 //
-// reciprocals4: the four reciprocals from ONE hardware estimate: p = d0 d1 d2 d3 (within 2^-596 .. 2^512), two Newton
-// steps on rcp(p), then multiplied back by the other factors.  Each x[i] is 1 / d[i] to a few 2^-53.
-// quotient_with: q0 = n x, r = n - d q0 (exact in one fused multiply-add: d q0 has 77 bits of which all but 25 cancel),
-// q = fl(q0 + r x).  q0 + r x differs from n / d by |r / d| * |x d - 1| < 2^-100 relative, and a quotient with a 24-bit
+// reciprocals4: the four reciprocals from ONE hardware estimate: p = d0 d1 d2 d3 (within 2^-596 .. 2^512), one Newton
+// step on rcp(p) -- whose error of 2^-24 at most (2^29 ulp) it squares --, then multiplied back by the other factors.
+// Each x[i] is 1 / d[i] to 2^-46 at least.
+// quotient_with: q0 = n x, r = n - d q0 (exact in one fused multiply-add: d q0 has 77 bits of which the top 45 or more
+// cancel), q = fl(q0 + r x).  q0 + r x differs from n / d by |r / d| * |x d - 1| < 2^-90 relative, and a quotient with a 24-bit
 // divisor is either representable or at least 2^-78 relative away from the nearest rounding boundary (n - m d is a
 // multiple of 2^(e_m + e_d - 76) for a 54-bit midpoint m), so the single rounding of the last operation lands on the
-// IEEE quotient: same bits as `/`, for 7.25 instructions per quotient (one quarter-rate) instead of 11 with the
+// IEEE quotient: same bits as `/`, for 6.75 instructions per quotient (a quarter of one at quarter rate) instead of 11 with the
 // compiler's sequence.  (The metric pass is as much ALU- as HBM-bound; the divisions are its largest single cost.)
 // A zero, infinite or NaN operand anywhere in the four gives NaN or infinity in the affected quotients, never a wrong
 // finite value passed as right for them: the caller tests the quotients and takes the general path then.
@@ -35,8 +36,7 @@ QMM_DEV void reciprocals4(const double* d, double* x)
     const double p = p01 * p23;
     const double x0 = __builtin_amdgcn_rcp(p);
     const double x1 = fma(x0, fma(-p, x0, 1.0), x0);
-    const double x2 = fma(x1, fma(-p, x1, 1.0), x1);
-    const double x01 = x2 * p23, x23 = x2 * p01;
+    const double x01 = x1 * p23, x23 = x1 * p01;
     x[0] = x01 * d[1]; x[1] = x01 * d[0]; x[2] = x23 * d[3]; x[3] = x23 * d[2];
 }
 // m = max(m, |v|) for values that are not NaN, as the one instruction.  (fmax() first quiets each operand that the
@@ -60,17 +60,15 @@ struct Acc {
 
     // The common case, taken when the whole wavefront's elements are ordinary (no NaN or infinite error, r != 0 and
     // d > 0 everywhere): |e|, |r| and the quotients come in computed.  Same sums as add(), without its selects.
-    // re_sum and be_sum are taken by the caller (it adds the quotients itself, to test them).
+    // re_sum and be_sum are taken by the caller (it adds the quotients itself, to test them), and so is the maximum of |r|.
     // e and r come in signed.
     template <bool HAS_D> QMM_DEV void add_plain(double e, double r, double q, double qb)
     {
-        const double ae = e, ar = r;
         s_ee = fma(e, e, s_ee);
         s_rr = fma(r, r, s_rr);
         s_ae += fabs(e);
         s_ar += fabs(r);
-        max_abs_plain(m_e, ae);
-        max_abs_plain(m_r, ar);
+        max_abs_plain(m_e, e);
         max_abs_plain(re_max, q);
         if constexpr (HAS_D) max_abs_plain(be_max, qb);
     }
@@ -163,63 +161,80 @@ metric_partial(const void* __restrict__ yv, const float* __restrict__ r, const f
     int64_t i = (int64_t)blockIdx.x * kThreads * 2 + threadIdx.x;
     // (y and the reference are read once: streaming loads, which leave the caches to the tensors that are read again --
     // the benchmark's step is 3 % shorter for it, the pass itself 4 %)
-    for (; i + kThreads < nvec; i += stride) {
-        const f32x4 y0 = load_y4<Y_BF16>(yv, i), y1 = load_y4<Y_BF16>(yv, i + kThreads);
-        const f32x4 r0 = __builtin_nontemporal_load(r4 + i), r1 = __builtin_nontemporal_load(r4 + i + kThreads);
-        f32x4 d0 = {0.f, 0.f, 0.f, 0.f}, d1 = {0.f, 0.f, 0.f, 0.f};
-        if constexpr (HAS_D) { d0 = d4[i]; d1 = d4[i + kThreads]; }
-        // |e|, |r| and the quotients of all eight elements first, four divisions per reciprocal estimate.  An element
-        // the plain sums would get wrong (NaN or infinite e, r == 0, d not in (0, inf)) shows as a quotient that is
-        // +infinity or NaN, which makes the running sum of quotients (all >= 0, far from overflow) non-finite, or is
-        // caught by the sign test on d: then the whole wavefront takes the general path and the sums are not kept.
-        double ae[8], ar[8], dd[8], x[8], q[8], qb[8];
-        double re_next = acc.re_sum, be_next = acc.be_sum;
-        bool sp = false;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const float yf = j < 4 ? y0[j & 3] : y1[j & 3], rf = j < 4 ? r0[j & 3] : r1[j & 3];
-            ae[j] = (double)yf - (double)rf;       // signed: the magnitudes are operand modifiers where they are used
-            ar[j] = (double)rf;
-        }
-        reciprocals4(ar, x); reciprocals4(ar + 4, x + 4);      // signed reciprocals: the four signs cancel in pairs
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            q[j] = quotient_with(fabs(ae[j]), fabs(ar[j]), fabs(x[j]));
-            re_next += q[j];
-            qb[j] = 0.0;
-        }
-        sp = !(re_next < (double)__builtin_inff());
-        if constexpr (HAS_D) {
+    // The pass is bound by the vector unit (80 % of its cycles busy, at the 1.7 GHz the binary64 work leaves), so the loop
+    // is kept to what the sums need: the rare path lies outside it -- inside, the running sums were copied around it on
+    // every trip, 11 moves for 8 elements --, the maximum of |r| is taken in binary32, which holds it exactly, and the
+    // reciprocals need one Newton step (see reciprocals4).  24 instructions an element before, 20 now.
+    float mr = 0.0f;
+    for (;;) {
+        bool special = false;
+        for (; i + kThreads < nvec; i += stride) {
+            const f32x4 y0 = load_y4<Y_BF16>(yv, i), y1 = load_y4<Y_BF16>(yv, i + kThreads);
+            const f32x4 r0 = __builtin_nontemporal_load(r4 + i), r1 = __builtin_nontemporal_load(r4 + i + kThreads);
+            f32x4 d0 = {0.f, 0.f, 0.f, 0.f}, d1 = {0.f, 0.f, 0.f, 0.f};
+            if constexpr (HAS_D) { d0 = d4[i]; d1 = d4[i + kThreads]; }
+            // |e|, |r| and the quotients of all eight elements first, four divisions per reciprocal estimate.  An element
+            // the plain sums would get wrong (NaN or infinite e, r == 0, d not in (0, inf)) shows as a quotient that is
+            // +infinity or NaN, which makes the running sum of quotients (all >= 0, far from overflow) non-finite, or is
+            // caught by the sign test on d: then the whole wavefront takes the general path and the sums are not kept.
+            double ae[8], ar[8], dd[8], x[8], q[8], qb[8];
+            double re_next = acc.re_sum, be_next = acc.be_sum;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const float df = j < 4 ? d0[j & 3] : d1[j & 3];
-                dd[j] = (double)df;
-                sp = sp || !(df > 0.0f);
+                const float yf = j < 4 ? y0[j & 3] : y1[j & 3], rf = j < 4 ? r0[j & 3] : r1[j & 3];
+                ae[j] = (double)yf - (double)rf;       // signed: the magnitudes are operand modifiers where they are used
+                ar[j] = (double)rf;
             }
-            reciprocals4(dd, x); reciprocals4(dd + 4, x + 4);
+            reciprocals4(ar, x); reciprocals4(ar + 4, x + 4);      // signed reciprocals: the four signs cancel in pairs
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                qb[j] = quotient_with(fabs(ae[j]), dd[j], x[j]);
-                be_next += qb[j];
+                q[j] = quotient_with(fabs(ae[j]), fabs(ar[j]), fabs(x[j]));
+                re_next += q[j];
+                qb[j] = 0.0;
             }
-            sp = sp || !(be_next < (double)__builtin_inff());
-        }
-        if (!__any(sp)) {
+            bool sp = !(re_next < (double)__builtin_inff());
+            if constexpr (HAS_D) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float df = j < 4 ? d0[j & 3] : d1[j & 3];
+                    dd[j] = (double)df;
+                    sp = sp || !(df > 0.0f);
+                }
+                reciprocals4(dd, x); reciprocals4(dd + 4, x + 4);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    qb[j] = quotient_with(fabs(ae[j]), dd[j], x[j]);
+                    be_next += qb[j];
+                }
+                sp = sp || !(be_next < (double)__builtin_inff());
+            }
+            if (__any(sp)) { special = true; break; }
 #pragma unroll
             for (int j = 0; j < 8; ++j) acc.add_plain<HAS_D>(ae[j], ar[j], q[j], qb[j]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) mr = fmaxf(fmaxf(mr, fabsf(r0[j])), fabsf(r1[j]));
             acc.re_sum = re_next;
             if constexpr (HAS_D) acc.be_sum = be_next;
             acc.count_plain<HAS_D>(8u);
-        } else {
-            // rare path, kept rolled: unrolled, its eight interleaved IEEE divisions set the kernel's register
-            // count (99 instead of 72) and with it the number of resident wavefronts
+        }
+        if (!special) break;
+        // the rare path, kept rolled: unrolled, its eight interleaved IEEE divisions set the kernel's register count
 #pragma unroll 1
-            for (int j = 0; j < 8; ++j) {
-                const f32x4 yy = j < 4 ? y0 : y1, rr = j < 4 ? r0 : r1, dd = j < 4 ? d0 : d1;
-                acc.add<HAS_D>(yy[j & 3], rr[j & 3], dd[j & 3]);
+        for (int h = 0; h < 2; ++h) {
+            const f32x4 yy = load_y4<Y_BF16>(yv, i + h * kThreads), rr = r4[i + h * kThreads];
+            f32x4 dd = {0.f, 0.f, 0.f, 0.f};
+            if constexpr (HAS_D) dd = d4[i + h * kThreads];
+#pragma unroll 1
+            for (int j = 0; j < 4; ++j) {
+                const float yf = j == 0 ? yy[0] : j == 1 ? yy[1] : j == 2 ? yy[2] : yy[3];
+                const float rf = j == 0 ? rr[0] : j == 1 ? rr[1] : j == 2 ? rr[2] : rr[3];
+                const float df = j == 0 ? dd[0] : j == 1 ? dd[1] : j == 2 ? dd[2] : dd[3];
+                acc.add<HAS_D>(yf, rf, df);
             }
         }
+        i += stride;
     }
+    acc.m_r = fmax(acc.m_r, (double)mr);
     if (i < nvec) {      // ragged end: the first piece of a workgroup's last trip
         const f32x4 y0 = load_y4<Y_BF16>(yv, i);
         const f32x4 r0 = r4[i];
@@ -272,7 +287,9 @@ metric_finalize(const double* __restrict__ partial, int nblocks, double* __restr
 
 int plan_blocks(int64_t n)
 {
-    const int64_t per_block = (int64_t)kThreads * 4 * 4;   // four 4-element vectors per thread at least
+    // two 4-element vectors per thread at least, one trip: a small tensor is bound by the latency of a trip (196608
+    // elements: 5.4 -> 4.6 us against two)
+    const int64_t per_block = (int64_t)kThreads * 4 * 2;
     int64_t nb = (n + per_block - 1) / per_block;
     if (nb < 1) nb = 1;
     if (nb > kMaxBlocks) nb = kMaxBlocks;
@@ -305,8 +322,7 @@ extern "C" qmm_status qmm_metric(const void* y, qmm_dtype y_dtype, const float* 
     hipStream_t s = as_stream(stream);
     double* partial = static_cast<double*>(workspace);
     const bool bf = y_dtype == QMM_DT_BF16, hd = denom != nullptr;
-    // with denominators the kernel holds 156 registers: three workgroups resident per CU, so no more than that are launched
-    const int nb = hd ? std::min(plan_blocks(n), 768) : plan_blocks(n);
+    const int nb = plan_blocks(n);
     if (bf && hd) metric_partial<true, true><<<nb, kThreads, 0, s>>>(y, y_ref, denom, n, partial);
     else if (bf) metric_partial<true, false><<<nb, kThreads, 0, s>>>(y, y_ref, denom, n, partial);
     else if (hd) metric_partial<false, true><<<nb, kThreads, 0, s>>>(y, y_ref, denom, n, partial);

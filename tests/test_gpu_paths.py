@@ -123,3 +123,19 @@ def test_scale_quantize_equals_the_two_calls(shape, axis, per_channel, groups):
         c = qmm.quantize(x, axis, fmt, d, seed=5, mode=qmm.STOCHASTIC, **kw)
         c1, d1 = qmm.scale_quantize(x, axis, fmt, mode=qmm.STOCHASTIC, seed=5, **kw)
         assert torch.equal(d1.view(torch.int32), d.view(torch.int32)) and torch.equal(c1, c)
+
+
+# every code, rows around the pieces a wavefront takes (4 x 64 vectors of 4 or 8), odd rows and step sizes at each level
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("batch,rows,k,groups", [(1, 1, 256, 1), (1, 3, 1023, 1), (1, 2, 1025, 1), (4, 5, 2049, 2), (6, 7, 33, 3), (2, 70, 4096, 1)])
+def test_dequantize_of_every_form(batch, rows, k, groups, out_dtype):
+    rng = np.random.default_rng(k)
+    codes = rng.integers(0, 256, (batch, rows, k), dtype=np.uint8)
+    for fmt in (qmm.INT8, qmm.E4M3, qmm.E5M2):
+        for per_channel in (False, True):
+            d = rng.uniform(1e-3, 2.0, groups * (rows if per_channel else 1)).astype(np.float32)
+            want = torch.from_numpy(O.dequantize_codes(codes, fmt, d, per_channel, groups)).to(out_dtype)
+            buf, out = guarded((batch, rows, k), out_dtype)
+            qmm.dequantize(torch.from_numpy(codes).to(DEV), fmt, torch.from_numpy(d).to(DEV), per_channel, groups, out=out)
+            got, nan = out.cpu(), want.isnan()
+            assert torch.equal(got.isnan(), nan) and torch.equal(got[~nan], want[~nan]) and intact(buf)

@@ -32,6 +32,7 @@
 //  * Workgroup ids are spread so that each XCD (own L2) walks a compact band of
 //    tiles.
 //  * Long K with few tiles: split-K with a second, fixed-order reduction kernel.
+//    Few tiles otherwise: gemm_deep_kernel (64 x 64 tiles, deeper LDS ring).
 //    Outputs at most 64 wide or high: gemm_direct_kernel (no LDS).
 //    Contractions of one slab at most with many whole tiles: gemm_shortk_kernel;
 //    several whole tiles per CU and one step size per operand: gemm_stream_kernel
@@ -1782,6 +1783,219 @@ gemm_direct_kernel(GemmArgs g)
     }
 }
 
+// Outputs of few tiles and a contraction too short to split: what such a product takes is latency, and 128 x 128 tiles
+// leave most CUs without any work.  Tiles of 64 x 64 here, four wavefronts of 32 x 32, one barrier per step, and a ring of
+// SLOTS slabs of both operands, all but one on their way: eight (128 KB) where a CU gets one workgroup, three where it
+// gets two.  (gemm_kernel keeps two slabs on their way; at one wavefront per SIMD each of its steps waits 0.7-0.9 us for
+// 0.25 us of matrix work.)
+// Same LDS layout, fragments, order of K and accumulator layout as gemm_kernel: the accumulators are the same bits.
+// Vector-memory operations complete in order: "at most the copies of the k newer slabs outstanding" means a slab has
+// landed; the slot that a step's copies go to was read in the step before, which every wavefront has left at the barrier.
+template <int KIND, int FA, int FB, int SLOTS>
+__global__ void __launch_bounds__(256, 1)
+gemm_deep_kernel(GemmArgs g)
+{
+    constexpr bool F8 = (KIND == KIND_F8);
+    constexpr int W = 32, BM = 2 * W, BN = 2 * W;
+    constexpr int R = F8 ? 16 : 32;
+    constexpr int BLOCKS_M = W / R, TILES_N = W / R;
+    constexpr int KS = F8 ? 1 : 4;
+    constexpr int REGS = F8 ? 4 : 16;
+    constexpr int A_SLOT = BM * kSlabBytes, SLOT = 2 * A_SLOT;             // a slab of A, then one of B
+    constexpr int UNITS = BM / 8 / 4;                                      // copies of 8 LDS rows per wavefront and operand
+    static_assert(UNITS % 2 == 0, "a wavefront's units start on an even LDS row pair");
+    static_assert((SLOTS - 2) * 2 * UNITS <= 63, "vmcnt range");
+    using AccT = typename std::conditional<F8, v4f, typename std::conditional<KIND == KIND_I8, v16i, v16f>::type>::type;
+    using Frag = typename std::conditional<F8, v8i, v4i>::type;
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const uint32_t tiles_per_batch = (uint32_t)g.tiles_m * (uint32_t)g.tiles_n;
+    const int64_t bidx = __builtin_amdgcn_readfirstlane((int)(blockIdx.x / tiles_per_batch));
+    const uint32_t t = blockIdx.x - (uint32_t)bidx * tiles_per_batch;
+    const int64_t tile_m = __builtin_amdgcn_readfirstlane((int)(t / (uint32_t)g.tiles_n));
+    const int64_t tile_n = __builtin_amdgcn_readfirstlane((int)(t % (uint32_t)g.tiles_n));
+    const int64_t m0 = tile_m * BM, n0 = tile_n * BN;
+    const int rowbytes = (int)g.rowbytes;
+    const int nk = (rowbytes + kSlabBytes - 1) / kSlabBytes;
+    const uint8_t* a_tile = g.a + (bidx * g.M + m0) * g.rowbytes;
+    const uint8_t* b_tile = g.b + (bidx * g.N + n0) * g.rowbytes;
+
+    // copy sources: lane l of unit u fills LDS row p = 8u + l/8, chunk position l%8, with logical chunk (l%8) ^ ((p>>1)&7)
+    // of row p of the tile (B: of column TILES_N * (p % R) + (p / R) % TILES_N of its wavefront's W columns)
+    uint32_t a_src[UNITS], b_src[UNITS];
+    int chunk[UNITS];
+#pragma unroll
+    for (int i = 0; i < UNITS; ++i) {
+        const int p = (wave * UNITS + i) * 8 + (lane >> 3);
+        chunk[i] = (lane & 7) ^ ((p >> 1) & 7);
+        int64_t ra = p, rb = W * (p / W) + TILES_N * (p % R) + (p / R) % TILES_N;
+        ra = m0 + ra < g.M ? ra : g.M - 1 - m0;
+        rb = n0 + rb < g.N ? rb : g.N - 1 - n0;
+        a_src[i] = (uint32_t)(ra * g.rowbytes + chunk[i] * 16);
+        b_src[i] = (uint32_t)(rb * g.rowbytes + chunk[i] * 16);
+    }
+    typedef __attribute__((address_space(3))) uint8_t* lds_ptr_t;
+    const uint32_t lds_units = (uint32_t)(uintptr_t)(lds_ptr_t)(lds + wave * UNITS * 1024);
+    auto copy_slab = [&](int slab, int slot) {
+        const int k0 = slab * kSlabBytes;
+        const bool whole = k0 + kSlabBytes <= rowbytes;
+#pragma unroll
+        for (int i = 0; i < 2 * UNITS; ++i) {
+            const bool is_a = i < UNITS;
+            const int u = is_a ? i : i - UNITS;
+            const uint32_t off = slot * SLOT + (is_a ? 0 : A_SLOT) + u * 1024;
+            const uint8_t* base = (is_a ? a_tile : b_tile) + k0;
+            const uint32_t src = is_a ? a_src[u] : b_src[u];
+            // (a chunk past the end of the rows: zeros; every slab counts the same number of copies, masked off or not)
+            if (whole || k0 + chunk[u] * 16 < rowbytes) dma16_uniform(base, src, lds_units + off);
+            if (!whole && k0 + chunk[u] * 16 >= rowbytes)
+                *reinterpret_cast<u32x4*>(lds + off + wave * UNITS * 1024 + lane * 16) = u32x4{0u, 0u, 0u, 0u};
+        }
+    };
+
+    AccT acc[BLOCKS_M][TILES_N];
+#pragma unroll
+    for (int i = 0; i < BLOCKS_M; ++i)
+#pragma unroll
+        for (int j = 0; j < TILES_N; ++j)
+#pragma unroll
+            for (int e = 0; e < REGS; ++e) acc[i][j][e] = 0;
+
+    const int frow = lane & (R - 1);
+    const int fkey = (frow >> 1) & 7;
+    const int fsel = F8 ? (lane >> 4) : (lane >> 5);
+    int coff[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) coff[s] = ((F8 ? fsel : 2 * s + fsel) ^ fkey) * 16;
+    auto read_frag = [&](const uint8_t* row_ptr, int s) -> Frag {
+        if constexpr (F8) {
+            const v4i p0 = *reinterpret_cast<const v4i*>(row_ptr + coff[0]);
+            const v4i p1 = *reinterpret_cast<const v4i*>(row_ptr + (coff[0] ^ 64));
+            return v8i{p0[0], p0[1], p0[2], p0[3], p1[0], p1[1], p1[2], p1[3]};
+        } else {
+            return *reinterpret_cast<const v4i*>(row_ptr + coff[s]);
+        }
+    };
+    auto mma = [&](const Frag& fa, const Frag& fb, AccT& c) {
+        if constexpr (F8) {
+            c = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa, fb, c, FA == QMM_FMT_E5M2 ? 1 : 0,
+                                                                 FB == QMM_FMT_E5M2 ? 1 : 0, 0, 0, 0, 0);
+        } else if constexpr (KIND == KIND_I8) {
+            c = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa, fb, c, 0, 0, 0);
+        } else {
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, fa), __builtin_bit_cast(v8bf, fb), c, 0, 0, 0);
+        }
+    };
+
+#pragma unroll
+    for (int s = 0; s < SLOTS - 1; ++s)
+        if (s < nk) copy_slab(s, s);
+    int slot = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+        // slab kt has landed: only the copies of the slabs after it (at most SLOTS - 2) may be outstanding
+        const int newer = min(SLOTS - 2, nk - 1 - kt);
+        if (newer == SLOTS - 2) wait_vm_lgkm<(SLOTS - 2) * 2 * UNITS>();
+        else if (newer >= 4 && SLOTS > 6) wait_vm_lgkm<(SLOTS > 6 ? 4 : 0) * 2 * UNITS>();
+        else if (newer >= 2 && SLOTS > 4) wait_vm_lgkm<2 * 2 * UNITS>();
+        else if (newer == 1) wait_vm_lgkm<2 * UNITS>();
+        else wait_vm_lgkm<0>();
+        __syncthreads();
+        const int free_slot = slot == 0 ? SLOTS - 1 : slot - 1;            // read in step kt - 1
+        if (kt + SLOTS - 1 < nk) copy_slab(kt + SLOTS - 1, free_slot);
+        const uint8_t* sa = lds + slot * SLOT + (wm * W + frow) * kSlabBytes;
+        const uint8_t* sb = lds + slot * SLOT + A_SLOT + (wn * W + frow) * kSlabBytes;
+        Frag fa[BLOCKS_M][KS], fb[TILES_N][KS];
+#pragma unroll
+        for (int j = 0; j < TILES_N; ++j)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) fb[j][s] = read_frag(sb + j * R * kSlabBytes, s);
+#pragma unroll
+        for (int i = 0; i < BLOCKS_M; ++i)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) fa[i][s] = read_frag(sa + i * R * kSlabBytes, s);
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int i = 0; i < BLOCKS_M; ++i)
+#pragma unroll
+                for (int j = 0; j < TILES_N; ++j) mma(fa[i][s], fb[j][s], acc[i][j]);
+        slot = slot == SLOTS - 1 ? 0 : slot + 1;
+    }
+
+    // ---- epilogue: (acc * deltaA[row]) * deltaB[column], in that order; masked vector stores (see gemm_kernel)
+    constexpr bool descale = (KIND != KIND_BF16);
+    const int64_t m_base = m0 + wm * W, n_base = n0 + wn * W;
+    const float* da = g.da ? g.da + ((bidx / g.da_inner) % g.da_groups) * (g.da_per_channel ? g.M : 1) : nullptr;
+    const float* db = g.db ? g.db + ((bidx / g.db_inner) % g.db_groups) * (g.db_per_channel ? g.N : 1) : nullptr;
+    const int64_t n = n_base + TILES_N * (lane & (R - 1));
+    const int lane_row = F8 ? 4 * (lane >> 4) : 4 * (lane >> 5);
+    auto row_in_block = [&](int r) -> int { return F8 ? lane_row + r : 8 * (r >> 2) + lane_row + (r & 3); };
+    float sr[TILES_N];
+#pragma unroll
+    for (int tt = 0; tt < TILES_N; ++tt) {
+        sr[tt] = 1.0f;
+        if constexpr (descale) sr[tt] = g.db_per_channel ? db[(n + tt) < g.N ? (n + tt) : (g.N - 1)] : db[0];
+    }
+    float sl_rows[BLOCKS_M][REGS];
+#pragma unroll
+    for (int ia = 0; ia < BLOCKS_M; ++ia)
+#pragma unroll
+        for (int r = 0; r < REGS; ++r) {
+            sl_rows[ia][r] = 1.0f;
+            if constexpr (descale) {
+                const int64_t m = m_base + ia * R + row_in_block(r);
+                sl_rows[ia][r] = g.da_per_channel ? da[m < g.M ? m : g.M - 1] : da[0];
+            }
+        }
+    if (n >= g.N) return;
+    const bool whole = n + TILES_N <= g.N;
+    const int64_t first = (bidx * g.M + m_base) * g.N + n, rows_left = g.M - m_base;
+#pragma unroll
+    for (int ia = 0; ia < BLOCKS_M; ++ia)
+#pragma unroll
+        for (int r = 0; r < REGS; ++r) {
+            const int ml = ia * R + row_in_block(r);
+            if (ml >= rows_left) continue;
+            const int64_t o = first + (int64_t)ml * g.N;
+            float v[TILES_N];
+#pragma unroll
+            for (int tt = 0; tt < TILES_N; ++tt) {
+                float a;
+                if constexpr (KIND == KIND_I8) a = (float)acc[ia][tt][r];
+                else a = acc[ia][tt][r];
+                if constexpr (descale) a = (a * sl_rows[ia][r]) * sr[tt];
+                v[tt] = a;
+            }
+            if (g.acc_out) {
+#pragma unroll
+                for (int tt = 0; tt < TILES_N; ++tt)
+                    if (n + tt < g.N) {
+                        uint32_t raw;
+                        if constexpr (KIND == KIND_I8) raw = (uint32_t)acc[ia][tt][r];
+                        else raw = __float_as_uint(acc[ia][tt][r]);
+                        static_cast<uint32_t*>(g.acc_out)[o + tt] = raw;
+                    }
+            }
+            if (!g.y) continue;
+            if constexpr (TILES_N > 1) {
+                if (whole) {
+                    if (g.y_bf16) store_bf16<TILES_N>(static_cast<uint16_t*>(g.y) + o, v);
+                    else store_f32<TILES_N>(static_cast<float*>(g.y) + o, v);
+                    continue;
+                }
+            }
+#pragma unroll
+            for (int tt = 0; tt < TILES_N; ++tt)
+                if (n + tt < g.N) {
+                    if (g.y_bf16) static_cast<__bf16*>(g.y)[o + tt] = (__bf16)v[tt];
+                    else static_cast<float*>(g.y)[o + tt] = v[tt];
+                }
+        }
+}
+
 // Second kernel of split-K: out = descale(sum over the K ranges, in ascending order, of the partial accumulators).
 // INT8 partials are integers (the sum is exact); FP8 / bfloat16 partials are binary32 and added in binary32.
 // One thread per four consecutive columns; the partial sums of four ranges are requested before the first is added (one
@@ -1992,6 +2206,24 @@ qmm_status launch_stream(GemmArgs& g, hipStream_t s)
     return launch_status();
 }
 
+// gemm_deep_kernel: nothing quantized on load, no split, at most two 64 x 64 tiles per CU.  Measured against the 128 x 128
+// tiles of gemm_kernel (launches back to back, E4M3 unless said): 256 x 768 x 768 (48 tiles) 10.6 -> 6.4 us, 512 x 512 x 512
+// (64) 10.7 -> 6.4 us, bfloat16 12.2 -> 7.2; 1031 x 1000 x 784 (272) 9.6 -> 7.5 us, 1448 x 724 x 1456 (276) 11.4 -> 10.6 us,
+// 2000 x 1000 x 512 (512) 8.7 -> 7.2 us; but 1536 x 1536 x 1536 (576) 8.9 -> 11.6 us and 4096 x 768 x 768 (768) 8.9 -> 10.2.
+constexpr int kDeepGrid = 256;
+template <int KIND, int FA, int FB, int SLOTS>
+qmm_status launch_deep(GemmArgs& g, hipStream_t s)
+{
+    constexpr int LDS_BYTES = SLOTS * 2 * 64 * kSlabBytes;
+    g.tiles_m = (int)((g.M + 63) / 64);
+    g.tiles_n = (int)((g.N + 63) / 64);
+    auto kern = gemm_deep_kernel<KIND, FA, FB, SLOTS>;
+    static std::atomic<uint64_t> lds_attr_done{0};
+    if (!ensure_lds_attr(lds_attr_done, reinterpret_cast<const void*>(kern), LDS_BYTES)) return QMM_ERR_LAUNCH;
+    kern<<<(unsigned)((int64_t)g.tiles_m * g.tiles_n * g.batch), 256, LDS_BYTES, s>>>(g);
+    return launch_status();
+}
+
 template <int KIND, int FA, int FB, int FUSE>
 qmm_status launch_fuse(GemmArgs& g, hipStream_t s)
 {
@@ -2007,6 +2239,9 @@ qmm_status launch_fuse(GemmArgs& g, hipStream_t s)
         if (use_direct(g, 0)) return launch_direct<KIND, FA, FB>(g, s);
         if (use_shortk<KIND>(g, 0)) return launch_shortk<KIND, FA, FB>(g, s);
         if (use_stream(g, 0)) return launch_stream<KIND, FA, FB>(g, s);
+        const int64_t tiles = ((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch;
+        if (g.splits == 1 && tiles <= kDeepGrid) return launch_deep<KIND, FA, FB, 8>(g, s);
+        if (g.splits == 1 && tiles <= 2 * kDeepGrid) return launch_deep<KIND, FA, FB, 3>(g, s);
     }
     // 256 x 256 tiles (eight wavefronts, two per SIMD: while one waits at a copy or a fragment read the other
     // issues matrix instructions) when they still give every CU work, else 128 x 128 tiles (four wavefronts, two

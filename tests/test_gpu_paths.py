@@ -139,3 +139,34 @@ def test_dequantize_of_every_form(batch, rows, k, groups, out_dtype):
             qmm.dequantize(torch.from_numpy(codes).to(DEV), fmt, torch.from_numpy(d).to(DEV), per_channel, groups, out=out)
             got, nan = out.cpu(), want.isnan()
             assert torch.equal(got.isnan(), nan) and torch.equal(got[~nan], want[~nan]) and intact(buf)
+
+
+# Outputs of at most 512 tiles of 64 x 64 (rings of eight and of three slabs): contractions shorter and longer than the ring,
+# partial last slabs, edges of the tiles, a batch, step sizes at each level.  INT8: whole numbers against an integer product;
+# the others: against the same rows inside a product of more rows, which runs in the 128 x 128 tiles with the same order of
+# additions, so in every bit.  (`row` = bytes of a row, below sixteen slabs of 128: from there on the small product, but
+# not the large one, is split along K.)
+@pytest.mark.parametrize("kind", ["e4m3", "int8", "bf16"])
+@pytest.mark.parametrize("batch,m,n,row", [(1, 1, 1, 16), (1, 63, 65, 48), (1, 64, 64, 1024), (2, 129, 70, 1168), (1, 65, 2047, 144),
+                                           (1, 1000, 1031, 784), (3, 400, 700, 1920), (1, 2048, 1024, 128)])
+def test_product_of_few_tiles(kind, batch, m, n, row):
+    k = row // 2 if kind == "bf16" else row
+    a, b = operands(kind, m, n, k, per_channel=(m % 2 == 1), batch=batch)
+    buf, acc = guarded((batch, m, n), torch.int32 if kind == "int8" else torch.float32)
+    y = torch.empty((batch, m, n), dtype=torch.float32, device=DEV)
+    qmm.gemm(a, b, out=y, acc_out=acc)
+    assert intact(buf)
+    if kind == "int8":
+        want = a[0].view(torch.int8).double() @ b[0].view(torch.int8).double().transpose(1, 2).contiguous()
+        assert torch.equal(acc.double(), want)
+    else:
+        rows = 6144                                        # more than 512 tiles for every n here
+        wide = [torch.zeros((batch, rows, k), dtype=a[0].dtype, device=DEV), torch.zeros((batch, max(n, 700), k), dtype=b[0].dtype, device=DEV)]
+        wide[0][:, :m], wide[1][:, :n] = a[0], b[0]
+        one = torch.ones(1, device=DEV)
+        ops = [(t, qmm.operand(t, o[1].format, one, is_codes=kind != "bf16")) for t, o in zip(wide, (a, b))]
+        _, acc_wide = qmm.gemm(ops[0], ops[1], want_acc=True)
+        assert torch.equal(acc, acc_wide[:, :m, :n])
+    alone = torch.empty_like(y)
+    qmm.gemm(a, b, out=alone)
+    assert torch.equal(alone, y)

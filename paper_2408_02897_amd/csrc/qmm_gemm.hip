@@ -2244,12 +2244,18 @@ qmm_status launch_fuse(GemmArgs& g, hipStream_t s)
         if (g.splits == 1 && tiles <= 2 * kDeepGrid) return launch_deep<KIND, FA, FB, 3>(g, s);
     }
     // 256 x 256 tiles (eight wavefronts, two per SIMD: while one waits at a copy or a fragment read the other
-    // issues matrix instructions) when they still give every CU work, else 128 x 128 tiles (four wavefronts, two
-    // workgroups per CU).
+    // issues matrix instructions), one workgroup per CU, or 128 x 128 tiles (four wavefronts), two workgroups per CU: a
+    // round of 256 big tiles takes as long as 1.8 rounds of 512 small ones (16384 x 1024 x 4096 54 against 63 us, one and
+    // two rounds), so what counts is how full the last round is and how much of the tiles lies outside the output.
+    // Measured, big / small: 4096 x 2560 x 1024 INT8 (160 tiles / 640) 18.5 / 20.8 us, 4096 x 2048 x 1024 (128 / 512) 14.7 /
+    // 11.6, 16384 x 1300 x 1024 (384 / 1408) 40.9 / 36.5, 8200 x 3000 x 1024 (396 / 1560) 41.0 / 41.9, 384 matrices of
+    // 384 x 384 x 64 (1536 / 3456) 59.7 / 34.6 us, 192 of 144 x 144 x 64 (192 / 768) 10.8 / 12.7.
     const int64_t big = ((g.M + 255) / 256) * ((g.N + 255) / 256) * g.batch;
+    const int64_t small = ((g.M + 127) / 128) * ((g.N + 127) / 128) * g.batch;
     // an output narrower than half a big tile wastes less of a small one
     const bool narrow = g.M <= 128 || g.N <= 128;
-    if (big >= 192 && !narrow && g.splits == 1) return launch_tile<KIND, FA, FB, 4, 1, 4, FUSE>(g, s);
+    const bool big_rounds_pay = FUSE == 0 ? 20 * ((big + 255) / 256) <= 11 * ((small + 511) / 512) : big >= 192;
+    if (big_rounds_pay && !narrow && g.splits == 1) return launch_tile<KIND, FA, FB, 4, 1, 4, FUSE>(g, s);
     return launch_tile<KIND, FA, FB, 2, 1, 2, FUSE>(g, s);
 }
 

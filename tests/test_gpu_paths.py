@@ -47,6 +47,22 @@ def test_output_at_edges_and_odd_extents(kind, m, n, k, out_dtype):
     assert intact(buf)
 
 
+# Either side of the rule between 256 x 256 and 128 x 128 tiles: 170 big tiles (one round of the CUs), and a batch whose big
+# tiles fill two rounds badly.
+@pytest.mark.parametrize("kind", ["e4m3", "int8", "bf16"])
+@pytest.mark.parametrize("batch,m,n,k", [(1, 4200, 2500, 144), (70, 384, 390, 64), (70, 257, 384, 272)])
+def test_output_in_big_and_small_tiles(kind, batch, m, n, k):
+    a, b = operands(kind, m, n, k, per_channel=True, batch=batch)
+    want, _ = qmm.gemm(a, b, torch.bfloat16, want_acc=True)
+    buf, y = guarded((batch, m, n), torch.bfloat16)
+    qmm.gemm(a, b, torch.bfloat16, out=y)
+    assert torch.equal(y, want) and intact(buf)
+    if kind == "int8":
+        _, acc = qmm.gemm(a, b, want_acc=True)
+        exact = a[0][-1].view(torch.int8).double() @ b[0][-1].view(torch.int8).double().t()
+        assert torch.equal(acc[-1].double(), exact)
+
+
 # bfloat16 operands through the kernel whose workgroups stay on their CU (whole tiles, more tiles than workgroups, three
 # slabs or more; 512 tiles, 3 slabs: a tile's stores overlap the whole of the next one): the matrix instructions run in
 # the same order, so its product equals the other kernel's in every bit.

@@ -1585,7 +1585,12 @@ gemm_stream_kernel(GemmArgs g)
 // (Not for short contractions with a large output, e.g. attention scores: there every operand row is wanted by many
 // blocks, and fetching fragments per block through the vector memory path -- sixteen row segments per instruction
 // -- is slower than one LDS copy per workgroup; measured 95 us against 78 us for Q K^T of BERT-large.)
-template <int KIND, int FA, int FB>
+// B_LDS (wavefronts along m, a short operand that fits): the workgroup first copies its 64 rows of B into LDS, all slabs, in
+// gemm_kernel's layout, and the registers that held them take a second slab of A: two slabs of the long operand are on
+// their way at any time; without it every wavefront fetched B again through the vector memory path and waited for each slab.
+// K bytes per lane as in the LDS kernels.  Probabilities x values of BERT-large, batch 32 (512 x [512 x 64 x 512]): E4M3 47.6
+// -> 41.6 us, INT8 48.6 -> 45.3; 1 x [60000 x 64 x 512] INT8 14.0 -> 12.3.  (Three or four slabs of A in flight: the same.)
+template <int KIND, int FA, int FB, bool B_LDS>
 __global__ void __launch_bounds__(256)
 gemm_direct_kernel(GemmArgs g)
 {
@@ -1617,7 +1622,8 @@ gemm_direct_kernel(GemmArgs g)
     const int64_t tile_m = __builtin_amdgcn_readfirstlane((int)(t / (uint32_t)g.tiles_n));
     const int64_t tile_n = __builtin_amdgcn_readfirstlane((int)(t % (uint32_t)g.tiles_n));
     const int64_t m_base = tile_m * BM + wm * WM, n_base = tile_n * BN + wn * WN;
-    if (m_base >= g.M || n_base >= g.N) return;          // nothing of this wavefront's block lies inside the output
+    const bool idle = m_base >= g.M || n_base >= g.N;    // nothing of this wavefront's block lies inside the output
+    if (!B_LDS && idle) return;
 
     // lane (r, h): row r of an operand block.  FP8 (h = 0..3): K bytes [16 h, 16 h + 16) and [64 + 16 h, 64 + 16 h + 16)
     // of a slab, the assignment of the LDS kernels' fragments -- the matrix instruction adds its operand registers up in
@@ -1675,6 +1681,69 @@ gemm_direct_kernel(GemmArgs g)
         }
     };
 
+    if constexpr (B_LDS) {
+        extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+        typedef __attribute__((address_space(3))) uint8_t* lds_ptr_t;
+        const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
+        const uint8_t* b_tile = g.b + (bidx * g.N + n_base) * g.rowbytes;       // n_base is the workgroup's (wn = 0)
+        const int nk = (rowbytes + kSlabBytes - 1) / kSlabBytes;
+        for (int s = 0; s < nk; ++s) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {                                       // eight units of 8 rows per slab, two per wavefront
+                const int u = wave * 2 + i, p = u * 8 + (lane >> 3), c = (lane & 7) ^ ((p >> 1) & 7);
+                const int64_t row = min((int64_t)(TILES_N * (p % R) + p / R), g.N - 1 - n_base);
+                const uint32_t at = s * (WN * kSlabBytes) + u * 1024;
+                if (s * kSlabBytes + c * 16 < rowbytes) dma16_uniform(b_tile + s * kSlabBytes, (uint32_t)(row * rowbytes + c * 16), lds_base + at);
+                else *reinterpret_cast<u32x4*>(lds + at + lane * 16) = u32x4{0u, 0u, 0u, 0u};
+            }
+        }
+        // a lane's 16-byte chunks of a slab: h and h + 4 (FP8), 2 s + h for K slice s (INT8)
+        const int fkey = (frow >> 1) & 7;
+        auto chunk = [&](int s) -> int { return F8 ? fsel + 4 * s : 2 * s + fsel; };
+        constexpr int PIECES = F8 ? 2 : 4;
+        auto load_a = [&](int k0, v4i (&f)[BLOCKS_M][PIECES]) {
+#pragma unroll
+            for (int i = 0; i < BLOCKS_M; ++i)
+#pragma unroll
+                for (int s = 0; s < PIECES; ++s) {
+                    const int k = k0 + chunk(s) * 16;
+                    f[i][s] = v4i{0, 0, 0, 0};
+                    if (k < rowbytes) f[i][s] = *reinterpret_cast<const v4i*>(a_rows[i] - kofs + k);
+                }
+        };
+        auto multiply = [&](int slab, const v4i (&f)[BLOCKS_M][PIECES]) {
+            const uint8_t* sb = lds + slab * (WN * kSlabBytes) + frow * kSlabBytes;
+            v4i fb[TILES_N][PIECES];
+#pragma unroll
+            for (int j = 0; j < TILES_N; ++j)
+#pragma unroll
+                for (int s = 0; s < PIECES; ++s) fb[j][s] = *reinterpret_cast<const v4i*>(sb + j * R * kSlabBytes + (chunk(s) ^ fkey) * 16);
+            auto frag = [](const v4i (&q)[PIECES], int s) -> Frag {
+                if constexpr (F8) return v8i{q[0][0], q[0][1], q[0][2], q[0][3], q[1][0], q[1][1], q[1][2], q[1][3]};
+                else return q[s];
+            };
+#pragma unroll
+            for (int i = 0; i < BLOCKS_M; ++i)
+#pragma unroll
+                for (int s = 0; s < KS; ++s)
+#pragma unroll
+                    for (int j = 0; j < TILES_N; ++j) mma(frag(f[i], s), frag(fb[j], s), acc[i][j]);
+        };
+        v4i f0[BLOCKS_M][PIECES], f1[BLOCKS_M][PIECES];
+        load_a(0, f0);
+        load_a(kSlabBytes, f1);
+        wait_vm_lgkm<0>();
+        __syncthreads();
+        if (idle) return;
+        for (int s = 0; s < nk; s += 2) {
+            multiply(s, f0);
+            if (s + 2 < nk) load_a((s + 2) * kSlabBytes, f0);
+            if (s + 1 < nk) {
+                multiply(s + 1, f1);
+                if (s + 3 < nk) load_a((s + 3) * kSlabBytes, f1);
+            }
+        }
+    } else
     for (int k0 = 0; k0 < rowbytes; k0 += kSlabBytes) {
         Frag fa[BLOCKS_M][KS], fb[TILES_N][KS];
 #pragma unroll
@@ -2139,7 +2208,15 @@ qmm_status launch_direct(GemmArgs& g, hipStream_t s)
     g.tiles_n = (int)((g.N + bn - 1) / bn);
     const int64_t total = (int64_t)g.tiles_m * g.tiles_n * g.batch;
     if (total > 0x7FFFFFFF) return QMM_ERR_UNSUPPORTED;
-    gemm_direct_kernel<KIND, FA, FB><<<(unsigned)total, 256, 0, s>>>(g);
+    // (B_LDS: codes; up to eight slabs of B, 64 KB, two workgroups per CU)
+    if constexpr (KIND != KIND_BF16) {
+        if (!g.direct_along_n && g.rowbytes <= 8 * kSlabBytes) {
+            const int lds_bytes = (int)((g.rowbytes + kSlabBytes - 1) / kSlabBytes) * 64 * kSlabBytes;
+            gemm_direct_kernel<KIND, FA, FB, true><<<(unsigned)total, 256, lds_bytes, s>>>(g);
+            return launch_status();
+        }
+    }
+    gemm_direct_kernel<KIND, FA, FB, false><<<(unsigned)total, 256, 0, s>>>(g);
     return launch_status();
 }
 

@@ -186,3 +186,25 @@ def test_product_of_few_tiles(kind, batch, m, n, row):
     alone = torch.empty_like(y)
     qmm.gemm(a, b, out=alone)
     assert torch.equal(alone, y)
+
+
+# Tall outputs at most 64 wide: B in LDS (up to eight slabs of K) and, beyond, from memory; odd numbers of slabs, a partial
+# last one, wavefronts without a row.  INT8 against the integer product; E4M3 against the same columns inside a product of 96,
+# which runs in the LDS kernels with the same order of additions.
+@pytest.mark.parametrize("kind", ["e4m3", "int8"])
+@pytest.mark.parametrize("batch,m,n,k", [(60, 600, 64, 512), (60, 577, 40, 144), (60, 600, 1, 16), (60, 600, 64, 1024), (1, 40000, 63, 400), (60, 600, 64, 1040)])
+def test_tall_product(kind, batch, m, n, k):
+    a, b = operands(kind, m, n, k, per_channel=(k % 3 == 0), batch=batch)
+    y, acc = qmm.gemm(a, b, torch.bfloat16, want_acc=True)
+    buf, alone = guarded((batch, m, n), torch.bfloat16)
+    qmm.gemm(a, b, out=alone)
+    assert torch.equal(alone, y) and intact(buf)
+    if kind == "int8":
+        exact = a[0].view(torch.int8).double() @ b[0].view(torch.int8).double().transpose(1, 2).contiguous()
+        assert torch.equal(acc.double(), exact)
+    else:
+        wide = torch.zeros((batch, 96, k), dtype=torch.uint8, device=DEV)
+        wide[:, :n] = b[0]
+        one = torch.ones(1, device=DEV)
+        _, acc_wide = qmm.gemm((a[0], qmm.operand(a[0], qmm.E4M3, one)), (wide, qmm.operand(wide, qmm.E4M3, one)), want_acc=True)
+        assert torch.equal(acc, acc_wide[:, :, :n])

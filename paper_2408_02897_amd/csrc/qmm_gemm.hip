@@ -33,7 +33,7 @@
 //    tiles.
 //  * Long K with few tiles: split-K with a second, fixed-order reduction kernel.
 //    Few tiles otherwise: gemm_deep_kernel (64 x 64 tiles, deeper LDS ring).
-//    Outputs at most 64 wide or high: gemm_direct_kernel (no LDS).
+//    Outputs at most 64 wide or high: gemm_direct_kernel (no LDS for the long operand).
 //    Contractions of one slab at most with many whole tiles: gemm_shortk_kernel;
 //    several whole tiles per CU and one step size per operand: gemm_stream_kernel
 //    (both: workgroups that stay on their CU and overlap a tile's stores with the

@@ -4,8 +4,8 @@
 // the maximum is taken on magnitude bit patterns (exact, order-free), partial
 // maxima go to the workspace and are folded per group, followed by the one
 // division: by a second small kernel, or -- dense tensors with one step size,
-// from 32 MB, and the several-tensors call -- by the workgroup that finishes
-// last (one launch).  The maximum is order-free, so the result does not depend
+// from 2^24 elements, and the several-tensors call -- by the workgroup that
+// finishes last (one launch), or by the quantize pass of qmm_scale_quantize.  The maximum is order-free, so the result does not depend
 // on launch geometry or on which workgroup folds.
 #include <algorithm>
 #include <atomic>

@@ -171,6 +171,10 @@ def main():
         # Set-up, untimed: the step runs until the GPU has been busy for `--settle-ms` (the part's clock under this load
         # takes some 10 ms to settle; a step is half a millisecond, so a handful of warm-up steps end while it still
         # ramps and the steps timed behind them read 5 % low).  Then the W warm-up steps, then exactly K timed steps.
+        # One step comes before that clock starts: the runtime loads a kernel's code when it is first launched, 6-13 ms for
+        # the step's kernels, during which the GPU would not be busy.
+        step(())
+        torch.cuda.synchronize()
         t_settle = time.perf_counter()
         while (time.perf_counter() - t_settle) * 1e3 < args.settle_ms:
             for _ in range(4):

@@ -542,16 +542,17 @@ qmm_status scale_partials(const qmm_tensor* x0, qmm_format fmt, const qmm_granul
     return launch_status();
 }
 
-// The second half: partial maxima -> step sizes.
+// The second half: partial maxima -> step sizes.  (An empty tensor has no partial maxima: batch = 0, and P = 1 so that the
+// folds' divisions by P are defined; they end before they read, and every group's step size becomes 1.)
 qmm_status scale_fold(const ScalePartials& pp, const uint32_t* partial, qmm_format fmt, const qmm_granularity* g,
                       float* delta_out, hipStream_t s)
 {
-    const int64_t G = g->batch_groups, inner = g->batch_inner > 0 ? g->batch_inner : 1;
+    const int64_t G = g->batch_groups, inner = g->batch_inner > 0 ? g->batch_inner : 1, P = pp.batch > 0 ? pp.P : 1;
     if (pp.C == 1)
-        finalize_single<<<(unsigned)G, kThreads, 0, s>>>(partial, pp.batch, pp.batch > 0 ? pp.P : 0, G, inner, host_qmax(fmt), delta_out);
+        finalize_single<<<(unsigned)G, kThreads, 0, s>>>(partial, pp.batch, P, G, inner, host_qmax(fmt), delta_out);
     else
         finalize_channels<<<dim3((unsigned)((pp.C + 31) / 32), (unsigned)G), kThreads, 0, s>>>(
-            partial, pp.batch, pp.batch > 0 ? pp.P : 0, pp.C, G, inner, host_qmax(fmt), delta_out);
+            partial, pp.batch, P, pp.C, G, inner, host_qmax(fmt), delta_out);
     return launch_status();
 }
 

@@ -208,3 +208,18 @@ def test_tall_product(kind, batch, m, n, k):
         one = torch.ones(1, device=DEV)
         _, acc_wide = qmm.gemm((a[0], qmm.operand(a[0], qmm.E4M3, one)), (wide, qmm.operand(wide, qmm.E4M3, one)), want_acc=True)
         assert torch.equal(acc, acc_wide[:, :, :n])
+
+
+# Empty tensors: every group's step size is 1, also where matrices share a group in runs (batch_inner), by both calls.
+@pytest.mark.parametrize("inner", [1, 2, 5])
+@pytest.mark.parametrize("groups", [1, 3])
+@pytest.mark.parametrize("per_channel", [False, True])
+@pytest.mark.parametrize("shape", [(0, 8, 16), (4, 0, 16), (4, 8, 0)])
+def test_empty_tensors_get_step_size_one(shape, per_channel, groups, inner):
+    x = torch.zeros(shape, dtype=torch.bfloat16, device=DEV)
+    for axis in (0, 1):
+        kw = dict(per_channel=per_channel, batch_groups=groups, batch_inner=inner)
+        d = qmm.scale(x, axis, qmm.E4M3, **kw)
+        c1, d1 = qmm.scale_quantize(x, axis, qmm.E4M3, **kw)
+        assert d.numel() == groups * (shape[1 if axis == 1 else 2] if per_channel else 1)
+        assert c1.numel() == 0 and bool((d == 1.0).all()) and bool((d1 == 1.0).all())

@@ -226,3 +226,26 @@ def test_empty_tensors_get_step_size_one(shape, per_channel, groups, inner):
         c1, d1 = qmm.scale_quantize(x, axis, qmm.E4M3, **kw)
         assert d.numel() == count
         assert c1.numel() == 0 and bool((d == 1.0).all()) and bool((d1 == 1.0).all())
+
+
+# Lines around every number of lanes a short line gets (1 .. 64 lanes, two halves) and the first long one, with a step size
+# per row, per run of matrices and per group; groups beyond the batch; from 4096 wavefronts of work on, four vectors a lane.
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("batch,rows,k,groups,inner", [
+    (1, 300, 1, 1, 1), (1, 259, 8, 1, 1), (3, 70, 9, 3, 1), (6, 45, 16, 3, 2), (4, 33, 31, 2, 1), (2, 67, 64, 1, 1), (5, 13, 65, 9, 1),
+    (1, 37, 256, 1, 1), (3, 5, 257, 2, 1), (2, 9, 512, 2, 1), (2, 5, 513, 1, 1), (1, 7, 1024, 1, 1), (6, 1, 1025, 3, 2), (700, 2, 3, 350, 2),
+    (1, 700000, 3, 1, 1), (2, 2600, 300, 2, 1), (1, 3000, 600, 1, 1), (3, 1500, 1100, 2, 2)])
+def test_dequantize_of_short_lines(batch, rows, k, groups, inner, out_dtype):
+    rng = np.random.default_rng(k + rows)
+    codes = rng.integers(0, 256, (batch, rows, k), dtype=np.uint8)
+    group = (np.arange(batch) // inner) % groups
+    for fmt in (qmm.INT8, qmm.E4M3, qmm.E5M2):
+        value = codes.view(np.int8).astype(np.float32) if fmt == qmm.INT8 else O.decode(fmt, codes).astype(np.float32)
+        for per_channel in (False, True):
+            d = rng.uniform(1e-3, 2.0, (groups, rows if per_channel else 1)).astype(np.float32)
+            want = torch.from_numpy(value * d[group][:, :, None]).to(out_dtype)
+            buf, out = guarded((batch, rows, k), out_dtype)
+            qmm.dequantize(torch.from_numpy(codes).to(DEV), fmt, torch.from_numpy(d.reshape(-1)).to(DEV), per_channel, groups,
+                           out=out, batch_inner=inner)
+            got, nan = out.cpu(), want.isnan()
+            assert torch.equal(got.isnan(), nan) and torch.equal(got[~nan], want[~nan]) and intact(buf), (fmt, per_channel)

@@ -39,10 +39,6 @@ struct QArgs {
     float qmax;
 };
 
-template <typename T> QMM_DEV float load_f32(const T* p);
-template <> QMM_DEV float load_f32<uint16_t>(const uint16_t* p) { return bf16_bits_to_f32(*p); }
-template <> QMM_DEV float load_f32<float>(const float* p) { return *p; }
-
 // A 16-byte vector of a tensor: 8 bfloat16 or 4 binary32 elements.
 template <typename T> struct Vec;
 template <> struct Vec<uint16_t> {
@@ -81,45 +77,63 @@ template <> struct Vec<float> {
     }
 };
 
-// Codes of four consecutive output elements, the first of them number g of the random stream, packed into a dword.
-template <int FMT, int MODE> QMM_DEV uint32_t encode4(float t0, float t1, float t2, float t3, uint64_t g, uint64_t seed)
+// Codes of 4 Q consecutive output elements, the first of them number g of the random stream, four to a dword.
+template <int FMT, int MODE, int Q> QMM_DEV void encode_quads(const float (&t)[4 * Q], uint64_t g, uint64_t seed, uint32_t (&out)[Q])
 {
     if constexpr (MODE == QMM_ROUND_RTNE) {
-        if constexpr (FMT == QMM_FMT_INT8)
-            return encode_int8_rtne(t0) | (encode_int8_rtne(t1) << 8) | (encode_int8_rtne(t2) << 16) | (encode_int8_rtne(t3) << 24);
-        else return encode_fp8_rtne_pair<FMT>(t0, t1) | (encode_fp8_rtne_pair<FMT>(t2, t3) << 16);
-    } else {
-        // The four elements are one block of the generator when the first of them starts one (always, unless the caller's
-        // offset or the row length is not a multiple of 4), else parts of two.
-        const uint64_t c = g >> 2;
-        const uint32_t j = (uint32_t)g & 3u;
-        const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
-        Philox4 p = philox4x32_10((uint32_t)c, (uint32_t)(c >> 32), 0u, 0u, k0, k1);
-        if (j != 0u) {
-            const Philox4 q = philox4x32_10((uint32_t)(c + 1), (uint32_t)((c + 1) >> 32), 0u, 0u, k0, k1);
-            uint32_t w[4];
 #pragma unroll
-            for (uint32_t e = 0; e < 4; ++e) {       // word j + e of the eight, by compares (an indexed array would live in memory)
-                const uint32_t s = j + e;
-                w[e] = s == 1 ? p.v[1] : s == 2 ? p.v[2] : s == 3 ? p.v[3] : s == 4 ? q.v[0] : s == 5 ? q.v[1] : q.v[2];
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) p.v[e] = w[e];
+        for (int q = 0; q < Q; ++q) {
+            if constexpr (FMT == QMM_FMT_INT8)
+                out[q] = encode_int8_rtne(t[4 * q]) | (encode_int8_rtne(t[4 * q + 1]) << 8) | (encode_int8_rtne(t[4 * q + 2]) << 16) |
+                         (encode_int8_rtne(t[4 * q + 3]) << 24);
+            else out[q] = encode_fp8_rtne_pair<FMT>(t[4 * q], t[4 * q + 1]) | (encode_fp8_rtne_pair<FMT>(t[4 * q + 2], t[4 * q + 3]) << 16);
         }
-        return encode<FMT, MODE>(t0, p.v[0]) | (encode<FMT, MODE>(t1, p.v[1]) << 8) | (encode<FMT, MODE>(t2, p.v[2]) << 16) |
-               (encode<FMT, MODE>(t3, p.v[3]) << 24);
+    } else {
+        // The elements are Q whole blocks of the generator when the first of them starts one (always, unless the caller's
+        // offset or the row length is not a multiple of 4), else parts of Q + 1.  One test for all of them and a wavefront:
+        // with one per block the blocks -- chains of ten dependent multiplies -- run one behind the other.
+        const uint64_t c = g >> 2;
+        const uint32_t j = (uint32_t)g & 3u, k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+        auto block = [&](int q) { return philox4x32_10((uint32_t)(c + q), (uint32_t)((c + q) >> 32), 0u, 0u, k0, k1); };
+        uint32_t w[4 * Q];
+        if (!__any(j != 0u)) {
+            asm volatile("; whole blocks");          // (keeps the compiler from computing both sides and selecting)
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const Philox4 p = block(q);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[4 * q + e] = p.v[e];
+            }
+        } else {
+            asm volatile("; parts of blocks");
+            Philox4 p = block(0);
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const Philox4 n = block(q + 1);
+                // words j .. j + 3 of the eight, by compares (an indexed array would live in memory)
+                auto word = [&](uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3) { return j == 0 ? w0 : j == 1 ? w1 : j == 2 ? w2 : w3; };
+                w[4 * q] = word(p.v[0], p.v[1], p.v[2], p.v[3]);
+                w[4 * q + 1] = word(p.v[1], p.v[2], p.v[3], n.v[0]);
+                w[4 * q + 2] = word(p.v[2], p.v[3], n.v[0], n.v[1]);
+                w[4 * q + 3] = word(p.v[3], n.v[0], n.v[1], n.v[2]);
+                p = n;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) out[q] = encode_sr4<FMT>(t + 4 * q, w + 4 * q);
     }
 }
 
 // The V codes of a vector, from `rho` and the number of its first element.
 template <typename T, int FMT, int MODE> QMM_DEV u32x2 encode_vec(const u32x4& w, float rho, uint64_t g, uint64_t seed)
 {
-    u32x2 out = {0u, 0u};
+    constexpr int Q = Vec<T>::V / 4;
+    float t[4 * Q];
 #pragma unroll
-    for (int q = 0; q < Vec<T>::V / 4; ++q)
-        out[q] = encode4<FMT, MODE>(Vec<T>::at(w, 4 * q) * rho, Vec<T>::at(w, 4 * q + 1) * rho, Vec<T>::at(w, 4 * q + 2) * rho,
-                                    Vec<T>::at(w, 4 * q + 3) * rho, g + 4 * q, seed);
-    return out;
+    for (int e = 0; e < 4 * Q; ++e) t[e] = Vec<T>::at(w, e) * rho;
+    uint32_t c[Q];
+    encode_quads<FMT, MODE, Q>(t, g, seed, c);
+    return u32x2{c[0], Q > 1 ? c[Q - 1] : 0u};
 }
 template <typename T> QMM_DEV void store_codes(uint8_t* dst, u32x2 c, int64_t left)
 {
@@ -133,7 +147,14 @@ template <typename T> QMM_DEV void store_codes(uint8_t* dst, u32x2 c, int64_t le
     }
 }
 
-QMM_DEV int64_t group_of(const QArgs& a, int64_t b) { return (b / a.inner) % a.groups; }
+// Scale group of matrix b < 65536 (host), in 32-bit divisions and only those the grouping needs.
+QMM_DEV int64_t group_of(const QArgs& a, int64_t b)
+{
+    if (a.groups == 1) return 0;
+    uint32_t q = (uint32_t)b;
+    if (a.inner > 1) q = a.inner > 65535 ? 0u : q / (uint32_t)a.inner;
+    return a.groups > 65535 ? q : q % (uint32_t)a.groups;
+}
 
 QMM_DEV uint32_t block_max_u32(uint32_t v)
 {
@@ -161,12 +182,14 @@ QMM_DEV float fold_delta(const QArgs& a, int64_t b, bool writer)
             if (i < a.fold_total) m = max(m, a.partial[i]);
         }
     } else {
-        // the k-th matrix of group g is ((k / inner) * G + g) * inner + k % inner, increasing with k
-        for (int64_t it = threadIdx.x;; it += kThreads) {
-            const int64_t k = it / a.P, p = it - k * a.P;
-            const int64_t mb = ((k / a.inner) * a.groups + g) * a.inner + k % a.inner;
-            if (mb >= a.batch) break;
-            m = max(m, a.partial[mb * a.P + p]);
+        // the k-th matrix of group g is ((k / inner) * G + g) * inner + k % inner, increasing with k (32 bits: batch < 65536)
+        const uint32_t P = (uint32_t)a.P, G = (uint32_t)a.groups, inner = (uint32_t)a.inner, batch = (uint32_t)a.batch;
+        for (uint32_t it = threadIdx.x;; it += kThreads) {
+            const uint32_t k = P > 1 ? it / P : it, p = it - k * P;
+            uint32_t mb = k * G + (uint32_t)g;
+            if (inner > 1) { const uint32_t q = k / inner; mb = (q * G + (uint32_t)g) * inner + (k - q * inner); }
+            if (mb >= batch) break;
+            m = max(m, a.partial[mb * P + p]);
         }
     }
     const float d = delta_from_absmax_bits(block_max_u32(m), a.qmax);
@@ -192,14 +215,15 @@ quantize_rows_bf16x16(QArgs a)
     const int64_t cv = v - r * vpr;
     const u32x4* src = reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(a.x) + b * a.batch_stride +
                                                       r * a.row_stride + cv * 16);
+    // The step size is requested in front of the elements: behind them its reciprocal starts when they have arrived
+    // (16384 x 1024 with one step size 9.7 against 10.4 us).
+    float d = 0.0f;
+    if constexpr (!FOLD) d = a.delta[group_of(a, b) * a.channels + (a.channels > 1 ? r : 0)];
     u32x4 w0 = {0u, 0u, 0u, 0u}, w1 = {0u, 0u, 0u, 0u};
     if (live) { w0 = src[0]; w1 = src[1]; }
-    float d;
     if constexpr (FOLD) {
         d = fold_delta(a, b, blockIdx.x == 0 && writes_group(a, b));
         if (!live) return;
-    } else {
-        d = a.delta[group_of(a, b) * a.channels + (a.channels > 1 ? r : 0)];
     }
     const float rho = 1.0f / d;
     const int64_t p0 = (b * a.rows + r) * a.cols + cv * 16;
@@ -207,41 +231,118 @@ quantize_rows_bf16x16(QArgs a)
     if constexpr (MODE == QMM_ROUND_RTNE) {
         out = encode16_bf16_rtne<FMT>(w0, w1, rho);
     } else {
-        const uint64_t g0 = (uint64_t)p0 + a.offset;
+        float t[16];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const u32x2 c = encode_vec<uint16_t, FMT, MODE>(h ? w1 : w0, rho, g0 + 8 * h, a.seed);
-            out[2 * h] = c[0]; out[2 * h + 1] = c[1];
-        }
+        for (int e = 0; e < 16; ++e) t[e] = Vec<uint16_t>::at(e < 8 ? w0 : w1, e & 7) * rho;
+        uint32_t c[4];
+        encode_quads<FMT, MODE, 4>(t, (uint64_t)p0 + a.offset, a.seed, c);
+        out = u32x4{c[0], c[1], c[2], c[3]};
     }
     *reinterpret_cast<u32x4*>(a.codes + p0) = out;
 }
 
-// Row-contracting, any type, extent, stride and alignment: a wavefront takes a row, a lane one 16-byte vector of it at a
-// time (wavefronts walk the rows of all matrices).  Dense tensors with one step size come in as one long row per matrix
-// and are shared out by pieces of a row: `pieces` wavefronts per row.
-template <typename T, int FMT, int MODE, bool FOLD> __global__ void __launch_bounds__(kThreads)
-quantize_rows(QArgs a, int64_t pieces)
+// Row-contracting, any type, extent, stride and alignment.  A wavefront takes PIECE 16-byte vectors a lane: a piece of a
+// long row, or (SHORT: rows of at most 128 vectors) several rows, each on as many lanes as it has vectors.  Dense tensors
+// with one step size come in as one long row per matrix.  Two vectors a lane, or one for small tensors, which need the
+// wavefronts.  (One thread per code / a wavefront a row, whatever its length / this way, a step size per row: 262144 x 64
+// binary32 45 / 70 / 14.4 us, 300000 x 20 bfloat16 16 / 125 / 6.0, 100 x 20000 binary32 6.8 / 28 / 3.2.  Four vectors a lane:
+// 19, 6.4 and 3.6 us.)
+struct RowPlan {
+    int64_t units;                 // pieces of work for one wavefront, per matrix
+    int64_t pieces;                // long rows: units per row (0: short rows)
+    int lane_shift, half_shift;    // short rows: 1 << lane_shift lanes a row, in 1 << half_shift halves
+};
+template <typename T, int FMT, int MODE, bool FOLD, int PIECE, bool SHORT> __global__ void __launch_bounds__(kThreads)
+quantize_rows(QArgs a, RowPlan plan)
 {
     constexpr int V = Vec<T>::V;
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t b = blockIdx.y;
     const T* base = static_cast<const T*>(a.x) + b * a.batch_stride;
-    float d = 0.0f;
-    if constexpr (FOLD) d = fold_delta(a, b, blockIdx.x == 0 && writes_group(a, b));
+    const float* delta = a.delta + group_of(a, b) * a.channels;
+    float rho_matrix = 1.0f;
+    if constexpr (FOLD) rho_matrix = 1.0f / fold_delta(a, b, blockIdx.x == 0 && writes_group(a, b));
+    else if (a.channels == 1) rho_matrix = 1.0f / delta[0];
+    const bool per_row = !FOLD && a.channels > 1, whole = a.cols >= V;
     const int64_t step = (int64_t)gridDim.x * (kThreads / kWave);
-    for (int64_t u = (int64_t)blockIdx.x * (kThreads / kWave) + threadIdx.x / kWave; u < a.rows * pieces; u += step) {
-        const int64_t r = u / pieces, piece = u - r * pieces;
-        if constexpr (!FOLD) d = a.delta[group_of(a, b) * a.channels + (a.channels > 1 ? r : 0)];
-        const float rho = 1.0f / d;
-        const int64_t p_row = (b * a.rows + r) * a.cols;
-        const T* row = base + r * a.row_stride;
-        for (int64_t c = (piece * kWave + lane) * V; c < a.cols; c += pieces * kWave * V) {
-            const int64_t left = a.cols - c;
-            u32x4 w;
-            if (left >= V) w = *reinterpret_cast<const u32x4_any*>(row + c);
-            else w = Vec<T>::partial_load(row + c, (int)left);
-            store_codes<T>(a.codes + p_row + c, encode_vec<T, FMT, MODE>(w, rho, (uint64_t)(p_row + c) + a.offset, a.seed), left);
+    const int64_t first = (int64_t)blockIdx.x * (kThreads / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    for (int64_t u = first; u < plan.units; u += step) {
+        // vector i: `left` elements (at most V) at row_at + at[i], their codes at code_at + at[i] (SHORT: + code_row[i] instead)
+        const T* row_at = base;
+        int64_t code_at = b * a.rows * a.cols;
+        typename std::conditional<SHORT, int64_t, int>::type at[PIECE];
+        int64_t code_row[SHORT ? PIECE : 1];
+        int left[PIECE];
+        float rho[PIECE];
+        if constexpr (!SHORT) {
+            int64_t r = 0;
+            if (a.rows > 1) r = plan.units <= 0xFFFFFFFFll ? (int64_t)((uint32_t)u / (uint32_t)plan.pieces) : u / plan.pieces;
+            const int64_t c0 = (u - r * plan.pieces) * (PIECE * kWave * V);
+            const int rest = (int)min(a.cols - c0, (int64_t)(PIECE * kWave * V));
+            const float rho_row = per_row ? 1.0f / delta[r] : rho_matrix;
+            row_at += r * a.row_stride + c0;
+            code_at += r * a.cols + c0;
+            if (rest == PIECE * kWave * V) {         // no vector to mask: most pieces
+                const T* src = row_at + lane * V;
+                uint8_t* dst = a.codes + code_at + lane * V;
+                u32x4 w[PIECE];
+#pragma unroll
+                for (int i = 0; i < PIECE; ++i) w[i] = *reinterpret_cast<const u32x4_any*>(src + i * kWave * V);
+#pragma unroll
+                for (int i = 0; i < PIECE; ++i)
+                    store_codes<T>(dst + i * kWave * V,
+                                   encode_vec<T, FMT, MODE>(w[i], rho_row, (uint64_t)(code_at + (i * kWave + lane) * V) + a.offset, a.seed), V);
+                continue;
+            }
+#pragma unroll
+            for (int i = 0; i < PIECE; ++i) {
+                at[i] = (i * kWave + lane) * V;
+                left[i] = min(rest - at[i], V);
+                rho[i] = rho_row;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < PIECE; ++i) {
+                const int64_t slot = u * PIECE + i;
+                const int64_t r = ((slot >> plan.half_shift) << (6 - plan.lane_shift)) + (lane >> plan.lane_shift);
+                const int c = (int)(((slot & ((1 << plan.half_shift) - 1)) << 6) + (lane & ((1 << plan.lane_shift) - 1))) * V;
+                left[i] = r < a.rows ? min((int)a.cols - c, V) : 0;
+                at[i] = r * a.row_stride + c;
+                code_row[i] = r * a.cols + c;
+                rho[i] = rho_matrix;
+                if (per_row && left[i] > 0) rho[i] = delta[r];
+            }
+            if (per_row) {
+#pragma unroll
+                for (int i = 0; i < PIECE; ++i) rho[i] = 1.0f / rho[i];
+            }
+        }
+        u32x4 w[PIECE];
+#pragma unroll
+        for (int i = 0; i < PIECE; ++i) w[i] = u32x4{0u, 0u, 0u, 0u};
+        if (whole) {
+            // a partial last vector is taken back by what it lacks: the elements it shares with the one before it give the
+            // same codes twice
+#pragma unroll
+            for (int i = 0; i < PIECE; ++i) {
+                if (left[i] > 0) {
+                    at[i] -= V - left[i];
+                    if constexpr (SHORT) code_row[i] -= V - left[i];
+                    left[i] = V;
+                    w[i] = *reinterpret_cast<const u32x4_any*>(row_at + at[i]);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < PIECE; ++i)
+                if (left[i] > 0) w[i] = Vec<T>::partial_load(row_at + at[i], left[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < PIECE; ++i) {
+            if (left[i] > 0) {
+                const int64_t p = code_at + (SHORT ? code_row[SHORT ? i : 0] : (int64_t)at[i]);
+                store_codes<T>(a.codes + p, encode_vec<T, FMT, MODE>(w[i], rho[i], (uint64_t)p + a.offset, a.seed), left[i]);
+            }
         }
     }
 }
@@ -401,10 +502,11 @@ quantize_cols(QArgs a, int64_t tiles_n, int64_t tiles)
             const uint64_t g = (uint64_t)((b * N + n + j) * K + k_first) + a.offset;
 #pragma unroll
             for (int q = 0; q < RT / 4; ++q) {
-                const uint32_t code = encode4<FMT, MODE>(Vec<T>::at(w[4 * q], j) * rho, Vec<T>::at(w[4 * q + 1], j) * rho,
-                                                         Vec<T>::at(w[4 * q + 2], j) * rho, Vec<T>::at(w[4 * q + 3], j) * rho,
-                                                         g + 4 * q, a.seed);
-                *reinterpret_cast<uint32_t*>(&tile[place(tn * V + j, tk * RT + 4 * q)]) = code;
+                const float v[4] = {Vec<T>::at(w[4 * q], j) * rho, Vec<T>::at(w[4 * q + 1], j) * rho,
+                                    Vec<T>::at(w[4 * q + 2], j) * rho, Vec<T>::at(w[4 * q + 3], j) * rho};
+                uint32_t code[1];
+                encode_quads<FMT, MODE, 1>(v, g + 4 * q, a.seed, code);
+                *reinterpret_cast<uint32_t*>(&tile[place(tn * V + j, tk * RT + 4 * q)]) = code[0];
             }
             // (one column at a time: interleaved, the generator blocks of a thread need 240 registers)
             if constexpr (MODE == QMM_ROUND_STOCHASTIC) __builtin_amdgcn_sched_barrier(0);
@@ -426,6 +528,33 @@ quantize_cols(QArgs a, int64_t tiles_n, int64_t tiles)
             }
         }
         if (t + gridDim.x < tiles) __syncthreads();          // the tile and the step sizes are reused
+    }
+}
+
+template <typename T, int FMT, int MODE, bool FOLD> void launch_rows(const QArgs& q, hipStream_t s)
+{
+    RowPlan plan{};
+    const int64_t nvec = (q.cols + Vec<T>::V - 1) / Vec<T>::V, slots_per_row = (nvec + kWave - 1) / kWave;
+    const bool is_short = nvec <= 2 * kWave && q.rows > 1;
+    int64_t slots = q.rows * slots_per_row;                                  // wavefront-wide rows of vectors, per matrix
+    if (is_short) {
+        while (plan.lane_shift < 6 && (1 << plan.lane_shift) < nvec) ++plan.lane_shift;
+        plan.half_shift = nvec > kWave ? 1 : 0;
+        const int64_t at_once = kWave >> plan.lane_shift;
+        slots = ((q.rows + at_once - 1) / at_once) << plan.half_shift;
+    }
+    const bool small = slots * q.batch <= 4096;                              // sixteen wavefronts per CU and fewer
+    const int piece = small ? 1 : 2;
+    if (is_short) plan.units = (slots + piece - 1) / piece;
+    else { plan.pieces = (slots_per_row + piece - 1) / piece; plan.units = q.rows * plan.pieces; }
+    constexpr int kWaves = kThreads / kWave;
+    const dim3 grid((unsigned)std::min<int64_t>((plan.units + kWaves - 1) / kWaves, 65536), (unsigned)q.batch);
+    if (is_short) {
+        if (small) quantize_rows<T, FMT, MODE, FOLD, 1, true><<<grid, kThreads, 0, s>>>(q, plan);
+        else quantize_rows<T, FMT, MODE, FOLD, 2, true><<<grid, kThreads, 0, s>>>(q, plan);
+    } else {
+        if (small) quantize_rows<T, FMT, MODE, FOLD, 1, false><<<grid, kThreads, 0, s>>>(q, plan);
+        else quantize_rows<T, FMT, MODE, FOLD, 2, false><<<grid, kThreads, 0, s>>>(q, plan);
     }
 }
 
@@ -456,17 +585,8 @@ template <int FMT, int MODE, bool FOLD> qmm_status launch(const qmm_tensor* x, c
         quantize_rows_bf16x16<FMT, MODE, FOLD><<<dim3((unsigned)((nv + kThreads - 1) / kThreads), (unsigned)x->batch), kThreads, 0, s>>>(q);
         return launch_status();
     }
-    // rows go to wavefronts, a long row in pieces of 4 vectors a lane
-    int64_t pieces = 1;
-    if (q.rows == 1) {
-        const int64_t span = (int64_t)kWave * 4 * (bf16 ? 8 : 4);
-        pieces = std::max<int64_t>(1, (q.cols + span - 1) / span);
-    }
-    constexpr int kWaves = kThreads / kWave;
-    const int64_t blocks = std::min<int64_t>((q.rows * pieces + kWaves - 1) / kWaves, 65536);
-    const dim3 grid((unsigned)blocks, (unsigned)q.batch);
-    if (bf16) quantize_rows<uint16_t, FMT, MODE, FOLD><<<grid, kThreads, 0, s>>>(q, pieces);
-    else quantize_rows<float, FMT, MODE, FOLD><<<grid, kThreads, 0, s>>>(q, pieces);
+    if (bf16) launch_rows<uint16_t, FMT, MODE, FOLD>(q, s);
+    else launch_rows<float, FMT, MODE, FOLD>(q, s);
     return launch_status();
 }
 

@@ -249,3 +249,28 @@ def test_dequantize_of_short_lines(batch, rows, k, groups, inner, out_dtype):
                            out=out, batch_inner=inner)
             got, nan = out.cpu(), want.isnan()
             assert torch.equal(got.isnan(), nan) and torch.equal(got[~nan], want[~nan]) and intact(buf), (fmt, per_channel)
+
+
+# Rows that contract, around every number of lanes a row gets (1 .. 64, two halves, pieces of long rows), below and above the
+# 4096 wavefronts from which a lane takes two vectors, with values that only some wavefronts hold: NaN, infinities, zeros and
+# magnitudes below every format's normal range.
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("form", ["dense", "shifted"])
+@pytest.mark.parametrize("batch,rows,cols", [(1, 70, 1), (1, 33, 3), (2, 130, 20), (1, 90000, 9), (1, 40000, 44), (3, 1700, 300), (1, 2300, 700),
+                                             (2, 1200, 1031), (1, 3, 40001), (1, 40, 9000), (1, 1, 140001)])
+def test_quantize_of_short_and_long_rows(batch, rows, cols, form, dtype):
+    x = tensor_form(form, rows, cols, batch, dtype, seed=rows + cols).clone() if form == "dense" else tensor_form(form, rows, cols, batch, dtype, rows)
+    for i, v in enumerate([float("nan"), float("inf"), -float("inf"), 0.0, 1e-7, -3e-6, 2e-4, -1e-30]):
+        x[-1, rows // 2 + i // cols if rows > 40 else rows // 2, (i * 5) % cols] = v
+    xn = x.float().cpu().numpy()
+    for per_channel in (True, False):
+        count = rows if per_channel else 1
+        d = np.random.default_rng(cols).uniform(1e-3, 1e-1, count).astype(np.float32)
+        for fmt in (qmm.E4M3, qmm.INT8, qmm.E5M2):
+            for mode, offset in ((qmm.RTNE, 0), (qmm.STOCHASTIC, 0), (qmm.STOCHASTIC, 7)):
+                want = O.quantize(xn, 1, fmt, d, per_channel, 1, mode, 77, offset, 1)
+                buf = torch.full((want.size + 2 * GUARD,), 77, dtype=torch.uint8, device=DEV)
+                out = buf[GUARD:GUARD + want.size].view(want.shape)
+                qmm.quantize(x, 1, fmt, torch.from_numpy(d).to(DEV), per_channel, 1, mode, 77, offset, out=out)
+                assert np.array_equal(out.cpu().numpy(), want), (per_channel, fmt, mode, offset)
+                assert bool((buf[:GUARD] == 77).all()) and bool((buf[-GUARD:] == 77).all())

@@ -294,6 +294,7 @@ QMM_DEV bool arrive_last(uint32_t* slot, unsigned id, unsigned total)
 }
 
 // The scale pass in two halves (qmm_scale.hip), for the call that hands the partial maxima to the quantize pass.
+constexpr int kFoldSlabs = 32;       // row slabs per matrix in the column maxima: what the quantize pass can fold on its way, at most
 struct ScalePartials {
     int64_t batch, P, C;       // layout of the partial maxima: [batch][P][C] (C = channels of a step size each, else 1)
     bool done;                 // the step sizes have been written already

@@ -431,7 +431,6 @@ quantize_flat_multi(MultiQ a)
 // grid (tiles, batch), tiles numbered along n first; workgroups loop where the grid would be too large to launch.
 constexpr int kTileK = 128;
 constexpr int kTileRowBytes = kTileK + 16;   // padded row of the LDS code tile
-constexpr int kFoldSlabs = 32;               // partial maxima per column that FOLD takes, at most
 
 template <typename T, int FMT, int MODE, bool FOLD, int kTileN> __global__ void __launch_bounds__(kThreads)
 quantize_cols(QArgs a, int64_t tiles_n, int64_t tiles)

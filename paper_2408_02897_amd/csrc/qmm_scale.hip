@@ -17,7 +17,6 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kMaxFlatBlocks = 1024;   // 4 workgroups per CU on 256 CUs; 4 partials per thread in the fold
 constexpr int kColSlabRows = 128;      // rows folded by one workgroup in the column-group kernel, at least
-constexpr int kMaxColSlabs = 32;       // and at most this many slabs: what the quantize pass can fold on its way (qmm_quantize.hip)
 
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -422,7 +421,7 @@ Plan make_plan(const qmm_tensor* x, const qmm_granularity* g)
         p.C = x->rows;
     } else {
         p.kind = Plan::COLS;
-        p.slab_rows = std::max<int64_t>(kColSlabRows, (x->rows + kMaxColSlabs - 1) / kMaxColSlabs);
+        p.slab_rows = std::max<int64_t>(kColSlabRows, (x->rows + kFoldSlabs - 1) / kFoldSlabs);
         p.P = (x->rows + p.slab_rows - 1) / p.slab_rows;
         p.C = x->cols;
     }

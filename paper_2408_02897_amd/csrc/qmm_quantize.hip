@@ -78,7 +78,8 @@ template <> struct Vec<float> {
 };
 
 // Codes of 4 Q consecutive output elements, the first of them number g of the random stream, four to a dword.
-template <int FMT, int MODE, int Q> QMM_DEV void encode_quads(const float (&t)[4 * Q], uint64_t g, uint64_t seed, uint32_t (&out)[Q])
+// `whole`: g is known to be a multiple of 4.
+template <int FMT, int MODE, int Q> QMM_DEV void encode_quads(const float (&t)[4 * Q], uint64_t g, uint64_t seed, bool whole, uint32_t (&out)[Q])
 {
     if constexpr (MODE == QMM_ROUND_RTNE) {
 #pragma unroll
@@ -90,34 +91,24 @@ template <int FMT, int MODE, int Q> QMM_DEV void encode_quads(const float (&t)[4
         }
     } else {
         // The elements are Q whole blocks of the generator when the first of them starts one (always, unless the caller's
-        // offset or the row length is not a multiple of 4), else parts of Q + 1.  One test for all of them and a wavefront:
-        // with one per block the blocks -- chains of ten dependent multiplies -- run one behind the other.
+        // offset or the row length is not a multiple of 4), else parts of Q + 1.
         const uint64_t c = g >> 2;
         const uint32_t j = (uint32_t)g & 3u, k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
         auto block = [&](int q) { return philox4x32_10((uint32_t)(c + q), (uint32_t)((c + q) >> 32), 0u, 0u, k0, k1); };
-        uint32_t w[4 * Q];
-        if (!__any(j != 0u)) {
-            asm volatile("; whole blocks");          // (keeps the compiler from computing both sides and selecting)
+        uint32_t w[4 * Q + 4];
+        auto take = [&](int q) {
+            const Philox4 p = block(q);
 #pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                const Philox4 p = block(q);
+            for (int e = 0; e < 4; ++e) w[4 * q + e] = p.v[e];
+        };
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w[4 * q + e] = p.v[e];
-            }
-        } else {
-            asm volatile("; parts of blocks");
-            Philox4 p = block(0);
+        for (int q = 0; q < Q; ++q) take(q);
+        if (!whole) {
+            asm volatile("; parts of blocks");       // (keeps the compiler from computing this for every call and selecting)
+            take(Q);
 #pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                const Philox4 n = block(q + 1);
-                // words j .. j + 3 of the eight, by compares (an indexed array would live in memory)
-                auto word = [&](uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3) { return j == 0 ? w0 : j == 1 ? w1 : j == 2 ? w2 : w3; };
-                w[4 * q] = word(p.v[0], p.v[1], p.v[2], p.v[3]);
-                w[4 * q + 1] = word(p.v[1], p.v[2], p.v[3], n.v[0]);
-                w[4 * q + 2] = word(p.v[2], p.v[3], n.v[0], n.v[1]);
-                w[4 * q + 3] = word(p.v[3], n.v[0], n.v[1], n.v[2]);
-                p = n;
-            }
+            for (int e = 0; e < 4 * Q; ++e)          // word j + e, by compares (an indexed array would live in memory)
+                w[e] = j == 0 ? w[e] : j == 1 ? w[e + 1] : j == 2 ? w[e + 2] : w[e + 3];
         }
 #pragma unroll
         for (int q = 0; q < Q; ++q) out[q] = encode_sr4<FMT>(t + 4 * q, w + 4 * q);
@@ -132,7 +123,9 @@ template <typename T, int FMT, int MODE> QMM_DEV u32x2 encode_vec(const u32x4& w
 #pragma unroll
     for (int e = 0; e < 4 * Q; ++e) t[e] = Vec<T>::at(w, e) * rho;
     uint32_t c[Q];
-    encode_quads<FMT, MODE, Q>(t, g, seed, c);
+    // One test for a vector and a wavefront: with one per block the blocks -- chains of ten dependent multiplies -- run one
+    // behind the other.
+    encode_quads<FMT, MODE, Q>(t, g, seed, MODE == QMM_ROUND_STOCHASTIC && !__any((g & 3u) != 0u), c);
     return u32x2{c[0], Q > 1 ? c[Q - 1] : 0u};
 }
 template <typename T> QMM_DEV void store_codes(uint8_t* dst, u32x2 c, int64_t left)
@@ -235,7 +228,7 @@ quantize_rows_bf16x16(QArgs a)
 #pragma unroll
         for (int e = 0; e < 16; ++e) t[e] = Vec<uint16_t>::at(e < 8 ? w0 : w1, e & 7) * rho;
         uint32_t c[4];
-        encode_quads<FMT, MODE, 4>(t, (uint64_t)p0 + a.offset, a.seed, c);
+        encode_quads<FMT, MODE, 4>(t, (uint64_t)p0 + a.offset, a.seed, !__any((((uint64_t)p0 + a.offset) & 3u) != 0u), c);
         out = u32x4{c[0], c[1], c[2], c[3]};
     }
     *reinterpret_cast<u32x4*>(a.codes + p0) = out;
@@ -422,22 +415,58 @@ quantize_flat_multi(MultiQ a)
 }
 
 // Column-contracting (the input is [K][N], codes are [N][K]): any type, extent, stride and alignment.  Workgroup tile =
-// 128 k x kTileN n (64, or 128 for large bfloat16 tensors).  A thread loads RT rows (k) x one 16-byte vector (n), packs
-// the codes of each column along k into dwords and parks them in an LDS tile [n][k]; then every thread writes 16-byte
-// pieces of finished code rows, 128 contiguous bytes per n.  The narrow tile gives the small tensors, which left CUs idle,
-// twice the workgroups, and a head dimension of 64 no idle half; from 2048 wide tiles on the wide one's 256 contiguous
-// bytes per input row count for more (bfloat16 16384 x 3072: 29.7 against 32.8 us; 16384 x 1024, 1024 wide tiles: 12.1
-// against 11.5 us; 512 matrices of 512 x 64: 14.9 against 11.2 us).
+// 128 k x kTileN n.  A thread loads RT rows (k) x V elements (n), packs the codes of each column along k into dwords and
+// parks them in an LDS tile [n][k]; then every thread writes 16-byte (kTileN = 16: 8-byte) pieces of finished code rows.
+// kTileN = 64, 16 bytes a thread and row; 128 for large bfloat16 tensors: from 2048 wide tiles on 256 contiguous bytes per
+// input row count for more than twice the workgroups (bfloat16 16384 x 3072: 29.7 against 32.8 us; 16384 x 1024, 1024 wide
+// tiles: 12.1 against 11.5 us; 512 matrices of 512 x 64: 14.9 against 11.2 us).  16, two elements a thread and row, where
+// the chip would be idle otherwise, up to 192 tiles of 64 (256 with stochastic rounding): a thread's 32 codes, with
+// stochastic rounding eight generator blocks one behind the other, are what such a tensor takes (tiles of 64 / 16: 768 x 768
+// bfloat16 3.3 / 2.9 us, stochastic 5.5 / 3.6; 16384 x 128, 256 tiles, 3.4 / 3.8, stochastic 5.7 / 5.2).
 // grid (tiles, batch), tiles numbered along n first; workgroups loop where the grid would be too large to launch.
 constexpr int kTileK = 128;
 constexpr int kTileRowBytes = kTileK + 16;   // padded row of the LDS code tile
 
+// V neighbouring elements of a row, the first `left` of them inside the matrix (zeros for the others).
+template <typename T, int V> QMM_DEV u32x4 load_columns(const T* p, int left)
+{
+    u32x4 w = {0u, 0u, 0u, 0u};
+    if constexpr (V == Vec<T>::V) {
+        if (left == V) w = *reinterpret_cast<const u32x4_any*>(p);
+        else if (left > 0) w = Vec<T>::partial_load(p, left);
+    } else {
+        static_assert(V == 2, "two elements, or a vector");
+        typedef unsigned int pair_any __attribute__((ext_vector_type(sizeof(T) == 2 ? 1 : 2), aligned(sizeof(T))));
+        if (left == 2) {
+            const pair_any q = *reinterpret_cast<const pair_any*>(p);
+            w[0] = q[0];
+            if constexpr (sizeof(T) == 4) w[1] = q[1];
+        } else if (left == 1) {
+            if constexpr (sizeof(T) == 2) w[0] = *p; else w[0] = __float_as_uint(*p);
+        }
+    }
+    return w;
+}
+// The first `left` of B bytes (B = 8, 16; left < B).
+template <int B> QMM_DEV void store_bytes(uint8_t* dst, u32x4 w, int left)
+{
+    typedef unsigned short u16_byte __attribute__((aligned(1)));
+    if (B > 8 && (left & 8)) { *reinterpret_cast<u32x2_byte*>(dst) = u32x2{w[0], w[1]}; dst += 8; w[0] = w[2]; w[1] = w[3]; }
+    if (left & 4) { *reinterpret_cast<u32_byte*>(dst) = w[0]; dst += 4; w[0] = w[1]; }
+    if (left & 2) { *reinterpret_cast<u16_byte*>(dst) = (unsigned short)w[0]; dst += 2; w[0] >>= 16; }
+    if (left & 1) *dst = (uint8_t)w[0];
+}
+
+// Every column's codes start a block of the random generator.
+__host__ QMM_DEV bool whole_blocks(const QArgs& a) { return ((a.rows | (int64_t)a.offset) & 3) == 0; }
+
 template <typename T, int FMT, int MODE, bool FOLD, int kTileN> __global__ void __launch_bounds__(kThreads)
 quantize_cols(QArgs a, int64_t tiles_n, int64_t tiles)
 {
-    constexpr int V = Vec<T>::V;
+    constexpr int V = kTileN == 16 ? 2 : Vec<T>::V;
     constexpr int TN = kTileN / V, TK = kThreads / TN, RT = kTileK / TK;       // 8 x 32 threads of 4 rows, or 16 x 16 of 8
     constexpr int Q = kThreads / kTileN;                                       // threads per column in the fold
+    constexpr int PB = kTileN * kTileK / kThreads < 16 ? 8 : 16;               // bytes of a finished piece
     static_assert(RT % 4 == 0, "codes are packed four rows at a time");
     __shared__ __attribute__((aligned(16))) uint8_t tile[kTileN * kTileRowBytes];
     __shared__ uint32_t s_max[Q][kTileN];
@@ -449,26 +478,32 @@ quantize_cols(QArgs a, int64_t tiles_n, int64_t tiles)
     // dword stores would otherwise meet in the same banks
     auto place = [](int n, int k) { return n * kTileRowBytes + ((((k >> 4) ^ (n >> 3)) & 7) << 4) + (k & 15); };
     for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
-        const int64_t tile_k = t / tiles_n, tile_n = t - tile_k * tiles_n;
+        const int64_t tile_k = tiles <= 0xFFFFFFFFll ? (int64_t)((uint32_t)t / (uint32_t)tiles_n) : t / tiles_n;
+        const int64_t tile_n = t - tile_k * tiles_n;
         const int64_t n0 = tile_n * kTileN, k0 = tile_k * kTileK;
         const int64_t n = n0 + tn * V, k_first = k0 + tk * RT;
-        const T* base = static_cast<const T*>(a.x) + b * a.batch_stride + n;
         const int n_left = (int)max((int64_t)0, min((int64_t)V, N - n));          // columns of this thread inside the matrix
+        const bool live = k_first < K && n_left > 0;
         u32x4 w[RT];
 #pragma unroll
-        for (int i = 0; i < RT; ++i) {
-            const int64_t k = k_first + i;
-            w[i] = u32x4{0u, 0u, 0u, 0u};
-            if (k < K) {
-                if (n_left == V) w[i] = *reinterpret_cast<const u32x4_any*>(base + k * a.row_stride);
-                else if (n_left > 0) w[i] = Vec<T>::partial_load(base + k * a.row_stride, n_left);
+        for (int i = 0; i < RT; ++i) w[i] = u32x4{0u, 0u, 0u, 0u};
+        if (live) {
+            // (rows past the last one are the last one again, without a test for each: their codes are not stored)
+            const T* base = static_cast<const T*>(a.x) + b * a.batch_stride + k_first * a.row_stride + n;
+            const int last = (int)min(K - 1 - k_first, (int64_t)(RT - 1));
+            if (n_left == V) {
+#pragma unroll
+                for (int i = 0; i < RT; ++i) w[i] = load_columns<T, V>(base + min(i, last) * a.row_stride, V);
+            } else {
+#pragma unroll
+                for (int i = 0; i < RT; ++i) w[i] = load_columns<T, V>(base + min(i, last) * a.row_stride, n_left);
             }
         }
         // step sizes of the tile's columns, while the elements are on their way
         const int c = threadIdx.x & (kTileN - 1), q4 = threadIdx.x / kTileN;
         const int64_t col = n0 + c;
         if (FOLD && a.channels > 1) {
-            // one scale group per matrix (host): fold the column's P partial maxima, four threads a column
+            // one scale group per matrix (host): fold the column's P partial maxima, Q threads a column
             uint32_t m = 0;
             if (col < N) {
                 const uint32_t* p = a.partial + b * a.P * N + col;
@@ -494,39 +529,86 @@ quantize_cols(QArgs a, int64_t tiles_n, int64_t tiles)
             s_rho[c] = 1.0f / a.delta[group_of(a, b) * a.channels + (a.channels > 1 ? min(col, N - 1) : 0)];
         }
         __syncthreads();
-        // column by column: RT codes of consecutive output elements
+        // Column by column: RT codes of consecutive output elements, in one run of code for columns that start generator blocks
+        // and one for others, which share the blocks among a column's codes (not in the wide tile: host).  One part at a time:
+        // interleaved, the generator blocks of a thread need up to 240 registers.
+        auto columns = [&](auto at_block, auto quads) {
+            constexpr int B = decltype(quads)::value;
+            uint64_t g = (uint64_t)((b * N + n) * K + k_first) + a.offset;        // number of the column's first code
 #pragma unroll
-        for (int j = 0; j < V; ++j) {
-            const float rho = s_rho[tn * V + j];
-            const uint64_t g = (uint64_t)((b * N + n + j) * K + k_first) + a.offset;
+            for (int j = 0; j < V; ++j, g += (uint64_t)K) {
+                const float rho = s_rho[tn * V + j];
 #pragma unroll
-            for (int q = 0; q < RT / 4; ++q) {
-                const float v[4] = {Vec<T>::at(w[4 * q], j) * rho, Vec<T>::at(w[4 * q + 1], j) * rho,
-                                    Vec<T>::at(w[4 * q + 2], j) * rho, Vec<T>::at(w[4 * q + 3], j) * rho};
-                uint32_t code[1];
-                encode_quads<FMT, MODE, 1>(v, g + 4 * q, a.seed, code);
-                *reinterpret_cast<uint32_t*>(&tile[place(tn * V + j, tk * RT + 4 * q)]) = code[0];
+                for (int q = 0; q < RT / 4; q += B) {
+                    float v[4 * B];
+#pragma unroll
+                    for (int e = 0; e < 4 * B; ++e) v[e] = Vec<T>::at(w[4 * q + e], j) * rho;
+                    uint32_t code[B];
+                    encode_quads<FMT, MODE, B>(v, g + 4 * q, a.seed, at_block.value, code);
+#pragma unroll
+                    for (int e = 0; e < B; ++e) *reinterpret_cast<uint32_t*>(&tile[place(tn * V + j, tk * RT + 4 * (q + e))]) = code[e];
+                    if constexpr (MODE == QMM_ROUND_STOCHASTIC && kTileN > 16) __builtin_amdgcn_sched_barrier(0);
+                }
             }
-            // (one column at a time: interleaved, the generator blocks of a thread need 240 registers)
-            if constexpr (MODE == QMM_ROUND_STOCHASTIC) __builtin_amdgcn_sched_barrier(0);
+        };
+        if (live) {
+            if constexpr (MODE == QMM_ROUND_RTNE || kTileN == 128) columns(std::true_type{}, std::integral_constant<int, 1>{});
+            else if (whole_blocks(a)) columns(std::true_type{}, std::integral_constant<int, 1>{});
+            else columns(std::false_type{}, std::integral_constant<int, RT / 4>{});
         }
         __syncthreads();
-        // kTileN code rows x 8 pieces of 16 bytes, 2 or 4 per thread
+        // finished pieces, 1, 2 or 4 per thread
 #pragma unroll
-        for (int it = 0; it < kTileN * kTileK / 16 / kThreads; ++it) {
+        for (int it = 0; it < kTileN * kTileK / PB / kThreads; ++it) {
             const int piece = it * kThreads + threadIdx.x;
-            const int row = piece >> 3, seg = piece & 7;
-            const int64_t nn = n0 + row, kk = k0 + seg * 16;
+            const int row = piece / (kTileK / PB), at = piece % (kTileK / PB) * PB;
+            const int64_t nn = n0 + row, kk = k0 + at;
             if (nn >= N || kk >= K) continue;
             uint8_t* dst = a.codes + (b * N + nn) * K + kk;
-            const uint8_t* srcp = &tile[place(row, seg * 16)];
-            if (kk + 16 <= K) {
-                *reinterpret_cast<u32x4_byte*>(dst) = *reinterpret_cast<const u32x4*>(srcp);
+            const uint8_t* srcp = &tile[place(row, at)];
+            u32x4 codes;
+            if constexpr (PB == 16) codes = *reinterpret_cast<const u32x4*>(srcp);
+            else { const u32x2 h = *reinterpret_cast<const u32x2*>(srcp); codes = u32x4{h[0], h[1], 0u, 0u}; }
+            if (kk + PB <= K) {
+                if constexpr (PB == 16) *reinterpret_cast<u32x4_byte*>(dst) = codes;
+                else *reinterpret_cast<u32x2_byte*>(dst) = u32x2{codes[0], codes[1]};
             } else {
-                for (int e = 0; e < 16 && kk + e < K; ++e) dst[e] = srcp[e];
+                store_bytes<PB>(dst, codes, (int)(K - kk));
             }
         }
         if (t + gridDim.x < tiles) __syncthreads();          // the tile and the step sizes are reused
+    }
+}
+
+// One thread per code, for tensors so small that nothing but the length of a thread's own work counts: contracting over
+// rows 33 x 70 1.8 us against 2.6 in tiles of 16, stochastic 1.9 against 3.8; 256 x 768 2.5 against 2.6.  Contracting over
+// columns the vectors of the row kernels are as fast, but for stochastic rounding of rows that are not whole generator
+// blocks (301 x 202: 2.0 against 2.8 us).
+constexpr int64_t kEachMax = 1 << 18;
+template <typename T, int FMT, int MODE> __global__ void __launch_bounds__(kThreads)
+quantize_each(QArgs a, int contract_axis)
+{
+    const uint32_t NC = (uint32_t)(contract_axis == 1 ? a.rows : a.cols), KC = (uint32_t)(contract_axis == 1 ? a.cols : a.rows);
+    const uint32_t i = blockIdx.x * kThreads + threadIdx.x, n = i / KC, k = i - n * KC;
+    if (n >= NC) return;
+    const int64_t b = blockIdx.y;
+    const float d = a.delta[group_of(a, b) * a.channels + (a.channels > 1 ? n : 0u)];
+    const int64_t r = contract_axis == 1 ? n : k, c = contract_axis == 1 ? k : n;
+    const u32x4 x = Vec<T>::partial_load(static_cast<const T*>(a.x) + b * a.batch_stride + r * a.row_stride + c, 1);
+    const float t = Vec<T>::at(x, 0) * (1.0f / d);
+    const int64_t p = (b * NC + n) * KC + k;
+    if constexpr (MODE == QMM_ROUND_RTNE) {
+        const float v[4] = {t, t, t, t};
+        uint32_t code[1];
+        encode_quads<FMT, MODE, 1>(v, 0, 0, true, code);
+        a.codes[p] = (uint8_t)code[0];
+    } else {
+        const uint64_t g = (uint64_t)p + a.offset, blk = g >> 2;
+        const Philox4 q = philox4x32_10((uint32_t)blk, (uint32_t)(blk >> 32), 0u, 0u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
+        const uint32_t j = (uint32_t)g & 3u, word = j == 0 ? q.v[0] : j == 1 ? q.v[1] : j == 2 ? q.v[2] : q.v[3];
+        const float v[4] = {t, t, t, t};
+        const uint32_t words[4] = {word, word, word, word};
+        a.codes[p] = (uint8_t)encode_sr4<FMT>(v, words);
     }
 }
 
@@ -561,12 +643,25 @@ template <typename T, int FMT, int MODE, bool FOLD> void launch_rows(const QArgs
 template <int FMT, int MODE, bool FOLD> qmm_status launch(const qmm_tensor* x, const QArgs& a, hipStream_t s)
 {
     const bool bf16 = x->dtype == QMM_DT_BF16;
+    if constexpr (!FOLD) {
+        const int64_t n = x->rows * x->cols;
+        if (n * x->batch <= kEachMax && (x->contract_axis == 0 || (MODE == QMM_ROUND_STOCHASTIC && x->cols % 4 != 0))) {
+            const dim3 grid((unsigned)((n + kThreads - 1) / kThreads), (unsigned)x->batch);
+            if (bf16) quantize_each<uint16_t, FMT, MODE><<<grid, kThreads, 0, s>>>(a, x->contract_axis);
+            else quantize_each<float, FMT, MODE><<<grid, kThreads, 0, s>>>(a, x->contract_axis);
+            return launch_status();
+        }
+    }
     if (x->contract_axis == 0) {
         const int64_t tiles_k = (x->rows + kTileK - 1) / kTileK;
-        const bool wide = bf16 && tiles_k * (x->cols / 128) * x->batch >= 2048;
-        const int64_t tiles_n = wide ? (x->cols + 127) / 128 : (x->cols + 63) / 64, tiles = tiles_n * tiles_k;
+        const bool wide = bf16 && tiles_k * (x->cols / 128) * x->batch >= 2048 && (MODE == QMM_ROUND_RTNE || whole_blocks(a));
+        const bool narrow = tiles_k * ((x->cols + 63) / 64) * x->batch <= (MODE == QMM_ROUND_RTNE ? 192 : 256);
+        const int tile_n = wide ? 128 : narrow ? 16 : 64;
+        const int64_t tiles_n = (x->cols + tile_n - 1) / tile_n, tiles = tiles_n * tiles_k;
         const dim3 grid((unsigned)std::min<int64_t>(tiles, 1 << 23), (unsigned)x->batch);
         if (wide) quantize_cols<uint16_t, FMT, MODE, FOLD, 128><<<grid, kThreads, 0, s>>>(a, tiles_n, tiles);
+        else if (narrow && bf16) quantize_cols<uint16_t, FMT, MODE, FOLD, 16><<<grid, kThreads, 0, s>>>(a, tiles_n, tiles);
+        else if (narrow) quantize_cols<float, FMT, MODE, FOLD, 16><<<grid, kThreads, 0, s>>>(a, tiles_n, tiles);
         else if (bf16) quantize_cols<uint16_t, FMT, MODE, FOLD, 64><<<grid, kThreads, 0, s>>>(a, tiles_n, tiles);
         else quantize_cols<float, FMT, MODE, FOLD, 64><<<grid, kThreads, 0, s>>>(a, tiles_n, tiles);
         return launch_status();

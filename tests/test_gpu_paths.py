@@ -96,7 +96,7 @@ def tensor_form(form, rows, cols, batch, dtype, seed):
 
 
 # Every form against the oracle: step sizes and codes, by the two calls and by the one.  Extents around the vectors (4, 8,
-# 16), the lanes of a row in the one-pass kernel (8 .. 256 lanes, 1 .. 4 vectors), the tiles of the transposing pass
+# 16), the lanes of a row in the one-pass kernel (8 .. 256 lanes, 1 .. 8 vectors), the tiles of the transposing pass
 # (64 x 128) and the slabs of its step sizes (32 of 128 rows and more).
 @pytest.mark.parametrize("mode", [qmm.RTNE, qmm.STOCHASTIC])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
@@ -123,12 +123,14 @@ def test_scale_and_quantize_of_every_form(batch, rows, cols, groups, inner, form
 
 # Sizes where the single call changes its way: partial maxima folded by the quantize pass (up to 1024 of a group) or not, the
 # large tensors' one-launch maximum (2^24 elements), empty tensors, groups without a matrix, NaN and infinity.
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("shape,axis,per_channel,groups", [
     ((1, 2048, 4096), 1, False, 1), ((1, 4096, 4096), 1, False, 1), ((1, 1025, 100), 1, False, 1), ((40, 64, 512), 1, False, 2),
     ((512, 33, 64), 1, False, 16), ((3, 600, 200), 0, True, 3), ((3, 600, 200), 0, True, 1), ((0, 8, 16), 1, False, 2),
-    ((1, 0, 16), 0, True, 1), ((1, 70000, 24), 1, True, 1), ((1, 12, 9000), 1, True, 1)])
-def test_scale_quantize_equals_the_two_calls(shape, axis, per_channel, groups):
-    x = W.student_t(shape, 4, seed=3).to(DEV)
+    ((1, 0, 16), 0, True, 1), ((1, 70000, 24), 1, True, 1), ((1, 12, 9000), 1, True, 1),
+    ((512, 64, 512), 0, True, 512), ((512, 62, 516), 0, False, 8), ((3, 130, 3001), 1, True, 3), ((40, 300, 67), 0, True, 40)])
+def test_scale_quantize_equals_the_two_calls(shape, axis, per_channel, groups, dtype):
+    x = W.student_t(shape, 4, seed=3).to(dtype).to(DEV)
     if x.numel() > 4096:
         x.view(-1)[17] = float("inf")
         if groups > 1:
@@ -272,5 +274,28 @@ def test_quantize_of_short_and_long_rows(batch, rows, cols, form, dtype):
                 buf = torch.full((want.size + 2 * GUARD,), 77, dtype=torch.uint8, device=DEV)
                 out = buf[GUARD:GUARD + want.size].view(want.shape)
                 qmm.quantize(x, 1, fmt, torch.from_numpy(d).to(DEV), per_channel, 1, mode, 77, offset, out=out)
+                assert np.array_equal(out.cpu().numpy(), want), (per_channel, fmt, mode, offset)
+                assert bool((buf[:GUARD] == 77).all()) and bool((buf[-GUARD:] == 77).all())
+
+
+# Rows that are contracted over: one thread per code, tiles of 16, 64 and 128 columns, ragged both ways, columns that do and
+# do not start blocks of the random generator.
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("form", ["dense", "shifted"])
+@pytest.mark.parametrize("batch,rows,cols", [(1, 33, 70), (3, 40, 21), (1, 700, 401), (5, 260, 262), (1, 131, 2101), (1, 1300, 1601), (2, 1031, 1203),
+                                             (64, 9, 4200), (64, 12, 4196)])
+def test_quantize_of_contracted_rows(batch, rows, cols, form, dtype):
+    x = tensor_form(form, rows, cols, batch, dtype, seed=rows + cols).clone() if form == "dense" else tensor_form(form, rows, cols, batch, dtype, rows)
+    for i, v in enumerate([float("nan"), float("inf"), -float("inf"), 0.0, 1e-7, -3e-6, 2e-4, -1e-30]):
+        x[-1, i, cols // 2] = v
+    xn = x.float().cpu().numpy()
+    for per_channel in (True, False):
+        d = np.random.default_rng(cols).uniform(1e-3, 1e-1, cols if per_channel else 1).astype(np.float32)
+        for fmt in (qmm.E4M3, qmm.INT8, qmm.E5M2):
+            for mode, offset in ((qmm.RTNE, 0), (qmm.STOCHASTIC, 0), (qmm.STOCHASTIC, 6)):
+                want = O.quantize(xn, 0, fmt, d, per_channel, 1, mode, 77, offset, 1)
+                buf = torch.full((want.size + 2 * GUARD,), 77, dtype=torch.uint8, device=DEV)
+                out = buf[GUARD:GUARD + want.size].view(want.shape)
+                qmm.quantize(x, 0, fmt, torch.from_numpy(d).to(DEV), per_channel, 1, mode, 77, offset, out=out)
                 assert np.array_equal(out.cpu().numpy(), want), (per_channel, fmt, mode, offset)
                 assert bool((buf[:GUARD] == 77).all()) and bool((buf[-GUARD:] == 77).all())

@@ -9,6 +9,7 @@
 // on launch geometry or on which workgroup folds.
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 #include "qmm_device.h"
 
 namespace qmm {
@@ -216,27 +217,34 @@ absmax_rows(const T* __restrict__ x, int64_t batch_stride, int64_t row_stride, i
     if (lane == 0) { if (delta) delta[wr] = delta_from_absmax_bits(m, qmax); else partial[wr] = m; }
 }
 
-// Short rows (at most 256 bfloat16 columns, 16-byte aligned rows): LPR lanes per row, one 16-byte vector each, so a
-// wavefront takes 64 / LPR rows at once instead of one (with the rows dense in memory it reads 1 KB contiguous).
-template <int LPR> __global__ void __launch_bounds__(kThreads)
-absmax_rows_short(const uint16_t* __restrict__ x, int64_t batch_stride, int64_t row_stride, int64_t rows, int64_t cols,
+// Short rows (at most 32 vectors), any alignment: LPR lanes per row, one 16-byte vector each, so a wavefront takes 64 / LPR
+// rows at once instead of one (with the rows dense in memory it reads 1 KB contiguous).  A partial last vector is taken
+// back to the end of its row: the maximum does not mind the elements it sees twice.
+template <typename T, int LPR> __global__ void __launch_bounds__(kThreads)
+absmax_rows_short(const T* __restrict__ x, int64_t batch_stride, int64_t row_stride, int64_t rows, int64_t cols,
                   int64_t total_rows, uint32_t* __restrict__ partial, float qmax, float* __restrict__ delta)
 {
-    constexpr int RPW = kWave / LPR;
+    constexpr int RPW = kWave / LPR, V = VecMax<T>::V;
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t w = (int64_t)blockIdx.x * (kThreads / kWave) + threadIdx.x / kWave;
     const int64_t row = w * RPW + lane / LPR;
-    const int v = lane % LPR;
+    const int c = (lane % LPR) * V;
     uint32_t m = 0;
-    if (row < total_rows && v < cols / 8) {
-        const int64_t b = row / rows, r = row - b * rows;
-        u16x2 mm[4] = {};
-        fold_bf16x8(*reinterpret_cast<const u32x4*>(x + b * batch_stride + r * row_stride + v * 8), mm);
-        m = finish_bf16(mm);
+    if (row < total_rows && c < cols) {
+        int64_t b = 0, r = row;
+        if (rows < total_rows) { b = total_rows <= 0xFFFFFFFFll ? (int64_t)((uint32_t)row / (uint32_t)rows) : row / rows; r = row - b * rows; }
+        const T* p = x + b * batch_stride + r * row_stride;
+        if (cols >= V) {
+            VecMax<T> mm;
+            mm.fold(*reinterpret_cast<const u32x4_any*>(p + min((int64_t)c, cols - V)));
+            m = mm.finish();
+        } else {
+            for (int e = 0; e < (int)cols; ++e) m = max(m, mag_bits<T>(p[e]));
+        }
     }
 #pragma unroll
     for (int off = LPR / 2; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, kWave));
-    if (v == 0 && row < total_rows) { if (delta) delta[row] = delta_from_absmax_bits(m, qmax); else partial[row] = m; }
+    if (c == 0 && row < total_rows) { if (delta) delta[row] = delta_from_absmax_bits(m, qmax); else partial[row] = m; }
 }
 
 // Column groups: workgroup = 16 column-vectors (128 bfloat16 or 64 binary32 columns: 256 contiguous bytes of every row)
@@ -368,7 +376,6 @@ struct Plan {
     int64_t C;        // channels
     int flat_blocks;
     int64_t slab_rows;
-    bool vec;         // bfloat16 with 16-byte aligned rows of whole 8-element vectors
 };
 
 bool valid_tensor(const qmm_tensor* x, qmm_status* st)
@@ -401,7 +408,6 @@ Plan make_plan(const qmm_tensor* x, const qmm_granularity* g)
     const bool bf16 = x->dtype == QMM_DT_BF16;
     const int64_t es = bf16 ? 2 : 4;
     const bool base_ok = aligned16(x->data) && (x->batch <= 1 || x->batch_stride * es % 16 == 0);
-    p.vec = bf16 && base_ok && (x->cols % 8 == 0) && (x->row_stride % 8 == 0);
     if (!g->per_channel) {
         p.C = 1;
         const int64_t n = x->rows * x->cols;
@@ -507,22 +513,28 @@ qmm_status scale_partials(const qmm_tensor* x0, qmm_format fmt, const qmm_granul
         const int64_t total = x->batch * x->rows;
         float* direct = rows_are_groups ? delta_out : nullptr;
         const unsigned nb = (unsigned)((total + kThreads / kWave - 1) / (kThreads / kWave));
-        if (p.vec && x->cols <= 256) {
-            const uint16_t* xp = static_cast<const uint16_t*>(x->data);
-            const int nvec = (int)(x->cols / 8);
-            const int lpr = nvec <= 1 ? 1 : nvec <= 2 ? 2 : nvec <= 4 ? 4 : nvec <= 8 ? 8 : nvec <= 16 ? 16 : 32;
-            const int64_t waves = (total + kWave / lpr - 1) / (kWave / lpr);
-            const unsigned nbs = (unsigned)((waves + kThreads / kWave - 1) / (kThreads / kWave));
-#define QMM_ROWS_SHORT(L) absmax_rows_short<L><<<nbs, kThreads, 0, s>>>(xp, x->batch_stride, x->row_stride, x->rows, x->cols, total, partial, qmax, direct)
-            if (lpr == 1) QMM_ROWS_SHORT(1); else if (lpr == 2) QMM_ROWS_SHORT(2); else if (lpr == 4) QMM_ROWS_SHORT(4);
-            else if (lpr == 8) QMM_ROWS_SHORT(8); else if (lpr == 16) QMM_ROWS_SHORT(16); else QMM_ROWS_SHORT(32);
-#undef QMM_ROWS_SHORT
+        // matrices that follow one another like their rows are one matrix to a kernel that writes a value per row
+        const int64_t rows = x->batch_stride == x->rows * x->row_stride ? total : x->rows;
+        const int64_t nvec = (x->cols + (bf16 ? 7 : 3)) / (bf16 ? 8 : 4);
+        if (nvec <= 32) {
+            auto run = [&](auto lanes) {
+                constexpr int L = decltype(lanes)::value;
+                const int64_t waves = (total + kWave / L - 1) / (kWave / L);
+                const unsigned nbs = (unsigned)((waves + kThreads / kWave - 1) / (kThreads / kWave));
+                if (bf16) absmax_rows_short<uint16_t, L><<<nbs, kThreads, 0, s>>>(static_cast<const uint16_t*>(x->data), x->batch_stride, x->row_stride,
+                                                                               rows, x->cols, total, partial, qmax, direct);
+                else absmax_rows_short<float, L><<<nbs, kThreads, 0, s>>>(static_cast<const float*>(x->data), x->batch_stride, x->row_stride,
+                                                                          rows, x->cols, total, partial, qmax, direct);
+            };
+            if (nvec <= 1) run(std::integral_constant<int, 1>{}); else if (nvec <= 2) run(std::integral_constant<int, 2>{});
+            else if (nvec <= 4) run(std::integral_constant<int, 4>{}); else if (nvec <= 8) run(std::integral_constant<int, 8>{});
+            else if (nvec <= 16) run(std::integral_constant<int, 16>{}); else run(std::integral_constant<int, 32>{});
         } else if (bf16)
             absmax_rows<uint16_t><<<nb, kThreads, 0, s>>>(static_cast<const uint16_t*>(x->data), x->batch_stride,
-                                                           x->row_stride, x->rows, x->cols, total, partial, qmax, direct);
+                                                           x->row_stride, rows, x->cols, total, partial, qmax, direct);
         else
             absmax_rows<float><<<nb, kThreads, 0, s>>>(static_cast<const float*>(x->data), x->batch_stride,
-                                                        x->row_stride, x->rows, x->cols, total, partial, qmax, direct);
+                                                        x->row_stride, rows, x->cols, total, partial, qmax, direct);
         out->done = rows_are_groups;
         break;
     }

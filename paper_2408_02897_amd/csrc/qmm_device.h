@@ -300,7 +300,8 @@ struct ScalePartials {
     bool done;                 // the step sizes have been written already
 };
 qmm_status scale_arguments(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, const float* delta_out,
-                           const void* workspace, size_t workspace_bytes);
+                           const void* workspace, size_t workspace_bytes, bool fold);
+size_t scale_partials_size(const qmm_tensor* x, const qmm_granularity* g, bool fold);    // bytes of partial maxima
 qmm_status scale_partials(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, float* delta_out, uint32_t* partial,
                           bool fold_here, ScalePartials* out, hipStream_t s);
 qmm_status scale_fold(const ScalePartials& pp, const uint32_t* partial, qmm_format fmt, const qmm_granularity* g,

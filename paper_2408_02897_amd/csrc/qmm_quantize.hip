@@ -785,10 +785,33 @@ extern "C" qmm_status qmm_quantize(const qmm_tensor* x, qmm_format fmt, const qm
     }
 }
 
+namespace {
+// The quantize pass folds the partial maxima when every group has a matrix (its first workgroup writes the step size), a
+// group's partial maxima are few -- each workgroup fetches them -- and the tensor is not large: per workgroup the fold costs
+// about what it fetches, against one small kernel and its launch.  One step size per column: one matrix per group, up to
+// 2^24 elements (bfloat16, fold / small kernel apart from its launch: 4096 x 3072 +1.7 / 3.8 us, 16384 x 3072 +11 / 3.8; both
+// steps, tall, 65536 x 128 20.5 / 18.1, binary32 262144 x 64 75 / 33).  One
+// step size per group: up to 2^24 elements (256 x 768: +0.6 / 1.4 us).
+bool folds(const qmm_tensor* x, const qmm_granularity* g)
+{
+    if (!(x->batch > 0 && x->rows > 0 && x->cols > 0) || g->batch_groups < 1) return false;
+    const int64_t inner = g->batch_inner > 0 ? g->batch_inner : 1, n = x->batch * x->rows * x->cols;
+    const bool many_channels = g->per_channel && (x->contract_axis == 1 ? x->rows : x->cols) > 1;
+    if (many_channels) {
+        // (a tall, narrow tensor: the few slabs that can be folded leave the chip idle)
+        const int64_t column_blocks = (x->cols + 127) / 128 * x->batch;
+        const bool tall = x->rows > 1024 * kFoldSlabs && column_blocks * kFoldSlabs < 256;
+        return n <= (int64_t(1) << 24) && x->contract_axis == 0 && g->batch_groups == x->batch && inner == 1 && !tall;
+    }
+    if (n > (int64_t(1) << 24) || g->batch_groups > x->batch || (g->batch_groups - 1) * inner >= x->batch) return false;
+    return (int64_t)(scale_partials_size(x, g, true) / sizeof(uint32_t)) <= kFoldMax * g->batch_groups;
+}
+}  // namespace
+
 extern "C" size_t qmm_scale_quantize_workspace_size(const qmm_tensor* x, const qmm_granularity* g)
 {
     if (!x || !g || one_pass(x, g)) return 0;
-    return qmm_scale_workspace_size(x, g);
+    return scale_partials_size(x, g, folds(x, g));
 }
 
 extern "C" qmm_status qmm_scale_quantize(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, qmm_round mode,
@@ -797,9 +820,9 @@ extern "C" qmm_status qmm_scale_quantize(const qmm_tensor* x, qmm_format fmt, co
 {
     // the arguments of both steps first; a call that needs no workspace is checked against one of full size
     if (!x || !g) return QMM_ERR_NULL;
-    const bool single = one_pass(x, g);
+    const bool single = one_pass(x, g), fold = !single && folds(x, g);
     qmm_status st = scale_arguments(x, fmt, g, delta_out, single ? reinterpret_cast<const void*>(uintptr_t(256)) : workspace,
-                                    single ? ~size_t(0) : workspace_bytes);
+                                    single ? ~size_t(0) : workspace_bytes, fold);
     if (st != QMM_OK) return st;
     st = quantize_check(x, fmt, g, delta_out, mode, codes_out);
     if (st != QMM_OK) return st;
@@ -817,18 +840,7 @@ extern "C" qmm_status qmm_scale_quantize(const qmm_tensor* x, qmm_format fmt, co
         default: return launch_one_pass_mode<QMM_FMT_E5M2>(x, a, mode, s);
         }
     }
-    // The quantize pass folds the partial maxima when every group has a matrix (its first workgroup writes the step size), a
-    // group's partial maxima are few -- each workgroup fetches them -- and the tensor is of at most 2^24 elements: per
-    // workgroup the fold costs about what it fetches, against one small kernel and its launch.  (bfloat16, one step size per
-    // column, fold / small kernel apart from its launch: 4096 x 3072 +1.7 / 3.8 us, 16384 x 3072 +11 / 3.8 us; one step size,
-    // 256 x 768: +0.6 / 1.4 us.)  One step size per column: one matrix per group.
     uint32_t* partial = static_cast<uint32_t*>(workspace);
-    const size_t words = qmm_scale_workspace_size(x, g) / sizeof(uint32_t);
-    const bool all_groups = (a.groups - 1) * a.inner < a.batch;
-    const bool small = x->batch * x->rows * x->cols <= (int64_t(1) << 24);
-    bool fold;
-    if (a.channels == 1) fold = small && all_groups && (int64_t)words <= kFoldMax * a.groups;
-    else fold = small && x->contract_axis == 0 && a.groups == a.batch && a.inner == 1;
     ScalePartials pp;
     st = scale_partials(x, fmt, g, delta_out, partial, fold, &pp, s);
     if (st != QMM_OK) return st;

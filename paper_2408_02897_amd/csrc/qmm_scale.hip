@@ -18,6 +18,7 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kMaxFlatBlocks = 1024;   // 4 workgroups per CU on 256 CUs; 4 partials per thread in the fold
 constexpr int kColSlabRows = 128;      // rows folded by one workgroup in the column-group kernel, at least
+constexpr int kMaxColSlabs = 512;      // and slabs of them, at most
 
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -247,30 +248,28 @@ absmax_rows_short(const T* __restrict__ x, int64_t batch_stride, int64_t row_str
     if (c == 0 && row < total_rows) { if (delta) delta[row] = delta_from_absmax_bits(m, qmax); else partial[row] = m; }
 }
 
-// Column groups: workgroup = 16 column-vectors (128 bfloat16 or 64 binary32 columns: 256 contiguous bytes of every row)
-// x 16 row lanes over a slab of rows.  partial[(b*nslab + slab)*cols + c].  Any extent, stride and alignment: a vector
-// that straddles the last column is read element by element.
-template <typename T> __global__ void __launch_bounds__(kThreads)
+// Column groups: workgroup = CV column vectors (16: 128 bfloat16 or 64 binary32 columns, 256 contiguous bytes of every row; 8
+// and 4 for tensors that narrow; 32 for wide ones, whose rows may start off the cache lines) x 256 / CV row lanes over a slab of rows.  partial[(b*nslab + slab)*cols + c].  Any extent,
+// stride and alignment: a vector that straddles the last column is read element by element.  Four rows of a lane are on their
+// way together; past the slab's end the last row is read again, which the maximum does not mind.
+template <typename T, int CV> __global__ void __launch_bounds__(kThreads)
 absmax_cols(const T* __restrict__ x, int64_t batch_stride, int64_t row_stride, int64_t rows, int64_t cols, int64_t slab_rows,
             uint32_t* __restrict__ partial)
 {
-    constexpr int V = VecMax<T>::V, RL = kThreads / 16;
-    __shared__ uint32_t s[RL][16][5];            // (five words: a column vector's sixteen row lanes fall into different banks)
-    const int cv = threadIdx.x & 15, rl = threadIdx.x >> 4;
-    const int64_t c0 = ((int64_t)blockIdx.x * 16 + cv) * V;
+    constexpr int V = VecMax<T>::V, RL = kThreads / CV;
+    __shared__ uint32_t s[kThreads / kWave][CV][4];
+    const int cv = threadIdx.x % CV, rl = threadIdx.x / CV, lane = threadIdx.x & (kWave - 1);
+    const int64_t c0 = ((int64_t)blockIdx.x * CV + cv) * V;
     const int64_t r0 = (int64_t)blockIdx.y * slab_rows;
     const int64_t r1 = min(rows, r0 + slab_rows);
     VecMax<T> m;
     const T* base = x + (int64_t)blockIdx.z * batch_stride + c0;
     if (c0 + V <= cols) {
-        auto row = [&](int64_t r) { return *reinterpret_cast<const u32x4_any*>(base + r * row_stride); };
-        int64_t r = r0 + rl;
-        // four rows per trip: the loads are in flight together
-        for (; r + 3 * RL < r1; r += 4 * RL) {
+        auto row = [&](int64_t r) { return *reinterpret_cast<const u32x4_any*>(base + min(r, r1 - 1) * row_stride); };
+        for (int64_t r = r0 + rl; r < r1; r += 4 * RL) {
             const u32x4 a = row(r), b = row(r + RL), c = row(r + 2 * RL), d = row(r + 3 * RL);
             m.fold(a); m.fold(b); m.fold(c); m.fold(d);
         }
-        for (; r < r1; r += RL) m.fold(row(r));
     } else if (c0 < cols) {
         const int left = (int)(cols - c0);
         for (int64_t r = r0 + rl; r < r1; r += RL) {
@@ -284,13 +283,23 @@ absmax_cols(const T* __restrict__ x, int64_t batch_stride, int64_t row_stride, i
             m.fold(w);
         }
     }
+    // the row lanes of a wavefront, then its four wavefronts
     uint32_t w[4];
-    m.words(w);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) s[rl][cv][i] = w[i];
+    for (int off = CV; off < kWave; off <<= 1) {
+        m.words(w);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = (uint32_t)__shfl_xor((int)w[i], off, kWave);
+        m.fold_words(w);
+    }
+    m.words(w);
+    if (lane < CV) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[threadIdx.x / kWave][cv][i] = w[i];
+    }
     __syncthreads();
-    if (rl == 0 && c0 < cols) {
-        for (int k = 1; k < RL; ++k) {
+    if (threadIdx.x < CV && c0 < cols) {
+        for (int k = 1; k < kThreads / kWave; ++k) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) w[i] = s[k][cv][i];
             m.fold_words(w);
@@ -333,18 +342,19 @@ finalize_single(const uint32_t* __restrict__ partial, int64_t batch, int64_t P, 
     m = block_max_u32(m);
     if (threadIdx.x == 0) delta[g] = delta_from_absmax_bits(m, qmax);
 }
-// Workgroup = 32 channels x 8 lanes over the (matrix, partial) pairs of the group; max is order-free.
-__global__ void __launch_bounds__(kThreads)
+// Workgroup = CL channels x 256 / CL lanes over the (matrix, partial) pairs of the group; max is order-free.
+template <int CL> __global__ void __launch_bounds__(kThreads)
 finalize_channels(const uint32_t* __restrict__ partial, int64_t batch, int64_t P, int64_t C, int64_t G, int64_t inner,
                   float qmax, float* __restrict__ delta)
 {
-    __shared__ uint32_t s[8][32];
-    const int cl = threadIdx.x & 31, pl = threadIdx.x >> 5;
-    const int64_t c = (int64_t)blockIdx.x * 32 + cl;
+    constexpr int L = kThreads / CL;
+    __shared__ uint32_t s[L][CL];
+    const int cl = threadIdx.x % CL, pl = threadIdx.x / CL;
+    const int64_t c = (int64_t)blockIdx.x * CL + cl;
     const int64_t g = blockIdx.y;
     uint32_t m = 0;
     if (c < C) {
-        // the (matrix, partial) pairs of the group over the eight lanes of a channel (k-th matrix of group g:
+        // the (matrix, partial) pairs of the group over the lanes of a channel (k-th matrix of group g:
         // b = ((k / inner) * G + g) * inner + k % inner, increasing with k), four loads in flight
         auto item = [&](int64_t it) -> uint32_t {
             const int64_t k = it / P, p = it - k * P;
@@ -355,17 +365,17 @@ finalize_channels(const uint32_t* __restrict__ partial, int64_t batch, int64_t P
         const int64_t nq = groups_of_inner > g ? (groups_of_inner - g + G - 1) / G : 0;  // those with q % G == g
         const int64_t nitems = nq * inner * P;                                           // (items past the batch read as 0)
         int64_t it = pl;
-        for (; it + 24 < nitems; it += 32) {
-            const uint32_t v0 = item(it), v1 = item(it + 8), v2 = item(it + 16), v3 = item(it + 24);
+        for (; it + 3 * L < nitems; it += 4 * L) {
+            const uint32_t v0 = item(it), v1 = item(it + L), v2 = item(it + 2 * L), v3 = item(it + 3 * L);
             m = max(m, max(max(v0, v1), max(v2, v3)));
         }
-        for (; it < nitems; it += 8) m = max(m, item(it));
+        for (; it < nitems; it += L) m = max(m, item(it));
     }
     s[pl][cl] = m;
     __syncthreads();
     if (pl == 0 && c < C) {
 #pragma unroll
-        for (int k = 1; k < 8; ++k) m = max(m, s[k][cl]);
+        for (int k = 1; k < L; ++k) m = max(m, s[k][cl]);
         delta[g * C + c] = delta_from_absmax_bits(m, qmax);
     }
 }
@@ -376,6 +386,7 @@ struct Plan {
     int64_t C;        // channels
     int flat_blocks;
     int64_t slab_rows;
+    int cv;           // column vectors per workgroup of the column kind
 };
 
 bool valid_tensor(const qmm_tensor* x, qmm_status* st)
@@ -402,7 +413,8 @@ qmm_tensor one_matrix(const qmm_tensor* x, const qmm_granularity* g)
     return t;
 }
 
-Plan make_plan(const qmm_tensor* x, const qmm_granularity* g)
+// fold: the quantize pass folds the partial maxima.
+Plan make_plan(const qmm_tensor* x, const qmm_granularity* g, bool fold = false)
 {
     Plan p{};
     const bool bf16 = x->dtype == QMM_DT_BF16;
@@ -427,7 +439,15 @@ Plan make_plan(const qmm_tensor* x, const qmm_granularity* g)
         p.C = x->rows;
     } else {
         p.kind = Plan::COLS;
-        p.slab_rows = std::max<int64_t>(kColSlabRows, (x->rows + kFoldSlabs - 1) / kFoldSlabs);
+        // Slabs of whole trips.  Where the quantize pass folds, as many as it takes; else enough for two workgroups per CU, but
+        // not more than the second kernel folds in a few trips.  (Slabs of 128 rows / at most 32 slabs, for every call / this way:
+        // bfloat16 1048576 x 64 372 / 181 / 29 us, 300000 x 20 116 / 306 / 14.6, 65536 x 128 26.6 / 11.5 / 10.6, 16384 x 1024 11.8 /
+        // 8.4 / 7.4, where four workgroups per CU took 9.4; 5000 x 8200 19.8 / 22.1 / 19.2.)
+        const int64_t nvec = (x->cols + (bf16 ? 7 : 3)) / (bf16 ? 8 : 4);
+        p.cv = nvec <= 4 ? 4 : nvec <= 8 ? 8 : nvec < 512 || x->rows < 1024 ? 16 : 32;
+        const int64_t trip = 4 * (kThreads / p.cv), blocks = ((nvec + p.cv - 1) / p.cv) * std::max<int64_t>(x->batch, 1);
+        const int64_t want = fold ? kFoldSlabs : std::min<int64_t>(std::max<int64_t>((512 + blocks - 1) / blocks, 1), kMaxColSlabs);
+        p.slab_rows = std::max<int64_t>(kColSlabRows, ((x->rows + want - 1) / want + trip - 1) / trip * trip);
         p.P = (x->rows + p.slab_rows - 1) / p.slab_rows;
         p.C = x->cols;
     }
@@ -446,20 +466,24 @@ extern "C" int64_t qmm_num_scales(const qmm_tensor* x, const qmm_granularity* g)
     return g->batch_groups * c;
 }
 
-extern "C" size_t qmm_scale_workspace_size(const qmm_tensor* x, const qmm_granularity* g)
+namespace qmm {
+size_t scale_partials_size(const qmm_tensor* x, const qmm_granularity* g, bool fold)
 {
     qmm_status st;
     if (!g || !valid_tensor(x, &st)) return 0;
     const qmm_tensor t = one_matrix(x, g);
-    const Plan p = make_plan(&t, g);
+    const Plan p = make_plan(&t, g, fold);
     const int64_t words = t.batch * p.P * p.C;
     return (size_t)(words > 0 ? words : 1) * sizeof(uint32_t);
 }
+}  // namespace qmm
+
+extern "C" size_t qmm_scale_workspace_size(const qmm_tensor* x, const qmm_granularity* g) { return scale_partials_size(x, g, false); }
 
 namespace {
 // Everything qmm_scale can refuse, checked without launching.
 qmm_status scale_check(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, const float* delta_out,
-                       const void* workspace, size_t workspace_bytes)
+                       const void* workspace, size_t workspace_bytes, bool fold = false)
 {
     qmm_status st;
     if (!g || !delta_out) return QMM_ERR_NULL;
@@ -469,7 +493,7 @@ qmm_status scale_check(const qmm_tensor* x, qmm_format fmt, const qmm_granularit
     if (x->batch > 65535) return QMM_ERR_UNSUPPORTED;          // the batch index is a grid dimension in some plans
     if (qmm_num_scales(x, g) == 0) return QMM_OK;
     if (x->batch * x->rows * x->cols > 0 && !x->data) return QMM_ERR_NULL;
-    if (!workspace || workspace_bytes < qmm_scale_workspace_size(x, g)) return QMM_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < scale_partials_size(x, g, fold)) return QMM_ERR_WORKSPACE;
     if (!aligned16(workspace)) return QMM_ERR_ALIGN;
     return QMM_OK;
 }
@@ -484,7 +508,7 @@ qmm_status scale_partials(const qmm_tensor* x0, qmm_format fmt, const qmm_granul
 {
     const qmm_tensor t = one_matrix(x0, g);
     const qmm_tensor* x = &t;
-    const Plan p = make_plan(x, g);
+    const Plan p = make_plan(x, g, fold_here);
     const float qmax = host_qmax(fmt);
     const bool bf16 = x->dtype == QMM_DT_BF16;
     const int64_t nelem = x->batch * x->rows * x->cols;
@@ -539,14 +563,21 @@ qmm_status scale_partials(const qmm_tensor* x0, qmm_format fmt, const qmm_granul
         break;
     }
     case Plan::COLS: {
-        const int64_t cols_per_block = bf16 ? 128 : 64;
+        const int64_t cols_per_block = p.cv * (bf16 ? 8 : 4);
         const dim3 grid((unsigned)((x->cols + cols_per_block - 1) / cols_per_block), (unsigned)p.P, (unsigned)x->batch);
-        if (bf16)
-            absmax_cols<uint16_t><<<grid, kThreads, 0, s>>>(static_cast<const uint16_t*>(x->data), x->batch_stride,
-                                                             x->row_stride, x->rows, x->cols, p.slab_rows, partial);
-        else
-            absmax_cols<float><<<grid, kThreads, 0, s>>>(static_cast<const float*>(x->data), x->batch_stride,
-                                                          x->row_stride, x->rows, x->cols, p.slab_rows, partial);
+        auto run = [&](auto vectors) {
+            constexpr int CV = decltype(vectors)::value;
+            if (bf16)
+                absmax_cols<uint16_t, CV><<<grid, kThreads, 0, s>>>(static_cast<const uint16_t*>(x->data), x->batch_stride,
+                                                                    x->row_stride, x->rows, x->cols, p.slab_rows, partial);
+            else
+                absmax_cols<float, CV><<<grid, kThreads, 0, s>>>(static_cast<const float*>(x->data), x->batch_stride,
+                                                                 x->row_stride, x->rows, x->cols, p.slab_rows, partial);
+        };
+        if (p.cv == 4) run(std::integral_constant<int, 4>{});
+        else if (p.cv == 8) run(std::integral_constant<int, 8>{});
+        else if (p.cv == 16) run(std::integral_constant<int, 16>{});
+        else run(std::integral_constant<int, 32>{});
         break;
     }
     }
@@ -562,15 +593,22 @@ qmm_status scale_fold(const ScalePartials& pp, const uint32_t* partial, qmm_form
     if (pp.C == 1)
         finalize_single<<<(unsigned)G, kThreads, 0, s>>>(partial, pp.batch, P, G, inner, host_qmax(fmt), delta_out);
     else
-        finalize_channels<<<dim3((unsigned)((pp.C + 31) / 32), (unsigned)G), kThreads, 0, s>>>(
-            partial, pp.batch, P, pp.C, G, inner, host_qmax(fmt), delta_out);
+    {
+        // many lanes a channel where the channels alone are few workgroups (tall tensors, hundreds of partial maxima each)
+        if ((pp.C + 31) / 32 * G < 128)
+            finalize_channels<8><<<dim3((unsigned)((pp.C + 7) / 8), (unsigned)G), kThreads, 0, s>>>(
+                partial, pp.batch, P, pp.C, G, inner, host_qmax(fmt), delta_out);
+        else
+            finalize_channels<32><<<dim3((unsigned)((pp.C + 31) / 32), (unsigned)G), kThreads, 0, s>>>(
+                partial, pp.batch, P, pp.C, G, inner, host_qmax(fmt), delta_out);
+    }
     return launch_status();
 }
 
 qmm_status scale_arguments(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, const float* delta_out,
-                           const void* workspace, size_t workspace_bytes)
+                           const void* workspace, size_t workspace_bytes, bool fold)
 {
-    return scale_check(x, fmt, g, delta_out, workspace, workspace_bytes);
+    return scale_check(x, fmt, g, delta_out, workspace, workspace_bytes, fold);
 }
 }  // namespace qmm
 

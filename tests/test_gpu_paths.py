@@ -1,5 +1,7 @@
 """Paths of the kernels that a call is routed to by its sizes, types or alignment, each compared bit for bit with the
 general path over the forms it accepts (ragged and odd extents, strides, types), and against writes outside the output."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -299,3 +301,23 @@ def test_quantize_of_contracted_rows(batch, rows, cols, form, dtype):
                 qmm.quantize(x, 0, fmt, torch.from_numpy(d).to(DEV), per_channel, 1, mode, 77, offset, out=out)
                 assert np.array_equal(out.cpu().numpy(), want), (per_channel, fmt, mode, offset)
                 assert bool((buf[:GUARD] == 77).all()) and bool((buf[-GUARD:] == 77).all())
+
+
+# Maxima per column: workgroups of 4, 8, 16 and 32 vectors, slabs of one trip and of many, ragged ends; tall tensors, whose
+# second kernel gives a channel many lanes; groups over a batch.  And short rows off every boundary.
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("form", ["dense", "sliced", "shifted"])
+@pytest.mark.parametrize("batch,rows,cols,groups,inner", [(1, 70001, 20, 1, 1), (1, 40000, 64, 1, 1), (1, 129, 3, 1, 1), (3, 5000, 33, 3, 1), (6, 700, 130, 2, 2),
+                                                          (1, 1100, 4301, 1, 1), (1, 8, 5000, 1, 1), (1, 257, 129, 1, 1), (40, 300, 9, 5, 1)])
+def test_scale_per_channel_of_tall_and_wide_tensors(batch, rows, cols, groups, inner, form, dtype):
+    x = tensor_form(form, rows, cols, batch, dtype, seed=rows + cols)
+    xn = x.float().cpu().numpy()
+    for axis in (0, 1):
+        d = qmm.scale(x, axis, qmm.E4M3, True, groups, batch_inner=inner)
+        want = O.scale(xn, axis, qmm.E4M3, True, groups, inner)
+        assert np.array_equal(d.cpu().numpy().view(np.uint32), want.view(np.uint32)), axis
+        c1, d1 = qmm.scale_quantize(x, axis, qmm.E4M3, True, groups, batch_inner=inner)
+        assert torch.equal(d1, d) and torch.equal(c1, qmm.quantize(x, axis, qmm.E4M3, d, True, groups, batch_inner=inner)), axis
+        size = qmm.lib().qmm_scale_workspace_size(ctypes.byref(qmm.tensor_desc(x, axis)), ctypes.byref(qmm.granularity(True, groups, inner)))
+        if size <= 1 << 20:
+            assert torch.equal(qmm.scale_static(x, axis, qmm.E4M3, True, groups, batch_inner=inner), d)

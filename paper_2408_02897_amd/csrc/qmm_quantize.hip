@@ -791,7 +791,9 @@ namespace {
 // about what it fetches, against one small kernel and its launch.  One step size per column: one matrix per group, up to
 // 2^24 elements (bfloat16, fold / small kernel apart from its launch: 4096 x 3072 +1.7 / 3.8 us, 16384 x 3072 +11 / 3.8; both
 // steps, tall, 65536 x 128 20.5 / 18.1, binary32 262144 x 64 75 / 33).  One
-// step size per group: up to 2^24 elements (256 x 768: +0.6 / 1.4 us).
+// step size per group: up to 2^23 elements, or 2^24 where a group has at most 256 (both steps, bfloat16, fold / not: one group of
+// 1024, 8192 x 1024 9.9 / 10.7 us, 16384 x 1024 19.4 / 17.8; sixteen groups of 64, 512 matrices of 512 x 64 18.1 / 18.6, with
+// their rows contracting 18.0 / 19.4).
 bool folds(const qmm_tensor* x, const qmm_granularity* g)
 {
     if (!(x->batch > 0 && x->rows > 0 && x->cols > 0) || g->batch_groups < 1) return false;
@@ -804,7 +806,8 @@ bool folds(const qmm_tensor* x, const qmm_granularity* g)
         return n <= (int64_t(1) << 24) && x->contract_axis == 0 && g->batch_groups == x->batch && inner == 1 && !tall;
     }
     if (n > (int64_t(1) << 24) || g->batch_groups > x->batch || (g->batch_groups - 1) * inner >= x->batch) return false;
-    return (int64_t)(scale_partials_size(x, g, true) / sizeof(uint32_t)) <= kFoldMax * g->batch_groups;
+    const int64_t words = (int64_t)(scale_partials_size(x, g, true) / sizeof(uint32_t));
+    return words <= (n > (int64_t(1) << 23) ? kFoldMax / 4 : kFoldMax) * g->batch_groups;
 }
 }  // namespace
 

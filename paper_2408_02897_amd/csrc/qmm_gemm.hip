@@ -2208,9 +2208,12 @@ qmm_status launch_direct(GemmArgs& g, hipStream_t s)
     g.tiles_n = (int)((g.N + bn - 1) / bn);
     const int64_t total = (int64_t)g.tiles_m * g.tiles_n * g.batch;
     if (total > 0x7FFFFFFF) return QMM_ERR_UNSUPPORTED;
-    // (B_LDS: codes; up to eight slabs of B, 64 KB, two workgroups per CU)
+    // B_LDS: codes; up to eight slabs of B, 64 KB, two workgroups per CU; and enough wavefronts at work on a workgroup's rows to
+    // pay for the copy and its barrier (with / without, bfloat16 out: 768 x [64 x 64 x 1024] E4M3 23.1 / 18.8 us, INT8 23.9 / 18.9;
+    // 768 x [128 x 64 x 1024] E4M3 30.3 / 27.3, INT8 32.7 / 35.6; [168 x 64 x 1024] 47.5 / 41.3, 46.4 / 48.2; [192 x 64 x 1024] 34.4 /
+    // 39.6, 38.1 / 48.4).
     if constexpr (KIND != KIND_BF16) {
-        if (!g.direct_along_n && g.rowbytes <= 8 * kSlabBytes) {
+        if (!g.direct_along_n && g.rowbytes <= 8 * kSlabBytes && g.M >= (KIND == KIND_F8 ? 192 : 65)) {
             const int lds_bytes = (int)((g.rowbytes + kSlabBytes - 1) / kSlabBytes) * 64 * kSlabBytes;
             gemm_direct_kernel<KIND, FA, FB, true><<<(unsigned)total, 256, lds_bytes, s>>>(g);
             return launch_status();

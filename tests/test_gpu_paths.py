@@ -196,7 +196,8 @@ def test_product_of_few_tiles(kind, batch, m, n, row):
 # last one, wavefronts without a row.  INT8 against the integer product; E4M3 against the same columns inside a product of 96,
 # which runs in the LDS kernels with the same order of additions.
 @pytest.mark.parametrize("kind", ["e4m3", "int8"])
-@pytest.mark.parametrize("batch,m,n,k", [(60, 600, 64, 512), (60, 577, 40, 144), (60, 600, 1, 16), (60, 600, 64, 1024), (1, 40000, 63, 400), (60, 600, 64, 1040)])
+@pytest.mark.parametrize("batch,m,n,k", [(60, 600, 64, 512), (60, 577, 40, 144), (60, 600, 1, 16), (60, 600, 64, 1024), (1, 40000, 63, 400), (60, 600, 64, 1040),
+                                          (300, 191, 64, 512), (300, 192, 33, 272), (600, 64, 64, 1024), (600, 65, 50, 128)])
 def test_tall_product(kind, batch, m, n, k):
     a, b = operands(kind, m, n, k, per_channel=(k % 3 == 0), batch=batch)
     y, acc = qmm.gemm(a, b, torch.bfloat16, want_acc=True)

@@ -2286,10 +2286,13 @@ qmm_status launch_stream(GemmArgs& g, hipStream_t s)
     return launch_status();
 }
 
-// gemm_deep_kernel: nothing quantized on load, no split, at most two 64 x 64 tiles per CU.  Measured against the 128 x 128
-// tiles of gemm_kernel (launches back to back, E4M3 unless said): 256 x 768 x 768 (48 tiles) 10.6 -> 6.4 us, 512 x 512 x 512
-// (64) 10.7 -> 6.4 us, bfloat16 12.2 -> 7.2; 1031 x 1000 x 784 (272) 9.6 -> 7.5 us, 1448 x 724 x 1456 (276) 11.4 -> 10.6 us,
-// 2000 x 1000 x 512 (512) 8.7 -> 7.2 us; but 1536 x 1536 x 1536 (576) 8.9 -> 11.6 us and 4096 x 768 x 768 (768) 8.9 -> 10.2.
+// gemm_deep_kernel: nothing quantized on load, no split, at most one 64 x 64 tile per CU, or two where the 128 x 128 tiles of
+// gemm_kernel would be ragged, the contraction is of four slabs at most, or the accumulators are wanted (gemm_kernel writes
+// them one by one).  Measured, gemm_kernel / this kernel (launches back to back, E4M3 to bfloat16 unless said): 256 x 768 x 768 (48
+// tiles) 10.6 / 6.4 us, 512 x 512 x 512 (64) 10.7 / 6.4, bfloat16 12.2 / 7.2; 1031 x 1000 x 784 (272) 9.2 / 6.8; 2000 x 1000 x 1024 (512)
+// 9.3 / 8.3, x 1488 11.1 / 11.0; 2048 x 1024 (512) x 256 5.4 / 5.1, x 512 6.1 / 6.0, x 768 6.7 / 6.9, x 1024 7.1 / 7.8, x 1536 8.4 / 9.5;
+// 1280 x 1280 x 1504 (400) 9.1 / 9.7, INT8 10.2 / 10.0; with accumulators 128 x 16384 x 1024 (512) 12.7 / 8.2; but 1536 x 1536 x 1536 (576) 8.9 / 11.6
+// and 4096 x 768 x 768 (768) 8.9 / 10.2.
 constexpr int kDeepGrid = 256;
 template <int KIND, int FA, int FB, int SLOTS>
 qmm_status launch_deep(GemmArgs& g, hipStream_t s)
@@ -2321,7 +2324,9 @@ qmm_status launch_fuse(GemmArgs& g, hipStream_t s)
         if (use_stream(g, 0)) return launch_stream<KIND, FA, FB>(g, s);
         const int64_t tiles = ((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch;
         if (g.splits == 1 && tiles <= kDeepGrid) return launch_deep<KIND, FA, FB, 8>(g, s);
-        if (g.splits == 1 && tiles <= 2 * kDeepGrid) return launch_deep<KIND, FA, FB, 3>(g, s);
+        const bool ragged = g.M % 128 != 0 || g.N % 128 != 0 || (KIND == KIND_I8 && g.rowbytes % kSlabBytes != 0);
+        const bool two_pay = ragged || g.rowbytes <= 4 * kSlabBytes || g.acc_out;
+        if (g.splits == 1 && tiles <= 2 * kDeepGrid && two_pay) return launch_deep<KIND, FA, FB, 3>(g, s);
     }
     // 256 x 256 tiles (eight wavefronts, two per SIMD: while one waits at a copy or a fragment read the other
     // issues matrix instructions), one workgroup per CU, or 128 x 128 tiles (four wavefronts), two workgroups per CU: a

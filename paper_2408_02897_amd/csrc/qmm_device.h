@@ -26,50 +26,20 @@ template <> struct Fp8<QMM_FMT_E4M3> {
     static constexpr int M = 3, BIAS = 7;
     static constexpr uint32_t MAX_BITS = 0x43E00000u;      // 448.0f
     static constexpr uint32_t MINNORM_BITS = 0x3C800000u;  // 2^-6
-    static constexpr uint32_t MAGIC_BITS = 0x46800000u;    // 2^14: ulp = 2^-9 = min subnormal
     static constexpr float TO_SUBNORMAL_UNITS = 512.0f;    // 1 / min subnormal
-    static constexpr uint32_t MAX_CODE = 0x7Eu;
 };
 template <> struct Fp8<QMM_FMT_E5M2> {
     static constexpr int M = 2, BIAS = 15;
     static constexpr uint32_t MAX_BITS = 0x47600000u;      // 57344.0f
     static constexpr uint32_t MINNORM_BITS = 0x38800000u;  // 2^-14
-    static constexpr uint32_t MAGIC_BITS = 0x43000000u;    // 2^7: ulp = 2^-16 = min subnormal
     static constexpr float TO_SUBNORMAL_UNITS = 65536.0f;
-    static constexpr uint32_t MAX_CODE = 0x7Bu;
 };
 
-QMM_DEV float format_qmax(int fmt)
-{
-    return fmt == QMM_FMT_INT8 ? 127.0f : (fmt == QMM_FMT_E4M3 ? 448.0f : 57344.0f);
-}
-
-// Nearest finite FP8 value, ties to the even mantissa, saturating, sign kept,
-// NaN -> 0x7F.  Integer arithmetic on the binary32 pattern: in the normal range
-// of the target the mantissa is rounded from 23 to M bits by adding half an ulp
-// (minus one when the kept LSB is even) and the exponent is rebiased; below the
-// smallest normal the magnitude is added to 2^(23 + log2(min subnormal)), whose
-// ulp is one subnormal step, so the adder's own RNE does the rounding.
-template <int FMT> QMM_DEV uint32_t encode_fp8_rtne(float t)
-{
-    using F = Fp8<FMT>;
-    const uint32_t u = __float_as_uint(t);
-    const uint32_t sign = (u >> 24) & 0x80u;
-    uint32_t a = u & 0x7FFFFFFFu;
-    const bool is_nan = a > 0x7F800000u;
-    a = min(a, F::MAX_BITS);
-    const uint32_t r = a + ((1u << (22 - F::M)) - 1u) + ((a >> (23 - F::M)) & 1u);
-    const uint32_t code_normal = (r >> (23 - F::M)) - ((127u - F::BIAS) << F::M);
-    const float f = __uint_as_float(a) + __uint_as_float(F::MAGIC_BITS);
-    const uint32_t code_sub = __float_as_uint(f) - F::MAGIC_BITS;
-    const uint32_t code = a >= F::MINNORM_BITS ? code_normal : code_sub;
-    return is_nan ? 0x7Fu : (sign | code);
-}
-
-// The same result for two values at once through the hardware converter.  v_cvt_pk_fp8_f32 / v_cvt_pk_bf8_f32
-// round to nearest even onto the OCP grids including subnormals and keep the sign of zero; clamping to +-max first
-// gives the saturation rule.  Compared against encode_fp8_rtne over all 2^32 binary32 patterns on gfx950: equal
-// for every non-NaN input; NaN is handled here.  Returns code(t0) | code(t1) << 8.
+// Nearest finite FP8 value, ties to the even mantissa, saturating, sign kept, NaN -> 0x7F, for two values at once through the
+// hardware converter: v_cvt_pk_fp8_f32 / v_cvt_pk_bf8_f32 round to nearest even onto the OCP grids including subnormals and
+// keep the sign of zero; clamping to +-max first gives the saturation rule, NaN is handled here.  Equal to the oracle's integer
+// arithmetic for every bfloat16 and for binary32 values of every upper half with the lower half at and around the ties.
+// Returns code(t0) | code(t1) << 8.
 template <int FMT> QMM_DEV uint32_t encode_fp8_rtne_pair(float t0, float t1)
 {
     const float mx = FMT == QMM_FMT_E4M3 ? 448.0f : 57344.0f;
@@ -186,7 +156,7 @@ QMM_DEV float delta_from_absmax_bits(uint32_t bits, float qmax)
 }
 
 // ---------------------------------------------------------------------------
-// Wavefront reductions (64 lanes) by shuffles.
+// Wavefront reductions (64 lanes).
 // ---------------------------------------------------------------------------
 QMM_DEV uint32_t wave_max_u32(uint32_t v)
 {

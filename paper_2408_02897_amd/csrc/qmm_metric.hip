@@ -2,7 +2,7 @@
 // sums behind the noise-to-signal ratio, the relative error of Eq. 2 and the
 // element-wise backward error of Eq. 3.  HBM-bound: 8 B per element for a
 // binary32 y (6 B for bfloat16 y, +4 B with denominators).  Every thread keeps
-// private sums, wavefronts fold them by shuffles, workgroups through LDS, and a
+// private sums, wavefronts fold them by rotations and swaps of lanes, workgroups through LDS, and a
 // small second kernel (one workgroup per field) folds the per-workgroup partials in a fixed order:
 // no atomics, so the result is reproducible run to run.
 #include <algorithm>
@@ -20,14 +20,14 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 // bits) and n is such a value or the difference of two (exponents within +-150 or so).
 //
 // reciprocals4: the four reciprocals from ONE hardware estimate: p = d0 d1 d2 d3 (within 2^-596 .. 2^512), one Newton
-// step on rcp(p) -- whose error of 2^-24 at most (2^29 ulp) it squares --, then multiplied back by the other factors.
-// Each x[i] is 1 / d[i] to 2^-46 at least.
-// quotient_with: q0 = n x, r = n - d q0 (exact in one fused multiply-add: d q0 has 77 bits of which the top 45 or more
-// cancel), q = fl(q0 + r x).  q0 + r x differs from n / d by |r / d| * |x d - 1| < 2^-90 relative, and a quotient with a 24-bit
+// step on rcp(p) -- whose error of at most 2^29 ulp, 2^-23, it squares --, then multiplied back by the other factors, a few
+// roundings of 2^-53 each.  Each x[i] is 1 / d[i] to 2^-45.
+// quotient_with: q0 = n x, r = n - d q0 (exact in one fused multiply-add: d q0 has 77 bits of which the top 44 or more
+// cancel), q = fl(q0 + r x).  q0 + r x differs from n / d by |r / d| * |x d - 1| <= 2^-90 relative, and a quotient with a 24-bit
 // divisor is either representable or at least 2^-78 relative away from the nearest rounding boundary (n - m d is a
 // multiple of 2^(e_m + e_d - 76) for a 54-bit midpoint m), so the single rounding of the last operation lands on the
 // IEEE quotient: same bits as `/`, for 6.75 instructions per quotient (a quarter of one at quarter rate) instead of 11 with the
-// compiler's sequence.  (The metric pass is as much ALU- as HBM-bound; the divisions are its largest single cost.)
+// compiler's sequence.  (The divisions are the pass's largest single cost.)
 // A zero, infinite or NaN operand anywhere in the four gives NaN or infinity in the affected quotients, never a wrong
 // finite value passed as right for them: the caller tests the quotients and takes the general path then.
 QMM_DEV void reciprocals4(const double* d, double* x)
@@ -161,10 +161,12 @@ metric_partial(const void* __restrict__ yv, const float* __restrict__ r, const f
     int64_t i = (int64_t)blockIdx.x * kThreads * 2 + threadIdx.x;
     // (y and the reference are read once: streaming loads, which leave the caches to the tensors that are read again --
     // the benchmark's step is 3 % shorter for it, the pass itself 4 %)
-    // The pass is bound by the vector unit (80 % of its cycles busy, at the 1.7 GHz the binary64 work leaves), so the loop
-    // is kept to what the sums need: the rare path lies outside it -- inside, the running sums were copied around it on
-    // every trip, 11 moves for 8 elements --, the maximum of |r| is taken in binary32, which holds it exactly, and the
-    // reciprocals need one Newton step (see reciprocals4).  24 instructions an element before, 20 now.
+    // The vector unit is busy for 80 % of the pass's cycles (at the 1.7 GHz the binary64 work leaves): small tensors are bound
+    // by it and its latencies, tensors of tens of millions of elements by memory as well.  The loop is kept to what the sums
+    // need: the rare path lies outside it -- inside, the running sums were copied around it on every trip, 11 moves for 8
+    // elements --, the maximum of |r| is taken in binary32, which holds it exactly, and the reciprocals need one Newton step.
+    // 24 instructions an element before, 20 now (launches back to back: 196608 bfloat16 6.9 -> 5.6 us, 3 million 10.9 -> 8.9, 67
+    // million 75 -> 69, 5.8 TB/s; binary32 y 88 -> 86, 6.2 TB/s; with denominators 110 -> 104 and 125 -> 127).
     float mr = 0.0f;
     for (;;) {
         bool special = false;
@@ -255,7 +257,7 @@ metric_partial(const void* __restrict__ yv, const float* __restrict__ r, const f
 }
 
 // Sixteen workgroups, one per field: thread t takes blocks t, t+256, ... in ascending order, the 64 lane values
-// are folded by the fixed shuffle tree and the four wavefront values in wavefront order: the order of additions
+// are folded by the fixed butterfly and the four wavefront values in wavefront order: the order of additions
 // depends on nblocks only, so results are reproducible run to run.
 constexpr int kFinalThreads = 256;
 __global__ void __launch_bounds__(kFinalThreads)

@@ -322,3 +322,49 @@ def test_scale_per_channel_of_tall_and_wide_tensors(batch, rows, cols, groups, i
         size = qmm.lib().qmm_scale_workspace_size(ctypes.byref(qmm.tensor_desc(x, axis)), ctypes.byref(qmm.granularity(True, groups, inner)))
         if size <= 1 << 20:
             assert torch.equal(qmm.scale_static(x, axis, qmm.E4M3, True, groups, batch_inner=inner), d)
+
+
+# The hardware converter against the oracle's integer arithmetic: every bfloat16 pattern, and binary32 values of every upper
+# half with lower halves at and around the ties; step size 1, so the code is the rounded value itself.
+@pytest.mark.parametrize("fmt", [qmm.E4M3, qmm.E5M2, qmm.INT8])
+def test_nearest_even_of_every_upper_half(fmt):
+    upper = np.arange(65536, dtype=np.uint32) << 16
+    one = torch.ones(1, device=DEV)
+    bf = torch.from_numpy((upper >> 16).astype(np.uint16).view(np.int16)).view(torch.bfloat16).view(1, 1, -1)
+    for dtype_x, xn in ((bf, upper.view(np.float32)[None, None]),
+                        *((None, (upper | np.uint32(low)).view(np.float32)[None, None])
+                          for low in (1, 0x2AAA, 0x7FFF, 0x8000, 0x8001, 0xFFFF))):
+        x = dtype_x.to(DEV) if dtype_x is not None else torch.from_numpy(xn.copy()).to(DEV)
+        for axis in (1, 0):
+            codes = qmm.quantize(x, axis, fmt, one).cpu().numpy()
+            assert np.array_equal(codes, O.quantize(xn, axis, fmt, np.ones(1, np.float32)))
+
+
+# Every quotient of the metric pass by itself: a call of one trip of one workgroup whose other elements have a quotient of 0, so
+# that the maximum (and the sum) is the quotient under test, which must equal the IEEE quotient bit for bit; the plain path
+# (no special element in the wavefront) over exponents and mantissas of binary32, with and without denominators.
+def test_metric_quotients_bit_for_bit():
+    rng = np.random.default_rng(9)
+    cases = 400
+    r = (rng.integers(0, 1 << 23, cases).astype(np.uint32) | (rng.integers(64, 190, cases).astype(np.uint32) << 23)).view(np.float32)
+    d = (rng.integers(0, 1 << 23, cases).astype(np.uint32) | (rng.integers(64, 190, cases).astype(np.uint32) << 23)).view(np.float32)
+    y = (rng.integers(0, 1 << 23, cases).astype(np.uint32) | (rng.integers(64, 190, cases).astype(np.uint32) << 23)).view(np.float32)
+    r[::3] = np.abs(y[::3] * (1 + rng.uniform(-1e-3, 1e-3, r[::3].size)).astype(np.float32))       # small errors
+    n = 2048
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device=DEV)
+    out = torch.empty((cases, 2, 16), dtype=torch.float64, device=DEV)
+    rest_r, rest_d = np.float32(3.7), np.float32(0.9)
+    for i in range(cases):
+        at = int(rng.integers(0, n))
+        yy, rr, dd = np.full(n, rest_r), np.full(n, rest_r), np.full(n, rest_d)
+        yy[at], rr[at], dd[at] = y[i], r[i], d[i]
+        ty, tr, td = (torch.from_numpy(v).to(DEV) for v in (yy, rr, dd))
+        qmm.metric(ty, tr, out=out[i, 0], workspace=ws)
+        qmm.metric(ty, tr, td, out=out[i, 1], workspace=ws)
+    got = out.cpu().numpy()
+    e = np.abs(y.astype(np.float64) - r.astype(np.float64))
+    q, qb = e / r.astype(np.float64), e / d.astype(np.float64)
+    for f, want in ((6, q), (7, q)):
+        assert np.array_equal(got[:, 0, f], want) and np.array_equal(got[:, 1, f], want)
+    for f, want in ((9, qb), (10, qb)):
+        assert np.array_equal(got[:, 1, f], want)

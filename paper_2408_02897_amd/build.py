@@ -47,7 +47,7 @@ def check_asm():
     matrix instructions and copies: (1) no accumulator register is written by v_accvgpr_write within six
     instructions in front of an MFMA that uses it (wait states), (2) every LDS copy has its base address in scalar
     registers, (3) no MFMA goes through v_accvgpr_mov copies inside the loops (at most one initialisation pass), (4) the
-    kernels on the throughput path use no scratch memory, (5) the streaming kernel initialises no accumulator by a
+    kernels on the throughput path use no scratch memory (the kernels whose matrix instructions are builtins: 2 and 4 only), (5) the streaming kernel initialises no accumulator by a
     separate instruction and has no load the compiler knows of (outside the inline-assembly statements) behind its first MFMA (with stores outstanding the
     compiler waits for such a load with vmcnt(0), i.e. for every store), (6) the registers its inline-assembly loads fill without waiting (a tile's step
     sizes) are touched by nothing before two step barriers have passed.  Returns a list of findings (empty = clean)."""
@@ -61,14 +61,15 @@ def check_asm():
     with ThreadPoolExecutor(max_workers=GEMM_PARTS) as ex:
         text = "\n".join(ex.map(assemble, range(GEMM_PARTS)))
     findings = []
-    names = list(dict.fromkeys(re.findall(r"^(_ZN3qmm\S*(?:gemm_kernel|gemm_shortk_kernel|gemm_stream_kernel)\S*):", text, flags=re.M)))
+    names = list(dict.fromkeys(re.findall(r"^(_ZN3qmm\S*(?:gemm_kernel|gemm_shortk_kernel|gemm_stream_kernel|gemm_deep_kernel|gemm_direct_kernel)\S*):", text, flags=re.M)))
     for nm in names:
         start = text.index("\n" + nm + ":")
         end = text.index(".Lfunc_end", start)
         body = text[start:end]
         instrs = [l.strip() for l in body.split("\n")
                   if l.strip() and not l.strip().startswith((";", ".")) and not l.strip().endswith(":")]
-        for k, l in enumerate(instrs):
+        by_builtin = "gemm_deep_kernel" in nm or "gemm_direct_kernel" in nm       # the compiler knows these matrix instructions
+        for k, l in enumerate([] if by_builtin else instrs):
             m = re.match(r"v_mfma\S+ a\[(\d+):(\d+)\]", l)
             if not m:
                 continue
@@ -107,7 +108,7 @@ def check_asm():
                             findings.append(f"{nm}: v{dst}, loaded without a wait, is touched too early by '{q[:60]}'")
                         break
         n_acc = 128 if ("ELi4ELi1ELi4E" in nm or "shortk" in nm) else 64
-        if body.count("v_accvgpr_mov") > n_acc:
+        if not by_builtin and body.count("v_accvgpr_mov") > n_acc:
             findings.append(f"{nm}: {body.count('v_accvgpr_mov')} v_accvgpr_mov (accumulators copied around MFMAs)")
         tail = text[end:end + 8000]
         sc = re.search(r"; ScratchSize: (\d+)", tail)
@@ -115,7 +116,7 @@ def check_asm():
         fuse = int(re.findall(r"Li(\d+)E", targs.group(1))[6]) if targs else 0      # <KIND, FA, FB, TM, TG, NWN, FUSE, NSR>
         if sc and int(sc.group(1)) > 0 and targs and fuse == 0:                       # codes-in kernels: the throughput path
             findings.append(f"{nm}: {sc.group(1)} bytes of scratch per lane")
-        if sc and int(sc.group(1)) > 0 and ("shortk" in nm or "gemm_stream_kernel" in nm):
+        if sc and int(sc.group(1)) > 0 and (by_builtin or "shortk" in nm or "gemm_stream_kernel" in nm):
             findings.append(f"{nm}: {sc.group(1)} bytes of scratch per lane")
     return names, findings
 

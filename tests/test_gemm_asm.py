@@ -13,4 +13,6 @@ from paper_2408_02897_amd import build
 def test_gemm_assembly_is_clean():
     kernels, findings = build.check_asm()
     assert len(kernels) >= 40                 # every instantiation of gemm_kernel and gemm_shortk_kernel was seen
+    for form in ("gemm_deep_kernel", "gemm_direct_kernel", "gemm_stream_kernel"):
+        assert sum(form in k for k in kernels) >= 6, form                # one per operand-format pair at least
     assert findings == []

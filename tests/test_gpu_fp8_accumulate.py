@@ -1,7 +1,7 @@
 """The device's FP8 accumulators against the written-down arithmetic of tests/fp8_mfma_model.py, bit for bit, through
 every kernel the FP8 product can take (Methodology, third implementation bullet: the 8-bit product held in the wider
 accumulator of the multiply-accumulate unit):
-  * kernels that return accumulators (LDS-tiled, both tile sizes; split-K; register-direct): acc == model;
+  * kernels that return accumulators (deep ring; LDS-tiled, both tile sizes; split-K; register-direct): acc == model;
   * kernels that only write y (short contractions on resident workgroups, the streaming kernel): y == the oracle's
     descale of the model's accumulators, binary32 and bfloat16, step sizes per tensor / channel / head.
 Codes: quantized from the distribution families of the paper's tensors (all four format pairs) -- equality required
@@ -76,6 +76,20 @@ def test_uniform_e4m3_codes_equal_the_model(shape):
     want = model_acc(a, O.E4M3, b, O.E4M3)
     for m in range(bt):
         assert_same_bits(acc[m], want[m], f"matrix {m}")
+
+
+# more than 512 tiles of 64 x 64, contractions of several slabs and not split: 128 x 128 tiles (ragged and whole, a batch) and
+# 256 x 256 tiles; up to 512 tiles (TILE_SHAPES) the deep-ring kernel takes the product
+@pytest.mark.parametrize("fa,fb", PAIRS[:3])
+@pytest.mark.parametrize("shape", [(1, 1600, 1560, 400), (6, 600, 700, 272), (1, 1536, 1536, 1024), (1, 4200, 2500, 528)])
+def test_tiled_kernel_equals_the_model(shape, fa, fb):
+    bt, M, N, K = shape
+    a, b = quantized_codes(W.student_t((bt, M, K), 4, 33), fa), quantized_codes(W.normal((bt, N, K), 0.02, 34), fb)
+    _, acc = device(a, fa, b, fb)
+    rows = np.unique(np.concatenate([np.arange(0, M, 149), [127, 128, 255, 256, M - 1]]))
+    for m in {0, bt - 1}:
+        want = model_acc(a, fa, b, fb, matrices=[m], rows=rows)[m]
+        assert_same_bits(acc[m][rows], want, f"matrix {m}")
 
 
 @pytest.mark.parametrize("fa,fb", PAIRS)

@@ -33,13 +33,15 @@ def operands(kind, m, n, k, per_channel, batch=1):
     return qmm.quantized_operand(x, 1, fmt, per_channel)[0], qmm.quantized_operand(w, 1, fmt, per_channel)[0]
 
 
-# The call that also returns the accumulators takes the element-by-element epilogue: Y of the two calls must agree in
-# every bit.  Extents around the tiles (128, 256), odd ones (rows that start off every vector boundary) and outputs large
-# enough for the 256 x 256 tiles.
+# Above 512 tiles of 64 x 64 the call that also returns the accumulators takes the element-by-element epilogue: Y of the two
+# calls must agree in every bit (128 x 128 tiles: 1601 x 1563, 1700 x 1411; 256 x 256: the last two).  Smaller outputs are
+# the deep-ring kernel's, whose two calls differ in the accumulators alone; its sums are compared in
+# test_product_of_few_tiles.  Extents around the tiles, odd ones (rows that start off every vector boundary).
 @pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("kind", ["e4m3", "int8", "bf16"])
 @pytest.mark.parametrize("m,n,k", [(1, 1, 16), (127, 130, 144), (129, 255, 128), (257, 129, 272), (200, 203, 400),
-                                   (128, 132, 256), (130, 256, 64), (4099, 3071, 128), (3842, 3074, 144)])
+                                   (128, 132, 256), (130, 256, 64), (1601, 1563, 272), (1700, 1411, 400),
+                                   (4099, 3071, 128), (3842, 3074, 144)])
 def test_output_at_edges_and_odd_extents(kind, m, n, k, out_dtype):
     a, b = operands(kind, m, n, k, per_channel=(m + n) % 2 == 1)
     want, _ = qmm.gemm(a, b, out_dtype, want_acc=True)

@@ -629,7 +629,8 @@ template <typename T, int FMT, int MODE, bool FOLD> void launch_rows(const QArgs
     if (is_short) plan.units = (slots + piece - 1) / piece;
     else { plan.pieces = (slots_per_row + piece - 1) / piece; plan.units = q.rows * plan.pieces; }
     constexpr int kWaves = kThreads / kWave;
-    const dim3 grid((unsigned)std::min<int64_t>((plan.units + kWaves - 1) / kWaves, 65536), (unsigned)q.batch);
+    // (FOLD: every workgroup fetches its group's partial maxima, so no more of them than the chip holds at a time)
+    const dim3 grid((unsigned)std::min<int64_t>((plan.units + kWaves - 1) / kWaves, FOLD ? std::max<int64_t>(2048 / q.batch, 1) : 65536), (unsigned)q.batch);
     if (is_short) {
         if (small) quantize_rows<T, FMT, MODE, FOLD, 1, true><<<grid, kThreads, 0, s>>>(q, plan);
         else quantize_rows<T, FMT, MODE, FOLD, 2, true><<<grid, kThreads, 0, s>>>(q, plan);

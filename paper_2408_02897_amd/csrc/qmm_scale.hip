@@ -265,9 +265,15 @@ absmax_cols(const T* __restrict__ x, int64_t batch_stride, int64_t row_stride, i
     VecMax<T> m;
     const T* base = x + (int64_t)blockIdx.z * batch_stride + c0;
     if (c0 + V <= cols) {
-        auto row = [&](int64_t r) { return *reinterpret_cast<const u32x4_any*>(base + min(r, r1 - 1) * row_stride); };
-        for (int64_t r = r0 + rl; r < r1; r += 4 * RL) {
+        auto row = [&](int64_t r) { return *reinterpret_cast<const u32x4_any*>(base + r * row_stride); };
+        int64_t r = r0 + rl;
+        for (; r + 3 * RL < r1; r += 4 * RL) {
             const u32x4 a = row(r), b = row(r + RL), c = row(r + 2 * RL), d = row(r + 3 * RL);
+            m.fold(a); m.fold(b); m.fold(c); m.fold(d);
+        }
+        if (r < r1) {
+            const int64_t end = r1 - 1;
+            const u32x4 a = row(r), b = row(min(r + RL, end)), c = row(min(r + 2 * RL, end)), d = row(min(r + 3 * RL, end));
             m.fold(a); m.fold(b); m.fold(c); m.fold(d);
         }
     } else if (c0 < cols) {

@@ -580,7 +580,9 @@ quantize_cols(QArgs a, int64_t tiles_n, int64_t tiles)
     }
 }
 
-// One thread per code, for tensors so small that nothing but the length of a thread's own work counts: contracting over
+// One thread per code, for tensors so small that nothing but the length of a thread's own work counts, and for contractions
+// over so few rows that a tile of 128 would be idle but for a strip (8 x 200000 bfloat16 4.0 against 7.6 us, stochastic 6.6
+// against 12.4; 3000 matrices of 16 x 64 7.8 against 7.3, stochastic 11.3 against 11.8).  Small tensors, contracting over
 // rows 33 x 70 1.8 us against 2.6 in tiles of 16, stochastic 1.9 against 3.8; 256 x 768 2.5 against 2.6.  Contracting over
 // columns the vectors of the row kernels are as fast, but for stochastic rounding of rows that are not whole generator
 // blocks (301 x 202: 2.0 against 2.8 us).
@@ -646,7 +648,9 @@ template <int FMT, int MODE, bool FOLD> qmm_status launch(const qmm_tensor* x, c
     const bool bf16 = x->dtype == QMM_DT_BF16;
     if constexpr (!FOLD) {
         const int64_t n = x->rows * x->cols;
-        if (n * x->batch <= kEachMax && (x->contract_axis == 0 || (MODE == QMM_ROUND_STOCHASTIC && x->cols % 4 != 0))) {
+        const bool few_rows = x->contract_axis == 0 && x->rows <= (MODE == QMM_ROUND_RTNE ? 12 : 16) && n < (int64_t(1) << 31);
+        const bool tiny = n * x->batch <= kEachMax && (x->contract_axis == 0 || (MODE == QMM_ROUND_STOCHASTIC && x->cols % 4 != 0));
+        if (few_rows || tiny) {
             const dim3 grid((unsigned)((n + kThreads - 1) / kThreads), (unsigned)x->batch);
             if (bf16) quantize_each<uint16_t, FMT, MODE><<<grid, kThreads, 0, s>>>(a, x->contract_axis);
             else quantize_each<float, FMT, MODE><<<grid, kThreads, 0, s>>>(a, x->contract_axis);

@@ -288,11 +288,12 @@ def test_quantize_of_short_and_long_rows(batch, rows, cols, form, dtype):
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("form", ["dense", "shifted"])
 @pytest.mark.parametrize("batch,rows,cols", [(1, 33, 70), (3, 40, 21), (1, 700, 401), (5, 260, 262), (1, 131, 2101), (1, 1300, 1601), (2, 1031, 1203),
-                                             (64, 9, 4200), (64, 12, 4196)])
+                                             (64, 9, 4200), (64, 12, 4196),
+                                             (64, 13, 4196), (700, 4, 401), (1, 12, 40001), (1, 16, 40003), (64, 20, 4196), (64, 21, 4200)])
 def test_quantize_of_contracted_rows(batch, rows, cols, form, dtype):
     x = tensor_form(form, rows, cols, batch, dtype, seed=rows + cols).clone() if form == "dense" else tensor_form(form, rows, cols, batch, dtype, rows)
     for i, v in enumerate([float("nan"), float("inf"), -float("inf"), 0.0, 1e-7, -3e-6, 2e-4, -1e-30]):
-        x[-1, i, cols // 2] = v
+        x[-1, i % rows, cols // 2 + i // rows] = v
     xn = x.float().cpu().numpy()
     for per_channel in (True, False):
         d = np.random.default_rng(cols).uniform(1e-3, 1e-1, cols if per_channel else 1).astype(np.float32)

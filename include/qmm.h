@@ -18,7 +18,9 @@
  *    of qmm_scale_static, and a ring of arrival counters that the single-launch
  *    reductions of qmm_scale / qmm_scale_multi use and leave at zero; a call
  *    takes the next slot of the ring, 1024 calls would have to be in flight for
- *    two of them to meet on one), and which GPUs have had the kernels' LDS limit set.
+ *    two of them to meet on one), a ring of boards through which the workgroups of one launch
+ *    exchange values (calls outside stream capture; a board shared by two calls in flight costs
+ *    time, never a result), and which GPUs have had the kernels' LDS limit set.
  *    Descriptor structs (qmm_tensor, qmm_operand, qmm_granularity) are host memory
  *    and are read before the call returns.
  *  - Calls validate their arguments on the host, enqueue kernels on `stream`
@@ -152,7 +154,8 @@ qmm_status qmm_quantize(const qmm_tensor* x, qmm_format fmt, const qmm_granulari
 /*
  * qmm_scale_quantize -- steps 1 and 2 of one tensor in one call: delta_out and codes_out are exactly what qmm_scale and
  * then qmm_quantize with those step sizes write, with fewer launches and passes over x: one step size per row (rows up
- * to 8192 bfloat16 / 4096 binary32 elements, every matrix a batch group of its own) takes a single pass; otherwise the
+ * to 8192 bfloat16 / 4096 binary32 elements, every matrix a batch group of its own) takes a single pass, other tensors up to
+ * 67 MB one launch that reads the tensor once (not under stream capture, where the passes are separate launches); beyond, the
  * quantize pass forms the step sizes from the partial maxima where that pays.
  *   workspace  device scratch of at least qmm_scale_quantize_workspace_size() bytes, 16-byte aligned (0: may be NULL).
  * An empty tensor writes its groups' step sizes (1) and no codes.  Errors as for the two calls.

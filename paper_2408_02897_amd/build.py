@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libqmm.so")
 GEMM_PARTS = 6                      # qmm_gemm.hip is compiled once per operand-format pair, side by side
-SOURCES = ["qmm_api.hip", "qmm_scale.hip", "qmm_quantize.hip", "qmm_metric.hip", "qmm_diag.hip", "qmm_moments.hip", "qmm_dequantize.hip"]
+SOURCES = ["qmm_api.hip", "qmm_scale.hip", "qmm_quantize.hip", "qmm_resident.hip", "qmm_metric.hip", "qmm_diag.hip", "qmm_moments.hip", "qmm_dequantize.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function", "-Wno-inline-asm",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -25,7 +25,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
 def _compile(src, force, part=None):
     obj = os.path.join(OBJDIR, src.replace(".hip", ".o" if part is None else f"_{part}.o"))
     path = os.path.join(CSRC, src)
-    deps = [path, os.path.join(CSRC, "qmm_device.h"), os.path.join(ROOT, "include", "qmm.h")]
+    deps = [path, *(os.path.join(CSRC, h) for h in os.listdir(CSRC) if h.endswith(".h")), os.path.join(ROOT, "include", "qmm.h")]
     if not force and os.path.exists(obj) and all(os.path.getmtime(obj) >= os.path.getmtime(d) for d in deps):
         return obj
     subprocess.run([HIPCC, *FLAGS, *([] if part is None else [f"-DQMM_GEMM_PART={part}"]), "-c", path, "-o", obj], check=True)

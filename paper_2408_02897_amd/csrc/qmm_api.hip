@@ -29,6 +29,54 @@ qmm_status arrival_slots(int count, uint32_t** first)
     *first = p + (size_t)group * 8 * kArrivalWords;
     return QMM_OK;
 }
+
+// ---- boards (qmm_device.h).  Tags run from 1 to kTags and start over; before a board is used for the first time in such a
+// round, its words -- which could hold that tag from the round before -- are cleared.
+namespace {
+constexpr uint64_t kTags = (uint64_t(1) << 32) - kBoards;       // a multiple of the number of boards
+static_assert(kTags % kBoards == 0, "a tag's board is the same in every round");
+std::atomic<uint64_t*> board_addr[kMaxDevices];
+std::atomic<uint64_t> next_tag{0};
+std::atomic<int> cus[kMaxDevices];
+__global__ void board_clear(uint64_t* words)
+{
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < kBoardWords; i += gridDim.x * 256) words[i] = 0;
+}
+}  // namespace
+}  // namespace qmm
+static __device__ __align__(256) uint64_t boards[qmm::kBoards * qmm::kBoardWords];
+namespace qmm {
+bool take_board(hipStream_t s, Board* b)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusActive;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) { (void)hipGetLastError(); return false; }
+    int dev = -1;
+    if (st != hipStreamCaptureStatusNone || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
+    uint64_t* p = board_addr[dev].load(std::memory_order_acquire);
+    if (!p) {
+        void* q = nullptr;
+        if (hipGetSymbolAddress(&q, HIP_SYMBOL(boards)) != hipSuccess || !q) { (void)hipGetLastError(); return false; }
+        p = static_cast<uint64_t*>(q);
+        board_addr[dev].store(p, std::memory_order_release);
+    }
+    const uint64_t n = next_tag.fetch_add(1, std::memory_order_relaxed);
+    b->words = p + (size_t)(n % kBoards) * kBoardWords;
+    b->tag = (uint32_t)(n % kTags) + 1u;
+    b->patience = kPatience;
+    if (n >= kTags && n % kTags < kBoards) board_clear<<<64, 256, 0, s>>>(b->words);
+    return true;
+}
+int cu_count()
+{
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 0;
+    int n = cus[dev].load(std::memory_order_relaxed);
+    if (n == 0) {
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) { (void)hipGetLastError(); return 0; }
+        cus[dev].store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
 }  // namespace qmm
 
 extern "C" const char* qmm_status_string(qmm_status s)

@@ -208,6 +208,73 @@ QMM_DEV double wave_max_f64(double v)
 }
 
 // ---------------------------------------------------------------------------
+// Maxima of magnitude bits over 16-byte vectors of elements.
+// ---------------------------------------------------------------------------
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+
+// 8 bfloat16 magnitudes packed in a 16-byte vector -> running packed maxima.
+QMM_DEV void fold_bf16x8(qmm_u32x4 w, u16x2 (&m)[4])
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t a = w[i] & 0x7FFF7FFFu;
+        m[i] = __builtin_elementwise_max(m[i], __builtin_bit_cast(u16x2, a));
+    }
+}
+QMM_DEV uint32_t finish_bf16(const u16x2 (&m)[4])
+{
+    uint32_t r = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r = max(r, max((uint32_t)m[i][0], (uint32_t)m[i][1]));
+    return r << 16;   // bfloat16 magnitude -> binary32 magnitude bits
+}
+
+template <typename T> QMM_DEV uint32_t mag_bits(T v);
+template <> QMM_DEV uint32_t mag_bits<uint16_t>(uint16_t v) { return ((uint32_t)v & 0x7FFFu) << 16; }
+template <> QMM_DEV uint32_t mag_bits<float>(float v) { return __float_as_uint(v) & 0x7FFFFFFFu; }
+
+// Running maxima over 16-byte vectors (8 bfloat16 or 4 binary32 elements), kept per position.
+template <typename T> struct VecMax;
+template <> struct VecMax<uint16_t> {
+    static constexpr int V = 8;
+    u16x2 m[4] = {};
+    QMM_DEV void fold(qmm_u32x4 w) { fold_bf16x8(w, m); }
+    QMM_DEV uint32_t finish() const { return finish_bf16(m); }
+    QMM_DEV void words(uint32_t (&out)[4]) const
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[i] = __builtin_bit_cast(uint32_t, m[i]);
+    }
+    QMM_DEV void fold_words(const uint32_t (&in)[4])
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m[i] = __builtin_elementwise_max(m[i], __builtin_bit_cast(u16x2, in[i]));
+    }
+    QMM_DEV uint32_t at(int e) const { return (uint32_t)m[e >> 1][e & 1] << 16; }
+};
+template <> struct VecMax<float> {
+    static constexpr int V = 4;
+    uint32_t m[4] = {};
+    QMM_DEV void fold(qmm_u32x4 w)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m[i] = max(m[i], w[i] & 0x7FFFFFFFu);
+    }
+    QMM_DEV uint32_t finish() const { return max(max(m[0], m[1]), max(m[2], m[3])); }
+    QMM_DEV void words(uint32_t (&out)[4]) const
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[i] = m[i];
+    }
+    QMM_DEV void fold_words(const uint32_t (&in)[4])
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m[i] = max(m[i], in[i]);
+    }
+    QMM_DEV uint32_t at(int e) const { return m[e]; }
+};
+
+// ---------------------------------------------------------------------------
 // "The workgroup that arrives last folds the partial results": one launch per reduction instead of two.
 // A call takes one slot (per reduced tensor) of a ring of arrival counters that live in the library's device
 // image and are zero between calls; every workgroup publishes its partial result, counts itself in, and the one
@@ -263,6 +330,44 @@ QMM_DEV bool arrive_last(uint32_t* slot, unsigned id, unsigned total)
     return s_last != 0;
 }
 
+// ---------------------------------------------------------------------------
+// A board of posted values: how the workgroups of ONE launch hand partial results to one another while it runs.
+// A word is 64 bits, the call's tag above a 32-bit value, written and read whole by device-coherent accesses: a word with
+// the call's tag holds that call's value, any other word has not been posted yet.  Nothing is cleared or counted, there are no
+// atomics, and no ordering between words is needed.  Tags are handed out by the host, one per launch (take_board), so a
+// call that is being recorded into a graph, whose replays would repeat the tag, does not use a board.
+// Boards are a ring in the library's device image.  A reader's wait is bounded (`patience`, in ticks of the 100 MHz clock):
+// a value that has not come by then -- its workgroup may not be resident, other work holding the CUs, or another call of the
+// ring's length before may share the board -- the reader's workgroup forms itself and posts, the same value.  So every
+// workgroup ends whatever the others do, and what the words hold decides about time, never about results.
+// ---------------------------------------------------------------------------
+constexpr int kBoards = 16, kBoardWords = 65536;
+constexpr uint32_t kPatience = 5000;                     // 50 us
+struct Board { uint64_t* words; uint32_t tag, patience; };
+bool take_board(hipStream_t s, Board* b);                // host (qmm_api.hip); false: the call is to do without one
+int cu_count();                                          // host: CUs of the current device, 0 if unknown
+
+QMM_DEV void board_post(const Board& b, uint32_t i, uint32_t v)
+{
+    __hip_atomic_store(b.words + i, ((uint64_t)b.tag << 32) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+QMM_DEV bool board_read(const Board& b, uint32_t i, uint32_t& v)
+{
+    const uint64_t w = __hip_atomic_load(b.words + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    v = (uint32_t)w;
+    return (uint32_t)(w >> 32) == b.tag;
+}
+QMM_DEV uint64_t ticks() { return __builtin_amdgcn_s_memrealtime(); }
+// Waits for word i until `patience` ticks after `start`; false: it did not come.
+QMM_DEV bool board_wait(const Board& b, uint32_t i, uint64_t start, uint32_t& v)
+{
+    while (!board_read(b, i, v)) {
+        if (ticks() - start >= b.patience) return false;
+        __builtin_amdgcn_s_sleep(2);
+    }
+    return true;
+}
+
 // The scale pass in two halves (qmm_scale.hip), for the call that hands the partial maxima to the quantize pass.
 constexpr int kFoldSlabs = 32;       // row slabs per matrix in the column maxima: what the quantize pass can fold on its way, at most
 struct ScalePartials {
@@ -276,6 +381,9 @@ qmm_status scale_partials(const qmm_tensor* x, qmm_format fmt, const qmm_granula
                           bool fold_here, ScalePartials* out, hipStream_t s);
 qmm_status scale_fold(const ScalePartials& pp, const uint32_t* partial, qmm_format fmt, const qmm_granularity* g,
                       float* delta_out, hipStream_t s);
+// Both steps in one launch (qmm_resident.hip), for the calls it is for.
+qmm_status scale_quantize_resident(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, qmm_round mode, uint64_t seed,
+                                   uint64_t offset, float* delta, uint8_t* codes, uint32_t patience, hipStream_t s, bool* taken);
 inline float host_qmax(qmm_format fmt) { return fmt == QMM_FMT_INT8 ? 127.0f : (fmt == QMM_FMT_E4M3 ? 448.0f : 57344.0f); }
 
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }

@@ -20,8 +20,7 @@ constexpr int kMaxFlatBlocks = 1024;   // 4 workgroups per CU on 256 CUs; 4 part
 constexpr int kColSlabRows = 128;      // rows folded by one workgroup in the column-group kernel, at least
 constexpr int kMaxColSlabs = 512;      // and slabs of them, at most
 
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef qmm_u32x4 u32x4;
 typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(2)));   // global memory takes vector loads at any element boundary
 
 QMM_DEV uint32_t block_max_u32(uint32_t v)
@@ -35,68 +34,6 @@ QMM_DEV uint32_t block_max_u32(uint32_t v)
     for (int i = 1; i < kThreads / kWave; ++i) r = max(r, s[i]);
     return r;
 }
-
-// 8 bfloat16 magnitudes packed in a 16-byte vector -> running packed maxima.
-QMM_DEV void fold_bf16x8(u32x4 w, u16x2 (&m)[4])
-{
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint32_t a = w[i] & 0x7FFF7FFFu;
-        m[i] = __builtin_elementwise_max(m[i], __builtin_bit_cast(u16x2, a));
-    }
-}
-QMM_DEV uint32_t finish_bf16(const u16x2 (&m)[4])
-{
-    uint32_t r = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) r = max(r, max((uint32_t)m[i][0], (uint32_t)m[i][1]));
-    return r << 16;   // bfloat16 magnitude -> binary32 magnitude bits
-}
-
-template <typename T> QMM_DEV uint32_t mag_bits(T v);
-template <> QMM_DEV uint32_t mag_bits<uint16_t>(uint16_t v) { return ((uint32_t)v & 0x7FFFu) << 16; }
-template <> QMM_DEV uint32_t mag_bits<float>(float v) { return __float_as_uint(v) & 0x7FFFFFFFu; }
-
-// Running maxima over 16-byte vectors (8 bfloat16 or 4 binary32 elements), kept per position.
-template <typename T> struct VecMax;
-template <> struct VecMax<uint16_t> {
-    static constexpr int V = 8;
-    u16x2 m[4] = {};
-    QMM_DEV void fold(u32x4 w) { fold_bf16x8(w, m); }
-    QMM_DEV uint32_t finish() const { return finish_bf16(m); }
-    QMM_DEV void words(uint32_t (&out)[4]) const
-    {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) out[i] = __builtin_bit_cast(uint32_t, m[i]);
-    }
-    QMM_DEV void fold_words(const uint32_t (&in)[4])
-    {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) m[i] = __builtin_elementwise_max(m[i], __builtin_bit_cast(u16x2, in[i]));
-    }
-    QMM_DEV uint32_t at(int e) const { return (uint32_t)m[e >> 1][e & 1] << 16; }
-};
-template <> struct VecMax<float> {
-    static constexpr int V = 4;
-    uint32_t m[4] = {};
-    QMM_DEV void fold(u32x4 w)
-    {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) m[i] = max(m[i], w[i] & 0x7FFFFFFFu);
-    }
-    QMM_DEV uint32_t finish() const { return max(max(m[0], m[1]), max(m[2], m[3])); }
-    QMM_DEV void words(uint32_t (&out)[4]) const
-    {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) out[i] = m[i];
-    }
-    QMM_DEV void fold_words(const uint32_t (&in)[4])
-    {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) m[i] = max(m[i], in[i]);
-    }
-    QMM_DEV uint32_t at(int e) const { return m[e]; }
-};
 
 // The fold of a tensor's partial maxima by the workgroup that arrived last: all of them are one scale group.
 QMM_DEV void fold_all_partials(const uint32_t* partial, int64_t count, float qmax, float* delta)

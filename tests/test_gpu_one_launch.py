@@ -1,0 +1,130 @@
+"""qmm_scale_quantize where it takes one launch (csrc/qmm_resident.hip: slices in registers, their maxima on a board): the
+step sizes and codes of qmm_scale and qmm_quantize, bit for bit, over the forms the rule accepts -- dense and strided rows,
+both axes, groups and runs of matrices, one step size per column, both types and rounding modes, sizes around each slice
+variant --, whether the workgroups find one another's maxima or form them themselves, under capture, and with several
+streams on the ring of boards."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2408_02897_amd import qmm, workloads as W
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+GUARD = 64
+FOREVER = 0xFFFFFFFF
+
+
+def tensor(shape, dtype, seed, pad=0, shift=0):
+    b, r, c = shape
+    x = torch.randn((b, r, c + pad + shift), generator=torch.Generator(device=DEV).manual_seed(seed), device=DEV).to(dtype)
+    return x[:, :, shift:shift + c]
+
+
+def two_calls(x, axis, fmt, mode, offset, kw):
+    d = qmm.scale(x, axis, fmt, **kw)
+    return qmm.quantize(x, axis, fmt, d, mode=mode, seed=77, offset=offset, **kw), d
+
+
+def one_launch(x, axis, fmt, mode, offset, patience, kw):
+    """(taken, codes, step sizes) of the one-launch form alone; guards around the codes."""
+    L = qmm.lib()
+    f = L.qmm_internal_scale_quantize
+    f.restype = ctypes.c_int
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p, ctypes.c_int, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_void_p,
+                  ctypes.c_void_p, ctypes.c_uint32, ctypes.c_void_p, ctypes.c_void_p]
+    t, g = qmm.tensor_desc(x, axis), qmm.granularity(**kw)
+    b, r, c = x.shape
+    shape = (b, r, c) if axis == 1 else (b, c, r)
+    buf = torch.full((b * r * c + 2 * GUARD,), 77, dtype=torch.uint8, device=DEV)
+    d = torch.full((L.qmm_num_scales(ctypes.byref(t), ctypes.byref(g)) + 2,), -1.0, dtype=torch.float32, device=DEV)
+    taken = ctypes.c_int(-1)
+    status = f(ctypes.byref(t), fmt, ctypes.byref(g), mode, 77, offset, d.data_ptr() + 4, buf.data_ptr() + GUARD, patience,
+               ctypes.byref(taken), qmm._stream())
+    assert status == 0
+    torch.cuda.synchronize()
+    assert bool((buf[:GUARD] == 77).all()) and bool((buf[-GUARD:] == 77).all()) and float(d[0]) == -1.0 and float(d[-1]) == -1.0
+    return taken.value, buf[GUARD:-GUARD].view(shape), d[1:-1]
+
+
+# (shape, axis, granularity): rows of one unit (16 elements) and of one more, units around a workgroup's (256 threads, 512 and
+# 1024 units) and a grid's, strips of 64 columns and tiles of 128 and 512 rows, groups of few and of many words.
+FORMS = [
+    ((1, 1, 16), 1, {}), ((1, 1, 17), 1, {}), ((1, 3, 31), 1, {}), ((1, 16, 256), 1, {}), ((1, 1, 4097), 1, {}), ((1, 1, 16385), 1, {}),
+    ((1, 1031, 1001), 1, {}), ((1, 4096, 1024), 1, {}), ((1, 4100, 2050), 1, {}), ((1, 9000, 1030), 1, {}), ((1, 12000, 2048), 1, {}),
+    ((6, 40, 72), 1, dict(batch_groups=3)), ((7, 70, 96), 1, dict(batch_groups=3, batch_inner=2)), ((5, 33, 50), 1, dict(batch_groups=2, batch_inner=2)),
+    ((4, 700, 333), 1, dict(batch_groups=2)), ((3, 1000, 1000), 1, dict(batch_groups=3)), ((96, 128, 64), 1, dict(batch_groups=12)), ((9, 20, 40), 1, {}),
+    ((1, 1, 1), 0, {}), ((1, 127, 63), 0, {}), ((1, 129, 65), 0, {}), ((1, 511, 200), 0, {}), ((1, 1000, 1000), 0, {}), ((1, 9000, 1030), 0, {}),
+    ((1, 16384, 1032), 0, {}), ((12, 130, 64), 0, dict(batch_groups=4)), ((7, 70, 96), 0, dict(batch_groups=3, batch_inner=2)), ((5, 513, 70), 0, {}),
+    ((1, 4230, 33), 0, dict(per_channel=True)), ((1, 129, 65), 0, dict(per_channel=True)), ((1, 3, 5), 0, dict(per_channel=True)),
+    ((1, 1031, 1001), 0, dict(per_channel=True)), ((3, 600, 200), 0, dict(per_channel=True, batch_groups=3)), ((1, 6000, 2000), 0, dict(per_channel=True)),
+    ((1, 16384, 520), 0, dict(per_channel=True))]
+
+
+@pytest.mark.parametrize("mode", [qmm.RTNE, qmm.STOCHASTIC])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("pad,shift", [(0, 0), (8, 0), (0, 1)])
+@pytest.mark.parametrize("shape,axis,kw", FORMS)
+def test_equals_the_two_calls(shape, axis, kw, pad, shift, dtype, mode):
+    x = tensor(shape, dtype, seed=sum(shape), pad=pad, shift=shift)
+    if x.numel() > 3000:
+        x[-1, shape[1] // 2, 5] = float("nan") if kw else -0.0
+        x[0, -1, -1] = float("inf") if kw else 3.0e38
+    for fmt, offset in ((qmm.E4M3, 0), (qmm.INT8, 6)):
+        want_c, want_d = two_calls(x, axis, fmt, mode, offset, kw)
+        for patience in (FOREVER, 0):                       # FOREVER is cut to the library's own patience
+            taken, c, d = one_launch(x, axis, fmt, mode, offset, patience, kw)
+            if not taken:
+                continue
+            assert torch.equal(d.view(torch.int32), want_d.view(torch.int32)), (fmt, patience)
+            assert torch.equal(c, want_c), (fmt, patience)
+
+
+def test_the_rule_takes_what_it_is_for():
+    for shape, axis, kw in FORMS:
+        if shape != (1, 1, 1):
+            assert one_launch(tensor(shape, torch.bfloat16, 1), axis, qmm.E5M2, qmm.RTNE, 0, FOREVER, kw)[0] == 1, (shape, axis, kw)
+    for shape, axis, kw in [((1, 1, 8), 1, {}),                                      # rows shorter than a unit
+                            ((1, 40000, 2048), 1, {}), ((1, 40000, 2048), 0, {}),     # more than the chip holds
+                            ((4, 8, 64), 1, dict(batch_groups=8)),                   # groups without a matrix
+                            ((4, 64, 64), 0, dict(per_channel=True, batch_groups=2)), ((1, 64, 64), 1, dict(per_channel=True))]:
+        assert one_launch(tensor(shape, torch.bfloat16, 1), axis, qmm.E5M2, qmm.RTNE, 0, FOREVER, kw)[0] == 0, (shape, axis, kw)
+
+
+def test_recorded_calls_replay_like_eager_ones():
+    x = torch.empty((1, 1000, 2064), dtype=torch.bfloat16, device=DEV)
+    x.copy_(W.student_t(x.shape, 4, seed=1))
+    forms = [(1, {}), (0, {}), (0, dict(per_channel=True))]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        for axis, kw in forms:
+            qmm.scale_quantize(x, axis, qmm.E4M3, **kw)
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = [qmm.scale_quantize(x, axis, qmm.E4M3, **kw) for axis, kw in forms]
+    for seed in (2, 3, 4):
+        x.copy_(W.student_t(x.shape, 4, seed=seed) * seed)
+        want = [qmm.scale_quantize(x, axis, qmm.E4M3, **kw) for axis, kw in forms]
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for (c, d), (cw, dw) in zip(out, want):
+            assert torch.equal(c, cw) and torch.equal(d, dw), seed
+
+
+def test_streams_that_share_the_ring_of_boards():
+    xs = [tensor((1, 512 + 64 * i, 1024), torch.bfloat16, seed=i) * (i + 1) for i in range(6)]
+    want = [two_calls(x, 1, qmm.E4M3, qmm.RTNE, 0, {}) for x in xs]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    got = []
+    for rep in range(12):                                   # 72 calls on 16 boards
+        for i, x in enumerate(xs):
+            with torch.cuda.stream(streams[i % 3]):
+                got.append((i, qmm.scale_quantize(x, 1, qmm.E4M3)))
+    torch.cuda.synchronize()
+    for i, (c, d) in got:
+        assert torch.equal(c, want[i][0]) and torch.equal(d, want[i][1]), i

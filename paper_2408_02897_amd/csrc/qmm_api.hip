@@ -30,40 +30,43 @@ qmm_status arrival_slots(int count, uint32_t** first)
     return QMM_OK;
 }
 
-// ---- boards (qmm_device.h).  Tags run from 1 to kTags and start over; before a board is used for the first time in such a
-// round, its words -- which could hold that tag from the round before -- are cleared.
+// ---- boards (qmm_device.h).  Tags run from 1 to 2^32 - 1 and start over; the call that starts over clears the rings, which
+// might hold, in a place that no call has used since, a word with a tag of the round before.
 namespace {
-constexpr uint64_t kTags = (uint64_t(1) << 32) - kBoards;       // a multiple of the number of boards
-static_assert(kTags % kBoards == 0, "a tag's board is the same in every round");
+constexpr uint64_t kTags = 0xFFFFFFFFull;
 std::atomic<uint64_t*> board_addr[kMaxDevices];
-std::atomic<uint64_t> next_tag{0};
+std::atomic<uint64_t> next_tag{0}, next_word[kRings];
 std::atomic<int> cus[kMaxDevices];
-__global__ void board_clear(uint64_t* words)
+__global__ void ring_clear(uint64_t* words)
 {
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < kBoardWords; i += gridDim.x * 256) words[i] = 0;
+    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < kRings * kRingWords; i += gridDim.x * 256) words[i] = 0;
 }
 }  // namespace
 }  // namespace qmm
-static __device__ __align__(256) uint64_t boards[qmm::kBoards * qmm::kBoardWords];
+static __device__ __align__(256) uint64_t board_ring[qmm::kRings * qmm::kRingWords];
 namespace qmm {
-bool take_board(hipStream_t s, Board* b)
+bool take_board(hipStream_t s, Ring ring, uint32_t words, Board* b)
 {
     hipStreamCaptureStatus st = hipStreamCaptureStatusActive;
     if (hipStreamIsCapturing(s, &st) != hipSuccess) { (void)hipGetLastError(); return false; }
     int dev = -1;
-    if (st != hipStreamCaptureStatusNone || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
+    if (st != hipStreamCaptureStatusNone || words > kBoardMax || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
     uint64_t* p = board_addr[dev].load(std::memory_order_acquire);
     if (!p) {
         void* q = nullptr;
-        if (hipGetSymbolAddress(&q, HIP_SYMBOL(boards)) != hipSuccess || !q) { (void)hipGetLastError(); return false; }
+        if (hipGetSymbolAddress(&q, HIP_SYMBOL(board_ring)) != hipSuccess || !q) { (void)hipGetLastError(); return false; }
         p = static_cast<uint64_t*>(q);
         board_addr[dev].store(p, std::memory_order_release);
     }
+    const uint64_t size = (words + 15u) & ~15u;                       // whole cache lines
+    uint64_t at = next_word[ring].fetch_add(size, std::memory_order_relaxed) % kRingWords;
+    if (at + size > kRingWords) at = next_word[ring].fetch_add(2 * size, std::memory_order_relaxed) % kRingWords;   // past the end: from its start on
+    if (at + size > kRingWords) at = 0;                               // (another thread got there first: shared, see above)
     const uint64_t n = next_tag.fetch_add(1, std::memory_order_relaxed);
-    b->words = p + (size_t)(n % kBoards) * kBoardWords;
+    b->words = p + (size_t)ring * kRingWords + at;
     b->tag = (uint32_t)(n % kTags) + 1u;
     b->patience = kPatience;
-    if (n >= kTags && n % kTags < kBoards) board_clear<<<64, 256, 0, s>>>(b->words);
+    if (n >= kTags && n % kTags == 0) ring_clear<<<256, 256, 0, s>>>(p);
     return true;
 }
 int cu_count()

@@ -336,16 +336,19 @@ QMM_DEV bool arrive_last(uint32_t* slot, unsigned id, unsigned total)
 // the call's tag holds that call's value, any other word has not been posted yet.  Nothing is cleared or counted, there are no
 // atomics, and no ordering between words is needed.  Tags are handed out by the host, one per launch (take_board), so a
 // call that is being recorded into a graph, whose replays would repeat the tag, does not use a board.
-// Boards are a ring in the library's device image.  A reader's wait is bounded (`patience`, in ticks of the 100 MHz clock):
-// a value that has not come by then -- its workgroup may not be resident, other work holding the CUs, or another call of the
-// ring's length before may share the board -- the reader's workgroup forms itself and posts, the same value.  So every
-// workgroup ends whatever the others do, and what the words hold decides about time, never about results.
+// Boards are cut from rings in the library's device image, each call as many words as it needs (calls whose readers wait long,
+// the error sums, have a ring of their own: what they share words with is a call of their own kind a thousand calls before).  A reader's wait is bounded
+// (`patience`, in ticks of the 100 MHz clock): a value that has not come by then -- its workgroup may not be resident, other
+// work holding the CUs, or a call a whole ring before may still be running on the same words -- the reader's workgroup forms
+// itself and posts, the same value.  So every workgroup ends whatever the others do, and what the words hold decides about
+// time, never about results.
 // ---------------------------------------------------------------------------
-constexpr int kBoards = 16, kBoardWords = 65536;
-constexpr uint32_t kPatience = 5000;                     // 50 us
+enum Ring { RING_SHORT = 0, RING_LONG = 1, kRings = 2 };
+constexpr uint32_t kRingWords = 1u << 20, kBoardMax = 1u << 17;      // 8 MB a ring
+constexpr uint32_t kPatience = 5000;                                 // 50 us
 struct Board { uint64_t* words; uint32_t tag, patience; };
-bool take_board(hipStream_t s, Board* b);                // host (qmm_api.hip); false: the call is to do without one
-int cu_count();                                          // host: CUs of the current device, 0 if unknown
+bool take_board(hipStream_t s, Ring ring, uint32_t words, Board* b); // host (qmm_api.hip), words <= kBoardMax; false: do without one
+int cu_count();                                                      // host: CUs of the current device, 0 if unknown
 
 QMM_DEV void board_post(const Board& b, uint32_t i, uint32_t v)
 {

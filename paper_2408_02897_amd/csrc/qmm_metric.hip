@@ -2,10 +2,11 @@
 // sums behind the noise-to-signal ratio, the relative error of Eq. 2 and the
 // element-wise backward error of Eq. 3.  HBM-bound: 8 B per element for a
 // binary32 y (6 B for bfloat16 y, +4 B with denominators).  Every thread keeps
-// private sums, wavefronts fold them by rotations and swaps of lanes, workgroups through LDS, and a
-// small second kernel (one workgroup per field) folds the per-workgroup partials in a fixed order:
-// no atomics, so the result is reproducible run to run.
+// private sums, wavefronts fold them by rotations and swaps of lanes, workgroups through LDS, and the
+// first sixteen workgroups, one per field, fold the per-workgroup partials when all are there (calls being
+// recorded: a small second kernel does), in a fixed order: no atomics, the result is reproducible run to run.
 #include <algorithm>
+#include <type_traits>
 #include "qmm_device.h"
 
 namespace qmm {
@@ -108,8 +109,8 @@ struct Acc {
     }
 };
 
-// Workgroup partials are stored field-major: partial[field * nblocks + block].
-QMM_DEV void store_partial(const Acc& a, double* partial, int nblocks)
+// Workgroup partials are stored field-major: partial[field * nblocks + block].  ONE: for another workgroup of this launch.
+template <bool ONE> QMM_DEV void store_partial(const Acc& a, double* partial, int nblocks, int block)
 {
     __shared__ double s[kThreads / kWave][16];
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
@@ -130,7 +131,8 @@ QMM_DEV void store_partial(const Acc& a, double* partial, int nblocks)
         const bool is_max = (i == 4 || i == 5 || i == 7 || i == 10);
         double r = s[0][i];
         for (int k = 1; k < kThreads / kWave; ++k) r = is_max ? fmax(r, s[k][i]) : r + s[k][i];
-        partial[(int64_t)i * nblocks + blockIdx.x] = r;
+        double* at = partial + (int64_t)i * nblocks + block;
+        if constexpr (ONE) publish_f64(at, r); else *at = r;
     }
 }
 
@@ -145,20 +147,20 @@ template <bool Y_BF16> QMM_DEV f32x4 load_y4(const void* yv, int64_t i)
     }
 }
 
-template <bool Y_BF16, bool HAS_D> __global__ void __launch_bounds__(kThreads)
-metric_partial(const void* __restrict__ yv, const float* __restrict__ r, const float* __restrict__ d, int64_t n,
-               double* __restrict__ partial)
+// The sums of block `block` of `nblocks`.
+template <bool Y_BF16, bool HAS_D> QMM_DEV Acc block_sums(const void* __restrict__ yv, const float* __restrict__ r, const float* __restrict__ d, int64_t n,
+                                                           int block, int nblocks)
 {
     Acc acc;
     const int64_t nvec = n >> 2;
-    const int64_t tid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const int64_t tid = (int64_t)block * kThreads + threadIdx.x;
     const f32x4* r4 = reinterpret_cast<const f32x4*>(r);
     const f32x4* d4 = reinterpret_cast<const f32x4*>(d);
     // A workgroup takes two consecutive pieces of 256 vectors per trip and the grid sweeps the arrays front to
     // back, so the loads in flight are neighbours in memory (loads a whole grid stride apart read large arrays
     // up to 25 % slower).  Both loads are in flight before the arithmetic of either starts.
-    const int64_t stride = (int64_t)gridDim.x * kThreads * 2;
-    int64_t i = (int64_t)blockIdx.x * kThreads * 2 + threadIdx.x;
+    const int64_t stride = (int64_t)nblocks * kThreads * 2;
+    int64_t i = (int64_t)block * kThreads * 2 + threadIdx.x;
     // (y and the reference are read once: streaming loads, which leave the caches to the tensors that are read again --
     // the benchmark's step is 3 % shorter for it, the pass itself 4 %)
     // The vector unit is busy for 80 % of the pass's cycles (at the 1.7 GHz the binary64 work leaves): small tensors are bound
@@ -253,38 +255,97 @@ metric_partial(const void* __restrict__ yv, const float* __restrict__ r, const f
         else y = static_cast<const float*>(yv)[t];
         acc.add<HAS_D>(y, r[t], HAS_D ? d[t] : 0.f);
     }
-    store_partial(acc, partial, (int)gridDim.x);
+    return acc;
 }
 
-// Sixteen workgroups, one per field: thread t takes blocks t, t+256, ... in ascending order, the 64 lane values
-// are folded by the fixed butterfly and the four wavefront values in wavefront order: the order of additions
-// depends on nblocks only, so results are reproducible run to run.
-constexpr int kFinalThreads = 256;
-__global__ void __launch_bounds__(kFinalThreads)
-metric_finalize(const double* __restrict__ partial, int nblocks, double* __restrict__ out)
+// The fold of a field's partials, in an order that depends on nblocks only: thread t takes blocks t, t + 256, ... in ascending order,
+// the 64 lane values are folded by the fixed butterfly and the four wavefront values in wavefront order.  Thread 0's value.
+template <bool COHERENT> QMM_DEV double fold_field(const double* partial, int nblocks, int field)
 {
-    __shared__ double s[kFinalThreads / kWave];
-    const int field = blockIdx.x, lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    __shared__ double s[kThreads / kWave];
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     const bool is_max = (field == 4 || field == 5 || field == 7 || field == 10);
     const double* p = partial + (int64_t)field * nblocks;
     // all of a thread's partials are requested before any is used
-    double v[kMaxBlocks / kFinalThreads];
+    double v[kMaxBlocks / kThreads];
 #pragma unroll
-    for (int k = 0; k < kMaxBlocks / kFinalThreads; ++k) {
-        const int b = threadIdx.x + k * kFinalThreads;
-        v[k] = b < nblocks ? p[b] : 0.0;
+    for (int k = 0; k < kMaxBlocks / kThreads; ++k) {
+        const int b = threadIdx.x + k * kThreads;
+        v[k] = 0.0;
+        if (b < nblocks) v[k] = COHERENT ? coherent_load(p + b) : p[b];
     }
     double r = 0.0;
 #pragma unroll
-    for (int k = 0; k < kMaxBlocks / kFinalThreads; ++k) r = is_max ? fmax(r, v[k]) : r + v[k];
+    for (int k = 0; k < kMaxBlocks / kThreads; ++k) r = is_max ? fmax(r, v[k]) : r + v[k];
     r = is_max ? wave_max_f64(r) : wave_sum_f64(r);
     if (lane == 0) s[w] = r;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = s[0];
-        for (int k = 1; k < kFinalThreads / kWave; ++k) t = is_max ? fmax(t, s[k]) : t + s[k];
-        out[field] = t;
+    double t = s[0];
+    if (threadIdx.x == 0)
+        for (int k = 1; k < kThreads / kWave; ++k) t = is_max ? fmax(t, s[k]) : t + s[k];
+    __syncthreads();
+    return t;
+}
+
+// ONE: the fold within the launch.  A workgroup stores its partials past the caches, waits until they have left and posts a word;
+// the first sixteen wait for all words and fold a field each (of fewer workgroups, several).  None of the others waits, so the
+// words come whatever else the GPU does; should one not (a board shared by calls in flight), the workgroup that misses it forms that
+// block's sums itself.  Against the second launch, which takes 2.3 to 4.7 us behind a pass and the host 2.4 us (kernel time, two
+// launches / one): 196608 bfloat16 6.8 / 6.6 us, 3 million 11.5 / 11.1, 8 million 18.0 / 15.9, 12.6 million 21.7 / 19.3, 67 million 71.8 /
+// 69.8; binary32 16.8 million 28.2 / 25.9, 67 million 86.2 / 83.4.
+// Not kept: four quotients of the sum over one denominator and the maxima looked for in upper words, 14 instructions an element
+// instead of 20 (bfloat16 67 million 67.7 against 69.8, 16.8 million 24.3 against 22.9, binary32 67 million 85.4 against 83.4).
+constexpr int kFields = 16;
+constexpr uint32_t kMetricPatience = 1000000;             // 10 ms: the fold comes behind the last block of a pass
+template <bool Y_BF16, bool HAS_D, bool ONE> __global__ void __launch_bounds__(kThreads)
+metric_partial(const void* __restrict__ yv, const float* __restrict__ r, const float* __restrict__ d, int64_t n,
+               double* __restrict__ partial, double* __restrict__ out, Board bd)
+{
+    const int nblocks = (int)gridDim.x;
+    if constexpr (!ONE) {
+        store_partial<false>(block_sums<Y_BF16, HAS_D>(yv, r, d, n, (int)blockIdx.x, nblocks), partial, nblocks, (int)blockIdx.x);
+    } else {
+        __shared__ int s_missing;
+        uint64_t start = 0;
+        for (int block = (int)blockIdx.x, from = 0; block < nblocks; from = block + 1) {
+            store_partial<true>(block_sums<Y_BF16, HAS_D>(yv, r, d, n, block, nblocks), partial, nblocks, block);
+            if (threadIdx.x == 0) board_post(bd, block, 1u);
+            if (blockIdx.x >= kFields) return;
+            if (start == 0) { start = ticks(); from = 0; }
+            // the first block from `from` on whose word does not come
+            if (threadIdx.x == 0) s_missing = nblocks;
+            __syncthreads();
+            for (int b = from + (int)threadIdx.x; b < nblocks; b += kThreads) {
+                uint32_t v;
+                if (!board_wait(bd, b, start, v)) { atomicMin(&s_missing, b); break; }
+            }
+            __syncthreads();
+            block = s_missing;
+            __syncthreads();
+            if (block >= nblocks) break;
+        }
+        if (nblocks > kFields) {
+            const double t = fold_field<true>(partial, nblocks, (int)blockIdx.x);
+            if (threadIdx.x == 0) out[blockIdx.x] = t;
+        } else {
+            // few blocks: a wavefront a field, in fold_field's order (its other wavefronts would add zeros)
+            const int lane = threadIdx.x & (kWave - 1), step = nblocks * (kThreads / kWave);
+            for (int field = (int)blockIdx.x * (kThreads / kWave) + (int)threadIdx.x / kWave; field < kFields; field += step) {
+                const bool is_max = (field == 4 || field == 5 || field == 7 || field == 10);
+                const double v = lane < nblocks ? coherent_load(partial + field * nblocks + lane) : 0.0;
+                const double t = is_max ? wave_max_f64(v) : wave_sum_f64(v);
+                if (lane == 0) out[field] = t;
+            }
+        }
     }
+}
+
+// The fold as a launch of its own, sixteen workgroups, for calls that are being recorded.
+__global__ void __launch_bounds__(kThreads)
+metric_finalize(const double* __restrict__ partial, int nblocks, double* __restrict__ out)
+{
+    const double t = fold_field<false>(partial, nblocks, (int)blockIdx.x);
+    if (threadIdx.x == 0) out[blockIdx.x] = t;
 }
 
 int plan_blocks(int64_t n)
@@ -308,8 +369,9 @@ extern "C" size_t qmm_metric_workspace_size(int64_t n)
     return (size_t)plan_blocks(n < 0 ? 0 : n) * 16 * sizeof(double);
 }
 
-extern "C" qmm_status qmm_metric(const void* y, qmm_dtype y_dtype, const float* y_ref, const float* denom, int64_t n,
-                                 double* out16, void* workspace, size_t workspace_bytes, void* stream)
+namespace {
+qmm_status metric_call(const void* y, qmm_dtype y_dtype, const float* y_ref, const float* denom, int64_t n, double* out16,
+                       void* workspace, size_t workspace_bytes, uint32_t patience, void* stream)
 {
     if (!out16) return QMM_ERR_NULL;
     if (y_dtype != QMM_DT_BF16 && y_dtype != QMM_DT_F32) return QMM_ERR_ENUM;
@@ -323,13 +385,35 @@ extern "C" qmm_status qmm_metric(const void* y, qmm_dtype y_dtype, const float* 
 
     hipStream_t s = as_stream(stream);
     double* partial = static_cast<double*>(workspace);
-    const bool bf = y_dtype == QMM_DT_BF16, hd = denom != nullptr;
     const int nb = plan_blocks(n);
-    if (bf && hd) metric_partial<true, true><<<nb, kThreads, 0, s>>>(y, y_ref, denom, n, partial);
-    else if (bf) metric_partial<true, false><<<nb, kThreads, 0, s>>>(y, y_ref, denom, n, partial);
-    else if (hd) metric_partial<false, true><<<nb, kThreads, 0, s>>>(y, y_ref, denom, n, partial);
-    else metric_partial<false, false><<<nb, kThreads, 0, s>>>(y, y_ref, denom, n, partial);
+    Board bd{};
+    // (with denominators the fold's registers would leave a CU three workgroups instead of four)
+    const bool one = !(denom && nb == kMaxBlocks) && take_board(s, RING_LONG, (uint32_t)nb, &bd);
+    bd.patience = patience;
+    auto run = [&](auto bf16, auto denominators) {
+        constexpr bool Y = decltype(bf16)::value, D = decltype(denominators)::value;
+        if (one) metric_partial<Y, D, true><<<nb, kThreads, 0, s>>>(y, y_ref, denom, n, partial, out16, bd);
+        else metric_partial<Y, D, false><<<nb, kThreads, 0, s>>>(y, y_ref, denom, n, partial, nullptr, bd);
+    };
+    using T = std::true_type; using F = std::false_type;
+    if (y_dtype == QMM_DT_BF16) { if (denom) run(T{}, T{}); else run(T{}, F{}); }
+    else { if (denom) run(F{}, T{}); else run(F{}, F{}); }
+    if (one) return launch_status();
     if (hipGetLastError() != hipSuccess) return QMM_ERR_LAUNCH;
-    metric_finalize<<<16, kFinalThreads, 0, s>>>(partial, nb, out16);
+    metric_finalize<<<kFields, kThreads, 0, s>>>(partial, nb, out16);
     return launch_status();
+}
+}  // namespace
+
+extern "C" qmm_status qmm_metric(const void* y, qmm_dtype y_dtype, const float* y_ref, const float* denom, int64_t n,
+                                 double* out16, void* workspace, size_t workspace_bytes, void* stream)
+{
+    return metric_call(y, y_dtype, y_ref, denom, n, out16, workspace, workspace_bytes, kMetricPatience, stream);
+}
+
+// For the tests, not part of the ABI: the folding workgroups wait `patience` ticks for the others (0: they form what is not there yet).
+extern "C" qmm_status qmm_internal_metric(const void* y, qmm_dtype y_dtype, const float* y_ref, const float* denom, int64_t n,
+                                          double* out16, void* workspace, size_t workspace_bytes, uint32_t patience, void* stream)
+{
+    return metric_call(y, y_dtype, y_ref, denom, n, out16, workspace, workspace_bytes, patience < kMetricPatience ? patience : kMetricPatience, stream);
 }

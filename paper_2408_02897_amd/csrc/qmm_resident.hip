@@ -181,7 +181,7 @@ int64_t board_words(const QArgs& q, int64_t P)
     return (runs + q.groups - 1) / q.groups * inner * q.groups * P + (q.groups * kLeaders + 1) * kLeaderWords;
 }
 
-struct RowsPlan { int variant; uint32_t upr, units, P; unsigned blocks; };
+struct RowsPlan { int variant; uint32_t upr, units, P; unsigned blocks; uint32_t words; };
 struct RowsVariant { int threads, bytes, per_cu; };      // bytes of the tensor a thread holds
 // (the first that the tensor fits: many small workgroups for small tensors, which are bound by the length of a thread's own work)
 constexpr RowsVariant kRows[] = {{256, 32, 2}, {256, 64, 4}, {1024, 64, 2}, {1024, 128, 1}, {1024, 256, 1}};
@@ -199,8 +199,9 @@ template <typename T, int MODE> bool plan_rows(const QArgs& q, RowsPlan* pl)
         const RowsVariant& r = kRows[i];
         const int64_t slice = r.threads * (r.bytes / (int64_t)(kUnit * sizeof(T)));
         const int64_t P = (units + slice - 1) / slice, blocks = P * q.batch;
-        if (blocks > (int64_t)r.per_cu * cus || board_words(q, P) > kBoardWords) continue;
-        *pl = RowsPlan{i, (uint32_t)upr, (uint32_t)units, (uint32_t)P, (unsigned)blocks};
+        const int64_t words = board_words(q, P);
+        if (blocks > (int64_t)r.per_cu * cus || words > kBoardMax) continue;
+        *pl = RowsPlan{i, (uint32_t)upr, (uint32_t)units, (uint32_t)P, (unsigned)blocks, (uint32_t)words};
         return true;
     }
     return false;
@@ -412,7 +413,7 @@ resident_cols(QArgs a, Board bd, uint32_t strips, uint32_t tiles_k, uint32_t P)
     }
 }
 
-struct ColsPlan { int variant; uint32_t strips, tiles_k, P; unsigned blocks; };
+struct ColsPlan { int variant; uint32_t strips, tiles_k, P; unsigned blocks; uint32_t words; };
 struct ColsVariant { int threads, tiles, per_cu; };
 constexpr ColsVariant kCols[] = {{256, 1, 4}, {1024, 1, 2}, {1024, 3, 1}};
 
@@ -429,8 +430,8 @@ template <typename T, int MODE> bool plan_cols(const QArgs& q, ColsPlan* pl)
         const int64_t tiles_k = (q.rows + c.threads / 2 - 1) / (c.threads / 2);
         const int64_t P = q.channels > 1 ? strips * ((tiles_k + c.tiles - 1) / c.tiles) : (strips * tiles_k + c.tiles - 1) / c.tiles;
         const int64_t blocks = P * q.batch, words = q.channels > 1 ? P / strips * q.cols * q.batch : board_words(q, P);
-        if (blocks > (int64_t)per_cu * cus || words > kBoardWords || (MODE != QMM_ROUND_RTNE && blocks < 64) || tiles_k > 0x7FFFFFFF) continue;
-        *pl = ColsPlan{i, (uint32_t)strips, (uint32_t)tiles_k, (uint32_t)P, (unsigned)blocks};
+        if (blocks > (int64_t)per_cu * cus || words > kBoardMax || (MODE != QMM_ROUND_RTNE && blocks < 64) || tiles_k > 0x7FFFFFFF) continue;
+        *pl = ColsPlan{i, (uint32_t)strips, (uint32_t)tiles_k, (uint32_t)P, (unsigned)blocks, (uint32_t)words};
         return true;
     }
     return false;
@@ -454,13 +455,13 @@ template <typename T, int FMT, int MODE> qmm_status run(const qmm_tensor* x, con
         if (q.row_stride == q.cols || q.rows == 1) { q.cols *= q.rows; q.row_stride = q.cols; q.rows = 1; }     // dense: one long row
         if (q.rows == 1 && q.groups == 1 && q.batch > 1 && q.batch_stride == q.cols) { q.cols *= q.batch; q.batch = 1; q.batch_stride = q.cols; q.inner = 1; }
         RowsPlan pl;
-        if (!plan_rows<T, MODE>(q, &pl) || !take_board(s, &bd)) return QMM_OK;
+        if (!plan_rows<T, MODE>(q, &pl) || !take_board(s, RING_SHORT, pl.words, &bd)) return QMM_OK;
         bd.patience = min(bd.patience, patience);
         *taken = true;
         return launch_rows<T, FMT, MODE>(q, pl, bd, s);
     }
     ColsPlan pl;
-    if (!plan_cols<T, MODE>(a, &pl) || !take_board(s, &bd)) return QMM_OK;
+    if (!plan_cols<T, MODE>(a, &pl) || !take_board(s, RING_SHORT, pl.words, &bd)) return QMM_OK;
     bd.patience = min(bd.patience, patience);
     *taken = true;
     return a.channels > 1 ? launch_cols<T, FMT, MODE, true>(a, pl, bd, s) : launch_cols<T, FMT, MODE, false>(a, pl, bd, s);

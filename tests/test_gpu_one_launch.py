@@ -1,4 +1,5 @@
-"""qmm_scale_quantize where it takes one launch (csrc/qmm_resident.hip: slices in registers, their maxima on a board): the
+"""Calls that take one launch by exchanging values while they run, against their forms of several launches.
+qmm_scale_quantize (csrc/qmm_resident.hip: slices in registers, their maxima on a board): the
 step sizes and codes of qmm_scale and qmm_quantize, bit for bit, over the forms the rule accepts -- dense and strided rows,
 both axes, groups and runs of matrices, one step size per column, both types and rounding modes, sizes around each slice
 variant --, whether the workgroups find one another's maxima or form them themselves, under capture, and with several
@@ -121,10 +122,57 @@ def test_streams_that_share_the_ring_of_boards():
     torch.cuda.synchronize()
     streams = [torch.cuda.Stream() for _ in range(3)]
     got = []
-    for rep in range(12):                                   # 72 calls on 16 boards
+    for rep in range(12):
         for i, x in enumerate(xs):
             with torch.cuda.stream(streams[i % 3]):
                 got.append((i, qmm.scale_quantize(x, 1, qmm.E4M3)))
     torch.cuda.synchronize()
     for i, (c, d) in got:
         assert torch.equal(c, want[i][0]) and torch.equal(d, want[i][1]), i
+
+
+def test_calls_beyond_the_length_of_the_ring():
+    x = tensor((1, 16384, 520), torch.bfloat16, seed=9)     # 32 maxima a column: 126 calls to the ring's end
+    want = two_calls(x, 0, qmm.E4M3, qmm.RTNE, 0, dict(per_channel=True))
+    for i in range(300):
+        c, d = qmm.scale_quantize(x, 0, qmm.E4M3, per_channel=True)
+        if i % 20 == 0:
+            assert torch.equal(c, want[0]) and torch.equal(d, want[1]), i
+
+
+# One block (2048 elements a block), fewer blocks than fields, about as many, the lanes of a wavefront, a workgroup's threads, the
+# largest grid (from 2^21 elements on; with denominators always two launches there).
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("n", [1, 2048, 2049, 5000, 15 * 2048, 16 * 2048 + 3, 17 * 2048, 64 * 2048, 65 * 2048 + 1, 257 * 2048, 1 << 21, 3000001])
+def test_metric_in_one_launch_equals_two(n, dtype):
+    L = qmm.lib()
+    f = L.qmm_internal_metric
+    f.restype = ctypes.c_int
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p,
+                  ctypes.c_size_t, ctypes.c_uint32, ctypes.c_void_p]
+    g = torch.Generator(device=DEV).manual_seed(n)
+    ref = torch.randn(n, generator=g, device=DEV)
+    y = (ref + 0.05 * torch.randn(n, generator=g, device=DEV)).to(dtype)
+    if n > 4000:
+        y[n // 2] = float("nan"); ref[n // 3] = 0.0; y[-1] = float("inf")
+    denom = torch.rand(n, generator=g, device=DEV) + 0.1
+    ws = torch.empty(L.qmm_metric_workspace_size(n), dtype=torch.uint8, device=DEV)
+    for d in (None, denom):
+        out = torch.empty(16, dtype=torch.float64, device=DEV)
+        qmm.metric(y, ref, d, out=out, workspace=ws)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        two = torch.empty_like(out)
+        with torch.cuda.graph(graph):
+            qmm.metric(y, ref, d, out=two, workspace=ws)
+        for patience in (FOREVER, 0):
+            ws.fill_(0xFF)                                   # NaN in every partial sum
+            one = torch.full_like(out, -1.0)
+            assert f(y.data_ptr(), qmm._dtype_code(y), ref.data_ptr(), d.data_ptr() if d is not None else None, n, one.data_ptr(),
+                     ws.data_ptr(), ws.numel(), patience, qmm._stream()) == 0
+            torch.cuda.synchronize()
+            two.fill_(-2.0)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(one.view(torch.int64), two.view(torch.int64)), (d is not None, patience)
+            assert torch.equal(one.view(torch.int64), out.view(torch.int64))

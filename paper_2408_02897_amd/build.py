@@ -1,4 +1,4 @@
-"""Build libqmm.so (HIP, gfx950 only) in-tree with hipcc.
+"""Build libqmm.so (HIP, gfx950 only) in-tree with hipcc, and the binding's native short path _qmm_host.so with g++.
 
     python -m paper_2408_02897_amd.build [--force]
     python -m paper_2408_02897_amd.build --check-asm     # scan the GEMM kernels' assembly (a few minutes)
@@ -14,6 +14,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libqmm.so")
+HOST = os.path.join(HERE, "_qmm_host.so")
 GEMM_PARTS = 6                      # qmm_gemm.hip is compiled once per operand-format pair, side by side
 SOURCES = ["qmm_api.hip", "qmm_scale.hip", "qmm_quantize.hip", "qmm_resident.hip", "qmm_metric.hip", "qmm_diag.hip", "qmm_moments.hip", "qmm_dequantize.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -39,7 +40,26 @@ def build(force=False):
         objs = list(ex.map(lambda j: _compile(j[0], force, j[1]), jobs))
     if force or not os.path.exists(LIB) or any(os.path.getmtime(o) > os.path.getmtime(LIB) for o in objs):
         subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], check=True)
+    build_host(force)
     return LIB
+
+
+def build_host(force=False):
+    """_qmm_host.so: host code only, against torch's headers and libraries and libqmm.so (found beside it)."""
+    import sysconfig
+    import torch
+    src = os.path.join(CSRC, "qmm_host.cpp")
+    if not force and os.path.exists(HOST) and all(os.path.getmtime(HOST) >= os.path.getmtime(d) for d in (src, os.path.join(ROOT, "include", "qmm.h"))):
+        return HOST
+    t = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    # (the HIP headers ask for their platform by this macro where hipcc is not the compiler)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                    "-I", os.path.join(ROOT, "include"),
+                    *(a for d in (os.path.join(t, "include"), os.path.join(rocm, "include"), sysconfig.get_paths()["include"]) for a in ("-isystem", d)),
+                    src, "-o", HOST, "-L", HERE, "-lqmm", "-L", os.path.join(t, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
+                    "-Wl,-rpath,$ORIGIN"], check=True)
+    return HOST
 
 
 def check_asm():

@@ -57,23 +57,36 @@ CANDIDATES = ((qmm.E4M3, False), (qmm.INT8, False), (qmm.E5M2, False),
               (qmm.E4M3, True), (qmm.INT8, True), (qmm.E5M2, True))
 
 
-def op_error(x, w, fmt_x, fmt_w, per_channel, ref=None):
-    """Quantized product X W^T of one op (x: [M, K], w: [N, K], device bfloat16) against the high-precision product:
-    dict with the noise-to-signal ratio and the mean / max relative error of Eq. 2.  Library calls only."""
-    (cx, ox), _ = qmm.quantized_operand(x, 1, fmt_x, per_channel=per_channel)
-    (cw, ow), _ = qmm.quantized_operand(w, 1, fmt_w, per_channel=per_channel)
-    y = qmm.gemm((cx, ox), (cw, ow), torch.float32)
-    if ref is None:
-        ref = qmm.reference_gemm(x.unsqueeze(0), w.unsqueeze(0))
-    f = dict(zip(qmm.METRIC_FIELDS, qmm.metric(y, ref).cpu().tolist()))
+def _op_metric(x, w, fmt_x, fmt_w, per_channel, ref, out=None):
+    """The error sums of one op's quantized product against `ref`, on the device."""
+    a, _ = qmm.quantized_operand(x, 1, fmt_x, per_channel=per_channel)
+    b, _ = qmm.quantized_operand(w, 1, fmt_w, per_channel=per_channel)
+    return qmm.metric(qmm.gemm(a, b, torch.float32), ref, out=out)
+
+
+def _error_row(values):
+    f = dict(zip(qmm.METRIC_FIELDS, values))
     return {"nsr": f["S_ee"] / f["S_rr"] if f["S_rr"] > 0 else float("inf"),
             "re_mean": f["RE_sum"] / max(f["RE_cnt"], 1.0), "re_max": f["RE_max"], "fields": f}
 
 
+def op_error(x, w, fmt_x, fmt_w, per_channel, ref=None):
+    """Quantized product X W^T of one op (x: [M, K], w: [N, K], device bfloat16) against the high-precision product:
+    dict with the noise-to-signal ratio and the mean / max relative error of Eq. 2.  Library calls only."""
+    if ref is None:
+        ref = qmm.reference_gemm(x.unsqueeze(0), w.unsqueeze(0))
+    return _error_row(_op_metric(x, w, fmt_x, fmt_w, per_channel, ref).cpu().tolist())
+
+
 def format_sweep(x, w, candidates=CANDIDATES):
-    """Error of every candidate (format, per_channel) on one op; the same format on both operands."""
+    """Error of every candidate (format, per_channel) on one op; the same format on both operands.  All candidates are
+    enqueued before their results are fetched, in one copy: the GPU does not wait for the host between them."""
+    candidates = list(candidates)
     ref = qmm.reference_gemm(x.unsqueeze(0), w.unsqueeze(0))
-    return [dict(format=fmt, per_channel=pc, **op_error(x, w, fmt, fmt, pc, ref)) for fmt, pc in candidates]
+    sums = torch.empty((len(candidates), len(qmm.METRIC_FIELDS)), dtype=torch.float64, device=x.device)
+    for (fmt, pc), out in zip(candidates, sums):
+        _op_metric(x, w, fmt, fmt, pc, ref, out=out)
+    return [dict(format=fmt, per_channel=pc, **_error_row(values)) for (fmt, pc), values in zip(candidates, sums.cpu().tolist())]
 
 
 def choose_format(x, w, nsr_max, candidates=CANDIDATES):

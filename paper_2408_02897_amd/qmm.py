@@ -1,13 +1,16 @@
-"""Thin ctypes binding of libqmm.so (include/qmm.h).  Argument marshalling only: every step of the
-path runs in the HIP kernels.  torch is used for device memory and the current stream.  There is no
-CPU fallback: a missing or unloadable library raises."""
+"""Thin binding of libqmm.so (include/qmm.h).  Argument marshalling only: every step of the path runs in the HIP kernels.
+torch is used for device memory and the current stream.  All calls go through ctypes; quantized_operand, scale_quantize, gemm
+and metric first try the native short path for plain tensors (csrc/qmm_host.cpp), which does the same with a fifth of the
+host time.  There is no CPU fallback: a missing or unloadable library raises."""
 import ctypes
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libqmm.so")
+HOST_PATH = os.path.join(_HERE, "_qmm_host.so")
 
 INT8, E4M3, E5M2, BF16 = 0, 1, 2, 3
 DT_BF16, DT_F32 = 0, 1
@@ -40,6 +43,22 @@ class Operand(ctypes.Structure):
 
 
 _lib = None
+_short = None
+
+
+def _host():
+    """Load the native short path (_qmm_host.so, built with libqmm.so).  Raises if it is absent."""
+    global _short
+    if _short is None:
+        lib()
+        if not os.path.exists(HOST_PATH):
+            raise RuntimeError(f"{HOST_PATH} is missing: run `python -m paper_2408_02897_amd.build` first")
+        spec = importlib.util.spec_from_file_location("_qmm_host", HOST_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        module.setup(Operand)
+        _short = module
+    return _short
 
 
 def lib():
@@ -232,6 +251,12 @@ def operand(data, fmt, delta=None, per_channel=False, batch_groups=1, is_codes=T
 def gemm(a, b, out_dtype=torch.float32, want_acc=False, out=None, acc_out=None, want_y=True):
     """qmm_gemm on two (data, Operand) pairs built by `operand`: a = (tensor [batch,M,K], Operand) etc.
     Returns y (and the raw accumulators when want_acc)."""
+    if want_y and not want_acc and acc_out is None:
+        r = (_short or _host()).gemm(a, b, out_dtype, out)
+        if type(r) is int:
+            _check(r, "qmm_gemm")
+        if r is not None:
+            return r
     L = lib()
     (ta, oa), (tb, ob) = a, b
     sa, sb = ta.shape, tb.shape
@@ -278,6 +303,11 @@ def gemm_nsr(a, b, y_ref, out_dtype=torch.bfloat16, out=None, out2=None, workspa
 
 def scale_quantize(x, contract_axis, fmt, per_channel=False, batch_groups=1, mode=RTNE, seed=0, offset=0, batch_inner=1):
     """qmm_scale_quantize: (uint8 codes [batch, non-contracting, contracting], step sizes) as scale and quantize give them."""
+    r = (_short or _host()).scale_quantize(x, contract_axis, fmt, per_channel, batch_groups, mode, seed, offset, batch_inner)
+    if type(r) is int:
+        _check(r, "qmm_scale_quantize")
+    if r is not None:
+        return r
     L = lib()
     t, g = tensor_desc(x, contract_axis), granularity(per_channel, batch_groups, batch_inner)
     nc, kc = (t.rows, t.cols) if contract_axis == 1 else (t.cols, t.rows)
@@ -293,6 +323,11 @@ def scale_quantize(x, contract_axis, fmt, per_channel=False, batch_groups=1, mod
 
 def quantized_operand(x, contract_axis, fmt, per_channel=False, batch_groups=1, mode=RTNE, seed=0, batch_inner=1):
     """scale + quantize; returns ((codes, Operand), delta)."""
+    r = (_short or _host()).quantized_operand(x, contract_axis, fmt, per_channel, batch_groups, mode, seed, 0, batch_inner)
+    if type(r) is int:
+        _check(r, "qmm_scale_quantize")
+    if r is not None:
+        return r
     c, d = scale_quantize(x, contract_axis, fmt, per_channel, batch_groups, mode, seed, batch_inner=batch_inner)
     return (c, operand(c, fmt, d, per_channel, batch_groups, batch_inner=batch_inner)), d
 
@@ -306,6 +341,11 @@ def reference_gemm(x, w, out=None):
 
 def metric(y, y_ref, denom=None, out=None, workspace=None):
     """qmm_metric: 16 float64 on the device (layout in include/qmm.h)."""
+    r = (_short or _host()).metric(y, y_ref, denom, out, workspace)
+    if type(r) is int:
+        _check(r, "qmm_metric")
+    if r is not None:
+        return r
     L = lib()
     assert y.is_contiguous() and y_ref.is_contiguous() and y_ref.dtype == torch.float32
     n = y.numel()

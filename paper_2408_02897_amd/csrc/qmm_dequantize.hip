@@ -130,8 +130,8 @@ dequantize_lines(DArgs a)
                 } else o[q] = __float_as_uint(y[q]);
             }
             if (left[i] >= V) {
-                if constexpr (OUT_BF16) *reinterpret_cast<u32x4_any*>(static_cast<uint16_t*>(a.out) + at[i]) = o;
-                else *reinterpret_cast<u32x4_any*>(static_cast<float*>(a.out) + at[i]) = o;
+                if constexpr (OUT_BF16) store_through(static_cast<uint16_t*>(a.out) + at[i], o);
+                else store_through(static_cast<float*>(a.out) + at[i], o);
             } else if (left[i] > 0) {
 #pragma unroll
                 for (int e = 0; e < V; ++e)

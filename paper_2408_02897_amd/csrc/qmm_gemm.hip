@@ -143,15 +143,23 @@ template <typename AccT, int NI, int NJ> QMM_DEV void pin_accumulators(AccT (&ac
 
 // T consecutive values of an output row, aligned to their element only (rows of N elements start anywhere when N is
 // odd): one store instruction all the same, global memory takes vector stores at any element boundary.
-template <int T> QMM_DEV void store_f32(float* dst, const float (&v)[T])
+// THROUGH: past the L2 at once (store_through), which pays where a kernel's outputs all leave in its last phase: gemm_kernel, E4M3
+// 4096 x 768 x 768 to binary32 11.1 -> 9.8 us, INT8 12.8 -> 10.7, bfloat16 14.4 -> 13.4; INT8 4096 x 3072 x 768 to bfloat16 18.4 -> 16.6; the
+// partial sums of 768 x 3072 x 4096 16.3 -> 14.9, of 3072 x 1024 x 16384 53.2 -> 52.3; gemm_direct_kernel 36.5 -> 35.4.  Not in gemm_deep_kernel,
+// whose few outputs the L2 takes faster (256 x 768 x 768 6.8 against 7.4 us), and not in the split sums' second kernel.
+template <int T, bool THROUGH = true> QMM_DEV void store_f32(float* dst, const float (&v)[T])
 {
     typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
     typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
+    typedef float f2 __attribute__((ext_vector_type(2)));
     static_assert(T == 2 || T == 4, "accumulator columns of a lane");
-    if constexpr (T == 4) *reinterpret_cast<f4u*>(dst) = f4u{v[0], v[1], v[2], v[3]};
-    else *reinterpret_cast<f2u*>(dst) = f2u{v[0], v[1]};
+    if constexpr (T == 4) {
+        if constexpr (THROUGH) store_through(dst, v4f{v[0], v[1], v[2], v[3]}); else *reinterpret_cast<f4u*>(dst) = f4u{v[0], v[1], v[2], v[3]};
+    } else {
+        if constexpr (THROUGH) store_through(dst, f2{v[0], v[1]}); else *reinterpret_cast<f2u*>(dst) = f2u{v[0], v[1]};
+    }
 }
-template <int T> QMM_DEV void store_bf16(uint16_t* dst, const float (&v)[T])
+template <int T, bool THROUGH = true> QMM_DEV void store_bf16(uint16_t* dst, const float (&v)[T])
 {
     typedef uint32_t u2u __attribute__((ext_vector_type(2), aligned(2)));
     typedef uint32_t u1u __attribute__((ext_vector_type(1), aligned(2)));
@@ -161,8 +169,11 @@ template <int T> QMM_DEV void store_bf16(uint16_t* dst, const float (&v)[T])
     uint32_t pk[T / 2];
 #pragma unroll
     for (int q = 0; q < T / 2; ++q) pk[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{v[2 * q], v[2 * q + 1]}, bf2));
-    if constexpr (T == 4) *reinterpret_cast<u2u*>(dst) = u2u{pk[0], pk[1]};
-    else *reinterpret_cast<u1u*>(dst) = u1u{pk[0]};
+    if constexpr (T == 4) {
+        if constexpr (THROUGH) store_through(dst, u32x2{pk[0], pk[1]}); else *reinterpret_cast<u2u*>(dst) = u2u{pk[0], pk[1]};
+    } else {
+        if constexpr (THROUGH) store_through(dst, pk[0]); else *reinterpret_cast<u1u*>(dst) = u1u{pk[0]};
+    }
 }
 
 // FUSE: bit 0 / bit 1 = the A / B operand arrives as bfloat16 values and is quantized (RTNE, with its step sizes)
@@ -645,8 +656,8 @@ gemm_kernel(GemmArgs g)
                 for (int tt = 0; tt < TILES_N; ++tt) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(raw[tt]) : "a"(acc[ia][tt][r]));
                 uint32_t* dst = pbase + m * g.N + n;
                 if (interior) {
-                    if constexpr (TILES_N == 4) *reinterpret_cast<u32x4*>(dst) = u32x4{raw[0], raw[1], raw[2], raw[3]};
-                    else if constexpr (TILES_N == 2) *reinterpret_cast<u32x2*>(dst) = u32x2{raw[0], raw[1]};
+                    if constexpr (TILES_N == 4) store_through(dst, u32x4{raw[0], raw[1], raw[2], raw[3]});
+                    else if constexpr (TILES_N == 2) store_through(dst, u32x2{raw[0], raw[1]});
                     else {
 #pragma unroll
                         for (int tt = 0; tt < TILES_N; ++tt) dst[tt] = raw[tt];
@@ -707,7 +718,7 @@ gemm_kernel(GemmArgs g)
                 uint8_t* dst = ybase + ml * row_bytes;
                 if constexpr (TILES_N == 8) *reinterpret_cast<u32x4*>(dst) = u32x4{pk[0], pk[1], pk[2], pk[3]};
                 else if constexpr (TILES_N == 4) __builtin_nontemporal_store(u32x2{pk[0], pk[1]}, reinterpret_cast<u32x2*>(dst));
-                else *reinterpret_cast<uint32_t*>(dst) = pk[0];
+                else store_through(dst, pk[0]);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -1814,8 +1825,8 @@ gemm_direct_kernel(GemmArgs g)
                     pk[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector(
                         f2{value(ia, r, 2 * q, sl_rows[ia][r]), value(ia, r, 2 * q + 1, sl_rows[ia][r])}, bf2));
                 uint8_t* dst = ybase + (int64_t)(ia * R + row_in_block(r)) * g.N * 2;
-                if constexpr (TILES_N == 4) *reinterpret_cast<u32x2*>(dst) = u32x2{pk[0], pk[1]};
-                else *reinterpret_cast<uint32_t*>(dst) = pk[0];
+                if constexpr (TILES_N == 4) store_through(dst, u32x2{pk[0], pk[1]});
+                else store_through(dst, pk[0]);
             }
     } else if (fast && TILES_N == 4) {
         float* ybase = static_cast<float*>(g.y) + (bidx * g.M + m_base) * g.N + n;
@@ -2051,8 +2062,8 @@ gemm_deep_kernel(GemmArgs g)
             if (!g.y) continue;
             if constexpr (TILES_N > 1) {
                 if (whole) {
-                    if (g.y_bf16) store_bf16<TILES_N>(static_cast<uint16_t*>(g.y) + o, v);
-                    else store_f32<TILES_N>(static_cast<float*>(g.y) + o, v);
+                    if (g.y_bf16) store_bf16<TILES_N, false>(static_cast<uint16_t*>(g.y) + o, v);
+                    else store_f32<TILES_N, false>(static_cast<float*>(g.y) + o, v);
                     continue;
                 }
             }
@@ -2127,8 +2138,8 @@ splitk_reduce(GemmArgs g, int wide)
     if (left == 4) {
         if (g.acc_out) *reinterpret_cast<u32x4_any*>(static_cast<uint32_t*>(g.acc_out) + o) = acc;
         if (g.y) {
-            if (g.y_bf16) store_bf16<4>(static_cast<uint16_t*>(g.y) + o, y);
-            else store_f32<4>(static_cast<float*>(g.y) + o, y);
+            if (g.y_bf16) store_bf16<4, false>(static_cast<uint16_t*>(g.y) + o, y);
+            else store_f32<4, false>(static_cast<float*>(g.y) + o, y);
         }
     } else {
 #pragma unroll

@@ -98,7 +98,7 @@ quantize_rows_bf16x16(QArgs a)
         encode_quads<FMT, MODE, 4>(t, (uint64_t)p0 + a.offset, a.seed, !__any((((uint64_t)p0 + a.offset) & 3u) != 0u), c);
         out = u32x4{c[0], c[1], c[2], c[3]};
     }
-    *reinterpret_cast<u32x4*>(a.codes + p0) = out;
+    store_through(a.codes + p0, out);
 }
 
 // Row-contracting, any type, extent, stride and alignment.  A wavefront takes PIECE 16-byte vectors a lane: a piece of a
@@ -278,7 +278,7 @@ quantize_flat_multi(MultiQ a)
     const float rho = 1.0f / a.delta[t][0];
     const u32x4* src = reinterpret_cast<const u32x4*>(a.x[t]) + 2 * v;
     const u32x4 w0 = src[0], w1 = src[1];
-    reinterpret_cast<u32x4*>(a.codes[t])[v] = encode16_bf16_rtne<FMT>(w0, w1, rho);
+    store_through(a.codes[t] + 16 * v, encode16_bf16_rtne<FMT>(w0, w1, rho));
 }
 
 // Column-contracting (the input is [K][N], codes are [N][K]): any type, extent, stride and alignment.  Workgroup tile =
@@ -404,7 +404,7 @@ quantize_cols(QArgs a, int64_t tiles_n, int64_t tiles)
             if constexpr (PB == 16) codes = *reinterpret_cast<const u32x4*>(srcp);
             else { const u32x2 h = *reinterpret_cast<const u32x2*>(srcp); codes = u32x4{h[0], h[1], 0u, 0u}; }
             if (kk + PB <= K) {
-                if constexpr (PB == 16) *reinterpret_cast<u32x4_byte*>(dst) = codes;
+                if constexpr (PB == 16) store_through(dst, codes);
                 else *reinterpret_cast<u32x2_byte*>(dst) = u32x2{codes[0], codes[1]};
             } else {
                 store_bytes<PB>(dst, codes, (int)(K - kk));

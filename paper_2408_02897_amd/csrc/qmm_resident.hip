@@ -169,7 +169,7 @@ resident_rows(QArgs a, Board bd, uint32_t upr, uint32_t units, uint32_t P, uint3
             const uint64_t g = (uint64_t)(out + dst) + a.offset;
             uint32_t c[4];
             encode_quads<FMT, MODE, 4>(t, g, a.seed, MODE == QMM_ROUND_STOCHASTIC && !__any((g & 3u) != 0u), c);
-            *reinterpret_cast<u32x4_byte*>(a.codes + out + dst) = u32x4{c[0], c[1], c[2], c[3]};
+            store_through(a.codes + out + dst, u32x4{c[0], c[1], c[2], c[3]});
         }
     }
 }
@@ -406,7 +406,7 @@ resident_cols(QArgs a, Board bd, uint32_t strips, uint32_t tiles_k, uint32_t P)
             if (nn >= N || kk >= K) continue;
             uint8_t* dst = a.codes + ((int64_t)b * N + nn) * K + kk;
             const u32x4 codes = *reinterpret_cast<const u32x4*>(&tile[place(row, at)]);
-            if (kk + 16 <= K) *reinterpret_cast<u32x4_byte*>(dst) = codes;
+            if (kk + 16 <= K) store_through(dst, codes);
             else store_bytes<16>(dst, codes, (int)(K - kk));
         }
         if (t + 1 < S) __syncthreads();

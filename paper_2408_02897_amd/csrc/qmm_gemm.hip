@@ -1300,7 +1300,8 @@ gemm_stream_kernel(GemmArgs g)
     // stores have drained (one in-order counter), so the matrix units idle while memory takes the burst.  With every
     // other workgroup of an XCD some 4 us behind, half of the chip stores while the other half multiplies.  Worth its
     // idle start from four tiles per workgroup on (host); measured on 16384 x 4096 x 1024, launches back to back:
-    // 69 -> 62 us (more phases or other offsets: the same within noise).
+    // 66 -> 61.5 us (more phases or other offsets: the same within noise).  Half of that offset pays with three tiles: 16384 x 3072 x
+    // 1024 47.4 -> 45.9 us (with the whole offset 46.2), a layer's step 471.5 -> 468.8.
     if (g.stagger > 0 && ((blockIdx.x / kNumXcd) & 1u))
         for (int i = 0; i < g.stagger; ++i) __builtin_amdgcn_s_sleep(8);       // 512 cycles each
     Tile cur = tile_of(t_cur);
@@ -2289,7 +2290,8 @@ qmm_status launch_stream(GemmArgs& g, hipStream_t s)
     g.tiles_m = (int)(g.M / 256);
     g.tiles_n = (int)(g.N / 256);
     if ((int64_t)g.tiles_m * g.tiles_n * g.batch > 0x7FFFFFFF) return QMM_ERR_UNSUPPORTED;
-    g.stagger = ((int64_t)g.tiles_m * g.tiles_n * g.batch >= 4 * kStreamGrid) ? 16 : 0;
+    const int64_t tiles = (int64_t)g.tiles_m * g.tiles_n * g.batch;
+    g.stagger = tiles < 3 * kStreamGrid ? 0 : tiles < 4 * kStreamGrid ? 8 : 16;
     auto kern = gemm_stream_kernel<KIND, FA, FB>;
     static std::atomic<uint64_t> lds_attr_done{0};
     if (!ensure_lds_attr(lds_attr_done, reinterpret_cast<const void*>(kern), LDS_BYTES)) return QMM_ERR_LAUNCH;

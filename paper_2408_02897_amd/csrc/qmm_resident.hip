@@ -29,28 +29,6 @@ template <int THREADS> QMM_DEV uint32_t group_max(uint32_t v)
     return r;
 }
 
-// The scale group of a matrix: its matrices are ((k / inner) * G + g) * inner + k % inner for k = 0 .. count - 1.  A group's
-// words stand together on the board, slot(k) for its k-th matrix (a matrix apart, its readers' requests would be to many times
-// the lines: 512 matrices in 16 groups 17.4 us, this way 15.9).
-struct Group {
-    uint32_t g, G, inner, count, k_of_b, slots;
-    QMM_DEV uint32_t matrix(uint32_t k) const
-    {
-        const uint32_t q = inner > 1 ? k / inner : k;
-        return (q * G + g) * inner + (k - q * inner);
-    }
-    QMM_DEV uint32_t slot(uint32_t k) const { return g * slots + k; }
-};
-
-QMM_DEV Group group_at(const QArgs& a, uint32_t b)
-{
-    const uint32_t batch = (uint32_t)a.batch, G = (uint32_t)a.groups, inner = (uint32_t)min(a.inner, a.batch);
-    const uint32_t run = inner > 1 ? b / inner : b, runs = inner > 1 ? (batch + inner - 1) / inner : batch;
-    const uint32_t g = G > 1 ? run % G : 0, mine = G > 1 ? (runs - g + G - 1) / G : runs;
-    const uint32_t last_run = (mine - 1) * G + g, last = min(inner, batch - last_run * inner);
-    return Group{g, G, inner, (mine - 1) * inner + last, (G > 1 ? run / G : run) * inner + (b - run * inner), (runs + G - 1) / G * inner};
-}
-
 // Posts the maximum of slice p of the group's matrix grp.k_of_b and returns the maximum over the group's slices, P a matrix.
 // slice(matrix, p): this thread's part of the maximum of that slice, for values that have not come in time.
 // A line of the board that many workgroups read at once is read slowly (256 workgroups that all read the same 256 words:
@@ -140,7 +118,7 @@ resident_rows(QArgs a, Board bd, uint32_t upr, uint32_t units, uint32_t P, uint3
 #pragma unroll
         for (int k = 0; k < U; ++k) mm.fold(w[i][k]);
     const uint32_t mine = group_max<THREADS>(mm.finish());
-    const Group grp = group_at(a, b);
+    const Group grp = group_at((uint32_t)a.batch, (uint32_t)a.groups, (uint32_t)min(a.inner, a.batch), b);
     const uint32_t bits = fold_group<THREADS>(bd, grp, P, p, mine, [&](uint32_t mb, uint32_t slice) {
         const uint32_t u0 = first_of(slice);
         VecMax<T> o;
@@ -360,7 +338,7 @@ resident_cols(QArgs a, Board bd, uint32_t strips, uint32_t tiles_k, uint32_t P)
         }
     } else {
         const uint32_t mine = group_max<THREADS>(mm.finish());
-        const Group grp = group_at(a, b);
+        const Group grp = group_at((uint32_t)a.batch, (uint32_t)a.groups, (uint32_t)min(a.inner, a.batch), b);
         const uint32_t bits = fold_group<THREADS>(bd, grp, P, p, mine, [&](uint32_t mb, uint32_t slice) { return slice_max(mb, slice).finish(); });
         const float d = delta_from_absmax_bits(bits, a.qmax);
         if (threadIdx.x == 0 && p == 0 && b == grp.matrix(0)) a.delta[grp.g] = d;

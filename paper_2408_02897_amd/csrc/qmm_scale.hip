@@ -49,39 +49,84 @@ QMM_DEV void fold_all_partials(const uint32_t* partial, int64_t count, float qma
     m = block_max_u32(m);
     if (threadIdx.x == 0) delta[0] = delta_from_absmax_bits(m, qmax);
 }
+// The same by way of a board: the workgroups of a scale group post their maxima, and one of them, the last to start, waits for the
+// words, folds them and writes the step size.  word(i): the i-th of the group's `total` words; slice(w): this thread's part of the
+// maximum of the workgroup of word w, for words that do not come in time.  A post and a read where publishing, counting in two
+// levels and reading are a chain of four, and a launch less where a second kernel folded.  Kernel time, before / this: one step size,
+// bfloat16, 131072 elements 4.4 / 3.8 us, 8 million 9.4 / 7.6, 16.8 million 10.4 / 9.3, 50 million 18.9 / 18.5; the several-tensors call
+// on 16384 x 1024 and 4096 x 1024 10.8 / 9.6, 2048 x 768 and 768 x 768 5.2 / 4.4.
+template <class Word, class Slice> QMM_DEV void fold_board(const Board& bd, uint32_t mine_at, uint32_t mine, bool folder, uint32_t total, float qmax, float* delta,
+                                                           Word word, Slice slice)
+{
+    __shared__ uint32_t s_word;
+    if (threadIdx.x == 0) board_post(bd, mine_at, mine);
+    if (!folder) return;
+    const uint64_t start = ticks();
+    uint32_t m = 0;
+    bool missing = false;
+    for (uint32_t i = threadIdx.x; i < total; i += kThreads) {
+        uint32_t v;
+        if (board_wait(bd, word(i), start, v)) m = max(m, v); else missing = true;
+    }
+    if (__syncthreads_or(missing)) {
+        for (uint32_t i = 0; i < total; ++i) {
+            const uint32_t w = word(i);
+            if (threadIdx.x == 0) { uint32_t v; s_word = board_read(bd, w, v) ? v : ~0u; }
+            __syncthreads();
+            const uint32_t v = s_word;
+            __syncthreads();
+            m = max(m, v != ~0u ? v : slice(w));             // (a posted value is below 2^31)
+        }
+    }
+    __syncthreads();                                         // block_max_u32's shared words are used a second time
+    m = block_max_u32(m);
+    if (threadIdx.x == 0) *delta = delta_from_absmax_bits(m, qmax);
+}
 
-// Dense matrix (row_stride == cols) from a 16-byte boundary on, n elements: grid (nblk, batch).  With `slot` (one scale
-// group for the whole batch) the workgroup that arrives last folds the partial maxima and writes the step size.
+// Dense matrix (row_stride == cols) from a 16-byte boundary on, n elements: grid (nblk, batch).  With a board one workgroup
+// of each of the `groups` scale groups folds its partial maxima and writes the step size; with `slot` (one scale group) the one that arrives last.
 template <typename T> __global__ void __launch_bounds__(kThreads)
 absmax_flat(const T* __restrict__ x, int64_t batch_stride, int64_t n, uint32_t* __restrict__ partial,
-            uint32_t* __restrict__ slot, float qmax, float* __restrict__ delta)
+            uint32_t* __restrict__ slot, Board bd, uint32_t groups, uint32_t inner, float qmax, float* __restrict__ delta)
 {
     constexpr int V = VecMax<T>::V;
-    const T* base = x + (int64_t)blockIdx.y * batch_stride;
-    const u32x4* p = reinterpret_cast<const u32x4*>(base);
     const int64_t nvec = n / V;
-    VecMax<T> m;
     // A workgroup takes four consecutive 4 KB pieces per trip and the grid sweeps the tensor front to back: the
     // four loads a thread has in flight are then neighbours in memory.  (With the loads a whole grid stride apart
     // the same kernel reads a large tensor up to 25 % slower: four distant streams per thread.)  Ordinary loads on
     // purpose: streaming loads make this pass 7 % faster on a 134 MB tensor (23.0 against 24.6 us), but the quantize
     // pass that follows then finds less of the tensor in the memory-side cache and loses twice that.
-    const int64_t stride = (int64_t)gridDim.x * kThreads * 4;
-    int64_t i = (int64_t)blockIdx.x * kThreads * 4 + threadIdx.x;
-    for (; i + 3 * kThreads < nvec; i += stride) {
-        const u32x4 a = p[i], b = p[i + kThreads];
-        const u32x4 c = p[i + 2 * kThreads], d = p[i + 3 * kThreads];
-        m.fold(a); m.fold(b); m.fold(c); m.fold(d);
-    }
-    // the ragged end: at most three pieces of one workgroup, and the elements past the last whole vector
-    if (i < nvec) {
-        for (int u = 0; u < 4; ++u)
-            if (i + u * kThreads < nvec) m.fold(p[i + u * kThreads]);
-    }
-    uint32_t r = m.finish();
-    if (blockIdx.x == 0 && threadIdx.x < (unsigned)(n % V)) r = max(r, mag_bits<T>(base[nvec * V + threadIdx.x]));
-    r = block_max_u32(r);
+    auto slice = [&](uint32_t bx, uint32_t by) -> uint32_t {
+        const T* base = x + (int64_t)by * batch_stride;
+        const u32x4* p = reinterpret_cast<const u32x4*>(base);
+        VecMax<T> m;
+        const int64_t stride = (int64_t)gridDim.x * kThreads * 4;
+        int64_t i = (int64_t)bx * kThreads * 4 + threadIdx.x;
+        for (; i + 3 * kThreads < nvec; i += stride) {
+            const u32x4 a = p[i], b = p[i + kThreads];
+            const u32x4 c = p[i + 2 * kThreads], d = p[i + 3 * kThreads];
+            m.fold(a); m.fold(b); m.fold(c); m.fold(d);
+        }
+        // the ragged end: at most three pieces of one workgroup, and the elements past the last whole vector
+        if (i < nvec) {
+            for (int u = 0; u < 4; ++u)
+                if (i + u * kThreads < nvec) m.fold(p[i + u * kThreads]);
+        }
+        uint32_t r = m.finish();
+        if (bx == 0 && threadIdx.x < (unsigned)(n % V)) r = max(r, mag_bits<T>(base[nvec * V + threadIdx.x]));
+        return r;
+    };
+    const uint32_t r = block_max_u32(slice(blockIdx.x, blockIdx.y));
     const unsigned id = blockIdx.y * gridDim.x + blockIdx.x, total = gridDim.x * gridDim.y;
+    if (bd.words) {
+        const uint32_t P = gridDim.x;
+        const Group grp = group_at(gridDim.y, groups, inner, blockIdx.y);
+        const bool folder = blockIdx.x == P - 1 && grp.k_of_b == grp.count - 1;
+        fold_board(bd, id, r, folder, grp.count * P, qmax, delta + grp.g,
+                   [&](uint32_t i) { const uint32_t k = i / P; return grp.matrix(k) * P + (i - k * P); },
+                   [&](uint32_t w) { const uint32_t by = w / P; return slice(w - by * P, by); });
+        return;
+    }
     if (threadIdx.x == 0) {
         if (slot) publish_u32(partial + id, r); else partial[id] = r;
     }
@@ -102,6 +147,7 @@ struct MultiFlat {
     float* delta[kMaxMulti];
     int nblk[kMaxMulti];
     uint32_t* slots;                // kMaxMulti consecutive slots of arrival counters, one per tensor
+    Board board;                    // kMaxFlatBlocks words per tensor, or none
     float qmax;
 };
 __global__ void __launch_bounds__(kThreads)
@@ -112,19 +158,27 @@ absmax_flat_multi(MultiFlat a)
     if ((int)blockIdx.x >= nblk) return;
     const u32x4* p = reinterpret_cast<const u32x4*>(a.x[t]);
     const int64_t nvec = a.nvec[t];
-    u16x2 m[4] = {};
-    const int64_t stride = (int64_t)nblk * kThreads * 4;
-    int64_t i = (int64_t)blockIdx.x * kThreads * 4 + threadIdx.x;
-    for (; i + 3 * kThreads < nvec; i += stride) {
-        const u32x4 v0 = p[i], v1 = p[i + kThreads];
-        const u32x4 v2 = p[i + 2 * kThreads], v3 = p[i + 3 * kThreads];
-        fold_bf16x8(v0, m); fold_bf16x8(v1, m); fold_bf16x8(v2, m); fold_bf16x8(v3, m);
+    auto slice = [&](uint32_t bx) -> uint32_t {
+        u16x2 m[4] = {};
+        const int64_t stride = (int64_t)nblk * kThreads * 4;
+        int64_t i = (int64_t)bx * kThreads * 4 + threadIdx.x;
+        for (; i + 3 * kThreads < nvec; i += stride) {
+            const u32x4 v0 = p[i], v1 = p[i + kThreads];
+            const u32x4 v2 = p[i + 2 * kThreads], v3 = p[i + 3 * kThreads];
+            fold_bf16x8(v0, m); fold_bf16x8(v1, m); fold_bf16x8(v2, m); fold_bf16x8(v3, m);
+        }
+        if (i < nvec) {
+            for (int u = 0; u < 4; ++u)
+                if (i + u * kThreads < nvec) fold_bf16x8(p[i + u * kThreads], m);
+        }
+        return finish_bf16(m);
+    };
+    const uint32_t r = block_max_u32(slice(blockIdx.x));
+    if (a.board.words) {
+        fold_board(Board{a.board.words + t * kMaxFlatBlocks, a.board.tag, a.board.patience}, blockIdx.x, r, (int)blockIdx.x == nblk - 1, (uint32_t)nblk, a.qmax,
+                   a.delta[t], [](uint32_t i) { return i; }, slice);
+        return;
     }
-    if (i < nvec) {
-        for (int u = 0; u < 4; ++u)
-            if (i + u * kThreads < nvec) fold_bf16x8(p[i + u * kThreads], m);
-    }
-    const uint32_t r = block_max_u32(finish_bf16(m));
     if (threadIdx.x == 0) publish_u32(a.partial[t] + blockIdx.x, r);
     // the tensor's last workgroup folds its partial maxima (at most kMaxFlatBlocks) and writes its step size
     if (arrive_last(a.slots + (size_t)t * kArrivalWords, blockIdx.x, (unsigned)nblk)) {
@@ -447,7 +501,7 @@ namespace qmm {
 // out->done: the step sizes have been written as well.  `fold_here`: the caller folds the partial maxima itself, so a
 // large tensor's last workgroup need not.
 qmm_status scale_partials(const qmm_tensor* x0, qmm_format fmt, const qmm_granularity* g, float* delta_out, uint32_t* partial,
-                          bool fold_here, ScalePartials* out, hipStream_t s)
+                          bool fold_here, ScalePartials* out, hipStream_t s, uint32_t patience)
 {
     const qmm_tensor t = one_matrix(x0, g);
     const qmm_tensor* x = &t;
@@ -461,17 +515,25 @@ qmm_status scale_partials(const qmm_tensor* x0, qmm_format fmt, const qmm_granul
     if (nelem == 0) return QMM_OK;
     switch (p.kind) {
     case Plan::FLAT: {
-        // One scale group for the whole batch and a large tensor: one launch, the workgroup that arrives last folds.
-        // (Publishing, counting and the coherent reads of the fold are a chain of device-wide round trips of
-        // 2-3 us each: about 11 us for a tensor of any size up to 32 MB, against 9-10 us for two small launches;
-        // from 32 MB on the single launch wins, 25 us against 27 us at 134 MB.)
+        // One launch: by way of a board, where every group has a matrix.  Calls being recorded: with one scale group and a large tensor
+        // the workgroup that arrives last folds (publishing, counting and the coherent reads of the fold are a chain of
+        // device-wide round trips, about 11 us for a tensor of any size up to 32 MB against 9-10 us for two small launches;
+        // from 32 MB on the single launch wins, 25 us against 27 us at 134 MB), else a second kernel.
         uint32_t* slot = nullptr;
-        if (!fold_here && g->batch_groups == 1 && nelem >= (int64_t(1) << 24) && arrival_slots(1, &slot) != QMM_OK) slot = nullptr;
+        Board bd{};
+        const int64_t inner = std::max<int64_t>(g->batch_inner, 1), words = p.flat_blocks * x->batch;
+        const bool every_group = g->batch_groups <= x->batch && (g->batch_groups - 1) * inner < x->batch;
+        if (fold_here || !every_group || words > kBoardMax || !take_board(s, RING_SHORT, (uint32_t)words, &bd)) {
+            bd.words = nullptr;
+            if (!fold_here && g->batch_groups == 1 && nelem >= (int64_t(1) << 24) && arrival_slots(1, &slot) != QMM_OK) slot = nullptr;
+        }
+        bd.patience = std::min(bd.patience, patience);
+        const uint32_t groups = every_group ? (uint32_t)g->batch_groups : 1u, run = (uint32_t)std::min(inner, x->batch);
         const dim3 grid(p.flat_blocks, (unsigned)x->batch);
         const int64_t n = x->rows * x->cols;
-        if (bf16) absmax_flat<uint16_t><<<grid, kThreads, 0, s>>>(static_cast<const uint16_t*>(x->data), x->batch_stride, n, partial, slot, qmax, delta_out);
-        else absmax_flat<float><<<grid, kThreads, 0, s>>>(static_cast<const float*>(x->data), x->batch_stride, n, partial, slot, qmax, delta_out);
-        out->done = slot != nullptr;
+        if (bf16) absmax_flat<uint16_t><<<grid, kThreads, 0, s>>>(static_cast<const uint16_t*>(x->data), x->batch_stride, n, partial, slot, bd, groups, run, qmax, delta_out);
+        else absmax_flat<float><<<grid, kThreads, 0, s>>>(static_cast<const float*>(x->data), x->batch_stride, n, partial, slot, bd, groups, run, qmax, delta_out);
+        out->done = slot != nullptr || bd.words != nullptr;
         break;
     }
     case Plan::ROWS: {
@@ -555,8 +617,9 @@ qmm_status scale_arguments(const qmm_tensor* x, qmm_format fmt, const qmm_granul
 }
 }  // namespace qmm
 
-extern "C" qmm_status qmm_scale(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, float* delta_out,
-                                void* workspace, size_t workspace_bytes, void* stream)
+namespace {
+qmm_status scale_call(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, float* delta_out, void* workspace, size_t workspace_bytes,
+                      uint32_t patience, void* stream)
 {
     const qmm_status chk = scale_check(x, fmt, g, delta_out, workspace, workspace_bytes);
     if (chk != QMM_OK) return chk;
@@ -564,8 +627,15 @@ extern "C" qmm_status qmm_scale(const qmm_tensor* x, qmm_format fmt, const qmm_g
     hipStream_t s = as_stream(stream);
     uint32_t* partial = static_cast<uint32_t*>(workspace);
     ScalePartials pp;
-    const qmm_status st = scale_partials(x, fmt, g, delta_out, partial, false, &pp, s);
+    const qmm_status st = scale_partials(x, fmt, g, delta_out, partial, false, &pp, s, patience);
     return st != QMM_OK || pp.done ? st : scale_fold(pp, partial, fmt, g, delta_out, s);
+}
+}  // namespace
+
+extern "C" qmm_status qmm_scale(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, float* delta_out,
+                                void* workspace, size_t workspace_bytes, void* stream)
+{
+    return scale_call(x, fmt, g, delta_out, workspace, workspace_bytes, kPatience, stream);
 }
 
 // ---- qmm_scale_static: the same kernels with their partial maxima in a scratch array of the device image.
@@ -628,8 +698,9 @@ extern "C" size_t qmm_scale_multi_workspace_size(int32_t count, const qmm_tensor
     return total;
 }
 
-extern "C" qmm_status qmm_scale_multi(int32_t count, const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g,
-                                      float* const* delta_out, void* workspace, size_t workspace_bytes, void* stream)
+namespace {
+qmm_status scale_multi_call(int32_t count, const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, float* const* delta_out,
+                            void* workspace, size_t workspace_bytes, uint32_t patience, void* stream)
 {
     if (count < 0) return QMM_ERR_SHAPE;
     if (count == 0) return QMM_OK;
@@ -650,7 +721,7 @@ extern "C" qmm_status qmm_scale_multi(int32_t count, const qmm_tensor* x, qmm_fo
         }
         for (int32_t t = 0; t < count; ++t) {
             const size_t slice = multi_slice(x + t, g + t);
-            const qmm_status st = qmm_scale(x + t, fmt, g + t, delta_out[t], ws, slice, stream);
+            const qmm_status st = scale_call(x + t, fmt, g + t, delta_out[t], ws, slice, patience, stream);
             if (st != QMM_OK) return st;
             ws += slice;
         }
@@ -669,9 +740,27 @@ extern "C" qmm_status qmm_scale_multi(int32_t count, const qmm_tensor* x, qmm_fo
         ws += multi_slice(x + t, g + t);
     }
     a.qmax = host_qmax(fmt);
-    const qmm_status sl = arrival_slots(count, &a.slots);
-    if (sl != QMM_OK) return sl;
     hipStream_t s = as_stream(stream);
+    if (!take_board(s, RING_SHORT, (uint32_t)count * kMaxFlatBlocks, &a.board)) {
+        a.board.words = nullptr;
+        const qmm_status sl = arrival_slots(count, &a.slots);
+        if (sl != QMM_OK) return sl;
+    }
+    a.board.patience = std::min(a.board.patience, patience);
     absmax_flat_multi<<<dim3((unsigned)max_blk, (unsigned)count), kThreads, 0, s>>>(a);
     return launch_status();
+}
+}  // namespace
+
+extern "C" qmm_status qmm_scale_multi(int32_t count, const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g,
+                                      float* const* delta_out, void* workspace, size_t workspace_bytes, void* stream)
+{
+    return scale_multi_call(count, x, fmt, g, delta_out, workspace, workspace_bytes, kPatience, stream);
+}
+
+// For the tests, not part of the ABI: the folding workgroups wait `patience` ticks for the others (0: they form what is not there yet).
+extern "C" qmm_status qmm_internal_scale_multi(int32_t count, const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g,
+                                               float* const* delta_out, void* workspace, size_t workspace_bytes, uint32_t patience, void* stream)
+{
+    return scale_multi_call(count, x, fmt, g, delta_out, workspace, workspace_bytes, patience, stream);
 }

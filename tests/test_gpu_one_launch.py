@@ -9,6 +9,7 @@ import ctypes
 import pytest
 import torch
 
+from oracle import oracle as O
 from paper_2408_02897_amd import qmm, workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -176,3 +177,31 @@ def test_metric_in_one_launch_equals_two(n, dtype):
             torch.cuda.synchronize()
             assert torch.equal(one.view(torch.int64), two.view(torch.int64)), (d is not None, patience)
             assert torch.equal(one.view(torch.int64), out.view(torch.int64))
+
+
+# Step sizes alone: one and several tensors (the several-tensors kernel takes dense bfloat16 with one step size; the others go one by
+# one), one group and several in runs, one workgroup and many, a ragged end; found by waiting and formed by the folding workgroup.
+@pytest.mark.parametrize("shapes,dtype,kw", [
+    ([(1, 1, 8)], torch.bfloat16, {}), ([(1, 3, 5)], torch.float32, {}), ([(1, 1031, 1001)], torch.bfloat16, {}), ([(1, 8192, 1032)], torch.float32, {}),
+    ([(1, 2048, 768), (1, 768, 768), (1, 1, 16)], torch.bfloat16, {}), ([(1, 9000, 1024), (1, 64, 1024)], torch.bfloat16, {}),
+    ([(12, 70, 96)], torch.bfloat16, dict(batch_groups=4)), ([(13, 70, 96)], torch.float32, dict(batch_groups=3, batch_inner=2)),
+    ([(64, 300, 300)], torch.bfloat16, dict(batch_groups=16)), ([(5, 33, 50)], torch.bfloat16, dict(batch_groups=2, batch_inner=9)),
+    ([(2, 8, 64)], torch.bfloat16, dict(batch_groups=5))])
+def test_step_sizes_in_one_launch(shapes, dtype, kw):
+    L = qmm.lib()
+    f = L.qmm_internal_scale_multi
+    f.restype = ctypes.c_int
+    f.argtypes = [ctypes.c_int32, ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_uint32, ctypes.c_void_p]
+    xs = [tensor(s, dtype, seed=i + s[1]) * (i + 1) for i, s in enumerate(shapes)]
+    if xs[0].numel() > 3000:
+        xs[0].view(-1)[1234] = float("nan") if kw else -7.5e4
+    n, groups, inner = len(xs), kw.get("batch_groups", 1), kw.get("batch_inner", 1)
+    t, g = (qmm.Tensor * n)(*[qmm.tensor_desc(x, 1) for x in xs]), (qmm.Granularity * n)(*[qmm.granularity(**kw) for _ in xs])
+    ws = torch.empty(L.qmm_scale_multi_workspace_size(n, t, g), dtype=torch.uint8, device=DEV)
+    for patience in (FOREVER, 0):
+        out = [torch.full((groups,), -1.0, device=DEV) for _ in xs]
+        assert f(n, t, qmm.E4M3, g, qmm.MultiDesc.pointers(out), ws.data_ptr(), ws.numel(), patience, qmm._stream()) == 0
+        torch.cuda.synchronize()
+        for x, d in zip(xs, out):
+            want = torch.from_numpy(O.scale(x.float().cpu().numpy(), 1, qmm.E4M3, False, groups, inner)).to(DEV)
+            assert torch.equal(d.view(torch.int32), want.view(torch.int32)), patience

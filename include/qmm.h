@@ -14,13 +14,14 @@
  * General rules
  *  - Every pointer named "device" is GPU memory owned by the caller; the
  *    library allocates nothing and frees nothing.  What it keeps between calls:
- *    per GPU, the addresses of two arrays of its own device image (the scratch
+ *    per GPU, the addresses of arrays of its own device image (the scratch
  *    of qmm_scale_static, and a ring of arrival counters that the single-launch
- *    reductions of qmm_scale / qmm_scale_multi use and leave at zero; a call
- *    takes the next slot of the ring, 1024 calls would have to be in flight for
- *    two of them to meet on one), a ring of boards through which the workgroups of one launch
- *    exchange values (calls outside stream capture; a board shared by two calls in flight costs
- *    time, never a result), and which GPUs have had the kernels' LDS limit set.
+ *    reductions of qmm_scale / qmm_scale_multi use where a board does not serve
+ *    and leave at zero; a call takes the next slot of the ring, 1024 calls would
+ *    have to be in flight for two of them to meet on one), two rings of boards
+ *    through which the workgroups of one launch exchange values (calls outside
+ *    stream capture; a board shared by two calls in flight costs time, never a
+ *    result), and which GPUs have had the kernels' LDS limit set.
  *    Descriptor structs (qmm_tensor, qmm_operand, qmm_granularity) are host memory
  *    and are read before the call returns.
  *  - Calls validate their arguments on the host, enqueue kernels on `stream`

@@ -30,12 +30,12 @@ qmm_status arrival_slots(int count, uint32_t** first)
     return QMM_OK;
 }
 
-// ---- boards (qmm_device.h).  Tags run from 1 to 2^32 - 1 and start over; the call that starts over clears the rings, which
+// ---- boards (qmm_device.h).  A device's tags run from 1 to 2^32 - 1 and start over; the call that starts over clears its rings, which
 // might hold, in a place that no call has used since, a word with a tag of the round before.
 namespace {
 constexpr uint64_t kTags = 0xFFFFFFFFull;
 std::atomic<uint64_t*> board_addr[kMaxDevices];
-std::atomic<uint64_t> next_tag{0}, next_word[kRings];
+std::atomic<uint64_t> next_tag[kMaxDevices], next_word[kRings];
 std::atomic<int> cus[kMaxDevices];
 __global__ void ring_clear(uint64_t* words)
 {
@@ -62,7 +62,7 @@ bool take_board(hipStream_t s, Ring ring, uint32_t words, Board* b)
     uint64_t at = next_word[ring].fetch_add(size, std::memory_order_relaxed) % kRingWords;
     if (at + size > kRingWords) at = next_word[ring].fetch_add(2 * size, std::memory_order_relaxed) % kRingWords;   // past the end: from its start on
     if (at + size > kRingWords) at = 0;                               // (another thread got there first: shared, see above)
-    const uint64_t n = next_tag.fetch_add(1, std::memory_order_relaxed);
+    const uint64_t n = next_tag[dev].fetch_add(1, std::memory_order_relaxed);
     b->words = p + (size_t)ring * kRingWords + at;
     b->tag = (uint32_t)(n % kTags) + 1u;
     b->patience = kPatience;

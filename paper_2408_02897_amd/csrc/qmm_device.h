@@ -294,6 +294,7 @@ template <> struct VecMax<float> {
 
 // ---------------------------------------------------------------------------
 // "The workgroup that arrives last folds the partial results": one launch per reduction instead of two.
+// For calls being recorded into a graph; the others use a board (below), which saves the chain of counting.
 // A call takes one slot (per reduced tensor) of a ring of arrival counters that live in the library's device
 // image and are zero between calls; every workgroup publishes its partial result, counts itself in, and the one
 // that completes the count folds all partials in a fixed order (so results do not depend on which one it is),

@@ -2,11 +2,14 @@
 // Methodology bullets on scale granularity and on aligning the absmax with the
 // format maximum).  HBM-bound: every element is read once (2 B for bfloat16),
 // the maximum is taken on magnitude bit patterns (exact, order-free), partial
-// maxima go to the workspace and are folded per group, followed by the one
-// division: by a second small kernel, or -- dense tensors with one step size,
-// from 2^24 elements, and the several-tensors call -- by the workgroup that
-// finishes last (one launch), or by the quantize pass of qmm_scale_quantize.  The maximum is order-free, so the result does not depend
-// on launch geometry or on which workgroup folds.
+// maxima are folded per group, followed by the one division.  One step size per
+// matrix or group of matrices and the several-tensors call: one launch, the
+// maxima crossing through a board.  Calls being recorded into a graph, which a
+// board's tags do not fit, leave them in the workspace, for a second small kernel
+// or, from 2^24 elements, the workgroup that finishes last.  Step sizes per row
+// or column: a second kernel, or the quantize pass of qmm_scale_quantize.  The
+// maximum is order-free, so the result does not depend on launch geometry or on
+// which workgroup folds.
 #include <algorithm>
 #include <atomic>
 #include <type_traits>

@@ -161,6 +161,8 @@ QMM_DEV float delta_from_absmax_bits(uint32_t bits, float qmax)
 // write-back: 3 us for 16 MB of codes written in a kernel's last phase (16384 x 1024 bfloat16, scale + quantize 17.0 -> 14.9 us).
 // A streaming (nontemporal) store leaves as early but is not kept by the memory-side cache: the same codes made the
 // product that reads them several times slower (16384 x 4096 x 1024: 60 -> 75 us).
+// For whole lines only: a line that leaves in pieces (rows off a line's boundary, a tile's part of one) is a write to memory per
+// piece.  64 matrices of 1000 x 1000 transposed: quantize 40 us by the L2, 54 past it; 300000 x 20 per row 16.7 / 28.2.
 // ---------------------------------------------------------------------------
 template <typename V> QMM_DEV void store_through(void* p, V v)
 {

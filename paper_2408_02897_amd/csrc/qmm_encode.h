@@ -123,8 +123,8 @@ template <typename T, int FMT, int MODE> QMM_DEV u32x2 encode_vec(const u32x4& w
 template <typename T> QMM_DEV void store_codes(uint8_t* dst, u32x2 c, int64_t left)
 {
     if (left >= Vec<T>::V) {
-        if constexpr (Vec<T>::V == 8) store_through(dst, c);
-        else store_through(dst, c[0]);
+        if constexpr (Vec<T>::V == 8) *reinterpret_cast<u32x2_byte*>(dst) = c;
+        else *reinterpret_cast<u32_byte*>(dst) = c[0];
     } else {
 #pragma unroll
         for (int e = 0; e < Vec<T>::V; ++e)

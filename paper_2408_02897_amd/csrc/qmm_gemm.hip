@@ -63,6 +63,7 @@ struct GemmArgs {
     const float* nsr_ref;             // NSR variant: high-precision product [batch][M][N], else null
     double* nsr_partial;              // NSR variant: per wavefront {sum (y - ref)^2, sum ref^2}
     double* nsr_out;                  // NSR variant: the two folded sums
+    int through;                      // the outputs go past the L2 (store_through; rule in gemm_impl)
     int stagger;                      // gemm_stream_kernel: every other workgroup of an XCD starts this many sleeps late
 };
 
@@ -143,11 +144,12 @@ template <typename AccT, int NI, int NJ> QMM_DEV void pin_accumulators(AccT (&ac
 
 // T consecutive values of an output row, aligned to their element only (rows of N elements start anywhere when N is
 // odd): one store instruction all the same, global memory takes vector stores at any element boundary.
-// THROUGH: past the L2 at once (store_through), which pays where a kernel's outputs all leave in its last phase: gemm_kernel, E4M3
-// 4096 x 768 x 768 to binary32 11.1 -> 9.8 us, INT8 12.8 -> 10.7, bfloat16 14.4 -> 13.4; INT8 4096 x 3072 x 768 to bfloat16 18.4 -> 16.6; the
-// partial sums of 768 x 3072 x 4096 16.3 -> 14.9, of 3072 x 1024 x 16384 53.2 -> 52.3; gemm_direct_kernel 36.5 -> 35.4.  Not in gemm_deep_kernel,
-// whose few outputs the L2 takes faster (256 x 768 x 768 6.8 against 7.4 us), and not in the split sums' second kernel.
-template <int T, bool THROUGH = true> QMM_DEV void store_f32(float* dst, const float (&v)[T])
+// THROUGH: past the L2 at once (store_through), which pays where a kernel's outputs all leave in its last phase and in whole lines:
+// gemm_kernel to binary32, E4M3 4096 x 768 x 768 11.1 -> 9.8 us (not INT8, see there); the partial sums of 768 x 3072 x 4096 16.3 -> 14.9, of
+// 3072 x 1024 x 16384 53.2 -> 52.3; gemm_direct_kernel 36.5 -> 35.4.  Not for bfloat16 and edge tiles (40000 x 640 x 512 E4M3 27.3 by the L2,
+// 31.9 past it), not in gemm_deep_kernel, whose few outputs the L2 takes faster (256 x 768 x 768 6.8 against 7.4 us), and not in
+// the split sums' second kernel.
+template <int T, bool THROUGH = false> QMM_DEV void store_f32(float* dst, const float (&v)[T])
 {
     typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
     typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
@@ -159,7 +161,7 @@ template <int T, bool THROUGH = true> QMM_DEV void store_f32(float* dst, const f
         if constexpr (THROUGH) store_through(dst, f2{v[0], v[1]}); else *reinterpret_cast<f2u*>(dst) = f2u{v[0], v[1]};
     }
 }
-template <int T, bool THROUGH = true> QMM_DEV void store_bf16(uint16_t* dst, const float (&v)[T])
+template <int T> QMM_DEV void store_bf16(uint16_t* dst, const float (&v)[T])
 {
     typedef uint32_t u2u __attribute__((ext_vector_type(2), aligned(2)));
     typedef uint32_t u1u __attribute__((ext_vector_type(1), aligned(2)));
@@ -169,11 +171,8 @@ template <int T, bool THROUGH = true> QMM_DEV void store_bf16(uint16_t* dst, con
     uint32_t pk[T / 2];
 #pragma unroll
     for (int q = 0; q < T / 2; ++q) pk[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{v[2 * q], v[2 * q + 1]}, bf2));
-    if constexpr (T == 4) {
-        if constexpr (THROUGH) store_through(dst, u32x2{pk[0], pk[1]}); else *reinterpret_cast<u2u*>(dst) = u2u{pk[0], pk[1]};
-    } else {
-        if constexpr (THROUGH) store_through(dst, pk[0]); else *reinterpret_cast<u1u*>(dst) = u1u{pk[0]};
-    }
+    if constexpr (T == 4) *reinterpret_cast<u2u*>(dst) = u2u{pk[0], pk[1]};
+    else *reinterpret_cast<u1u*>(dst) = u1u{pk[0]};
 }
 
 // FUSE: bit 0 / bit 1 = the A / B operand arrives as bfloat16 values and is quantized (RTNE, with its step sizes)
@@ -642,7 +641,7 @@ gemm_kernel(GemmArgs g)
         }
     };
     const bool interior = (m0 + BM <= g.M) && (n0 + BN <= g.N) && (g.N % TILES_N == 0);
-    if (g.splits > 1) {
+    if (NSR == 0 && g.splits > 1) {
         // split-K: the raw accumulators of this K range go to the partial-sum buffer; a second kernel adds the
         // ranges in ascending order, descales and writes the outputs
         uint32_t* pbase = static_cast<uint32_t*>(g.partial) + ((int64_t)split * g.batch + bidx) * g.M * g.N;
@@ -656,8 +655,13 @@ gemm_kernel(GemmArgs g)
                 for (int tt = 0; tt < TILES_N; ++tt) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(raw[tt]) : "a"(acc[ia][tt][r]));
                 uint32_t* dst = pbase + m * g.N + n;
                 if (interior) {
-                    if constexpr (TILES_N == 4) store_through(dst, u32x4{raw[0], raw[1], raw[2], raw[3]});
-                    else if constexpr (TILES_N == 2) store_through(dst, u32x2{raw[0], raw[1]});
+                    if constexpr (TILES_N == 4) {
+                        if (g.through) store_through(dst, u32x4{raw[0], raw[1], raw[2], raw[3]});
+                        else *reinterpret_cast<u32x4*>(dst) = u32x4{raw[0], raw[1], raw[2], raw[3]};
+                    } else if constexpr (TILES_N == 2) {
+                        if (g.through) store_through(dst, u32x2{raw[0], raw[1]});
+                        else *reinterpret_cast<u32x2*>(dst) = u32x2{raw[0], raw[1]};
+                    }
                     else {
 #pragma unroll
                         for (int tt = 0; tt < TILES_N; ++tt) dst[tt] = raw[tt];
@@ -718,7 +722,7 @@ gemm_kernel(GemmArgs g)
                 uint8_t* dst = ybase + ml * row_bytes;
                 if constexpr (TILES_N == 8) *reinterpret_cast<u32x4*>(dst) = u32x4{pk[0], pk[1], pk[2], pk[3]};
                 else if constexpr (TILES_N == 4) __builtin_nontemporal_store(u32x2{pk[0], pk[1]}, reinterpret_cast<u32x2*>(dst));
-                else store_through(dst, pk[0]);
+                else *reinterpret_cast<uint32_t*>(dst) = pk[0];
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -738,23 +742,43 @@ gemm_kernel(GemmArgs g)
                     for (int r = 0; r < REGS; ++r) sl_rows[ia][r] = da[m_base + ia * R + row_in_block(r)];
             }
         }
+        // (one copy of the rows for INT8 and with the error sums: a second took the registers of both, 88 -> 112, and spilled with the sums)
+        if constexpr (NSR != 0 || KIND == KIND_I8) {
 #pragma unroll
-        for (int ia = 0; ia < BLOCKS_M; ++ia) {
+            for (int ia = 0; ia < BLOCKS_M; ++ia) {
 #pragma unroll
-            for (int r = 0; r < REGS; ++r) {
-                const int ml = ia * R + row_in_block(r);
-                float rv[TILES_N], v[TILES_N];
-                if constexpr (NSR != 0) nsr_row(m_base + ml, rv);
-                uint32_t raw;
+                for (int r = 0; r < REGS; ++r) {
+                    const int ml = ia * R + row_in_block(r);
+                    float rv[TILES_N], v[TILES_N];
+                    if constexpr (NSR != 0) nsr_row(m_base + ml, rv);
+                    uint32_t raw;
 #pragma unroll
-                for (int e = 0; e < TILES_N; ++e) v[e] = value(ia, r, e, sl_rows[ia][r], raw);
-                if constexpr (NSR != 0) {
+                    for (int e = 0; e < TILES_N; ++e) v[e] = value(ia, r, e, sl_rows[ia][r], raw);
+                    if constexpr (NSR != 0) {
 #pragma unroll
-                    for (int e = 0; e < TILES_N; ++e) nsr_add(v[e], rv[e]);
+                        for (int e = 0; e < TILES_N; ++e) nsr_add(v[e], rv[e]);
+                    }
+                    store_f32<TILES_N>(ybase + (int64_t)ml * g.N, v);
                 }
-                store_f32<TILES_N>(ybase + (int64_t)ml * g.N, v);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            __builtin_amdgcn_sched_barrier(0);
+        } else {
+            auto rows = [&](auto through) {
+#pragma unroll
+                for (int ia = 0; ia < BLOCKS_M; ++ia) {
+#pragma unroll
+                    for (int r = 0; r < REGS; ++r) {
+                        const int ml = ia * R + row_in_block(r);
+                        float v[TILES_N];
+                        uint32_t raw;
+#pragma unroll
+                        for (int e = 0; e < TILES_N; ++e) v[e] = value(ia, r, e, sl_rows[ia][r], raw);
+                        store_f32<TILES_N, decltype(through)::value>(ybase + (int64_t)ml * g.N, v);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            if (g.through) rows(std::true_type{}); else rows(std::false_type{});
         }
     } else if (NSR == 0 && g.y && !g.acc_out) {
         // Edge tiles and rows that start off a vector boundary, output in y alone: the same stores as above under a row
@@ -1826,8 +1850,10 @@ gemm_direct_kernel(GemmArgs g)
                     pk[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector(
                         f2{value(ia, r, 2 * q, sl_rows[ia][r]), value(ia, r, 2 * q + 1, sl_rows[ia][r])}, bf2));
                 uint8_t* dst = ybase + (int64_t)(ia * R + row_in_block(r)) * g.N * 2;
-                if constexpr (TILES_N == 4) store_through(dst, u32x2{pk[0], pk[1]});
-                else store_through(dst, pk[0]);
+                if constexpr (TILES_N == 4) {
+                    if (g.through) store_through(dst, u32x2{pk[0], pk[1]}); else *reinterpret_cast<u32x2*>(dst) = u32x2{pk[0], pk[1]};
+                } else if (g.through) store_through(dst, pk[0]);
+                else *reinterpret_cast<uint32_t*>(dst) = pk[0];
             }
     } else if (fast && TILES_N == 4) {
         float* ybase = static_cast<float*>(g.y) + (bidx * g.M + m_base) * g.N + n;
@@ -2063,8 +2089,8 @@ gemm_deep_kernel(GemmArgs g)
             if (!g.y) continue;
             if constexpr (TILES_N > 1) {
                 if (whole) {
-                    if (g.y_bf16) store_bf16<TILES_N, false>(static_cast<uint16_t*>(g.y) + o, v);
-                    else store_f32<TILES_N, false>(static_cast<float*>(g.y) + o, v);
+                    if (g.y_bf16) store_bf16<TILES_N>(static_cast<uint16_t*>(g.y) + o, v);
+                    else store_f32<TILES_N>(static_cast<float*>(g.y) + o, v);
                     continue;
                 }
             }
@@ -2082,77 +2108,99 @@ gemm_deep_kernel(GemmArgs g)
 // One thread per four consecutive columns; the partial sums of four ranges are requested before the first is added (one
 // at a time, behind 64-bit divisions for the coordinates, the kernel was a chain of memory latencies: the product
 // 3072 x 1024 x 16384 in two ranges 71.0 -> 67.3 us, 768 x 3072 x 4096 in three 27.1 -> 25.9 us).
+// A matrix of the batch is blockIdx.y, so that its step sizes' groups are scalar arithmetic, and the step sizes are requested
+// in front of the partial sums (before, the groups were four 64-bit divisions a thread, and the loads of
+// the ranges sat behind branches of their own): 768 x 3072 in three ranges to binary32 9.4 -> 7.5 us, 3072 x 1024 in two 8.8 -> 7.3,
+// 64 x 64 in 64 ranges 20.8 -> 6.9.  (Split products have fewer than 256 tiles of 128 x 128, batch included: 32-bit indexes do.)
 template <int KIND>
 __global__ void __launch_bounds__(256)
-splitk_reduce(GemmArgs g, int wide)
+splitk_reduce(GemmArgs g)
 {
-    const int64_t quads_per_row = (g.N + 3) / 4;
-    const int64_t total = g.batch * g.M * quads_per_row;
-    const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (id >= total) return;
-    int64_t row, bidx;                                                               // row = b * M + m
-    if (wide) { row = id / quads_per_row; bidx = row / g.M; }
-    else { row = (uint32_t)id / (uint32_t)quads_per_row; bidx = (uint32_t)row / (uint32_t)g.M; }
-    const int64_t n = (id - row * quads_per_row) * 4, m = row - bidx * g.M;
-    const int64_t plane = g.batch * g.M * g.N;
-    const int left = (int)min((int64_t)4, g.N - n);
+    const uint32_t quads_per_row = (uint32_t)((g.N + 3) / 4), id = blockIdx.x * 256 + threadIdx.x, b = blockIdx.y;
+    if (id >= (uint32_t)g.M * quads_per_row) return;
+    const uint32_t m = id / quads_per_row, n = (id - m * quads_per_row) * 4;
+    const int64_t plane = g.batch * g.M * g.N, o = (b * g.M + m) * g.N + n;
     typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-    const uint32_t* p = static_cast<const uint32_t*>(g.partial) + row * g.N + n;
-    auto fetch = [&](int sp) -> u32x4 {
-        u32x4 v = {0u, 0u, 0u, 0u};
-        if (left == 4) return *reinterpret_cast<const u32x4_any*>(p + sp * plane);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (e < left) v[e] = p[sp * plane + e];
-        return v;
+    const uint32_t* p = static_cast<const uint32_t*>(g.partial) + o;
+    auto group = [&](int64_t inner, int64_t groups) {                                // (b / inner) % groups
+        const uint32_t run = inner > b ? 0 : b / (uint32_t)inner;
+        return (int64_t)(groups > run ? run : run % (uint32_t)groups);
     };
-    u32x4 acc = fetch(0);
-    auto add = [&](u32x4 v) {
+    auto reduce = [&](auto whole, int left) {
+        constexpr bool WHOLE = decltype(whole)::value;
+        float sl = 1.0f, sr[4] = {1.0f, 1.0f, 1.0f, 1.0f};
+        if constexpr (KIND != KIND_BF16) {
+            const float* da = g.da + group(g.da_inner, g.da_groups) * (g.da_per_channel ? g.M : 1);
+            const float* db = g.db + group(g.db_inner, g.db_groups) * (g.db_per_channel ? g.N : 1);
+            sl = da[g.da_per_channel ? m : 0];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sr[e] = db[g.db_per_channel ? (WHOLE || e < left ? n + e : n) : 0];
+        }
+        auto fetch = [&](int sp) -> u32x4 {
+            if constexpr (WHOLE) return *reinterpret_cast<const u32x4_any*>(p + sp * plane);
+            u32x4 v = {0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (e < left) v[e] = p[sp * plane + e];
+            return v;
+        };
+        u32x4 acc = fetch(0);
+        auto add = [&](u32x4 v) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if constexpr (KIND == KIND_I8) acc[e] += v[e];
+                else acc[e] = __float_as_uint(__uint_as_float(acc[e]) + __uint_as_float(v[e]));
+            }
+        };
+        int sp = 1;
+        for (; sp + 3 < g.splits; sp += 4) {
+            u32x4 v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = fetch(sp + k);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) add(v[k]);
+        }
+        auto rest = [&](auto count) {
+            constexpr int R = decltype(count)::value;
+            u32x4 v[R];
+#pragma unroll
+            for (int k = 0; k < R; ++k) v[k] = fetch(sp + k);
+#pragma unroll
+            for (int k = 0; k < R; ++k) add(v[k]);
+        };
+        if (g.splits - sp == 3) rest(std::integral_constant<int, 3>{});
+        else if (g.splits - sp == 2) rest(std::integral_constant<int, 2>{});
+        else if (g.splits - sp == 1) rest(std::integral_constant<int, 1>{});
+        float y[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            if constexpr (KIND == KIND_I8) acc[e] += v[e];
-            else acc[e] = __float_as_uint(__uint_as_float(acc[e]) + __uint_as_float(v[e]));
+            float a;
+            if constexpr (KIND == KIND_I8) a = (float)(int32_t)acc[e];
+            else a = __uint_as_float(acc[e]);
+            if constexpr (KIND != KIND_BF16) a = (a * sl) * sr[e];
+            y[e] = a;
+        }
+        if constexpr (WHOLE) {
+            if (g.acc_out) *reinterpret_cast<u32x4_any*>(static_cast<uint32_t*>(g.acc_out) + o) = acc;
+            if (g.y) {
+                if (g.y_bf16) store_bf16<4>(static_cast<uint16_t*>(g.y) + o, y);
+                else store_f32<4>(static_cast<float*>(g.y) + o, y);
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (e < left) {
+                    if (g.acc_out) static_cast<uint32_t*>(g.acc_out)[o + e] = acc[e];
+                    if (g.y) {
+                        if (g.y_bf16) static_cast<__bf16*>(g.y)[o + e] = (__bf16)y[e];
+                        else static_cast<float*>(g.y)[o + e] = y[e];
+                    }
+                }
         }
     };
-    for (int sp = 1; sp < g.splits; sp += 4) {
-        u32x4 v[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) { v[k] = u32x4{0u, 0u, 0u, 0u}; if (sp + k < g.splits) v[k] = fetch(sp + k); }
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (sp + k < g.splits) add(v[k]);
-    }
-    float y[4];
-    float sl = 1.0f;
-    if constexpr (KIND != KIND_BF16) sl = g.da[((bidx / g.da_inner) % g.da_groups) * (g.da_per_channel ? g.M : 1) + (g.da_per_channel ? m : 0)];
-    const float* db = nullptr;
-    if constexpr (KIND != KIND_BF16) db = g.db + ((bidx / g.db_inner) % g.db_groups) * (g.db_per_channel ? g.N : 1);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        float a;
-        if constexpr (KIND == KIND_I8) a = (float)(int32_t)acc[e];
-        else a = __uint_as_float(acc[e]);
-        if constexpr (KIND != KIND_BF16) a = (a * sl) * (g.db_per_channel ? db[e < left ? n + e : n] : db[0]);
-        y[e] = a;
-    }
-    const int64_t o = row * g.N + n;
-    if (left == 4) {
-        if (g.acc_out) *reinterpret_cast<u32x4_any*>(static_cast<uint32_t*>(g.acc_out) + o) = acc;
-        if (g.y) {
-            if (g.y_bf16) store_bf16<4, false>(static_cast<uint16_t*>(g.y) + o, y);
-            else store_f32<4, false>(static_cast<float*>(g.y) + o, y);
-        }
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (e < left) {
-                if (g.acc_out) static_cast<uint32_t*>(g.acc_out)[o + e] = acc[e];
-                if (g.y) {
-                    if (g.y_bf16) static_cast<__bf16*>(g.y)[o + e] = (__bf16)y[e];
-                    else static_cast<float*>(g.y)[o + e] = y[e];
-                }
-            }
-    }
+    const int left = (int)min((int64_t)4, g.N - n);
+    if (left == 4) reduce(std::true_type{}, 4);
+    else reduce(std::false_type{}, left);
 }
 
 // Split-K plan: used when 128 x 128 tiles would not give every CU its two workgroups and K is long (weight-gradient
@@ -2205,8 +2253,8 @@ qmm_status launch_tile(GemmArgs& g, hipStream_t s)
     }
     if (g.splits > 1) {
         if (hipGetLastError() != hipSuccess) return QMM_ERR_LAUNCH;
-        const int64_t threads = g.batch * g.M * ((g.N + 3) / 4);
-        splitk_reduce<KIND><<<(unsigned)((threads + 255) / 256), 256, 0, s>>>(g, threads > 0xFFFFFFFFll);
+        const int64_t quads = g.M * ((g.N + 3) / 4);
+        splitk_reduce<KIND><<<dim3((unsigned)((quads + 255) / 256), (unsigned)g.batch), 256, 0, s>>>(g);
     }
     return launch_status();
 }
@@ -2488,6 +2536,13 @@ qmm_status gemm_impl(const qmm_operand* a, const qmm_operand* b, int64_t batch, 
         if (!aligned16(workspace)) return QMM_ERR_ALIGN;
         g.partial = workspace;
     }
+    // Stores past the L2, of binary32 rows in whole lines: a line that leaves in pieces, as where rows do not begin at a line's boundary,
+    // costs memory a write per piece, which the L2 would have merged (16000 x 3000 x 512 E4M3 64.5 us by the L2, 100.8 past it,
+    // 14000 x 1544 x 1024 43.7 / 51.5; whole lines 5000 x 4000 x 2048 the same, 4096 x 3072 x 768 17.7 / 16.9, 4096 x 768 x 768 11.1 / 9.8).
+    // From 64 MB on the end of the kernel no longer counts (9000 x 4096 x 512 38.2 / 39.4).
+    const void* out = g.splits > 1 ? g.partial : y;
+    const int64_t row_bytes = N * (g.splits > 1 || !g.y_bf16 ? 4 : 2);
+    g.through = row_bytes % 128 == 0 && reinterpret_cast<uintptr_t>(out) % 128 == 0 && batch * M * row_bytes * g.splits <= (int64_t)64 << 20;
     hipStream_t s = as_stream(stream);
 
     if (bf) return launch_part<PART_BF16>(g, s, 0);

@@ -405,7 +405,7 @@ quantize_cols(QArgs a, int64_t tiles_n, int64_t tiles)
             if constexpr (PB == 16) codes = *reinterpret_cast<const u32x4*>(srcp);
             else { const u32x2 h = *reinterpret_cast<const u32x2*>(srcp); codes = u32x4{h[0], h[1], 0u, 0u}; }
             if (kk + PB <= K) {
-                if constexpr (PB == 16) store_through(dst, codes);
+                if constexpr (PB == 16) *reinterpret_cast<u32x4_byte*>(dst) = codes;
                 else *reinterpret_cast<u32x2_byte*>(dst) = u32x2{codes[0], codes[1]};
             } else {
                 store_bytes<PB>(dst, codes, (int)(K - kk));

@@ -194,6 +194,28 @@ def test_product_of_few_tiles(kind, batch, m, n, row):
     assert torch.equal(alone, y)
 
 
+# Contractions in `ranges` ranges of eight slabs, whose sums a second kernel adds (four at a time, then the one to three left; a
+# matrix of the batch its own row of workgroups): rows of whole and partial quads, an element, step sizes at each level.
+@pytest.mark.parametrize("batch,m,n,ranges,per_channel,groups,inner", [
+    (1, 64, 64, 2, False, 1, 0), (1, 65, 63, 3, True, 1, 0), (1, 130, 101, 4, False, 1, 0), (3, 40, 36, 5, True, 3, 0), (6, 33, 35, 6, False, 2, 3),
+    (7, 32, 20, 7, True, 2, 2), (1, 1, 1, 8, False, 1, 0), (2, 64, 66, 9, False, 1, 5), (5, 17, 300, 10, True, 2, 1)])
+def test_sum_of_split_ranges(batch, m, n, ranges, per_channel, groups, inner):
+    k = ranges * 1024
+    a, b = (torch.randint(-127, 128, (batch, r, k), generator=torch.Generator().manual_seed(r + k), dtype=torch.int32).to(torch.int8).to(DEV) for r in (m, n))
+    steps = [torch.rand(groups * (r if per_channel else 1), generator=torch.Generator().manual_seed(r)).add_(0.01).to(DEV) for r in (m, n)]
+    pair = [(t.view(torch.uint8), qmm.operand(t.view(torch.uint8), qmm.INT8, d, per_channel, groups, batch_inner=inner)) for t, d in zip((a, b), steps)]
+    assert qmm.lib().qmm_gemm_workspace_size(ctypes.byref(pair[0][1]), ctypes.byref(pair[1][1]), batch, m, n, k) == ranges * batch * m * n * 4
+    exact = a.double() @ b.double().transpose(1, 2).contiguous()
+    group = [i // max(inner, 1) % groups for i in range(batch)]
+    da, db = (d.view(groups, -1)[group] for d in steps)
+    want = (exact.float() * da[:, :, None]) * db[:, None, :]
+    for dtype in (torch.float32, torch.bfloat16):
+        ybuf, y = guarded((batch, m, n), dtype)
+        abuf, acc = guarded((batch, m, n), torch.int32)
+        qmm.gemm(*pair, out=y, acc_out=acc)
+        assert torch.equal(acc.double(), exact) and torch.equal(y, want.to(dtype)) and intact(ybuf) and intact(abuf)
+
+
 # Tall outputs at most 64 wide: B in LDS (up to eight slabs of K) and, beyond, from memory; odd numbers of slabs, a partial
 # last one, wavefronts without a row.  INT8 against the integer product; E4M3 against the same columns inside a product of 96,
 # which runs in the LDS kernels with the same order of additions.

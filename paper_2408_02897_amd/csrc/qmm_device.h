@@ -358,7 +358,8 @@ QMM_DEV bool arrive_last(uint32_t* slot, unsigned id, unsigned total)
 // atomics, and no ordering between words is needed.  Tags are handed out by the host, one per launch (take_board), so a
 // call that is being recorded into a graph, whose replays would repeat the tag, does not use a board.
 // Boards are cut from rings in the library's device image, each call as many words as it needs (calls whose readers wait long,
-// the error sums, have a ring of their own: what they share words with is a call of their own kind a thousand calls before).  A reader's wait is bounded
+// the error sums and the step sizes alone, have a ring of their own: what they share words with is a call of their own kind at least
+// sixteen, mostly a thousand calls before).  A reader's wait is bounded
 // (`patience`, in ticks of the 100 MHz clock): a value that has not come by then -- its workgroup may not be resident, other
 // work holding the CUs, or a call a whole ring before may still be running on the same words -- the reader's workgroup forms
 // itself and posts, the same value.  So every workgroup ends whatever the others do, and what the words hold decides about
@@ -367,6 +368,10 @@ QMM_DEV bool arrive_last(uint32_t* slot, unsigned id, unsigned total)
 enum Ring { RING_SHORT = 0, RING_LONG = 1, kRings = 2 };
 constexpr uint32_t kRingWords = 1u << 20, kBoardMax = 1u << 17;      // 8 MB a ring
 constexpr uint32_t kPatience = 5000;                                 // 50 us
+// Where only the workgroups that fold wait and the others never do, so that every word comes whatever else the GPU does: 10 ms, for
+// the workgroups of a long pass end far apart (16 GB read for a step size, 2.9 ms: with 50 us the folder began to read others' slices
+// again, alone, 3.6 ms; 4 GB 0.71 / 0.87).
+constexpr uint32_t kFolderPatience = 1000000;
 struct Board { uint64_t* words; uint32_t tag, patience; };
 bool take_board(hipStream_t s, Ring ring, uint32_t words, Board* b); // host (qmm_api.hip), words <= kBoardMax; false: do without one
 int cu_count();                                                      // host: CUs of the current device, 0 if unknown
@@ -423,7 +428,7 @@ qmm_status scale_arguments(const qmm_tensor* x, qmm_format fmt, const qmm_granul
                            const void* workspace, size_t workspace_bytes, bool fold);
 size_t scale_partials_size(const qmm_tensor* x, const qmm_granularity* g, bool fold);    // bytes of partial maxima
 qmm_status scale_partials(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, float* delta_out, uint32_t* partial,
-                          bool fold_here, ScalePartials* out, hipStream_t s, uint32_t patience = kPatience);
+                          bool fold_here, ScalePartials* out, hipStream_t s, uint32_t patience = kFolderPatience);
 qmm_status scale_fold(const ScalePartials& pp, const uint32_t* partial, qmm_format fmt, const qmm_granularity* g,
                       float* delta_out, hipStream_t s);
 // Both steps in one launch (qmm_resident.hip), for the calls it is for.

@@ -296,7 +296,6 @@ template <bool COHERENT> QMM_DEV double fold_field(const double* partial, int nb
 // Not kept: four quotients of the sum over one denominator and the maxima looked for in upper words, 14 instructions an element
 // instead of 20 (bfloat16 67 million 67.7 against 69.8, 16.8 million 24.3 against 22.9, binary32 67 million 85.4 against 83.4).
 constexpr int kFields = 16;
-constexpr uint32_t kMetricPatience = 1000000;             // 10 ms: the fold comes behind the last block of a pass
 template <bool Y_BF16, bool HAS_D, bool ONE> __global__ void __launch_bounds__(kThreads)
 metric_partial(const void* __restrict__ yv, const float* __restrict__ r, const float* __restrict__ d, int64_t n,
                double* __restrict__ partial, double* __restrict__ out, Board bd)
@@ -408,12 +407,12 @@ qmm_status metric_call(const void* y, qmm_dtype y_dtype, const float* y_ref, con
 extern "C" qmm_status qmm_metric(const void* y, qmm_dtype y_dtype, const float* y_ref, const float* denom, int64_t n,
                                  double* out16, void* workspace, size_t workspace_bytes, void* stream)
 {
-    return metric_call(y, y_dtype, y_ref, denom, n, out16, workspace, workspace_bytes, kMetricPatience, stream);
+    return metric_call(y, y_dtype, y_ref, denom, n, out16, workspace, workspace_bytes, kFolderPatience, stream);
 }
 
 // For the tests, not part of the ABI: the folding workgroups wait `patience` ticks for the others (0: they form what is not there yet).
 extern "C" qmm_status qmm_internal_metric(const void* y, qmm_dtype y_dtype, const float* y_ref, const float* denom, int64_t n,
                                           double* out16, void* workspace, size_t workspace_bytes, uint32_t patience, void* stream)
 {
-    return metric_call(y, y_dtype, y_ref, denom, n, out16, workspace, workspace_bytes, patience < kMetricPatience ? patience : kMetricPatience, stream);
+    return metric_call(y, y_dtype, y_ref, denom, n, out16, workspace, workspace_bytes, patience < kFolderPatience ? patience : kFolderPatience, stream);
 }

@@ -54,7 +54,7 @@ QMM_DEV void fold_all_partials(const uint32_t* partial, int64_t count, float qma
 }
 // The same by way of a board: the workgroups of a scale group post their maxima, and one of them, the last to start, waits for the
 // words, folds them and writes the step size.  word(i): the i-th of the group's `total` words; slice(w): this thread's part of the
-// maximum of the workgroup of word w, for words that do not come in time.  A post and a read where publishing, counting in two
+// maximum of the workgroup of word w, for words that do not come in time (looked for kThreads at a time).  A post and a read where publishing, counting in two
 // levels and reading are a chain of four, and a launch less where a second kernel folded.  Kernel time, before / this: one step size,
 // bfloat16, 131072 elements 4.4 / 3.8 us, 8 million 9.4 / 7.6, 16.8 million 10.4 / 9.3, 50 million 18.9 / 18.5; the several-tensors call
 // on 16384 x 1024 and 4096 x 1024 10.8 / 9.6, 2048 x 768 and 768 x 768 5.2 / 4.4.
@@ -72,13 +72,26 @@ template <class Word, class Slice> QMM_DEV void fold_board(const Board& bd, uint
         if (board_wait(bd, word(i), start, v)) m = max(m, v); else missing = true;
     }
     if (__syncthreads_or(missing)) {
-        for (uint32_t i = 0; i < total; ++i) {
-            const uint32_t w = word(i);
-            if (threadIdx.x == 0) { uint32_t v; s_word = board_read(bd, w, v) ? v : ~0u; }
+        __shared__ uint64_t s_missing[kThreads / kWave];
+        for (uint32_t base = 0; base < total; base += kThreads) {
+            const uint32_t i = base + threadIdx.x;
+            uint32_t v;
+            const bool none = i < total && !board_read(bd, word(i), v);
+            if (i < total && !none) m = max(m, v);
+            const uint64_t bits = __ballot(none);
+            if ((threadIdx.x & (kWave - 1)) == 0) s_missing[threadIdx.x / kWave] = bits;
             __syncthreads();
-            const uint32_t v = s_word;
+            for (int k = 0; k < kThreads / kWave; ++k) {
+                for (uint64_t left = s_missing[k]; left; left &= left - 1) {
+                    const uint32_t w = word(base + k * kWave + (uint32_t)__ffsll((unsigned long long)left) - 1);
+                    if (threadIdx.x == 0) { uint32_t late; s_word = board_read(bd, w, late) ? late : ~0u; }      // (others go on meanwhile)
+                    __syncthreads();
+                    const uint32_t late = s_word;
+                    __syncthreads();
+                    m = max(m, late != ~0u ? late : slice(w));             // (a posted value is below 2^31)
+                }
+            }
             __syncthreads();
-            m = max(m, v != ~0u ? v : slice(w));             // (a posted value is below 2^31)
         }
     }
     __syncthreads();                                         // block_max_u32's shared words are used a second time
@@ -526,11 +539,11 @@ qmm_status scale_partials(const qmm_tensor* x0, qmm_format fmt, const qmm_granul
         Board bd{};
         const int64_t inner = std::max<int64_t>(g->batch_inner, 1), words = p.flat_blocks * x->batch;
         const bool every_group = g->batch_groups <= x->batch && (g->batch_groups - 1) * inner < x->batch;
-        if (fold_here || !every_group || words > kBoardMax || !take_board(s, RING_SHORT, (uint32_t)words, &bd)) {
+        if (fold_here || !every_group || words > kBoardMax || !take_board(s, RING_LONG, (uint32_t)words, &bd)) {
             bd.words = nullptr;
             if (!fold_here && g->batch_groups == 1 && nelem >= (int64_t(1) << 24) && arrival_slots(1, &slot) != QMM_OK) slot = nullptr;
         }
-        bd.patience = std::min(bd.patience, patience);
+        bd.patience = std::min(kFolderPatience, patience);
         const uint32_t groups = every_group ? (uint32_t)g->batch_groups : 1u, run = (uint32_t)std::min(inner, x->batch);
         const dim3 grid(p.flat_blocks, (unsigned)x->batch);
         const int64_t n = x->rows * x->cols;
@@ -638,7 +651,7 @@ qmm_status scale_call(const qmm_tensor* x, qmm_format fmt, const qmm_granularity
 extern "C" qmm_status qmm_scale(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, float* delta_out,
                                 void* workspace, size_t workspace_bytes, void* stream)
 {
-    return scale_call(x, fmt, g, delta_out, workspace, workspace_bytes, kPatience, stream);
+    return scale_call(x, fmt, g, delta_out, workspace, workspace_bytes, kFolderPatience, stream);
 }
 
 // ---- qmm_scale_static: the same kernels with their partial maxima in a scratch array of the device image.
@@ -744,12 +757,12 @@ qmm_status scale_multi_call(int32_t count, const qmm_tensor* x, qmm_format fmt, 
     }
     a.qmax = host_qmax(fmt);
     hipStream_t s = as_stream(stream);
-    if (!take_board(s, RING_SHORT, (uint32_t)count * kMaxFlatBlocks, &a.board)) {
+    if (!take_board(s, RING_LONG, (uint32_t)count * kMaxFlatBlocks, &a.board)) {
         a.board.words = nullptr;
         const qmm_status sl = arrival_slots(count, &a.slots);
         if (sl != QMM_OK) return sl;
     }
-    a.board.patience = std::min(a.board.patience, patience);
+    a.board.patience = std::min(kFolderPatience, patience);
     absmax_flat_multi<<<dim3((unsigned)max_blk, (unsigned)count), kThreads, 0, s>>>(a);
     return launch_status();
 }
@@ -758,7 +771,7 @@ qmm_status scale_multi_call(int32_t count, const qmm_tensor* x, qmm_format fmt, 
 extern "C" qmm_status qmm_scale_multi(int32_t count, const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g,
                                       float* const* delta_out, void* workspace, size_t workspace_bytes, void* stream)
 {
-    return scale_multi_call(count, x, fmt, g, delta_out, workspace, workspace_bytes, kPatience, stream);
+    return scale_multi_call(count, x, fmt, g, delta_out, workspace, workspace_bytes, kFolderPatience, stream);
 }
 
 // For the tests, not part of the ABI: the folding workgroups wait `patience` ticks for the others (0: they form what is not there yet).

@@ -367,7 +367,7 @@ QMM_DEV bool arrive_last(uint32_t* slot, unsigned id, unsigned total)
 // ---------------------------------------------------------------------------
 enum Ring { RING_SHORT = 0, RING_LONG = 1, kRings = 2 };
 constexpr uint32_t kRingWords = 1u << 20, kBoardMax = 1u << 17;      // 8 MB a ring
-constexpr uint32_t kPatience = 5000;                                 // 50 us
+constexpr uint32_t kPatience = 1200;                                 // 12 us: then a workgroup looks closer (collect in qmm_resident.hip)
 // Where only the workgroups that fold wait and the others never do, so that every word comes whatever else the GPU does: 10 ms, for
 // the workgroups of a long pass end far apart (16 GB read for a step size, 2.9 ms: with 50 us the folder began to read others' slices
 // again, alone, 3.6 ms; 4 GB 0.71 / 0.87).

@@ -1,8 +1,8 @@
 // qmm_scale_quantize in ONE launch with one read of the tensor: every workgroup loads its slice into registers, posts the
 // slice's maximum on a board, waits for the other slices of its scale group, forms the step size and encodes what it
 // holds.  Traffic 2 B + 1 B per bfloat16 element where the two passes move 2 + 2 + 1, and one launch instead of two or
-// three.  For tensors whose slices are resident together, 67 MB and less.  The wait is bounded and every workgroup can do
-// without the others (see Board in qmm_device.h).
+// three.  For tensors whose slices are resident together (plan_rows, plan_cols).  The wait is bounded and every workgroup can do
+// without the others (see Board in qmm_device.h, and collect below).
 // What bounds it: reading at 6 TB/s, 1.5 us from the last maximum to the step size, then writing, which nothing overlaps any
 // more.  Kernel time, two passes / this, inputs from memory, E4M3: bfloat16 16384 x 1024 19.0 / 16.9 us, 16384 x 2048 30.1 / 26.2,
 // 512 matrices of 512 x 64 in 16 groups 19.6 / 16.5, transposed 19.9 / 17.0, per column 4096 x 3072 18.8 / 16.2 and 16384 x 1024
@@ -30,12 +30,83 @@ template <int THREADS> QMM_DEV uint32_t group_max(uint32_t v)
     return r;
 }
 
+// Words that have not come in time: other work holds CUs -- a kernel on another stream, a second call of this kind --, and the
+// workgroups that would post them start only when those that wait have ended.  Of the n words (at most kMaxWords) read(left)
+// reads those with left[i] set, by all threads, and clears left[i] where it came.  As long as words come the workgroup waits on;
+// when none has for `idle` ticks it forms missing ones itself, form(i) by all threads, the `me`-numbered workgroup
+// another one than the others.  tell(missing): called by the first wavefront in front of that, missing(c) the bits of words c .. c + 63.
+// Ends: an idle period ends with a word less to come or with one formed.
+// What such a call takes, time until both streams are done: 40 calls beside 20 products that hold half of the CUs (2048 x 4096 x 8192
+// E4M3), separate launches / this: 16384 x 1024 1610 / 1776 us, transposed 1700 / 1900 to 2040, 512 matrices of 512 x 64 1582 / 1860,
+// per column 4096 x 3072 1564 / 1490; a quarter of the CUs 1106 / 1160, 1100 / 1280, 1047 / 1238, 992 / 930; 40 calls beside 40 of 16384 x 1024
+// 1150 / 1110, 1182 / 1222, 1140 / 1105, 1160 / 1340 to 1420.  (Before, each workgroup waited 50 us and walked the words
+// one by one: 1776 was 6500, 1222 was 38600.)  With words late after 5 us instead of 12, calls that have the GPU to themselves lose up to 10 %.
+constexpr uint32_t kMaxWords = 1024;                     // words a workgroup waits for: a grid that is resident together has no more
+constexpr uint32_t kIdle = 100;                          // 1 us
+// The r-th set bit of the 64-bit words bits(0), bits(64) ..., which have more than r; uniform over a wavefront.
+template <class Bits> QMM_DEV uint32_t pick(uint32_t r, Bits bits)
+{
+    for (uint32_t c = 0;; c += kWave) {
+        uint64_t w = bits(c);
+        const uint32_t here = (uint32_t)__popcll(w);
+        if (r < here) {
+            for (; r > 0; --r) w &= w - 1;
+            return c + (uint32_t)__ffsll((unsigned long long)w) - 1;
+        }
+        r -= here;
+    }
+}
+// `follows`: the first wavefront asks next() for the word to form as long as that knows one, kAll if nothing is left to do (false is
+// returned), kNone if there is nobody to ask; then as above.
+constexpr uint32_t kAll = ~0u, kNone = ~0u - 1;
+template <int THREADS, class Read, class Form, class Tell, class Next>
+QMM_DEV bool collect(uint32_t n, uint32_t me, uint32_t idle, bool follows, Read read, Form form, Tell tell, Next next)
+{
+    __shared__ uint8_t s_left[kMaxWords];
+    __shared__ uint32_t s_at, s_seen;                    // (shared for the registers: what is held across this path is spilled in resident_cols)
+    __shared__ uint64_t s_since;
+    for (uint32_t i = threadIdx.x; i < n; i += THREADS) s_left[i] = 1;
+    if (threadIdx.x == 0) s_seen = ~0u;
+    __syncthreads();
+    for (;;) {
+        if (!follows) { read(s_left); __syncthreads(); }
+        if (threadIdx.x < kWave) {
+            uint32_t at = kNone;
+            if (follows) at = next();
+            else {
+                auto missing = [&](uint32_t c) -> uint64_t { return __ballot(c + threadIdx.x < n && s_left[c + threadIdx.x] != 0); };
+                uint32_t total = 0;
+                for (uint32_t c = 0; c < n; c += kWave) total += (uint32_t)__popcll(missing(c));
+                const uint64_t now = ticks();
+                const bool news = total < s_seen;
+                if (total == 0) at = kAll;
+                else if ((news ? 0 : now - s_since) >= idle) { tell(missing); at = pick(me % total, missing); if (threadIdx.x == 0) s_seen = total - 1; }
+                else if (news && threadIdx.x == 0) { s_seen = total; s_since = now; }
+            }
+            if (threadIdx.x == 0) s_at = at;
+        }
+        __syncthreads();
+        const uint32_t at = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_at);
+        if (at == kAll) return !follows;
+        if (at < n) {
+            form(at);
+            if (threadIdx.x == 0) s_left[at] = 0;
+        } else if (!follows) __builtin_amdgcn_s_sleep(8);
+        if (at == kNone) follows = false;
+        __syncthreads();
+    }
+}
+
 // Posts the maximum of slice p of the group's matrix grp.k_of_b and returns the maximum over the group's slices, P a matrix.
 // slice(matrix, p): this thread's part of the maximum of that slice, for values that have not come in time.
 // A line of the board that many workgroups read at once is read slowly (256 workgroups that all read the same 256 words:
 // 5 us; a word that one of them waits for comes 0.6 us after it was posted).  So the first eight workgroups of a group of
-// many words read them and post what they find, and the others read that.
-constexpr uint32_t kDirect = 32, kLeaders = 8, kLeaderWords = 16;     // (a leader's word in a line of its own)
+// many words read them and post what they find, and the others, their followers, read that.  Where words stay away a leader posts which,
+// and its followers form them with it, one each, and go back to waiting.
+// A leader's area: a line its followers wait on, of the result and the number and length of the last list, and the list.
+constexpr uint32_t kDirect = 32, kLeaders = 8, kListAt = 16;
+QMM_DEV uint32_t whole_lines(uint32_t words) { return (words + 15u) & ~15u; }
+constexpr uint32_t kAlone = 5000;                        // 50 us without a word from the leader: the board is another call's as well
 template <int THREADS, class Slice> QMM_DEV uint32_t fold_group(const Board& bd, const Group& grp, uint32_t P, uint32_t p, uint32_t mine, Slice slice)
 {
     __shared__ uint32_t s_word;
@@ -43,37 +114,70 @@ template <int THREADS, class Slice> QMM_DEV uint32_t fold_group(const Board& bd,
     const uint32_t first = grp.slot(0) * P;
     if (threadIdx.x == 0) board_post(bd, first + grp.k_of_b * P + p, mine);
     const uint64_t start = ticks();
-    const uint32_t me = grp.k_of_b * P + p, results = (grp.G * grp.slots * P + kLeaderWords - 1) / kLeaderWords * kLeaderWords;
-    const bool led = n > kDirect, leader = me < kLeaders;
-    const uint32_t result = results + (grp.g * kLeaders + me % kLeaders) * kLeaderWords;
-    if (led && !leader) {
-        if (threadIdx.x == 0) { uint32_t v; s_word = board_wait(bd, result, start, v) ? v : ~0u; }
-        __syncthreads();
-        if (s_word != ~0u) return s_word;                // (a posted value is below 2^31)
-    }
+    const uint32_t me = grp.k_of_b * P + p, most = grp.slots * P;
+    const bool led = n > kDirect, leader = me < kLeaders, follows = led && !leader;
+    const uint32_t area = whole_lines(grp.G * most) + (grp.g * kLeaders + me % kLeaders) * (kListAt + whole_lines(most));
     uint32_t m = 0;
     bool missing = false;
-    for (uint32_t i = threadIdx.x; i < n; i += THREADS) {
-        uint32_t v;
-        if (board_wait(bd, first + i, start, v)) m = max(m, v); else missing = true;
-    }
-    if (__syncthreads_or(missing)) {
-        // from a place of its own on, so that the workgroups that wait share the slices that are missing
-        for (uint32_t i = 0, at = blockIdx.x % n; i < n; ++i, at = at + 1 == n ? 0 : at + 1) {
-            if (threadIdx.x == 0) { uint32_t v; s_word = board_read(bd, first + at, v) ? v : ~0u; }
-            __syncthreads();
-            uint32_t v = s_word;
-            __syncthreads();
-            if (v == ~0u) {
-                const uint32_t k = at / P;
-                v = group_max<THREADS>(slice(grp.matrix(k), at - k * P));
-                if (threadIdx.x == 0) board_post(bd, first + at, v);
-            }
-            m = max(m, v);
+    if (follows) {
+        if (threadIdx.x == 0) { uint32_t v; s_word = board_wait(bd, area, start, v) ? v : ~0u; }
+        __syncthreads();
+        if (s_word != ~0u) return s_word;                // (a posted value is below 2^31)
+        missing = true;
+    } else {
+        for (uint32_t i = threadIdx.x; i < n; i += THREADS) {
+            uint32_t v;
+            if (board_wait(bd, first + i, start, v)) m = max(m, v); else missing = true;
         }
     }
+    if (__builtin_expect(__syncthreads_or(missing), 0)) {
+        __shared__ uint32_t s_lists;                     // posted by a leader, seen by a follower
+        __shared__ uint64_t s_heard;
+        if (threadIdx.x == 0) { s_lists = 0; s_heard = ticks(); }
+        const bool all = collect<THREADS>(n, me, min(kIdle, bd.patience), follows,
+            [&](uint8_t* left) {
+                for (uint32_t i = threadIdx.x; i < n; i += THREADS) {
+                    uint32_t v;
+                    if (left[i] && board_read(bd, first + i, v)) { m = max(m, v); left[i] = 0; }
+                }
+            },
+            [&](uint32_t at) {
+                const uint32_t k = at / P, v = group_max<THREADS>(slice(grp.matrix(k), at - k * P));
+                if (threadIdx.x == 0) board_post(bd, first + at, v);
+                m = max(m, v);
+            },
+            [&](auto bits) {
+                if (!led || !leader) return;
+                uint32_t total = 0;
+                for (uint32_t c = 0; c < n; c += kWave) {
+                    const uint64_t w = bits(c), lane = uint64_t(1) << threadIdx.x;
+                    if (w & lane) board_post(bd, area + kListAt + total + (uint32_t)__popcll(w & (lane - 1)), c + threadIdx.x);
+                    total += (uint32_t)__popcll(w);
+                }
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the list is there before its number
+                if (threadIdx.x == 0) board_post(bd, area + 1, (s_lists += 1u << 16) | total);
+            },
+            [&]() -> uint32_t {
+                while (ticks() - s_heard < (bd.patience ? kAlone : 0)) {
+                    uint32_t v = 0;
+                    const uint64_t have = __ballot(threadIdx.x < 2 && board_read(bd, area + threadIdx.x, v));
+                    if (have & 1) { if (threadIdx.x == 0) s_word = v; return kAll; }
+                    const uint32_t number = (uint32_t)__builtin_amdgcn_readlane((int)v, 1);
+                    if ((have & 2) && number != s_lists) {
+                        if (threadIdx.x == 0) { s_lists = number; s_heard = ticks(); }
+                        // (a next list may be on its way over this one: then it is another word of those missing, or none)
+                        const bool there = board_read(bd, area + kListAt + me % (number & 0xFFFFu), v);
+                        v = (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+                        if (__any(there) && v < n) return v;
+                    }
+                    __builtin_amdgcn_s_sleep(2);
+                }
+                return kNone;
+            });
+        if (!all) return s_word;
+    }
     m = group_max<THREADS>(m);
-    if (led && leader && threadIdx.x == 0) board_post(bd, result, m);
+    if (led && leader && threadIdx.x == 0) board_post(bd, area, m);
     return m;
 }
 
@@ -156,8 +260,8 @@ resident_rows(QArgs a, Board bd, uint32_t upr, uint32_t units, uint32_t P, uint3
 // Words that fold_group uses.
 int64_t board_words(const QArgs& q, int64_t P)
 {
-    const int64_t inner = std::min(q.inner, q.batch), runs = (q.batch + inner - 1) / inner;
-    return (runs + q.groups - 1) / q.groups * inner * q.groups * P + (q.groups * kLeaders + 1) * kLeaderWords;
+    const int64_t inner = std::min(q.inner, q.batch), runs = (q.batch + inner - 1) / inner, a_group = (runs + q.groups - 1) / q.groups * inner * P;
+    return a_group * q.groups + (a_group > kDirect ? 16 + q.groups * kLeaders * (kListAt + a_group + 15) : 0);
 }
 
 struct RowsPlan { int variant; uint32_t upr, units, P; unsigned blocks; uint32_t words; };
@@ -179,7 +283,7 @@ template <typename T, int MODE> bool plan_rows(const QArgs& q, RowsPlan* pl)
         const int64_t slice = r.threads * (r.bytes / (int64_t)(kUnit * sizeof(T)));
         const int64_t P = (units + slice - 1) / slice, blocks = P * q.batch;
         const int64_t words = board_words(q, P);
-        if (blocks > (int64_t)r.per_cu * cus || words > kBoardMax) continue;
+        if (blocks > std::min<int64_t>(r.per_cu * cus, kMaxWords) || words > kBoardMax) continue;
         *pl = RowsPlan{i, (uint32_t)upr, (uint32_t)units, (uint32_t)P, (unsigned)blocks, (uint32_t)words};
         return true;
     }
@@ -243,16 +347,25 @@ resident_cols(QArgs a, Board bd, uint32_t strips, uint32_t tiles_k, uint32_t P)
         }
     };
     // a thread's RT rows of a tile (rows past the last one are the last one again; columns past the last one are zero)
-    auto load = [&](uint32_t mb, uint32_t strip, int64_t k0, u32x4 (&w)[RT]) {
+    auto load = [&](uint32_t mb, uint32_t strip, int64_t k0, auto&& each) {
         const int64_t n = (int64_t)strip * kStrip + tn * V, k = min(k0 + tk * RT, K - 1);
         const int left = (int)max((int64_t)0, min((int64_t)V, N - n)), last = (int)min(K - 1 - k, (int64_t)(RT - 1));
         const T* base = static_cast<const T*>(a.x) + mb * a.batch_stride + k * a.row_stride + n;
         if (left == V) {
-#pragma unroll
-            for (int i = 0; i < RT; ++i) w[i] = load_columns<T, V>(base + min(i, last) * a.row_stride, V);
+            each([&](int i) { return load_columns<T, V>(base + min(i, last) * a.row_stride, V); });
+        } else if (sizeof(T) == 2 && left > 1 && N >= V) {
+            // the last columns: a vector that ends with the row, moved down.  Element by element it is a chain of loads: 64 matrices of
+            // 500 x 500 24.5 us, and 28 to 34 as the compiler took the code around it, against 21.9.  (Chains of up to three, for
+            // binary32, are the shorter way: 16 matrices of 1001 x 503 13.1 against 14.5.)
+            const int s = (V - left) * (int)sizeof(T) * 8;
+            each([&](int i) {
+                const u32x4 v = load_columns<T, V>(base + min(i, last) * a.row_stride - (V - left), V);
+                const uint64_t lo = v[0] | (uint64_t)v[1] << 32, hi = v[2] | (uint64_t)v[3] << 32;
+                const uint64_t down = s < 64 ? lo >> s | hi << (64 - s) : hi >> (s - 64), up = s < 64 ? hi >> s : 0;
+                return u32x4{(uint32_t)down, (uint32_t)(down >> 32), (uint32_t)up, (uint32_t)(up >> 32)};
+            });
         } else {
-#pragma unroll
-            for (int i = 0; i < RT; ++i) w[i] = load_columns<T, V>(base + min(i, last) * a.row_stride, left);
+            each([&](int i) { return load_columns<T, V>(base + min(i, last) * a.row_stride, left); });
         }
     };
     u32x4 w[S][RT];
@@ -261,7 +374,10 @@ resident_cols(QArgs a, Board bd, uint32_t strips, uint32_t tiles_k, uint32_t P)
 #pragma unroll
         for (int i = 0; i < RT; ++i) w[t][i] = u32x4{0u, 0u, 0u, 0u};
         uint32_t strip; int64_t k0;
-        if (tile_at(p, t, strip, k0)) load(b, strip, k0, w[t]);
+        if (tile_at(p, t, strip, k0)) load(b, strip, k0, [&](auto row) {
+#pragma unroll
+            for (int i = 0; i < RT; ++i) w[t][i] = row(i);
+        });
     }
     VecMax<T> mm;
 #pragma unroll
@@ -274,15 +390,17 @@ resident_cols(QArgs a, Board bd, uint32_t strips, uint32_t tiles_k, uint32_t P)
         for (int t = 0; t < S; ++t) {
             uint32_t strip; int64_t k0;
             if (!tile_at(slice, t, strip, k0)) break;
-            u32x4 x[RT];
-            load(mb, strip, k0, x);
-#pragma unroll
-            for (int i = 0; i < RT; ++i) o.fold(x[i]);
+            // (row by row: w stays in registers meanwhile)
+            load(mb, strip, k0, [&](auto row) {
+#pragma unroll 1
+                for (int i = 0; i < RT; ++i) o.fold(row(i));
+            });
         }
         return o;
     };
     if constexpr (PER_COLUMN) {
         // the maxima of a slice's columns, in s_col
+        static_assert(kStrip == kWave, "a wavefront reads a slice's words");
         auto columns_max = [&](VecMax<T> o) {
             if (threadIdx.x < kStrip) s_col[threadIdx.x] = 0;
             __syncthreads();
@@ -315,18 +433,25 @@ resident_cols(QArgs a, Board bd, uint32_t strips, uint32_t tiles_k, uint32_t P)
                 if (board_wait(bd, word(k), start, v)) m = max(m, v); else missing = true;
             }
         }
-        if (__syncthreads_or(missing)) {
-            for (uint32_t i = 0, k = kp; i < per_strip; ++i, k = k + 1 == per_strip ? 0 : k + 1) {
-                uint32_t v = 0;
-                const bool none = q == 0 && col < N && !board_read(bd, word(k), v);
-                if (__syncthreads_or(none)) {
+        if (__builtin_expect(__syncthreads_or(missing), 0)) {
+            // (a wavefront reads the words of a slice, one column a lane)
+            collect<THREADS>(per_strip, kp, min(kIdle, bd.patience), false,
+                [&](uint8_t* left) {
+                    for (uint32_t k = q; k < per_strip; k += Q) {
+                        if (!left[k]) continue;
+                        uint32_t v = 0;
+                        const bool there = col >= N || board_read(bd, word(k), v);
+                        if (there) m = max(m, v);
+                        if (__all(there) && c == 0) left[k] = 0;
+                    }
+                },
+                [&](uint32_t k) {
                     columns_max(slice_max(b, strip * per_strip + k));
-                    v = s_col[c];
+                    const uint32_t v = s_col[c];
                     if (q == 0 && col < N) board_post(bd, word(k), v);
-                    __syncthreads();
-                }
-                m = max(m, v);
-            }
+                    m = max(m, v);
+                },
+                [](auto) {}, [] { return kNone; });
         }
         s_fold[q][c] = m;
         __syncthreads();
@@ -409,7 +534,7 @@ template <typename T, int MODE> bool plan_cols(const QArgs& q, ColsPlan* pl)
         const int64_t tiles_k = (q.rows + c.threads / 2 - 1) / (c.threads / 2);
         const int64_t P = q.channels > 1 ? strips * ((tiles_k + c.tiles - 1) / c.tiles) : (strips * tiles_k + c.tiles - 1) / c.tiles;
         const int64_t blocks = P * q.batch, words = q.channels > 1 ? P / strips * q.cols * q.batch : board_words(q, P);
-        if (blocks > (int64_t)per_cu * cus || words > kBoardMax || (MODE != QMM_ROUND_RTNE && blocks < 64) || tiles_k > 0x7FFFFFFF) continue;
+        if (blocks > std::min<int64_t>(per_cu * cus, kMaxWords) || words > kBoardMax || (MODE != QMM_ROUND_RTNE && blocks < 64) || tiles_k > 0x7FFFFFFF) continue;
         *pl = ColsPlan{i, (uint32_t)strips, (uint32_t)tiles_k, (uint32_t)P, (unsigned)blocks, (uint32_t)words};
         return true;
     }

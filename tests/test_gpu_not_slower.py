@@ -48,11 +48,63 @@ def scale_call(x, **kw):
 
 
 # The workgroups of a long pass end more than 50 us apart: a folding workgroup that waited no longer began to read the
-# others' slices again, alone (16 GB: 1.23 times the separate launches; now 1.0).
+# others' slices again, alone (8 GB: 1.32 times the separate launches; now 1.0).
 def test_step_size_of_many_gigabytes():
-    x = torch.empty((1, 1 << 21, 4096), dtype=torch.bfloat16, device=DEV).normal_()
+    x = torch.empty((1, 1 << 20, 4096), dtype=torch.bfloat16, device=DEV).normal_()
     x[0, 12345, 77] = -300.0
     call, out = scale_call(x)
-    ratio = eager_over_recorded(call, 3)
+    ratio = max(eager_over_recorded(call, 10) for _ in range(2))
     assert float(out) == torch.tensor(300.0 / 448.0).item()
     assert ratio < 1.1, ratio
+
+
+def side_by_side(a, na, b, nb, reps=5):
+    """Time until na calls of `a` on one stream and nb of `b` on another are done over what they take one after the other."""
+    sa, sb = torch.cuda.Stream(), torch.cuda.Stream()
+
+    def both():
+        torch.cuda.synchronize()
+        e0, ea, eb = (torch.cuda.Event(enable_timing=True) for _ in range(3))
+        e0.record(sa)
+        sb.wait_event(e0)
+        for i in range(max(na, nb)):
+            if i < na:
+                with torch.cuda.stream(sa):
+                    a()
+            if i < nb:
+                with torch.cuda.stream(sb):
+                    b()
+        ea.record(sa), eb.record(sb)
+        torch.cuda.synchronize()
+        return max(e0.elapsed_time(ea), e0.elapsed_time(eb)) * 1e3
+    alone = na * microseconds(a, na) + nb * microseconds(b, nb)
+    both()
+    return statistics.median(both() for _ in range(reps)) / alone
+
+
+# Calls whose workgroups wait for one another, planned for the whole chip, beside other work that holds part of it: found and formed
+# what does not come, results as ever.  (Two of them side by side took 2 to 30 times what they take in turn, one beside a product of half
+# the CUs 2 to 4 times; now 1.0 and 1.1 to 1.3.)
+@pytest.mark.parametrize("axis,shape,kw", [(1, (1, 16384, 1024), {}), (0, (1, 16384, 1024), {}), (1, (512, 512, 64), dict(batch_groups=16)),
+                                           (0, (1, 4096, 3072), dict(per_channel=True))])
+def test_scale_quantize_beside_other_work(axis, shape, kw):
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    x = torch.randn(shape, generator=gen, device=DEV).bfloat16()
+    other = torch.randn((1, 16384, 1024), generator=gen, device=DEV).bfloat16()
+    want_d = qmm.scale(x, axis, qmm.E4M3, **kw)
+    want_c = qmm.quantize(x, axis, qmm.E4M3, want_d, **kw)
+    one = torch.ones(1, device=DEV)
+    a, b = ((t, qmm.operand(t, qmm.E4M3, one)) for t in (torch.randint(0, 100, (1, r, 8192), dtype=torch.uint8, device=DEV) for r in (2048, 4096)))
+    y = torch.empty((1, 2048, 4096), dtype=torch.bfloat16, device=DEV)
+    got = []
+
+    def call():
+        got.append(qmm.scale_quantize(x, axis, qmm.E4M3, **kw))
+        if len(got) > 4:
+            got.pop(0)
+    for name, work, n in (("another call", lambda: qmm.scale_quantize(other, 1, qmm.E4M3), 40), ("a product", lambda: qmm.gemm(a, b, out=y), 20)):
+        ratio = side_by_side(work, n, call, 40)
+        torch.cuda.synchronize()
+        for c, d in got:
+            assert torch.equal(d, want_d) and torch.equal(c, want_c), name
+        assert ratio < 2.0, (name, ratio)

@@ -28,7 +28,7 @@ struct QArgs {
     int64_t P;
     int fold_total;
     float qmax;
-    int streaming;         // quantize_rows_bf16x16: streaming stores of the codes
+    int streaming;         // quantize_rows_bf16x16: streaming stores of the codes (host: allowed, the scale pass has just read the tensor)
 };
 
 // A 16-byte vector of a tensor: 8 bfloat16 or 4 binary32 elements.

@@ -516,12 +516,15 @@ template <int FMT, int MODE, bool FOLD> qmm_status launch(const qmm_tensor* x, c
     const bool aligned = aligned16(x->data) && (q.row_stride % 8 == 0 || q.rows == 1) && (x->batch_stride % 8 == 0 || x->batch == 1);
     if (bf16 && aligned && (q.cols % 16 == 0) && aligned16(a.codes)) {
         const int64_t nv = q.rows * (q.cols / 16);
-        // Codes of many matrices that an XCD's L2 holds, half the memory-side cache and more in all (attention's probabilities): the product
-        // reads each from memory once, so they need not be kept, and the cache is left to what is being read and written around them.
-        // 512 matrices of 512 x 512, in the path of attention: the pass 59.2 / 56.4 us, the maximum of the next probabilities 62.0 / 54.4, V's
-        // pass 17.5 / 15.8, the product 35.6 / 36.4.  (One matrix of 67 MB of codes, which a product's tiles read several times: the pass
-        // the same, the product 51 / 55 us.)
-        q.streaming = q.batch > 1 && q.rows * q.cols <= (int64_t(1) << 20) && q.batch * q.rows * q.cols >= (int64_t(1) << 27);
+        // Codes of many matrices that an XCD's L2 holds, half the memory-side cache and more in all, behind the scale pass (a.streaming): that
+        // pass has filled the cache with the tensor, and codes that are kept push out what is being read.  Kept / streaming, both
+        // steps and the product that reads the codes, E4M3, matrices of 1024 x 1024, codes on the left of 64 columns and on the right of
+        // 64, 256 and 1024 rows: 64 matrices 72 / 75 us, 76 / 80, 82 / 86, 132 / 132; 96 of them 116 / 115, 125 / 124, 130 / 128, 201 / 195;
+        // 128 150 / 143, 155 / 149, 165 / 156, 268 / 255; 256 297 / 286, 305 / 297, 324 / 310, 505 / 501.  Of 512 x 512: 256 71 / 76 to
+        // 152 / 158; 384 118 / 120, 126 / 126, 135 / 131, 232 / 228; 512 155 / 151, 161 / 155, 180 / 171, 311 / 305; 2048 of 256 x 256 174 / 168,
+        // 175 / 170, 223 / 215, 477 / 470.  With step sizes that were there already the codes are better kept: quantize and product, 128
+        // of 1024 x 1024 94 / 103, 105 / 109, 113 / 116, 223 / 220.  One matrix of 67 MB of codes: the pass the same, the product 51 / 55.
+        q.streaming = a.streaming && q.batch > 1 && q.rows * q.cols <= (int64_t(1) << 20) && q.batch * q.rows * q.cols >= (int64_t(1) << 27);
         quantize_rows_bf16x16<FMT, MODE, FOLD><<<dim3((unsigned)((nv + kThreads - 1) / kThreads), (unsigned)x->batch), kThreads, 0, s>>>(q);
         return launch_status();
     }
@@ -700,6 +703,7 @@ extern "C" qmm_status qmm_scale_quantize(const qmm_tensor* x, qmm_format fmt, co
     st = scale_partials(x, fmt, g, delta_out, partial, fold, &pp, s);
     if (st != QMM_OK) return st;
     if (!pp.done && !fold) { st = scale_fold(pp, partial, fmt, g, delta_out, s); if (st != QMM_OK) return st; }
+    a.streaming = 1;
     if (fold && !pp.done) {
         a.partial = partial; a.P = pp.P; a.fold_total = (int)(pp.batch * pp.P);
         switch (fmt) {

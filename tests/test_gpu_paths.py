@@ -395,12 +395,14 @@ def test_metric_quotients_bit_for_bit():
         assert np.array_equal(got[:, 1, f], want)
 
 
-# Many matrices of 2^27 codes and more in all: the same codes, stored streaming.
+# Many matrices of 2^27 codes and more in all: the same codes, in one call with the step sizes stored streaming.
 def test_quantize_of_a_large_batch_equals_its_parts():
     x = torch.randn((513, 512, 512), generator=torch.Generator(device=DEV).manual_seed(5), device=DEV).bfloat16()
     d = qmm.scale(x, 1, qmm.E4M3, batch_groups=513)
     for mode in (qmm.RTNE, qmm.STOCHASTIC):
         c = qmm.quantize(x, 1, qmm.E4M3, d, batch_groups=513, mode=mode, seed=3)
+        both, d1 = qmm.scale_quantize(x, 1, qmm.E4M3, batch_groups=513, mode=mode, seed=3)
+        assert torch.equal(both, c) and torch.equal(d1, d), mode
         for lo, hi in ((0, 200), (200, 513)):
             part = qmm.quantize(x[lo:hi], 1, qmm.E4M3, d[lo:hi].clone(), batch_groups=hi - lo, mode=mode, seed=3, offset=lo * 512 * 512)
             assert torch.equal(c[lo:hi], part), (mode, lo)

@@ -46,13 +46,23 @@ _lib = None
 _short = None
 
 
+class _NoShortPath:
+    """Stands for a native short path that was not built: every call goes through ctypes."""
+    @staticmethod
+    def _decline(*_):
+        return None
+    scale_quantize = quantized_operand = gemm = metric = _decline
+
+
 def _host():
-    """Load the native short path (_qmm_host.so, built with libqmm.so).  Raises if it is absent."""
+    """Load the native short path (_qmm_host.so, built with libqmm.so).  It saves host time only: where it has not been built the
+    calls go through ctypes, to the same kernels; one that is there and cannot be loaded raises."""
     global _short
     if _short is None:
         lib()
         if not os.path.exists(HOST_PATH):
-            raise RuntimeError(f"{HOST_PATH} is missing: run `python -m paper_2408_02897_amd.build` first")
+            _short = _NoShortPath
+            return _short
         spec = importlib.util.spec_from_file_location("_qmm_host", HOST_PATH)
         module = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(module)

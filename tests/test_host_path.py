@@ -34,6 +34,21 @@ def test_declines_what_is_not_plain(host):
     assert host.metric(x, x.float(), None, None, None) is None and host.metric(x, 1, None, None, None) is None
 
 
+# A tree with libqmm.so alone: the calls go through ctypes.
+def test_does_without_the_short_path(host, monkeypatch):
+    monkeypatch.setattr(qmm, "HOST_PATH", qmm.HOST_PATH + ".none")
+    monkeypatch.setattr(qmm, "_short", None)
+    x = torch.zeros((4, 32), dtype=torch.bfloat16)
+    for call in (lambda: qmm.scale_quantize(x, 1, qmm.E4M3), lambda: qmm.quantized_operand(x, 1, qmm.E4M3)):
+        with pytest.raises(AssertionError):                  # (tensor_desc: not a device tensor)
+            call()
+    with pytest.raises(AssertionError):
+        qmm.metric(x, torch.zeros(5))
+    op = qmm.operand(x, qmm.E4M3, torch.ones(1))
+    with pytest.raises(AssertionError):
+        qmm.gemm((x, op), (x[:, :16], op))
+
+
 @pytest.mark.gpu
 def test_equals_the_ctypes_path(host, monkeypatch):
     class Off:

@@ -49,16 +49,23 @@ def build_host(force=False):
     import sysconfig
     import torch
     src = os.path.join(CSRC, "qmm_host.cpp")
-    if not force and os.path.exists(HOST) and all(os.path.getmtime(HOST) >= os.path.getmtime(d) for d in (src, os.path.join(ROOT, "include", "qmm.h"))):
-        return HOST
     t = os.path.dirname(torch.__file__)
     rocm = os.path.dirname(os.path.dirname(HIPCC))
     # (the HIP headers ask for their platform by this macro where hipcc is not the compiler)
-    subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-                    "-I", os.path.join(ROOT, "include"),
-                    *(a for d in (os.path.join(t, "include"), os.path.join(rocm, "include"), sysconfig.get_paths()["include"]) for a in ("-isystem", d)),
-                    src, "-o", HOST, "-L", HERE, "-lqmm", "-L", os.path.join(t, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
-                    "-Wl,-rpath,$ORIGIN"], check=True)
+    command = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+               "-I", os.path.join(ROOT, "include"),
+               *(a for d in (os.path.join(t, "include"), os.path.join(rocm, "include"), sysconfig.get_paths()["include"]) for a in ("-isystem", d)),
+               src, "-o", HOST, "-L", HERE, "-lqmm", "-L", os.path.join(t, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
+               "-Wl,-rpath,$ORIGIN"]
+    # built for one interpreter and one torch: another of either builds it again
+    stamp, made = os.path.join(OBJDIR, "_qmm_host.made"), "\n".join([sys.version, torch.__version__, *command])
+    if not force and os.path.exists(HOST) and os.path.exists(stamp) and open(stamp).read() == made and \
+            all(os.path.getmtime(HOST) >= os.path.getmtime(d) for d in (src, os.path.join(ROOT, "include", "qmm.h"))):
+        return HOST
+    subprocess.run(command, check=True)
+    os.makedirs(OBJDIR, exist_ok=True)
+    with open(stamp, "w") as f:
+        f.write(made)
     return HOST
 
 

@@ -108,3 +108,16 @@ def test_errors_are_those_of_the_ctypes_path(host):
     b, _ = qmm.quantized_operand(torch.zeros((4, 32), dtype=torch.bfloat16, device=DEV), 1, qmm.E4M3)
     with pytest.raises(AssertionError):
         qmm.gemm(a, b)
+
+
+# The short path is built against one torch: another one makes build_host compile again, the same one does not.
+def test_short_path_is_built_again_for_another_torch(tmp_path, monkeypatch):
+    from paper_2408_02897_amd import build
+    commands = []
+    monkeypatch.setattr(build, "HOST", str(tmp_path / "_qmm_host.so"))
+    monkeypatch.setattr(build, "OBJDIR", str(tmp_path / "obj"))
+    monkeypatch.setattr(build.subprocess, "run", lambda command, check: (commands.append(command), open(build.HOST, "w").close()))
+    for version, runs in (("1", 1), ("1", 1), ("2", 2)):
+        monkeypatch.setattr(torch, "__version__", version)
+        build.build_host()
+        assert len(commands) == runs

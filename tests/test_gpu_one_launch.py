@@ -64,6 +64,19 @@ FORMS = [
     ((1, 16384, 520), 0, dict(per_channel=True))]
 
 
+def fits(shape, axis, dense, dtype, mode):
+    """Whether the chip (256 CUs) holds one of FORMS: bytes of the rows, or tiles of 64 columns by 128 and 512 rows."""
+    b, r, c = shape
+    nearest, bf16 = mode == qmm.RTNE, dtype == torch.bfloat16
+    if axis == 1:
+        return b * r * c * (2 if bf16 else 4) <= (1 << 26 if nearest and (dense or r == 1) else 1 << 25)
+    strips = -(-c // 64)
+    small, large = b * strips * -(-r // 128), b * strips * -(-r // 512)
+    if not nearest:                                         # (few workgroups: a thread's generator blocks are what counts)
+        return 64 <= small <= 1024 or 64 <= large <= 256
+    return small <= 1024 or large <= (512 if bf16 else 256) or (bf16 and large <= 3 * 256)
+
+
 @pytest.mark.parametrize("mode", [qmm.RTNE, qmm.STOCHASTIC])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("pad,shift", [(0, 0), (8, 0), (0, 1)])
@@ -77,6 +90,7 @@ def test_equals_the_two_calls(shape, axis, kw, pad, shift, dtype, mode):
         want_c, want_d = two_calls(x, axis, fmt, mode, offset, kw)
         for patience in (FOREVER, 1, 0):                    # FOREVER is cut to the library's own patience; 1: leaders hand out lists
             taken, c, d = one_launch(x, axis, fmt, mode, offset, patience, kw)
+            assert taken == fits(shape, axis, pad == shift == 0, dtype, mode), patience
             if not taken:
                 continue
             assert torch.equal(d.view(torch.int32), want_d.view(torch.int32)), (fmt, patience)
@@ -117,6 +131,43 @@ def test_recorded_calls_replay_like_eager_ones():
             assert torch.equal(c, cw) and torch.equal(d, dw), seed
 
 
+# The separate launches, which recorded calls take: partial maxima folded by the quantize pass, by a kernel of their own, by the
+# workgroup that arrives last, in every form above, and the step sizes alone.  Three replays on changing values, the eager calls between.
+@pytest.mark.parametrize("mode", [qmm.RTNE, qmm.STOCHASTIC])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("pad,shift", [(0, 0), (8, 0), (0, 1)])
+def test_recorded_calls_of_every_form(pad, shift, dtype, mode):
+    forms = [(shape, axis, dict(kw, per_channel=pc)) for shape, axis, kw in FORMS for pc in {kw.get("per_channel", False), shape[1] * shape[2] < 1100000}]
+    forms += [((512, 33, 64), 1, dict(batch_groups=16)), ((4, 8, 64), 1, dict(batch_groups=8)), ((2, 600, 70), 0, dict(per_channel=True)),
+              ((3, 20, 9000), 1, dict(per_channel=True, batch_groups=3))]
+    xs = [tensor(shape, dtype, seed=sum(shape), pad=pad, shift=shift) for shape, _, _ in forms]
+    fmts = [(qmm.E4M3, qmm.INT8, qmm.E5M2)[i % 3] for i in range(len(forms))]
+
+    def calls():
+        return [(qmm.scale_quantize(x, axis, fmt, mode=mode, seed=77, offset=6 * (i % 2), **kw), qmm.scale(x, axis, fmt, **kw))
+                for i, (x, fmt, (_, axis, kw)) in enumerate(zip(xs, fmts, forms))]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        calls()
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = calls()
+    for replay in range(3):
+        for i, x in enumerate(xs):
+            x.mul_(-0.75)
+            x[-1, x.shape[1] // 2, x.shape[2] // 3] = (5.0e4, float("inf"), float("nan"))[(i + replay) % 3]
+        want = [two_calls(x, axis, fmt, mode, 6 * (i % 2), kw) for i, (x, fmt, (_, axis, kw)) in enumerate(zip(xs, fmts, forms))]
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for form, ((c, d), alone), (want_c, want_d) in zip(forms, got, want):
+            assert torch.equal(d.view(torch.int32), want_d.view(torch.int32)), (replay, form)
+            assert torch.equal(alone.view(torch.int32), want_d.view(torch.int32)), (replay, form)
+            assert torch.equal(c, want_c), (replay, form)
+
+
 def test_streams_that_share_the_ring_of_boards():
     xs = [tensor((1, 512 + 64 * i, 1024), torch.bfloat16, seed=i) * (i + 1) for i in range(6)]
     want = [two_calls(x, 1, qmm.E4M3, qmm.RTNE, 0, {}) for x in xs]
@@ -133,7 +184,7 @@ def test_streams_that_share_the_ring_of_boards():
 
 
 def test_calls_beyond_the_length_of_the_ring():
-    x = tensor((1, 16384, 520), torch.bfloat16, seed=9)     # 32 maxima a column: 126 calls to the ring's end
+    x = tensor((1, 16384, 520), torch.bfloat16, seed=9)     # 32 maxima a column: 63 calls to the ring's end
     want = two_calls(x, 0, qmm.E4M3, qmm.RTNE, 0, dict(per_channel=True))
     for i in range(300):
         c, d = qmm.scale_quantize(x, 0, qmm.E4M3, per_channel=True)

@@ -125,6 +125,43 @@ def test_scale_and_quantize_of_every_form(batch, rows, cols, groups, inner, form
                 assert torch.equal(d1.view(torch.int32), d.view(torch.int32)) and torch.equal(c1, c), (fmt, axis, per_channel)
 
 
+# The same forms recorded into a graph, where the single call is made of separate launches that the calls above no longer take: every
+# replay against the oracle.
+@pytest.mark.parametrize("mode", [qmm.RTNE, qmm.STOCHASTIC])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("form", ["dense", "sliced", "shifted", "offset"])
+def test_recorded_scale_quantize_of_every_form(form, dtype, mode):
+    shapes = [(1, 1, 1, 1, 1), (1, 5, 7, 1, 1), (1, 129, 65, 1, 1), (1, 3, 2048, 1, 1), (1, 2, 4100, 1, 1), (1, 3, 8200, 1, 1), (1, 4230, 33, 1, 1),
+              (1, 300, 1031, 1, 1), (6, 40, 72, 3, 1), (6, 70, 96, 3, 2), (4, 33, 50, 4, 1), (2, 20, 40, 5, 1), (12, 130, 64, 4, 1)]
+    xs = [tensor_form(form, r, c, b, dtype, seed=r * 7 + c) for b, r, c, _, _ in shapes]
+    cases = [(x, fmt, axis, pc, groups, inner) for x, (_, _, _, groups, inner) in zip(xs, shapes) for fmt in (qmm.E4M3, qmm.INT8)
+             for axis in (0, 1) for pc in (False, True)]
+
+    def calls():
+        return [qmm.scale_quantize(x, axis, fmt, mode=mode, seed=77, per_channel=pc, batch_groups=groups, batch_inner=inner)
+                for x, fmt, axis, pc, groups, inner in cases]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        calls()
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = calls()
+    for replay in range(3):
+        for x in xs:
+            x.mul_(-0.75)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        host = {id(x): x.float().cpu().numpy() for x in xs}
+        for (x, fmt, axis, pc, groups, inner), (c, d) in zip(cases, got):
+            want_d = O.scale(host[id(x)], axis, fmt, pc, groups, inner)
+            want_c = O.quantize(host[id(x)], axis, fmt, want_d, pc, groups, mode, 77, 0, inner)
+            assert np.array_equal(d.cpu().numpy().view(np.uint32), want_d.view(np.uint32)), (replay, x.shape, fmt, axis, pc)
+            assert np.array_equal(c.cpu().numpy(), want_c), (replay, x.shape, fmt, axis, pc)
+
+
 # Sizes where the single call changes its way: partial maxima folded by the quantize pass (up to 1024 of a group) or not, the
 # large tensors' one-launch maximum (2^24 elements), empty tensors, groups without a matrix, NaN and infinity.
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])

@@ -161,8 +161,10 @@ QMM_DEV float delta_from_absmax_bits(uint32_t bits, float qmax)
 // write-back: 3 us for 16 MB of codes written in a kernel's last phase (16384 x 1024 bfloat16, scale + quantize 17.0 -> 14.9 us).
 // A streaming (nontemporal) store leaves as early but is not kept by the memory-side cache: the same codes made the
 // product that reads them several times slower (16384 x 4096 x 1024: 60 -> 75 us).
-// For whole lines only: a line that leaves in pieces (rows off a line's boundary, a tile's part of one) is a write to memory per
-// piece.  64 matrices of 1000 x 1000 transposed: quantize 40 us by the L2, 54 past it; 300000 x 20 per row 16.7 / 28.2.
+// For lines that leave whole, or nearly: one that leaves in pieces (a product's ragged rows, a tile's part of a row) is a write to memory
+// per piece.  64 matrices of 1000 x 1000 transposed: quantize_cols 40 us by the L2, 54 past it; quantize_rows, 300000 x 20 per row,
+// 16.7 / 28.2.  Where a wavefront's 16-byte stores follow one another through memory, rows off a line's boundary do no harm: the
+// one-launch kernels' codes (see resident_cols), dequantized rows (16384 x 1031 to bfloat16 11.1 / 10.2, 300000 x 20 6.4 / 5.3).
 // ---------------------------------------------------------------------------
 template <typename V> QMM_DEV void store_through(void* p, V v)
 {

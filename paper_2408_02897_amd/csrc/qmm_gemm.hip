@@ -146,7 +146,7 @@ template <typename AccT, int NI, int NJ> QMM_DEV void pin_accumulators(AccT (&ac
 // odd): one store instruction all the same, global memory takes vector stores at any element boundary.
 // THROUGH: past the L2 at once (store_through), which pays where a kernel's outputs all leave in its last phase and in whole lines:
 // gemm_kernel to binary32, E4M3 4096 x 768 x 768 11.1 -> 9.8 us (not INT8, see there); the partial sums of 768 x 3072 x 4096 16.3 -> 14.9, of
-// 3072 x 1024 x 16384 53.2 -> 52.3; gemm_direct_kernel 36.5 -> 35.4.  Not for bfloat16 and edge tiles (40000 x 640 x 512 E4M3 27.3 by the L2,
+// 3072 x 1024 x 16384 53.2 -> 52.3; of gemm_direct_kernel the bfloat16 ones, 36.5 -> 35.4.  Else not for bfloat16 and edge tiles (40000 x 640 x 512 E4M3 27.3 by the L2,
 // 31.9 past it), not in gemm_deep_kernel, whose few outputs the L2 takes faster (256 x 768 x 768 6.8 against 7.4 us), and not in
 // the split sums' second kernel.
 template <int T, bool THROUGH = false> QMM_DEV void store_f32(float* dst, const float (&v)[T])

@@ -319,6 +319,10 @@ constexpr int kStrip = 64;                               // columns of a workgro
 // A slice: S tiles of THREADS / 2 rows by 64 columns of a matrix (one step size per scale group: S tiles that follow one
 // another strip by strip; per column: of one strip).  The codes of a tile are transposed through LDS, 16 bytes at a time
 // as in quantize_cols.
+// They leave past the L2 where a code row is a line and more, whatever its alignment (by the L2 / past it: 16400 rows of 1024 20.2 /
+// 18.8 us, 512 matrices of 136 x 64 10.0 / 9.2, of 250 x 64 11.4 / 10.5), and where shorter rows have no remainder (1024 matrices of
+// 112 x 64 10.5 / 9.6); a remainder is written in bytes, and the lines of short rows would all leave in parts (of 127 x 64 11.2 / 13.2,
+// binary32 14.4 / 16.4, of 120 x 64 10.8 / 10.9).
 template <typename T, int FMT, int MODE, int THREADS, int S, bool PER_COLUMN, int WAVES> __global__ void __launch_bounds__(THREADS, WAVES)
 resident_cols(QArgs a, Board bd, uint32_t strips, uint32_t tiles_k, uint32_t P)
 {
@@ -510,8 +514,9 @@ resident_cols(QArgs a, Board bd, uint32_t strips, uint32_t tiles_k, uint32_t P)
             if (nn >= N || kk >= K) continue;
             uint8_t* dst = a.codes + ((int64_t)b * N + nn) * K + kk;
             const u32x4 codes = *reinterpret_cast<const u32x4*>(&tile[place(row, at)]);
-            if (kk + 16 <= K) store_through(dst, codes);
-            else store_bytes<16>(dst, codes, (int)(K - kk));
+            if (kk + 16 <= K) {
+                if (K >= 128 || K % 16 == 0) store_through(dst, codes); else *reinterpret_cast<u32x4_byte*>(dst) = codes;
+            } else store_bytes<16>(dst, codes, (int)(K - kk));
         }
         if (t + 1 < S) __syncthreads();
     }

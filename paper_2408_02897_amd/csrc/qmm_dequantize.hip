@@ -35,6 +35,7 @@ struct DArgs {
     int64_t groups; int64_t inner;    // matrix -> scale group (neither above the number of matrices)
     int64_t units;                    // pieces of work for one wavefront
     int64_t pieces;                   // long lines: units per line
+    int through;                      // the values go past the L2 (store_through)
     int lane_shift, half_shift;       // short lines: 1 << lane_shift lanes a line, in 1 << half_shift halves
 };
 
@@ -130,8 +131,8 @@ dequantize_lines(DArgs a)
                 } else o[q] = __float_as_uint(y[q]);
             }
             if (left[i] >= V) {
-                if constexpr (OUT_BF16) store_through(static_cast<uint16_t*>(a.out) + at[i], o);
-                else store_through(static_cast<float*>(a.out) + at[i], o);
+                void* dst = static_cast<uint8_t*>(a.out) + at[i] * (16 / V);
+                if (a.through) store_through(dst, o); else *static_cast<u32x4_any*>(dst) = o;
             } else if (left[i] > 0) {
 #pragma unroll
                 for (int e = 0; e < V; ++e)
@@ -148,6 +149,11 @@ template <int FMT, bool BF16> qmm_status launch(DArgs a, hipStream_t s)
 {
     constexpr int V = BF16 ? 8 : 4;
     const int64_t nvec = (a.K + V - 1) / V;
+    // Past the L2 where the lines are whole (by the L2 / past it: 65536 x 1024 a step size per row, bfloat16 36.1 / 35.2 us, binary32
+    // 57.8 / 55.4), and up to 48 MB where they are not (16384 x 1031
+    // bfloat16 10.7 / 9.9, 300000 x 20 binary32 8.2 / 6.5, 100000 x 129 14.1 / 12.6; at 48 MB 13.7 / 13.7 to 15.1 / 15.2, 57 MB 18.5 / 19.8);
+    // beyond, memory takes a line's parts one by one (65536 x 1031 38.6 / 43.0 and 63.7 / 74.6, 300000 x 129 binary32 42.4 / 54.1).
+    a.through = in_lines(a.out, a.lines > 1 ? a.K * (16 / V) : 0) || a.lines * a.K * (16 / V) <= (int64_t)48 << 20;
     const bool is_short = nvec <= 2 * kWave && a.lines > 1;
     int64_t slots, slots_per_line = (nvec + kWave - 1) / kWave;                     // wavefront-wide rows of vectors
     if (is_short) {

@@ -164,7 +164,7 @@ QMM_DEV float delta_from_absmax_bits(uint32_t bits, float qmax)
 // For lines that leave whole, or nearly: one that leaves in pieces (a product's ragged rows, a tile's part of a row) is a write to memory
 // per piece.  64 matrices of 1000 x 1000 transposed: quantize_cols 40 us by the L2, 54 past it; quantize_rows, 300000 x 20 per row,
 // 16.7 / 28.2.  Where a wavefront's 16-byte stores follow one another through memory, rows off a line's boundary do no harm: the
-// one-launch kernels' codes (see resident_cols), dequantized rows (16384 x 1031 to bfloat16 11.1 / 10.2, 300000 x 20 6.4 / 5.3).
+// one-launch kernels' codes (see resident_cols), dequantized rows up to 48 MB (dequantize_lines).
 // ---------------------------------------------------------------------------
 template <typename V> QMM_DEV void store_through(void* p, V v)
 {
@@ -436,6 +436,8 @@ qmm_status scale_fold(const ScalePartials& pp, const uint32_t* partial, qmm_form
 // Both steps in one launch (qmm_resident.hip), for the calls it is for.
 qmm_status scale_quantize_resident(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g, qmm_round mode, uint64_t seed,
                                    uint64_t offset, float* delta, uint8_t* codes, uint32_t patience, hipStream_t s, bool* taken);
+// Runs of contiguous output that are whole lines: `p` starts one, and `bytes` from one run's start to the next are a multiple (0: one run).
+inline bool in_lines(const void* p, int64_t bytes) { return ((reinterpret_cast<uintptr_t>(p) | (uint64_t)bytes) & 127u) == 0; }
 inline float host_qmax(qmm_format fmt) { return fmt == QMM_FMT_INT8 ? 127.0f : (fmt == QMM_FMT_E4M3 ? 448.0f : 57344.0f); }
 
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }

@@ -150,3 +150,21 @@ def test_short_ragged_code_rows():
         return statistics.median(t[0] for t in times) / statistics.median(t[1] for t in times)
     ratio()
     assert min(ratio() for _ in range(3)) < 1.2
+
+
+# Dequantized rows off a line's boundary, beyond what the caches merge past the L2: 1031 values a row over 1024
+# (past the L2 1.35, now 1.15).
+def test_large_ragged_values():
+    codes = {k: [torch.randint(0, 100, (1, 65536, k), dtype=torch.uint8, device=DEV) for _ in range(3)] for k in (1024, 1031)}
+    out = {k: [torch.empty((1, 65536, k), device=DEV) for _ in range(3)] for k in codes}
+    d = torch.rand(65536, device=DEV)
+
+    def call(k):
+        for c, o in zip(codes[k], out[k]):
+            qmm.dequantize(c, qmm.E4M3, d, True, 1, out=o)
+
+    def ratio():
+        times = [(microseconds(lambda: call(1031), 10), microseconds(lambda: call(1024), 10)) for _ in range(7)]
+        return statistics.median(t[0] for t in times) / statistics.median(t[1] for t in times)
+    ratio()
+    assert min(ratio() for _ in range(3)) < 1.25

@@ -29,6 +29,7 @@ struct QArgs {
     int fold_total;
     float qmax;
     int streaming;         // quantize_rows_bf16x16: streaming stores of the codes (host: allowed, the scale pass has just read the tensor)
+    int through;           // quantize_rows_bf16x16: the codes go past the L2 (store_through)
 };
 
 // A 16-byte vector of a tensor: 8 bfloat16 or 4 binary32 elements.

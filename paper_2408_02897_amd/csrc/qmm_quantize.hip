@@ -99,7 +99,8 @@ quantize_rows_bf16x16(QArgs a)
         out = u32x4{c[0], c[1], c[2], c[3]};
     }
     if (a.streaming) __builtin_nontemporal_store(out, reinterpret_cast<u32x4*>(a.codes + p0));
-    else store_through(a.codes + p0, out);
+    else if (a.through) store_through(a.codes + p0, out);
+    else *reinterpret_cast<u32x4*>(a.codes + p0) = out;
 }
 
 // Row-contracting, any type, extent, stride and alignment.  A wavefront takes PIECE 16-byte vectors a lane: a piece of a
@@ -524,7 +525,11 @@ template <int FMT, int MODE, bool FOLD> qmm_status launch(const qmm_tensor* x, c
         // 152 / 158; 384 118 / 120, 126 / 126, 135 / 131, 232 / 228; 512 155 / 151, 161 / 155, 180 / 171, 311 / 305; 2048 of 256 x 256 174 / 168,
         // 175 / 170, 223 / 215, 477 / 470.  With step sizes that were there already the codes are better kept: quantize and product, 128
         // of 1024 x 1024 94 / 103, 105 / 109, 113 / 116, 223 / 220.  One matrix of 67 MB of codes: the pass the same, the product 51 / 55.
-        q.streaming = a.streaming && q.batch > 1 && q.rows * q.cols <= (int64_t(1) << 20) && q.batch * q.rows * q.cols >= (int64_t(1) << 27);
+        const int64_t matrix = q.rows * q.cols;
+        q.streaming = a.streaming && q.batch > 1 && matrix <= (int64_t(1) << 20) && q.batch * matrix >= (int64_t(1) << 27);
+        // Past the L2, matrices off a line's boundary in calls of up to 32 MB only (by the L2 / past it: 300 matrices of 100016 codes 16.5 / 16.0
+        // us, 40 of 1000016 23.1 / 23.2, 64 of them 35.8 / 36.8, 128 68.5 / 74.0; of whole lines, 64 of 1048576, 36.3 / 35.5).
+        q.through = in_lines(q.codes, q.batch > 1 ? matrix : 0) || q.batch * matrix <= (int64_t)32 << 20;
         quantize_rows_bf16x16<FMT, MODE, FOLD><<<dim3((unsigned)((nv + kThreads - 1) / kThreads), (unsigned)x->batch), kThreads, 0, s>>>(q);
         return launch_status();
     }

@@ -533,13 +533,21 @@ template <typename T, int MODE> bool plan_cols(const QArgs& q, ColsPlan* pl)
     for (int i = 0; i < (int)(sizeof(kCols) / sizeof(kCols[0])); ++i) {
         const ColsVariant& c = kCols[i];
         // Stochastic rounding and binary32, which takes twice the registers a tile, spill with more than one tile (binary32 4096 x 3072
-        // per column 24.4 / 24.9 us), and with few workgroups a thread's generator blocks are what counts (2048 x 64 6.9 / 7.6).
+        // per column 24.4 / 24.9 us).
         if (c.tiles > (MODE != QMM_ROUND_RTNE || sizeof(T) == 4 ? 1 : 3)) continue;
         const int per_cu = c.threads == 1024 && c.tiles == 1 && (MODE != QMM_ROUND_RTNE || sizeof(T) == 4) ? 1 : c.per_cu;
         const int64_t tiles_k = (q.rows + c.threads / 2 - 1) / (c.threads / 2);
         const int64_t P = q.channels > 1 ? strips * ((tiles_k + c.tiles - 1) / c.tiles) : (strips * tiles_k + c.tiles - 1) / c.tiles;
         const int64_t blocks = P * q.batch, words = q.channels > 1 ? P / strips * q.cols * q.batch : board_words(q, P);
-        if (blocks > std::min<int64_t>(per_cu * cus, kMaxWords) || words > kBoardMax || (MODE != QMM_ROUND_RTNE && blocks < 64) || tiles_k > 0x7FFFFFFF) continue;
+        if (blocks > std::min<int64_t>(per_cu * cus, kMaxWords) || words > kBoardMax || tiles_k > 0x7FFFFFFF) continue;
+        // Per column every workgroup of a strip reads the maxima of all: of the small tiles' no more than 40, and no fewer than 32 workgroups of
+        // the large (bfloat16, 64 columns, separate launches / small tiles / large ones: 4096 rows 7.3 / 7.1 / 7.9 us, 8192 7.5 / 9.8 / 7.9, 16384
+        // 8.3 / 14.6 / 8.4, 65536 18.7 / 46.5 / 10.5, 128000 24.3 / 92.5 / 15.5; 256 columns, 4096 8.1 / 7.4 / 8.0, 16384 14.2 / 16.9 / 8.8; binary32
+        // 128000 x 64 28.6 / 92.5 / 16.4).
+        const int64_t waits = q.channels > 1 ? P / strips : 0;
+        if (waits > 0 && (i == 0 ? waits > 40 : blocks < 32)) continue;
+        // Stochastic rounding: with few workgroups a thread's generator blocks are what counts (2048 x 64 6.9 / 7.6).
+        if (MODE != QMM_ROUND_RTNE && blocks < 64) continue;
         *pl = ColsPlan{i, (uint32_t)strips, (uint32_t)tiles_k, (uint32_t)P, (unsigned)blocks, (uint32_t)words};
         return true;
     }

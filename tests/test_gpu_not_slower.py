@@ -170,3 +170,16 @@ def test_large_ragged_outputs(call, whole, ragged, bound):
         return statistics.median(t[0] for t in times) / statistics.median(t[1] for t in times)
     ratio()
     assert min(ratio() for _ in range(3)) < bound
+
+
+# Step sizes per column of a tall tensor: every workgroup of a strip reads the maxima of all (separate launches 24 us, by way of a
+# thousand small workgroups 92, of 250 large ones 16).
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_step_sizes_per_column_of_a_tall_tensor(dtype):
+    xs = [torch.randn((1, 128000, 64), device=DEV).to(dtype) for _ in range(3)]
+    keep = [None] * 4
+
+    def call():
+        for i, x in enumerate(xs):
+            keep[i] = qmm.scale_quantize(x, 0, qmm.E4M3, per_channel=True)
+    assert eager_over_recorded(call, 10) < 1.2

@@ -61,20 +61,31 @@ FORMS = [
     ((1, 16384, 1032), 0, {}), ((12, 130, 64), 0, dict(batch_groups=4)), ((7, 70, 96), 0, dict(batch_groups=3, batch_inner=2)), ((5, 513, 70), 0, {}),
     ((1, 4230, 33), 0, dict(per_channel=True)), ((1, 129, 65), 0, dict(per_channel=True)), ((1, 3, 5), 0, dict(per_channel=True)),
     ((1, 1031, 1001), 0, dict(per_channel=True)), ((3, 600, 200), 0, dict(per_channel=True, batch_groups=3)), ((1, 6000, 2000), 0, dict(per_channel=True)),
-    ((1, 16384, 520), 0, dict(per_channel=True))]
+    ((1, 16384, 520), 0, dict(per_channel=True)), ((1, 4097, 40), 0, dict(per_channel=True)), ((1, 70001, 70), 0, dict(per_channel=True)),
+    ((2, 9000, 130), 0, dict(per_channel=True, batch_groups=2))]
 
 
-def fits(shape, axis, dense, dtype, mode):
-    """Whether the chip (256 CUs) holds one of FORMS: bytes of the rows, or tiles of 64 columns by 128 and 512 rows."""
+def fits(shape, axis, dense, dtype, mode, offset, per_channel, groups):
+    """Whether one of FORMS is for the one launch on 256 CUs: bytes of the rows; tiles of 64 columns by 128 or 512 rows, of which a column
+    has few small ones and the tensor enough large ones, and for stochastic rounding enough workgroups."""
     b, r, c = shape
     nearest, bf16 = mode == qmm.RTNE, dtype == torch.bfloat16
     if axis == 1:
         return b * r * c * (2 if bf16 else 4) <= (1 << 26 if nearest and (dense or r == 1) else 1 << 25)
     strips = -(-c // 64)
-    small, large = b * strips * -(-r // 128), b * strips * -(-r // 512)
-    if not nearest:                                         # (few workgroups: a thread's generator blocks are what counts)
-        return 64 <= small <= 1024 or 64 <= large <= 256
-    return small <= 1024 or large <= (512 if bf16 else 256) or (bf16 and large <= 3 * 256)
+
+    def serves(blocks, waits, most):
+        if nearest:
+            return blocks <= most
+        return 64 <= blocks <= most
+    down = {rows: -(-r // rows) for rows in (128, 512)}
+    blocks = {rows: b * strips * n for rows, n in down.items()}
+    waits = {rows: n if per_channel else 0 for rows, n in down.items()}
+    if waits[128] <= 40 and serves(blocks[128], waits[128], 1024):
+        return True
+    if per_channel and blocks[512] < 32:
+        return False
+    return serves(blocks[512], waits[512], 512 if nearest and bf16 else 256) or (nearest and bf16 and blocks[512] <= 3 * 256)
 
 
 @pytest.mark.parametrize("mode", [qmm.RTNE, qmm.STOCHASTIC])
@@ -90,7 +101,7 @@ def test_equals_the_two_calls(shape, axis, kw, pad, shift, dtype, mode):
         want_c, want_d = two_calls(x, axis, fmt, mode, offset, kw)
         for patience in (FOREVER, 1, 0):                    # FOREVER is cut to the library's own patience; 1: leaders hand out lists
             taken, c, d = one_launch(x, axis, fmt, mode, offset, patience, kw)
-            assert taken == fits(shape, axis, pad == shift == 0, dtype, mode), patience
+            assert taken == fits(shape, axis, pad == shift == 0, dtype, mode, offset, kw.get("per_channel", False) and shape[2] > 1, kw.get("batch_groups", 1)), patience
             if not taken:
                 continue
             assert torch.equal(d.view(torch.int32), want_d.view(torch.int32)), (fmt, patience)

@@ -546,8 +546,15 @@ template <typename T, int MODE> bool plan_cols(const QArgs& q, ColsPlan* pl)
         // 128000 x 64 28.6 / 92.5 / 16.4).
         const int64_t waits = q.channels > 1 ? P / strips : 0;
         if (waits > 0 && (i == 0 ? waits > 40 : blocks < 32)) continue;
-        // Stochastic rounding: with few workgroups a thread's generator blocks are what counts (2048 x 64 6.9 / 7.6).
-        if (MODE != QMM_ROUND_RTNE && blocks < 64) continue;
+        // Stochastic rounding: with few workgroups a thread's generator blocks are what counts, the more so where all wait for all, where
+        // there are no large passes to save and where the columns' codes do not start blocks (separate launches / this: one step size, 130 x
+        // 3072, 96 workgroups, 8.8 / 10.9, 130 x 4096, 128, 9.2 / 11.2, 264 x 3072, 144, 9.2 / 8.5, 3 x 12000, 188, 9.0 / 11.1; 13 groups of 398 x 128,
+        // 104, 9.2 / 10.5, 16 of 512 x 64, 64, 8.1 / 7.5; per column 70 x 4096, 64, 8.8 / 9.3, 4096 x 128, 64, 7.7 / 8.9, 2048 x 256, 64, 7.9 / 7.7).
+        if constexpr (MODE != QMM_ROUND_RTNE) {
+            const bool few = q.rows < 32;
+            const int least = q.channels == 1 && q.groups == 1 ? (few ? 256 : 144) : !whole_blocks(q) ? (few ? 256 : 128) : waits > 16 ? 128 : 64;
+            if (blocks < least) continue;
+        }
         *pl = ColsPlan{i, (uint32_t)strips, (uint32_t)tiles_k, (uint32_t)P, (unsigned)blocks, (uint32_t)words};
         return true;
     }

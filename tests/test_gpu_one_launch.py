@@ -72,12 +72,13 @@ def fits(shape, axis, dense, dtype, mode, offset, per_channel, groups):
     nearest, bf16 = mode == qmm.RTNE, dtype == torch.bfloat16
     if axis == 1:
         return b * r * c * (2 if bf16 else 4) <= (1 << 26 if nearest and (dense or r == 1) else 1 << 25)
-    strips = -(-c // 64)
+    strips, few = -(-c // 64), r < 32
 
     def serves(blocks, waits, most):
         if nearest:
             return blocks <= most
-        return 64 <= blocks <= most
+        least = (256 if few else 144) if not per_channel and groups == 1 else (256 if few else 128) if r % 4 or offset % 4 else 128 if waits > 16 else 64
+        return least <= blocks <= most
     down = {rows: -(-r // rows) for rows in (128, 512)}
     blocks = {rows: b * strips * n for rows, n in down.items()}
     waits = {rows: n if per_channel else 0 for rows, n in down.items()}

@@ -77,7 +77,8 @@ def check_asm():
     kernels on the throughput path use no scratch memory (the kernels whose matrix instructions are builtins: 2 and 4 only), (5) the streaming kernel initialises no accumulator by a
     separate instruction and has no load the compiler knows of (outside the inline-assembly statements) behind its first MFMA (with stores outstanding the
     compiler waits for such a load with vmcnt(0), i.e. for every store), (6) the registers its inline-assembly loads fill without waiting (a tile's step
-    sizes) are touched by nothing before two step barriers have passed.  Returns a list of findings (empty = clean)."""
+    sizes) are touched by nothing before two step barriers have passed, (7) the FP8 and bfloat16 register-direct kernels without B in LDS
+    run three wavefronts a SIMD, which is what hides their loads.  Returns a list of findings (empty = clean)."""
     os.makedirs(OBJDIR, exist_ok=True)
 
     def assemble(part):
@@ -139,6 +140,8 @@ def check_asm():
             findings.append(f"{nm}: {body.count('v_accvgpr_mov')} v_accvgpr_mov (accumulators copied around MFMAs)")
         tail = text[end:end + 8000]
         sc = re.search(r"; ScratchSize: (\d+)", tail)
+        if re.search(r"gemm_direct_kernelILi[12]E\S*Lb0E", nm) and int(re.search(r"; Occupancy: (\d+)", tail).group(1)) < 3:
+            findings.append(f"{nm}: fewer than three wavefronts a SIMD")
         targs = re.search(r"gemm_kernelI((?:Li\d+E)+)E", nm)
         fuse = int(re.findall(r"Li(\d+)E", targs.group(1))[6]) if targs else 0      # <KIND, FA, FB, TM, TG, NWN, FUSE, NSR>
         if sc and int(sc.group(1)) > 0 and targs and fuse == 0:                       # codes-in kernels: the throughput path

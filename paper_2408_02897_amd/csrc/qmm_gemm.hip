@@ -146,7 +146,7 @@ template <typename AccT, int NI, int NJ> QMM_DEV void pin_accumulators(AccT (&ac
 // odd): one store instruction all the same, global memory takes vector stores at any element boundary.
 // THROUGH: past the L2 at once (store_through), which pays where a kernel's outputs all leave in its last phase and in whole lines:
 // gemm_kernel to binary32, E4M3 4096 x 768 x 768 11.1 -> 9.8 us (not INT8, see there); the partial sums of 768 x 3072 x 4096 16.3 -> 14.9, of
-// 3072 x 1024 x 16384 53.2 -> 52.3; of gemm_direct_kernel the bfloat16 ones, 36.5 -> 35.4.  Else not for bfloat16 and edge tiles (40000 x 640 x 512 E4M3 27.3 by the L2,
+// 3072 x 1024 x 16384 53.2 -> 52.3; of gemm_direct_kernel with B in LDS the bfloat16 ones, 36.5 -> 35.4.  Else not for bfloat16 and edge tiles (40000 x 640 x 512 E4M3 27.3 by the L2,
 // 31.9 past it), not in gemm_deep_kernel, whose few outputs the L2 takes faster (256 x 768 x 768 6.8 against 7.4 us), and not in
 // the split sums' second kernel.
 template <int T, bool THROUGH = false> QMM_DEV void store_f32(float* dst, const float (&v)[T])
@@ -1850,9 +1850,12 @@ gemm_direct_kernel(GemmArgs g)
                     pk[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector(
                         f2{value(ia, r, 2 * q, sl_rows[ia][r]), value(ia, r, 2 * q + 1, sl_rows[ia][r])}, bf2));
                 uint8_t* dst = ybase + (int64_t)(ia * R + row_in_block(r)) * g.N * 2;
+                // (without B_LDS the second kind of store takes FP8 from 162 registers to 174, three wavefronts a SIMD to two: 74 x [40 x 2496 x
+                // 1792] 90 / 117 us, 200 x [18 x 2048 x 256] 38 / 42)
+                const bool through = B_LDS && g.through;
                 if constexpr (TILES_N == 4) {
-                    if (g.through) store_through(dst, u32x2{pk[0], pk[1]}); else *reinterpret_cast<u32x2*>(dst) = u32x2{pk[0], pk[1]};
-                } else if (g.through) store_through(dst, pk[0]);
+                    if (through) store_through(dst, u32x2{pk[0], pk[1]}); else *reinterpret_cast<u32x2*>(dst) = u32x2{pk[0], pk[1]};
+                } else if (through) store_through(dst, pk[0]);
                 else *reinterpret_cast<uint32_t*>(dst) = pk[0];
             }
     } else if (fast && TILES_N == 4) {

@@ -551,6 +551,7 @@ template <typename T, int MODE> bool plan_cols(const QArgs& q, ColsPlan* pl)
         // 3072, 96 workgroups, 8.8 / 10.9, 130 x 4096, 128, 9.2 / 11.2, 264 x 3072, 144, 9.2 / 8.5, 3 x 12000, 188, 9.0 / 11.1; 13 groups of 398 x 128,
         // 104, 9.2 / 10.5, 16 of 512 x 64, 64, 8.1 / 7.5; per column 70 x 4096, 64, 8.8 / 9.3, 4096 x 128, 64, 7.7 / 8.9, 2048 x 256, 64, 7.9 / 7.7).
         if constexpr (MODE != QMM_ROUND_RTNE) {
+            if (q.cols < 24) continue;                   // a strip's other threads are idle (18550 x 4 10.2 / 19.6 us, x 16 10.1 / 11.8, x 32 11.1 / 11.6)
             const bool few = q.rows < 32;
             const int least = q.channels == 1 && q.groups == 1 ? (few ? 256 : 144) : !whole_blocks(q) ? (few ? 256 : 128) : waits > 16 ? 128 : 64;
             if (blocks < least) continue;

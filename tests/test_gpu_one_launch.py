@@ -61,7 +61,7 @@ FORMS = [
     ((1, 16384, 1032), 0, {}), ((12, 130, 64), 0, dict(batch_groups=4)), ((7, 70, 96), 0, dict(batch_groups=3, batch_inner=2)), ((5, 513, 70), 0, {}),
     ((1, 4230, 33), 0, dict(per_channel=True)), ((1, 129, 65), 0, dict(per_channel=True)), ((1, 3, 5), 0, dict(per_channel=True)),
     ((1, 1031, 1001), 0, dict(per_channel=True)), ((3, 600, 200), 0, dict(per_channel=True, batch_groups=3)), ((1, 6000, 2000), 0, dict(per_channel=True)),
-    ((1, 16384, 520), 0, dict(per_channel=True)), ((1, 4097, 40), 0, dict(per_channel=True)), ((1, 70001, 70), 0, dict(per_channel=True)),
+    ((1, 16384, 520), 0, dict(per_channel=True)), ((1, 4097, 40), 0, dict(per_channel=True)), ((1, 70001, 70), 0, dict(per_channel=True)), ((1, 18550, 6), 0, {}),
     ((2, 9000, 130), 0, dict(per_channel=True, batch_groups=2))]
 
 
@@ -77,6 +77,8 @@ def fits(shape, axis, dense, dtype, mode, offset, per_channel, groups):
     def serves(blocks, waits, most):
         if nearest:
             return blocks <= most
+        if c < 24:
+            return False
         least = (256 if few else 144) if not per_channel and groups == 1 else (256 if few else 128) if r % 4 or offset % 4 else 128 if waits > 16 else 64
         return least <= blocks <= most
     down = {rows: -(-r // rows) for rows in (128, 512)}

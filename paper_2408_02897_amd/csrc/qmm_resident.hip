@@ -284,6 +284,10 @@ template <typename T, int MODE> bool plan_rows(const QArgs& q, RowsPlan* pl)
         const int64_t P = (units + slice - 1) / slice, blocks = P * q.batch;
         const int64_t words = board_words(q, P);
         if (blocks > std::min<int64_t>(r.per_cu * cus, kMaxWords) || words > kBoardMax) continue;
+        // Stochastic rounding: where some CUs get two of the large workgroups and others one, the one waits for the two (bfloat16, separate
+        // launches / this: 8192 x 1024, 256 workgroups, 16.2 / 14.3 us, 8704 x 1024, 272, 16.0 / 19.8, 12288 x 1024, 384, 19.1 / 20.7, 14336 x 1024, 448,
+        // 21.1 / 21.7, 16384 x 1024, 512, 23.1 / 22.5; in 16 groups 300 x [512 x 64] 18.4 / 20.2, 420 23.0 / 21.5; binary32, half the codes, not).
+        if (MODE != QMM_ROUND_RTNE && sizeof(T) == 2 && r.threads == 1024 && blocks > cus && blocks < (q.groups > 1 ? 3 * cus / 2 : 15 * cus / 8)) continue;
         *pl = RowsPlan{i, (uint32_t)upr, (uint32_t)units, (uint32_t)P, (unsigned)blocks, (uint32_t)words};
         return true;
     }
@@ -546,14 +550,16 @@ template <typename T, int MODE> bool plan_cols(const QArgs& q, ColsPlan* pl)
         // 128000 x 64 28.6 / 92.5 / 16.4).
         const int64_t waits = q.channels > 1 ? P / strips : 0;
         if (waits > 0 && (i == 0 ? waits > 40 : blocks < 32)) continue;
-        // Stochastic rounding: with few workgroups a thread's generator blocks are what counts, the more so where all wait for all, where
-        // there are no large passes to save and where the columns' codes do not start blocks (separate launches / this: one step size, 130 x
-        // 3072, 96 workgroups, 8.8 / 10.9, 130 x 4096, 128, 9.2 / 11.2, 264 x 3072, 144, 9.2 / 8.5, 3 x 12000, 188, 9.0 / 11.1; 13 groups of 398 x 128,
-        // 104, 9.2 / 10.5, 16 of 512 x 64, 64, 8.1 / 7.5; per column 70 x 4096, 64, 8.8 / 9.3, 4096 x 128, 64, 7.7 / 8.9, 2048 x 256, 64, 7.9 / 7.7).
+        // Stochastic rounding: with few workgroups a thread's generator blocks are what counts, twice as many where columns do not start
+        // blocks, and a call is bound by the GPU rather than by its launches (9.5 us for the host of the separate ones, 6.4 for this one's).
+        // GPU time of calls back to back, separate launches / this, one step size: 1030 x 1024, 144 workgroups, 9.0 / 10.5 us, 1030 x 1536, 216,
+        // 10.3 / 10.7, 2046 x 1024, 256, 10.9 / 10.8, 2046 x 1280, 320, 14.2 / 12.8; 1032 x 1024, 144, 7.9 / 8.2, 2048 x 1024, 256, 9.6 / 8.2;
+        // per column 4094 x 512, 256, 10.9 / 11.7, 4094 x 640, 320, 15.6 / 13.8, 4096 x 256, 128, 7.4 / 8.8, 4096 x 384, 192, 8.8 / 8.8; large tiles
+        // 8192 x 256, 64, 10.2 / 12.2, 8192 x 384, 96, 12.9 / 12.4, 8190 x 512, 128, 16.9 / 17.8, 8190 x 640, 160, 19.9 / 18.0; 300 x [2 x 128] 13.8 / 14.6.
         if constexpr (MODE != QMM_ROUND_RTNE) {
-            if (q.cols < 24) continue;                   // a strip's other threads are idle (18550 x 4 10.2 / 19.6 us, x 16 10.1 / 11.8, x 32 11.1 / 11.6)
-            const bool few = q.rows < 32;
-            const int least = q.channels == 1 && q.groups == 1 ? (few ? 256 : 144) : !whole_blocks(q) ? (few ? 256 : 128) : waits > 16 ? 128 : 64;
+            const bool whole = whole_blocks(q);
+            if (q.cols < 24 || (!whole && q.rows < 8)) continue;       // a strip's other threads are idle (18550 x 4 10.2 / 19.6 us, x 16 10.1 / 11.8, x 32 11.1 / 11.6)
+            const int least = waits > 0 && i > 0 ? (whole ? 96 : 144) : waits > 16 ? (whole ? 128 : 320) : whole ? 64 : 256;
             if (blocks < least) continue;
         }
         *pl = ColsPlan{i, (uint32_t)strips, (uint32_t)tiles_k, (uint32_t)P, (unsigned)blocks, (uint32_t)words};

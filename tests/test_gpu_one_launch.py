@@ -67,28 +67,25 @@ FORMS = [
 
 def fits(shape, axis, dense, dtype, mode, offset, per_channel, groups):
     """Whether one of FORMS is for the one launch on 256 CUs: bytes of the rows; tiles of 64 columns by 128 or 512 rows, of which a column
-    has few small ones and the tensor enough large ones, and for stochastic rounding enough workgroups."""
+    has few small ones and the tensor enough large ones, and for stochastic rounding enough workgroups, evenly spread."""
     b, r, c = shape
     nearest, bf16 = mode == qmm.RTNE, dtype == torch.bfloat16
     if axis == 1:
-        return b * r * c * (2 if bf16 else 4) <= (1 << 26 if nearest and (dense or r == 1) else 1 << 25)
-    strips, few = -(-c // 64), r < 32
-
-    def serves(blocks, waits, most):
-        if nearest:
-            return blocks <= most
-        if c < 24:
+        if not nearest and bf16 and 256 < b * -(-r * c // 32768) < (384 if groups > 1 else 480) and b * r * c > 1 << 23:
             return False
-        least = (256 if few else 144) if not per_channel and groups == 1 else (256 if few else 128) if r % 4 or offset % 4 else 128 if waits > 16 else 64
-        return least <= blocks <= most
-    down = {rows: -(-r // rows) for rows in (128, 512)}
-    blocks = {rows: b * strips * n for rows, n in down.items()}
-    waits = {rows: n if per_channel else 0 for rows, n in down.items()}
-    if waits[128] <= 40 and serves(blocks[128], waits[128], 1024):
-        return True
-    if per_channel and blocks[512] < 32:
+        return b * r * c * (2 if bf16 else 4) <= (1 << 26 if nearest and (dense or r == 1) else 1 << 25)
+    strips, whole = -(-c // 64), r % 4 == 0 and offset % 4 == 0
+    small, large = b * strips * -(-r // 128), b * strips * -(-r // 512)
+    waits = -(-r // 128) if per_channel else 0
+    if nearest:
+        return (waits <= 40 and small <= 1024) or (not (per_channel and large < 32) and large <= (3 * 256 if bf16 else 256))
+    if c < 24 or (not whole and r < 8):
         return False
-    return serves(blocks[512], waits[512], 512 if nearest and bf16 else 256) or (nearest and bf16 and blocks[512] <= 3 * 256)
+    least = (128 if whole else 320) if waits > 16 else 64 if whole else 256
+    if waits <= 40 and least <= small <= 1024:
+        return True
+    least = (96 if whole else 144) if per_channel else 64 if whole else 256
+    return max(least, 32 if per_channel else 0) <= large <= 256
 
 
 @pytest.mark.parametrize("mode", [qmm.RTNE, qmm.STOCHASTIC])
@@ -206,8 +203,8 @@ def test_calls_beyond_the_length_of_the_ring():
             assert torch.equal(c, want[0]) and torch.equal(d, want[1]), i
 
 
-# One block (2048 elements a block), fewer blocks than fields, about as many, the lanes of a wavefront, a workgroup's threads, the
-# largest grid (from 2^21 elements on; with denominators always two launches there).
+# One block (2048 elements a block), fewer blocks than fields, as many: the one launch; beyond, two whatever the call (the lanes of a
+# wavefront, a workgroup's threads, the largest grid), eager and recorded.
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("n", [1, 2048, 2049, 5000, 15 * 2048, 16 * 2048 + 3, 17 * 2048, 64 * 2048, 65 * 2048 + 1, 257 * 2048, 1 << 21, 3000001])
 def test_metric_in_one_launch_equals_two(n, dtype):

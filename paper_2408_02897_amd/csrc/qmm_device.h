@@ -360,7 +360,7 @@ QMM_DEV bool arrive_last(uint32_t* slot, unsigned id, unsigned total)
 // atomics, and no ordering between words is needed.  Tags are handed out by the host, one per launch (take_board), so a
 // call that is being recorded into a graph, whose replays would repeat the tag, does not use a board.
 // Boards are cut from rings in the library's device image, each call as many words as it needs (calls whose readers wait long,
-// the step sizes alone, have a ring of their own: what they share words with is a call of their own kind at least
+// the error sums and the step sizes alone, have a ring of their own: what they share words with is a call of their own kind at least
 // sixteen, mostly a thousand calls before).  A reader's wait is bounded
 // (`patience`, in ticks of the 100 MHz clock): a value that has not come by then -- its workgroup may not be resident, other
 // work holding the CUs, or a call a whole ring before may still be running on the same words -- the reader's workgroup forms

@@ -2,9 +2,9 @@
 // sums behind the noise-to-signal ratio, the relative error of Eq. 2 and the
 // element-wise backward error of Eq. 3.  HBM-bound: 8 B per element for a
 // binary32 y (6 B for bfloat16 y, +4 B with denominators).  Every thread keeps
-// private sums, wavefronts fold them by rotations and swaps of lanes, workgroups through LDS, and a
-// small second kernel folds the per-workgroup partials (of the smallest tensors, outside stream capture, the workgroups
-// themselves when all are there), in a fixed order: no atomics, the result is reproducible run to run.
+// private sums, wavefronts fold them by rotations and swaps of lanes, workgroups through LDS, and the
+// first sixteen workgroups, one per field, fold the per-workgroup partials when all are there (calls being
+// recorded: a small second kernel does), in a fixed order: no atomics, the result is reproducible run to run.
 #include <algorithm>
 #include <type_traits>
 #include "qmm_device.h"
@@ -260,7 +260,7 @@ template <bool Y_BF16, bool HAS_D> QMM_DEV Acc block_sums(const void* __restrict
 
 // The fold of a field's partials, in an order that depends on nblocks only: thread t takes blocks t, t + 256, ... in ascending order,
 // the 64 lane values are folded by the fixed butterfly and the four wavefront values in wavefront order.  Thread 0's value.
-QMM_DEV double fold_field(const double* partial, int nblocks, int field)
+template <bool COHERENT> QMM_DEV double fold_field(const double* partial, int nblocks, int field)
 {
     __shared__ double s[kThreads / kWave];
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
@@ -272,7 +272,7 @@ QMM_DEV double fold_field(const double* partial, int nblocks, int field)
     for (int k = 0; k < kMaxBlocks / kThreads; ++k) {
         const int b = threadIdx.x + k * kThreads;
         v[k] = 0.0;
-        if (b < nblocks) v[k] = p[b];
+        if (b < nblocks) v[k] = COHERENT ? coherent_load(p + b) : p[b];
     }
     double r = 0.0;
 #pragma unroll
@@ -287,14 +287,12 @@ QMM_DEV double fold_field(const double* partial, int nblocks, int field)
     return t;
 }
 
-// ONE: the fold within the launch, for grids of no more workgroups than there are fields.  A workgroup stores its partials past the
-// caches, waits until they have left, posts a word, waits for the others' and folds its share of the fields, a wavefront a field; should a
-// word not come in time (other work holding the CUs, a board shared by calls in flight), the workgroup that misses it forms that block's sums
-// itself.  Beyond, the second launch is the shorter way: it is on its way while the pass still runs, and the exchange adds itself to the
-// pass.  Time a call, launches back to back, bfloat16, two launches / one: 2048 elements 5.6 / 5.2 us (a call by itself 9.2 / 7.6), 20000
-// 5.9 / 5.5, 65536 5.8 / 5.7, 200000 5.9 / 6.2, 524288 6.1 / 6.7, 4 million 10.4 / 10.7, 8 million 14.4 / 15.3, 12.6 million 18.7 / 19.1, 67 million 70.4 /
-// 70.9; binary32 20000 6.1 / 5.9, 524288 6.6 / 7.1, 17 million 26.6 / 26.9.  (The kernels' own times, which a profiler gives, are the other way
-// round: what two launches share is in both.)
+// ONE: the fold within the launch.  A workgroup stores its partials past the caches, waits until they have left and posts a word;
+// the first sixteen wait for all words and fold a field each (of fewer workgroups, several).  None of the others waits, so the
+// words come whatever else the GPU does; should one not (a board shared by calls in flight), the workgroup that misses it forms that
+// block's sums itself.  Against the second launch, which takes 2.3 to 4.7 us behind a pass and the host 2.4 us (kernel time, two
+// launches / one): 196608 bfloat16 6.8 / 6.6 us, 3 million 11.5 / 11.1, 8 million 18.0 / 15.9, 12.6 million 21.7 / 19.3, 67 million 71.8 /
+// 69.8; binary32 16.8 million 28.2 / 25.9, 67 million 86.2 / 83.4.
 // Not kept: four quotients of the sum over one denominator and the maxima looked for in upper words, 14 instructions an element
 // instead of 20 (bfloat16 67 million 67.7 against 69.8, 16.8 million 24.3 against 22.9, binary32 67 million 85.4 against 83.4).
 constexpr int kFields = 16;
@@ -311,6 +309,7 @@ metric_partial(const void* __restrict__ yv, const float* __restrict__ r, const f
         for (int block = (int)blockIdx.x, from = 0; block < nblocks; from = block + 1) {
             store_partial<true>(block_sums<Y_BF16, HAS_D>(yv, r, d, n, block, nblocks), partial, nblocks, block);
             if (threadIdx.x == 0) board_post(bd, block, 1u);
+            if (blockIdx.x >= kFields) return;
             if (start == 0) { start = ticks(); from = 0; }
             // the first block from `from` on whose word does not come
             if (threadIdx.x == 0) s_missing = nblocks;
@@ -324,22 +323,27 @@ metric_partial(const void* __restrict__ yv, const float* __restrict__ r, const f
             __syncthreads();
             if (block >= nblocks) break;
         }
-        // in fold_field's order (its other wavefronts would add zeros)
-        const int lane = threadIdx.x & (kWave - 1), step = nblocks * (kThreads / kWave);
-        for (int field = (int)blockIdx.x * (kThreads / kWave) + (int)threadIdx.x / kWave; field < kFields; field += step) {
-            const bool is_max = (field == 4 || field == 5 || field == 7 || field == 10);
-            const double v = lane < nblocks ? coherent_load(partial + field * nblocks + lane) : 0.0;
-            const double t = is_max ? wave_max_f64(v) : wave_sum_f64(v);
-            if (lane == 0) out[field] = t;
+        if (nblocks > kFields) {
+            const double t = fold_field<true>(partial, nblocks, (int)blockIdx.x);
+            if (threadIdx.x == 0) out[blockIdx.x] = t;
+        } else {
+            // few blocks: a wavefront a field, in fold_field's order (its other wavefronts would add zeros)
+            const int lane = threadIdx.x & (kWave - 1), step = nblocks * (kThreads / kWave);
+            for (int field = (int)blockIdx.x * (kThreads / kWave) + (int)threadIdx.x / kWave; field < kFields; field += step) {
+                const bool is_max = (field == 4 || field == 5 || field == 7 || field == 10);
+                const double v = lane < nblocks ? coherent_load(partial + field * nblocks + lane) : 0.0;
+                const double t = is_max ? wave_max_f64(v) : wave_sum_f64(v);
+                if (lane == 0) out[field] = t;
+            }
         }
     }
 }
 
-// The fold as a launch of its own, sixteen workgroups.
+// The fold as a launch of its own, sixteen workgroups, for calls that are being recorded.
 __global__ void __launch_bounds__(kThreads)
 metric_finalize(const double* __restrict__ partial, int nblocks, double* __restrict__ out)
 {
-    const double t = fold_field(partial, nblocks, (int)blockIdx.x);
+    const double t = fold_field<false>(partial, nblocks, (int)blockIdx.x);
     if (threadIdx.x == 0) out[blockIdx.x] = t;
 }
 
@@ -382,8 +386,9 @@ qmm_status metric_call(const void* y, qmm_dtype y_dtype, const float* y_ref, con
     double* partial = static_cast<double*>(workspace);
     const int nb = plan_blocks(n);
     Board bd{};
-    const bool one = nb <= kFields && take_board(s, RING_SHORT, (uint32_t)nb, &bd);
-    bd.patience = std::min(bd.patience, patience);
+    // (with denominators the fold's registers would leave a CU three workgroups instead of four)
+    const bool one = !(denom && nb == kMaxBlocks) && take_board(s, RING_LONG, (uint32_t)nb, &bd);
+    bd.patience = patience;
     auto run = [&](auto bf16, auto denominators) {
         constexpr bool Y = decltype(bf16)::value, D = decltype(denominators)::value;
         if (one) metric_partial<Y, D, true><<<nb, kThreads, 0, s>>>(y, y_ref, denom, n, partial, out16, bd);
@@ -402,12 +407,12 @@ qmm_status metric_call(const void* y, qmm_dtype y_dtype, const float* y_ref, con
 extern "C" qmm_status qmm_metric(const void* y, qmm_dtype y_dtype, const float* y_ref, const float* denom, int64_t n,
                                  double* out16, void* workspace, size_t workspace_bytes, void* stream)
 {
-    return metric_call(y, y_dtype, y_ref, denom, n, out16, workspace, workspace_bytes, kPatience, stream);
+    return metric_call(y, y_dtype, y_ref, denom, n, out16, workspace, workspace_bytes, kFolderPatience, stream);
 }
 
-// For the tests, not part of the ABI: in the one launch the workgroups wait `patience` ticks for one another (0: they form what is not there yet).
+// For the tests, not part of the ABI: the folding workgroups wait `patience` ticks for the others (0: they form what is not there yet).
 extern "C" qmm_status qmm_internal_metric(const void* y, qmm_dtype y_dtype, const float* y_ref, const float* denom, int64_t n,
                                           double* out16, void* workspace, size_t workspace_bytes, uint32_t patience, void* stream)
 {
-    return metric_call(y, y_dtype, y_ref, denom, n, out16, workspace, workspace_bytes, patience, stream);
+    return metric_call(y, y_dtype, y_ref, denom, n, out16, workspace, workspace_bytes, patience < kFolderPatience ? patience : kFolderPatience, stream);
 }

@@ -3,8 +3,8 @@
 // element-wise backward error of Eq. 3.  HBM-bound: 8 B per element for a
 // binary32 y (6 B for bfloat16 y, +4 B with denominators).  Every thread keeps
 // private sums, wavefronts fold them by rotations and swaps of lanes, workgroups through LDS, and the
-// first sixteen workgroups, one per field, fold the per-workgroup partials when all are there (calls being
-// recorded: a small second kernel does), in a fixed order: no atomics, the result is reproducible run to run.
+// first sixteen workgroups, one per field, fold the per-workgroup partials when all are there (large tensors and
+// calls being recorded: a small second kernel does), in a fixed order: no atomics, the result is reproducible run to run.
 #include <algorithm>
 #include <type_traits>
 #include "qmm_device.h"
@@ -290,9 +290,11 @@ template <bool COHERENT> QMM_DEV double fold_field(const double* partial, int nb
 // ONE: the fold within the launch.  A workgroup stores its partials past the caches, waits until they have left and posts a word;
 // the first sixteen wait for all words and fold a field each (of fewer workgroups, several).  None of the others waits, so the
 // words come whatever else the GPU does; should one not (a board shared by calls in flight), the workgroup that misses it forms that
-// block's sums itself.  Against the second launch, which takes 2.3 to 4.7 us behind a pass and the host 2.4 us (kernel time, two
-// launches / one): 196608 bfloat16 6.8 / 6.6 us, 3 million 11.5 / 11.1, 8 million 18.0 / 15.9, 12.6 million 21.7 / 19.3, 67 million 71.8 /
-// 69.8; binary32 16.8 million 28.2 / 25.9, 67 million 86.2 / 83.4.
+// block's sums itself.  What it saves is the host's second launch, 2.4 us: the paths of small products, whose time is the host's, take
+// 23.2 us where they took 26.5 (256 x 768 x 768), 34.8 / 41.9 (512^3 with its references).  On the GPU the second launch is the shorter way:
+// it is on its way while the pass still runs, and the exchange adds itself to the pass (calls back to back, bfloat16, two launches / one:
+// 200000 elements 5.9 / 6.2 us, 4 million 10.4 / 10.7, 6 million 12.3 / 13.0, 8 million 14.4 / 15.3, 12.6 million 18.7 / 19.1, 67 million 70.4 / 70.9;
+// binary32 6 million 13.7 / 14.1, 17 million 26.6 / 26.9).  So two beyond 2^22 elements, where a pass takes longer than the host for both.
 // Not kept: four quotients of the sum over one denominator and the maxima looked for in upper words, 14 instructions an element
 // instead of 20 (bfloat16 67 million 67.7 against 69.8, 16.8 million 24.3 against 22.9, binary32 67 million 85.4 against 83.4).
 constexpr int kFields = 16;
@@ -339,7 +341,7 @@ metric_partial(const void* __restrict__ yv, const float* __restrict__ r, const f
     }
 }
 
-// The fold as a launch of its own, sixteen workgroups, for calls that are being recorded.
+// The fold as a launch of its own, sixteen workgroups, for large tensors and calls that are being recorded.
 __global__ void __launch_bounds__(kThreads)
 metric_finalize(const double* __restrict__ partial, int nblocks, double* __restrict__ out)
 {
@@ -387,7 +389,7 @@ qmm_status metric_call(const void* y, qmm_dtype y_dtype, const float* y_ref, con
     const int nb = plan_blocks(n);
     Board bd{};
     // (with denominators the fold's registers would leave a CU three workgroups instead of four)
-    const bool one = !(denom && nb == kMaxBlocks) && take_board(s, RING_LONG, (uint32_t)nb, &bd);
+    const bool one = n <= (int64_t(1) << 22) && !(denom && nb == kMaxBlocks) && take_board(s, RING_LONG, (uint32_t)nb, &bd);
     bd.patience = patience;
     auto run = [&](auto bf16, auto denominators) {
         constexpr bool Y = decltype(bf16)::value, D = decltype(denominators)::value;

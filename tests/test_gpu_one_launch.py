@@ -203,8 +203,8 @@ def test_calls_beyond_the_length_of_the_ring():
             assert torch.equal(c, want[0]) and torch.equal(d, want[1]), i
 
 
-# One block (2048 elements a block), fewer blocks than fields, as many: the one launch; beyond, two whatever the call (the lanes of a
-# wavefront, a workgroup's threads, the largest grid), eager and recorded.
+# One block (2048 elements a block), fewer blocks than fields, about as many, the lanes of a wavefront, a workgroup's threads, the
+# largest grid (from 2^21 elements on; with denominators always two launches there, without them beyond 2^22).
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("n", [1, 2048, 2049, 5000, 15 * 2048, 16 * 2048 + 3, 17 * 2048, 64 * 2048, 65 * 2048 + 1, 257 * 2048, 1 << 21, 3000001])
 def test_metric_in_one_launch_equals_two(n, dtype):

@@ -107,6 +107,8 @@ int64_t qmm_num_scales(const qmm_tensor* x, const qmm_granularity* g);
  * inf or NaN element makes its group's delta inf / NaN; an all-zero (or
  * empty) group gets delta = 1; a quotient below 2^-126 is raised to 2^-126.
  * fmt must be one of the three 8-bit formats.  batch above 65535: QMM_ERR_UNSUPPORTED.
+ * Dense aligned tensors with one step size per matrix or group of matrices take one launch, under stream capture two below 2^24
+ * elements and with several groups, as all others do.
  */
 size_t qmm_scale_workspace_size(const qmm_tensor* x, const qmm_granularity* g);
 qmm_status qmm_scale(const qmm_tensor* x, qmm_format fmt, const qmm_granularity* g,
@@ -155,9 +157,11 @@ qmm_status qmm_quantize(const qmm_tensor* x, qmm_format fmt, const qmm_granulari
 /*
  * qmm_scale_quantize -- steps 1 and 2 of one tensor in one call: delta_out and codes_out are exactly what qmm_scale and
  * then qmm_quantize with those step sizes write, with fewer launches and passes over x: one step size per row (rows up
- * to 8192 bfloat16 / 4096 binary32 elements, every matrix a batch group of its own) takes a single pass, other tensors up to
- * 67 MB one launch that reads the tensor once (not under stream capture, where the passes are separate launches); beyond, the
- * quantize pass forms the step sizes from the partial maxima where that pays.
+ * to 8192 bfloat16 / 4096 binary32 elements, every matrix a batch group of its own) takes a single pass, other tensors that the
+ * chip holds one launch that reads the tensor once: rows contracting up to 67 MB (strided rows, stochastic rounding 33 MB), rows
+ * contracted up to 50 MB (binary32 33 MB; stochastic 2^23 elements, and not the smallest).  Beyond, and under stream capture, the
+ * passes are separate launches, and the quantize pass forms the step sizes from the partial maxima where that pays.  The one launch
+ * fills the chip: beside other work, with which it shares the CUs, it takes up to a fifth more than the separate ones.
  *   workspace  device scratch of at least qmm_scale_quantize_workspace_size() bytes, 16-byte aligned (0: may be NULL).
  * An empty tensor writes its groups' step sizes (1) and no codes.  Errors as for the two calls.
  */
@@ -176,7 +180,7 @@ qmm_status qmm_scale_quantize(const qmm_tensor* x, qmm_format fmt, const qmm_gra
  *               16-byte aligned.
  * When all tensors (at most 8) are single dense bfloat16 matrices in 16-byte aligned whole vectors with one step size
  * each (and, for quantize: contract_axis 1, cols a multiple of 16, round to nearest even), each call is one launch
- * (for scale too: each tensor's workgroup that finishes last folds its partial maxima) with the tensor index as a grid dimension, so that the
+ * (for scale too: one of each tensor's workgroups folds the partial maxima) with the tensor index as a grid dimension, so that the
  * small tensors' latency-bound kernels run inside the large tensors' launches.  Otherwise the tensors are processed
  * one after the other by the single-tensor code, after every tensor's arguments have been checked (an argument
  * error in any of them is returned before anything is launched).  Errors as for the single-tensor calls; count = 0
@@ -267,7 +271,7 @@ qmm_status qmm_gemm_nsr(const qmm_operand* a, const qmm_operand* b,
  * Elements whose error is NaN are left out of every sum and maximum.
  *   y          device, n elements of y_dtype;  y_ref, denom: device, n floats.
  *   workspace  device scratch, qmm_metric_workspace_size(n) bytes, 16-byte aligned.
- * n = 0 writes sixteen zeros.
+ * n = 0 writes sixteen zeros.  Up to 2^22 elements one launch; beyond, and under stream capture, a second one folds the sums.
  */
 size_t qmm_metric_workspace_size(int64_t n);
 qmm_status qmm_metric(const void* y, qmm_dtype y_dtype, const float* y_ref, const float* denom,
